@@ -1238,15 +1238,20 @@ q8_status cgru_decoder_step_f32(q8_ctx *ctx, const q8_cgru_weights_f32 *w, const
     float *e = cv.take<float>((size_t)n * l);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "cgru_decoder_step_f32: workspace too small");
     // Eq. 3: s' = r(y, s_prev)
-    const q8i_f32_job j1[2] = {{&w->r.Wx, y_emb, E, w->r.bx, gx, 3 * H}, {&w->r.Wh, s_prev, H, w->r.bh, gh, 3 * H}};
-    TRY(q8i_gemv_f32(ctx, j1, 2, n));
-    TRY(q8i_gru_gates(ctx, gx, gh, s_prev, H, s_mid, H, H, n));
+    if (q8i_gru_f32_ok(&w->r, false, y_emb, s_prev, s_mid, n)) {
+        TRY(q8i_gru_f32(ctx, &w->r, y_emb, s_prev, nullptr, s_mid, n));
+    } else {
+        const q8i_f32_job j1[2] = {{&w->r.Wx, y_emb, E, w->r.bx, gx, 3 * H}, {&w->r.Wh, s_prev, H, w->r.bh, gh, 3 * H}};
+        TRY(q8i_gemv_f32(ctx, j1, 2, n));
+        TRY(q8i_gru_gates(ctx, gx, gh, s_prev, H, s_mid, H, H, n));
+    }
     // u(s') of Eq. 6 and the recurrent half of GRU q
     const q8i_f32_job j2[2] = {{&w->att_U, s_mid, H, nullptr, a, A}, {&w->q.Wh, s_mid, H, w->q.bh, gh, 3 * H}};
     TRY(q8i_gemv_f32(ctx, j2, 2, n));
     // Eq. 5-6
     TRY(q8i_attention(ctx, P, enc_h, l, A, C, a, w->att_v, n, e, alpha_out, ctx_out, nullptr, 0, nullptr, nullptr, 0, nullptr));
     // Eq. 4: s = q(H_t, s')
+    if (q8i_gru_f32_ok(&w->q, true, ctx_out, s_mid, s_out, n)) return q8i_gru_f32(ctx, &w->q, ctx_out, s_mid, gh, s_out, n);
     const q8i_f32_job j3 = {&w->q.Wx, ctx_out, C, w->q.bx, gx, 3 * H};
     TRY(q8i_gemv_f32(ctx, &j3, 1, n));
     return q8i_gru_gates(ctx, gx, gh, s_mid, H, s_out, H, H, n);
@@ -1281,13 +1286,16 @@ q8_status output_logits_f32(q8_ctx *ctx, const q8_readout_weights_f32 *ro, const
     double *ps = cv.take<double>(ngrp * n);
     float *lg = logits ? logits : cv.take<float>((size_t)n * V);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "output_logits_f32: workspace too small");
-    const q8i_f32_job j[3] = {{&ro->W_s, s, ro->W_s.cols, nullptr, part[0], R}, {&ro->W_y, y_emb, ro->W_y.cols, nullptr, part[1], R},
-                              {&ro->W_c, ctx_vec, ro->W_c.cols, nullptr, part[2], R}};
-    TRY(q8i_gemv_f32(ctx, j, 3, n));
-    TRY(q8i_readout_combine(ctx, part[0], part[1], part[2], ro->b_t, R, n, t, 0, nullptr, nullptr, nullptr));
+    if (q8i_readout_f32_ok(ro, s, y_emb, ctx_vec, t, n)) {
+        TRY(q8i_readout_f32(ctx, ro, s, y_emb, ctx_vec, t, n));
+    } else {
+        const q8i_f32_job j[3] = {{&ro->W_s, s, ro->W_s.cols, nullptr, part[0], R}, {&ro->W_y, y_emb, ro->W_y.cols, nullptr, part[1], R},
+                                  {&ro->W_c, ctx_vec, ro->W_c.cols, nullptr, part[2], R}};
+        TRY(q8i_gemv_f32(ctx, j, 3, n));
+        TRY(q8i_readout_combine(ctx, part[0], part[1], part[2], ro->b_t, R, n, t, 0, nullptr, nullptr, nullptr));
+    }
     const q8i_f32_job jo = {W_out, t, R, b_out, lg, V};
-    TRY(q8i_gemv_f32(ctx, &jo, 1, n));
-    TRY(q8i_logit_stats(ctx, lg, n, V, pm, ps));
+    TRY(q8i_gemv_f32(ctx, &jo, 1, n, pm, ps));                 // logits and their tiles' statistics
     return q8i_select_logits(ctx, pm, ps, lg, V, n, k, lse, topk_logp, topk_idx);
 }
 

@@ -291,8 +291,15 @@ struct q8i_f32_job {            // Y [n x ldy] = W . X + bias in fp32 (the 32-bi
     float *Y;
     int ldy;
 };
-q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n);          // njobs <= 3, n <= 8
-q8_status q8i_logit_stats(q8_ctx *ctx, const float *logits, int n, int V, float *part_max, double *part_sum);
+// njobs <= 3, n <= 8; part_max / part_sum (one job; else NULL): (max, sum of exp) of every 16-row tile [n x tiles]
+q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n, float *part_max = nullptr, double *part_sum = nullptr);
+// a GRU cell, and the readout's first layer, in one launch each where the vectors fit into LDS and no output lies over
+// an input (..._ok); gh_pre: the recurrent pre-activations [n x 3H] are there already
+bool q8i_gru_f32_ok(const q8_gru_weights_f32 *g, bool gh_pre, const float *x, const float *h_prev, const float *h_out, int n);
+q8_status q8i_gru_f32(q8_ctx *ctx, const q8_gru_weights_f32 *g, const float *x, const float *h_prev, const float *gh_pre,
+                      float *h_out, int n);
+bool q8i_readout_f32_ok(const q8_readout_weights_f32 *ro, const float *s, const float *y, const float *c, const float *t_out, int n);
+q8_status q8i_readout_f32(q8_ctx *ctx, const q8_readout_weights_f32 *ro, const float *s, const float *y, const float *c, float *t_out, int n);
 q8_status q8i_select_logits(q8_ctx *ctx, const float *part_max, const double *part_sum, const float *logits, int V, int n,
                             int k, float *lse, float *topk_logp, int32_t *topk_idx);
 size_t q8i_beam_state_bytes(int max_steps);

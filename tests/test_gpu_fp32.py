@@ -75,3 +75,67 @@ def test_output_layer_f32(q, ctx, oracle, V, n):
         assert_close(r["logits"][j], logits, "logits", rel=2e-7)
         assert_same(r["topk_idx"][j], idx); assert_close(r["topk_logp"][j], lp)
         assert_close(r["lse"][j:j + 1], np.array([lse]), "lse")
+
+
+@pytest.mark.parametrize("rows,cols,n", [(1, 1, 1), (17, 255, 3), (2047, 257, 8), (2048, 1030, 7), (8193, 260, 8), (16, 4096, 4), (3000, 2044, 8)])
+def test_gemv_f32_edges(q, ctx, rows, cols, n):
+    """Remainders of the row groups (1, 2 and 4 rows per wave) and of the column chunks, rows padded with NaN, vectors
+    that lie apart or off 16-byte boundaries.  Sums in double and one rounding: half a last place of the sum, and half
+    of the biased sum's."""
+    import ctypes as C
+    import torch
+    rng = np.random.default_rng(rows * 3 + cols)
+    W, X, b = (rng.standard_normal(s).astype(np.float32) for s in ((rows, cols), (n, cols), (rows,)))
+    ref = (X.astype(np.float64) @ W.T.astype(np.float64)).astype(np.float32) + b
+    ld = (cols + 3) // 4 * 4 + 4
+    buf = np.full((rows, ld), np.nan, np.float32)
+    buf[:, :cols] = W
+    Wd = ctx.f32(buf)
+    mat = q.binding._MatF(Wd.data_ptr(), rows, cols, ld)
+    for gap, shift in ((0, 0), (4, 0), (3, 1)):
+        Xd = torch.full((n * (cols + gap) + shift,), float("nan"), device=ctx.device)
+        view = Xd[shift:].as_strided((n, cols), (cols + gap, 1))
+        view.copy_(ctx.f32(X))
+        Y = ctx.empty(n, rows)
+        ctx.check(ctx.lib.q8_gemv_f32(ctx.handle, C.byref(mat), C.c_void_p(view.data_ptr()), n, cols + gap,
+                                      C.c_void_p(ctx.f32(b).data_ptr()), C.c_void_p(Y.data_ptr()), rows))
+        assert_close(Y, ref, "product, vectors %d floats apart" % (cols + gap), rel=3e-7)
+
+
+@pytest.mark.parametrize("E,H,A,C,n", [(4, 4, 4, 8, 1), (36, 44, 28, 88, 8), (512, 1024, 64, 2048, 3), (1024, 1028, 16, 2056, 7)])
+def test_cells_in_one_launch_equal_products_and_gates(q, ctx, oracle, E, H, A, C, n):
+    """The GRU cells and the readout in one launch each against the launches apart, which an output that lies over an
+    input still takes."""
+    p = synth.cgru_step(seed=3, E=E, H=H, A=A, l=5, n_beam=n)
+    gru = _fp32_weights(q, ctx, p)
+    w = q.CgruWeightsF32(gru("dec_r"), q.MatF(ctx, p["att.U"]), ctx.f32(p["att.v"]), gru("dec_q"))
+    P = ctx.f32(np.random.default_rng(1).standard_normal((5, A)).astype(np.float32))
+    enc, y, s = ctx.f32(p["enc_h"]), ctx.f32(p["y_emb"]), ctx.f32(p["s_prev"])
+    apart = q.cgru_decoder_step_f32(ctx, w, P, enc, y, s)
+    over = q.cgru_decoder_step_f32(ctx, w, P, enc, y, s, bind=True)
+    args = list(over.args)
+    args[-1] = args[6]                                        # s' over s_prev
+    ctx.check(over.fn(*args))
+    assert_same(s, np_(apart["s_mid"]), "s'")
+    for k in ("s", "ctx", "alpha"):
+        assert_same(over.out[k], np_(apart[k]), k)
+    rng = np.random.default_rng(2)
+    R = H
+    ro = q.ReadoutWeightsF32(*[q.MatF(ctx, rng.standard_normal((R, d)).astype(np.float32) * 0.05) for d in (H, E, C)],
+                             ctx.f32(rng.standard_normal(R).astype(np.float32)))
+    for V in (16, 33):
+        W = q.MatF(ctx, rng.standard_normal((V, R)).astype(np.float32))
+        b = ctx.f32(rng.standard_normal(V).astype(np.float32))
+        sv, cv = ctx.f32(rng.standard_normal((n, H)).astype(np.float32)), ctx.f32(rng.standard_normal((n, C)).astype(np.float32))
+        one = q.output_logits_f32(ctx, ro, W, b, sv, y, cv, k=12)
+        lg = np_(one["logits"]).astype(np.float64)
+        lse = np.log(np.exp(lg - lg.max(1, keepdims=True)).sum(1)) + lg.max(1)
+        assert_close(one["lse"], lse, "log-sum-exp")
+        order = np.lexsort((np.broadcast_to(np.arange(V), lg.shape), -lg))[:, :12]
+        assert_same(one["topk_idx"], order.astype(np.int32), "top-k")
+        two = q.output_logits_f32(ctx, ro, W, b, sv, y, cv, k=12, bind=True)
+        args = list(two.args)
+        args[-1] = args[4]                                    # t over s (R = H)
+        ctx.check(two.fn(*args))
+        assert_same(sv, np_(one["t"]), "t")
+        assert_same(two.out["logits"], np_(one["logits"]), "logits")
