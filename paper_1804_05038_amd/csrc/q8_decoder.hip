@@ -344,7 +344,128 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_split_kernel(AttArgs a)
 }
 
 // Many hypotheses (sentences side by side): throughput matters, not the latency of one
-// energy, and the work is split over two kernels.  First the energies: block (g, b) of 256
+// energy, and the work is split over two kernels.  First the energies, bound by double-precision
+// instructions.  The hypotheses of a sentence attend over the same P, so the exponential of
+//   tanh(x) = 1 - 2 / (e^{2x} + 1),  x = fl(P_ij + a_bj)  (the fp32 sum that Eq. 6's tanh is taken of),
+// is put together from e^{2P} (once per entry of P, for all hypotheses) and e^{2a} (once per block, for all its
+// positions) as e^{2P} e^{2a} (1 + 2 (x - (P + a))): the sum's rounding error, at most half a last place, is
+// known exactly in double and its square is below 1e-15 of what it corrects.  The reciprocals of a thread's four
+// columns share one estimate (the reciprocal of their product, one third-order step: 2^-24.4 cubed) and part by
+// multiplications.  T is within 1e-15 of tanh(x), as q8_tanh_rn is, and rounded to float as there, so the
+// energies are the same but for a last place of T in some 1e-8 of the entries: 15 double-precision operations per
+// (hypothesis, entry) instead of 33.  Products of four e^{2x} + 1 stay inside the range while |P|, |a| <= 44; a
+// wave that sees larger (or non-finite) values takes q8_tanh_rn for that position.
+// A thread owns four columns, with a and e^{2a} of NB hypotheses in registers.  The positions of all sentences, back
+// to back, are dealt to the blocks in even runs (the host knows neither the lengths nor their sum): a grid over
+// (positions of the longest sentence, sentences) left some compute units with twice the work of others.  A run is
+// worked off in segments of at most ATTE_SEG positions of one sentence; each begins with the exponentials of its
+// hypotheses.  64 / 200 sentences of 10 to 60 words at beam 5, A = 1024 (kernel trace): 27.7 / 76.0 us with one tanh
+// each -> 16.2 / 31.7 us.  A beam of 1 shares nothing and stays with attention_panel_kernel.
+#define ATTE_SEG 16
+#define ATTE_BLOCKS 768
+#define ATTE_RANGE 44.0f
+template <int NB>
+__global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int n_sent)
+{
+    __shared__ double s_part[4][ATTE_SEG][NB];
+    __shared__ int s_first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int h0 = blockIdx.y * NB, A = a.A;
+    const long long total = a.sent_off[n_sent];
+    const int pend = (int)(total * (blockIdx.x + 1) / gridDim.x);
+    int pos = (int)(total * blockIdx.x / gridDim.x);
+    if (pos >= pend) return;
+    for (int s = tid; s < n_sent; s += 256)                  // the sentence of the run's first position
+        if (a.sent_off[s] <= pos && pos < a.sent_off[s + 1]) s_first = s;
+    __syncthreads();
+    int sent = __builtin_amdgcn_readfirstlane(s_first);
+    while (pos < pend) {
+        while (a.sent_off[sent + 1] <= pos) ++sent;
+        const int o = a.sent_off[sent], np = min(min(pend, a.sent_off[sent + 1]) - pos, ATTE_SEG);
+        const __amdgpu_buffer_rsrc_t rp = q8_rsrc(a.P + (size_t)pos * A, (size_t)np * A * sizeof(float));
+        for (int j0 = 0; j0 < A; j0 += 1024) {
+            const int j = j0 + tid * 4;
+            const unsigned col = j < A ? (unsigned)j * 4u : Q8_OOB;
+            auto load4 = [&](__amdgpu_buffer_rsrc_t r, unsigned off) {
+                return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+            };
+            float4 av[NB], pv;
+#pragma unroll
+            for (int h = 0; h < NB; ++h)         // (a pass past the beam repeats its last hypothesis and stores nothing for it)
+                av[h] = load4(q8_rsrc(a.a + (size_t)(sent * a.beam + min(h0 + h, a.beam - 1)) * A, (size_t)A * sizeof(float)), col);
+            const float4 vv = load4(q8_rsrc(a.v, (size_t)A * sizeof(float)), col);
+            pv = load4(rp, col);
+            double ea[NB][4];
+            bool far = false;
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                const float f[4] = {av[h].x, av[h].y, av[h].z, av[h].w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    far |= !(fabsf(f[c]) <= ATTE_RANGE);
+                    ea[h][c] = q8_exp_d(2.0 * (double)fminf(fmaxf(f[c], -ATTE_RANGE), ATTE_RANGE));
+                }
+            }
+            const double v[4] = {(double)vv.x, (double)vv.y, (double)vv.z, (double)vv.w};
+            for (int p = 0; p < np; ++p) {
+                const float pf[4] = {pv.x, pv.y, pv.z, pv.w};
+                pv = load4(rp, j < A ? (unsigned)((p + 1) * A + j) * 4u : Q8_OOB);          // (past the last position: zeros)
+                double acc[NB];
+#pragma unroll
+                for (int h = 0; h < NB; ++h) acc[h] = 0.0;
+                bool slow = far;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) slow |= !(fabsf(pf[c]) <= ATTE_RANGE);
+                if (!__any(slow)) {
+                    double ep[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) ep[c] = 2.0 * q8_exp_d(2.0 * (double)pf[c]);
+#pragma unroll
+                    for (int h = 0; h < NB; ++h) {
+                        const float af[4] = {av[h].x, av[h].y, av[h].z, av[h].w};
+                        double d[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            // what the sum lost in rounding, exactly (Knuth's two-sum), with the sign turned
+                            const float x = pf[c] + af[c], t = x - pf[c], lost = (pf[c] - (x - t)) + (af[c] - t);
+                            const double e2 = ep[c] * ea[h][c];                    // 2 e^{2 (P + a)}
+                            d[c] = fma(e2, -(double)lost, fma(e2, 0.5, 1.0));
+                        }
+                        const double d01 = d[0] * d[1], d23 = d[2] * d[3], dd = d01 * d23;
+                        double y = __builtin_amdgcn_rcp(dd);
+                        const double e = fma(-dd, y, 1.0);
+                        y = fma(y, fma(e, e, e), y);
+                        const double y01 = y * d23, y23 = y * d01;
+                        acc[h] = fma(v[0], (double)(float)fma(-2.0, y01 * d[1], 1.0), acc[h]);
+                        acc[h] = fma(v[1], (double)(float)fma(-2.0, y01 * d[0], 1.0), acc[h]);
+                        acc[h] = fma(v[2], (double)(float)fma(-2.0, y23 * d[3], 1.0), acc[h]);
+                        acc[h] = fma(v[3], (double)(float)fma(-2.0, y23 * d[2], 1.0), acc[h]);
+                    }
+                } else {
+#pragma unroll
+                    for (int h = 0; h < NB; ++h) {
+                        const float af[4] = {av[h].x, av[h].y, av[h].z, av[h].w};
+                        for (int c = 0; c < 4; ++c) acc[h] = fma(v[c], (double)tanh_rn(pf[c] + af[c]), acc[h]);
+                    }
+                }
+                const double tot = wave_sums_d<NB>(acc, lane);
+                const int h = wave_sums_index<NB>(lane);
+                if ((lane & 15) < (NB + 3) / 4 && h < NB) s_part[wave][p][h] = j0 ? s_part[wave][p][h] + tot : tot;
+            }
+        }
+        __syncthreads();
+        if (tid < np * NB) {
+            const int p = tid / NB, h = tid - p * NB;
+            if (h0 + h < a.beam)
+                a.e[(size_t)(sent * a.beam + h0 + h) * a.lde + (pos - o) + p] =
+                    (float)((s_part[0][p][h] + s_part[1][p][h]) + (s_part[2][p][h] + s_part[3][p][h]));
+        }
+        __syncthreads();
+        pos += np;
+    }
+}
+
+// The same with one tanh per entry, for beams of one: block (g, b) of 256
 // threads takes source positions 8 g .. 8 g + 7 of hypothesis b; thread (p, c) =
 // (tid / 32, tid % 32) sums columns 4 c + 128 u, u = 0, 1, ..., of position 8 g + p, and the
 // 32 partial sums of a position are added across lanes.
@@ -697,7 +818,22 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
         }
     }
     if (panel) {
-        Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_panel_kernel, dim3((l + ATTP_POS - 1) / ATTP_POS, n), dim3(256), 0, t);
+        if (sent_off && beam > 1) {
+            // hypotheses per pass: at most five share a block's exponentials (registers), wider beams go in two even passes
+            const int passes = beam > 5 ? 2 : 1, nb = (beam + passes - 1) / passes, n_sent = n / beam;
+            // three blocks per compute unit in all (256 / 512 / 768 / 1024 blocks: 16.9 / 17.0 / 16.2 / 18.3 us at 64 sentences,
+            // 36.4 / 32.9 / 31.7 / 32.3 at 200: fewer hide less, more make the exponentials of a more often); no more than
+            // there can be positions
+            const long long most = (long long)n_sent * l;
+            const int runs = ATTE_BLOCKS / passes;
+            const dim3 grid(most < runs ? (unsigned)most : runs, passes);
+            if (nb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, grid, dim3(256), 0, t, n_sent);
+            else if (nb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, grid, dim3(256), 0, t, n_sent);
+            else if (nb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, grid, dim3(256), 0, t, n_sent);
+            else Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<5>, grid, dim3(256), 0, t, n_sent);
+        } else {
+            Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_panel_kernel, dim3((l + ATTP_POS - 1) / ATTP_POS, n), dim3(256), 0, t);
+        }
         // (block numbers are dealt to sentences in groups of eight, see the kernel: the grid covers whole groups)
         const int nsent = sent_off ? (n + beam - 1) / beam : 0;
         const int fin_blocks = sent_off ? (nsent + 7) / 8 * 8 * beam : n;

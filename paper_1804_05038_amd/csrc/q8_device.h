@@ -104,6 +104,38 @@ __device__ __forceinline__ double wave_sum_d(double v)
            __longlong_as_double((long long)(((unsigned long long)hi1 << 32) | lo1));
 }
 
+// CNT sums over the wave: the first two stages pair values, so that each half (then each row of 16 lanes)
+// carries on with half of them, about 5 instructions per value instead of 18.  Lane L returns sum
+// wave_sums_index<CNT>(L), where L % 16 < Q = ceil(CNT / 4) and that index is below CNT.
+template <int CNT>
+__device__ __forceinline__ double wave_sums_d(const double (&v)[CNT], int lane)
+{
+    constexpr int Q = (CNT + 3) / 4;
+    auto swap_add = [](double a, double b, auto sw) {
+        const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+        const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+        const auto l = sw(al, bl), h = sw(ah, bh);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    };
+    double h[2 * Q], mine = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2 * Q; ++i)            // lanes 0-31: value i, lanes 32-63: value i + 2 Q
+        h[i] = swap_add(i < CNT ? v[i] : 0.0, i + 2 * Q < CNT ? v[i + 2 * Q] : 0.0,
+                        [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); });
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {              // even rows: value i, odd rows: value i + Q
+        double s = swap_add(h[i], h[i + Q], [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); });
+        s += dpp_mov_d<DPP_XOR1>(s);
+        s += dpp_mov_d<DPP_XOR2>(s);
+        s += dpp_mov_d<DPP_HALF_MIRROR>(s);
+        s += dpp_mov_d<DPP_MIRROR>(s);
+        mine = (lane & 15) == i ? s : mine;
+    }
+    return mine;
+}
+template <int CNT>
+__device__ __forceinline__ int wave_sums_index(int lane) { return (CNT + 3) / 4 * ((lane >> 5) * 2 + ((lane >> 4) & 1)) + (lane & 15); }
+
 template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long v)
 {

@@ -138,38 +138,6 @@ __device__ __forceinline__ void f32_x_store(const F32X<XB> &R, float *s, const f
         for (int k = threadIdx.x; k < pitch; k += 256) s[(size_t)j * pitch + k] = k < cols ? X[(size_t)j * ldx + k] : 0.0f;
 }
 
-// CNT sums over the wave: the first two stages pair values, so that each half (then each row of 16 lanes)
-// carries on with half of them, about 5 instructions per value instead of 18.  Lane L returns sum
-// f32_sum_index<CNT>(L), where L % 16 < Q = ceil(CNT / 4) and that index is below CNT.
-template <int CNT>
-__device__ __forceinline__ double f32_wave_sums(const double (&v)[CNT], int lane)
-{
-    constexpr int Q = (CNT + 3) / 4;
-    auto swap_add = [](double a, double b, auto sw) {
-        const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
-        const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
-        const auto l = sw(al, bl), h = sw(ah, bh);
-        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    };
-    double h[2 * Q], mine = 0.0;
-#pragma unroll
-    for (int i = 0; i < 2 * Q; ++i)            // lanes 0-31: value i, lanes 32-63: value i + 2 Q
-        h[i] = swap_add(i < CNT ? v[i] : 0.0, i + 2 * Q < CNT ? v[i + 2 * Q] : 0.0,
-                        [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); });
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {              // even rows: value i, odd rows: value i + Q
-        double s = swap_add(h[i], h[i + Q], [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); });
-        s += dpp_mov_d<DPP_XOR1>(s);
-        s += dpp_mov_d<DPP_XOR2>(s);
-        s += dpp_mov_d<DPP_HALF_MIRROR>(s);
-        s += dpp_mov_d<DPP_MIRROR>(s);
-        mine = (lane & 15) == i ? s : mine;
-    }
-    return mine;
-}
-template <int CNT>
-__device__ __forceinline__ int f32_sum_index(int lane) { return (CNT + 3) / 4 * ((lane >> 5) * 2 + ((lane >> 4) & 1)) + (lane & 15); }
-
 // Plain products: the block stages the vectors once and its waves walk over groups of RW rows.
 // STATS (one product, RW = 4): the block's four waves hold the 16 rows of a tile, and the tile's
 // (max, sum of exp) per vector go to part_max / part_sum, which the selection kernel starts from.
@@ -215,7 +183,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
 #pragma unroll
             for (int j = 0; j < N; ++j) acc[u][j] = 0.0;
         // the bias of the sum this lane will store: asked for ahead of everything that it would have to wait behind
-        const int idx = f32_sum_index<RW * N>(lane), u = idx / N, j = idx - u * N, rw = r0 + u;
+        const int idx = wave_sums_index<RW * N>(lane), u = idx / N, j = idx - u * N, rw = r0 + u;
         const bool mine = (lane & 15) < (RW * N + 3) / 4 && idx < RW * N;
         const float bias = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(mine && rw < rows ? (unsigned)rw * 4u : Q8_OOB), 0, 0));
         f32_product<N, RW, UN>(R, row, s_x, pitch, cols, lane, acc);
@@ -224,7 +192,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
         double v[RW * N];
 #pragma unroll
         for (int e = 0; e < RW * N; ++e) v[e] = acc[e / N][e % N];
-        float y = (float)f32_wave_sums<RW * N>(v, lane);
+        float y = (float)wave_sums_d<RW * N>(v, lane);
         if (J.bias) y = y + bias;
         if (mine && rw < rows) J.Y[(size_t)j * J.ldy + rw] = y;
         if constexpr (STATS) {
@@ -294,8 +262,8 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
         double v[3 * N];
 #pragma unroll
         for (int e = 0; e < 3 * N; ++e) v[e] = acc[e / N][e % N];
-        float y = (float)f32_wave_sums<3 * N>(v, lane);
-        const int idx = f32_sum_index<3 * N>(lane), g = idx / N;
+        float y = (float)wave_sums_d<3 * N>(v, lane);
+        const int idx = wave_sums_index<3 * N>(lane), g = idx / N;
         if ((lane & 15) < (3 * N + 3) / 4 && idx < 3 * N && unit < H) {
             if (bias) y = y + bias[g * H + unit];
             s_pre[wave][base + idx] = y;
@@ -367,8 +335,8 @@ __global__ __launch_bounds__(256) void readout_f32_kernel(F32ReadoutArgs a)
         for (int j = 0; j < N; ++j) v[m * N + j] = acc[0][j];
         s += (size_t)N * pitch;
     }
-    const float y = (float)f32_wave_sums<3 * N>(v, lane);
-    const int idx = f32_sum_index<3 * N>(lane);
+    const float y = (float)wave_sums_d<3 * N>(v, lane);
+    const int idx = wave_sums_index<3 * N>(lane);
     if ((lane & 15) < (3 * N + 3) / 4 && idx < 3 * N) s_pre[wave][idx] = y;
     __builtin_amdgcn_wave_barrier();
     if (lane < N && unit < a.R) {

@@ -517,3 +517,39 @@ def test_panel_search_wait_that_gives_up_is_reported_and_the_next_search_is_good
         assert_same(a, b, "after the abandoned run")
     for a, b in zip(again[2], good[2]):
         assert a[0].tolist() == b[0].tolist() and a[1:] == b[1:]
+
+
+@pytest.mark.parametrize("beam,A,lens", [(2, 4, [1, 7, 3, 2, 9]), (3, 28, [5, 40, 1, 1, 2]), (4, 1000, [33, 17, 16]), (5, 1028, [1] * 40),
+                                         (5, 1024, [60, 3, 31, 17]), (6, 2052, [9, 8]), (7, 1024, [130, 2]), (8, 64, [18, 33, 4])])
+def test_shared_exponentials_of_the_energies(q, ctx, beam, A, lens):
+    """The batched energies, whose tanh is put together from e^{2P} and e^{2a}, against the definition in 64 bits:
+    small arguments, ones that cancel, and entries of P and a beyond the range of the shared form (there a wave takes
+    one tanh per entry).  An energy is a sum in double rounded once, so an attention weight is within a few last
+    places of its energy's: 4 ulp of |e| <= 64 here."""
+    E = H = 36
+    p = synth.cgru_step(seed=beam, E=E, H=H, A=A, l=1, n_beam=len(lens) * beam)
+    rng = np.random.default_rng(A + beam)
+    L, n = sum(lens), len(lens) * beam
+    P = rng.standard_normal((L, A)).astype(np.float32)
+    P[::3] *= 1e-4
+    P[1::7, : max(1, A // 5)] *= 60.0                         # some beyond 44
+    P[L // 2, 0], P[L - 1, A - 1] = 3e4, -2e30
+    enc = rng.standard_normal((L, 2 * H)).astype(np.float32)
+    p["att.v"] = (rng.standard_normal(A) * 2.0 / np.sqrt(A)).astype(np.float32)
+    for gain in (0.05, 400.0):                                # u's weights: small and large a
+        U = gpu_mat(q, ctx, p["att.U"] * np.float32(gain), False)
+        gru = lambda pre: gpu_gru(q, ctx, p, pre)
+        w = q.CgruWeights(gru("dec_r"), U, ctx.f32(p["att.v"]), gru("dec_q"))
+        off = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=ctx.device)
+        r = q.cgru_decoder_step_batch_q8(ctx, w, ctx.f32(P), ctx.f32(enc), off, beam, max(lens), ctx.f32(p["y_emb"]), ctx.f32(p["s_prev"]))
+        a = np_(q.q8_gemm_narrow(ctx, U, r["s_mid"].contiguous()))
+        if gain > 1:
+            assert np.abs(a).max() > 44
+        v = p["att.v"].astype(np.float64)
+        for s, l in enumerate(lens):
+            o = sum(lens[:s])
+            for b in range(s * beam, (s + 1) * beam):
+                x = (P[o:o + l] + a[b]).astype(np.float32).astype(np.float64)
+                e = np.tanh(x) @ v
+                al = np.exp(e - e.max()) / np.exp(e - e.max()).sum()
+                assert_close(r["alpha"][b, :l], al, "alpha of slot %d" % b, rel=4 * 64 * 2.0 ** -23)
