@@ -1013,6 +1013,7 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
     float *gxf = cv.take<float>((size_t)total_l * 3 * H), *gxb = cv.take<float>((size_t)total_l * 3 * H);
     int8_t *xq = cv.take<int8_t>((size_t)panel * fwd->Wx.ld);
     float *xs = cv.take<float>(panel);
+    const size_t mark = cv.off;
     int8_t *hqf = cv.take<int8_t>((size_t)n_sent * fwd->Wh.ld), *hqb = cv.take<int8_t>((size_t)n_sent * fwd->Wh.ld);
     float *hsf = cv.take<float>(n_sent), *hsb = cv.take<float>(n_sent);
     float *ghf = cv.take<float>((size_t)n_sent * 3 * H), *ghb = cv.take<float>((size_t)n_sent * 3 * H);
@@ -1027,6 +1028,17 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
         TRY(q8i_gemm_jobs(ctx, gj, 2, cnt));
     }
     // the recurrences, all sentences and both directions per time step
+    if (q8i_enc_cell_ok(fwd, bwd, n_sent)) {
+        // (in the room of the other form's codes, scales and pre-activations, which is more)
+        cv.off = mark;
+        const size_t nm = (size_t)2 * n_sent * ((H + 31) / 32);
+        float *h[2], *pm[2];
+        for (int u = 0; u < 2; ++u) { h[u] = cv.take<float>((size_t)2 * n_sent * H); pm[u] = cv.take<float>(nm); }
+        if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_encode_batch: workspace too small");
+        for (int t = 0; t < max_l; ++t)
+            TRY(q8i_enc_cell(ctx, fwd, bwd, sent_off, n_sent, t, enc_h, gxf, gxb, h[(t + 1) & 1], h[t & 1], pm[(t + 1) & 1], pm[t & 1]));
+        return Q8_OK;
+    }
     for (int t = 0; t < max_l; ++t) {
         TRY(q8i_enc_step(ctx, 0, sent_off, n_sent, t, H, fwd->Wh.ld, enc_h, gxf, gxb, ghf, ghb, hqf, hqb, hsf, hsb));
         const q8i_gemm_job gj[2] = {{&fwd->Wh, hqf, hsf, fwd->bh, ghf, 3 * H, nullptr, nullptr, nullptr, 0},

@@ -553,3 +553,28 @@ def test_shared_exponentials_of_the_energies(q, ctx, beam, A, lens):
                 e = np.tanh(x) @ v
                 al = np.exp(e - e.max()) / np.exp(e - e.max()).sum()
                 assert_close(r["alpha"][b, :l], al, "alpha of slot %d" % b, rel=4 * 64 * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("E,H,lens,tiled", [(36, 4, [3, 1], False), (64, 64, [2] * 9 + [5], True), (620, 1000, [4, 9, 1], False), (64, 256, [1, 2, 3] * 6, True),
+                                            (48, 96, [3, 1, 4] * 22, False), (48, 100, [2, 1] * 65, False), (32, 1024, [1, 3] * 130, True)])
+def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
+    """The batched encoder's one launch per position at the edges of its blocks (32 units, 16 / 32 / 64 slots, one slot
+    group and more), sentences that end at different steps: the states of q8_encode, which runs another kernel per
+    position, bit for bit; with the workspace that q8_encode_batch_bytes asks for, and no more than it."""
+    rng = np.random.default_rng(H + len(lens))
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=len(lens) + (k == "b"), I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], False), gpu_mat(q, big, p[k + "Wh"], tiled), big.f32(p[k + "bx"]), big.f32(p[k + "bh"]))
+         for k in ("f", "b")]
+    L = sum(lens)
+    X = big.f32(rng.standard_normal((L, E)).astype(np.float32))
+    from paper_1804_05038_amd import binding
+    header = 256 * 1024
+    ctx = q.Context(workspace_bytes=header + binding.q8_encode_batch_bytes(G[0], L, len(lens)))
+    for _ in range(2):
+        enc = q.q8_encode_batch(ctx, G[0], G[1], X, list(lens))
+    q.q8_encoder_options(big, False)
+    off = [0] + list(np.cumsum(lens))
+    for i in sorted({*range(min(12, len(lens))), *range(max(0, len(lens) - 3), len(lens))}):
+        rows = slice(int(off[i]), int(off[i + 1]))
+        assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
