@@ -677,171 +677,194 @@ struct PanelArgs {
     const float *xscale, *bias;
     float *part_max;       // [n x ntiles]
     double *part_sum;
-    int rows, ld, n, ntiles, cols_per_group;
+    int rows, ld, n, ntiles, cols_per_group, bias_rows;
     float w_scale;
 };
 
-#define VP_WAVES 16        // at most; the launch picks the number of waves that divides the row tiles most evenly
-#define VP_MAX_NT 16
+typedef int v16i __attribute__((ext_vector_type(16)));
+#define VP_WAVES 8
+#define VP_MAX_COLS 256
+#define VP_STAGE 1536      // bytes of LDS per wave: a unit's statistics on their way out
 
-// One row tile against U column tiles starting at column tile t0: U independent accumulation
-// chains keep the matrix core busy (a single chain waits ~44 cycles per step) and their
-// epilogues interleave.  FULL: all 16 rows and all 16 U columns exist, nothing is masked (the
-// masked form costs about twice the vector instructions, which are what bounds this kernel:
-// per result tile 8 matrix-core steps stand against some 50 vector instructions).
-template <int KC, int U, bool FULL>
-__device__ __forceinline__ void panel_tiles(const PanelArgs &a, const v4i (&A)[KC], const int8_t *bt, int pitch, const float *s_c,
-                                            int tile, int t0, int nt, int cols, int c_base, float4 b, int i, int g)
+// max of eight values (the plain form costs a canonicalization of every operand)
+__device__ __forceinline__ float vp_max8(const float *v)
 {
-    v4i acc[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc[u] = (v4i){0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < KC; ++s)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // column tiles past the panel read the first tile of the group again (in bounds); their results are dropped
-            const v4i bv = *(const v4i *)(bt + ((FULL || t0 + u < nt) ? u : 0) * 16 * pitch + 64 * s);
-            acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[s], bv, acc[u], 0, 0, 0);
-        }
-    const int row0 = tile * 16 + 4 * g;
-    const float bias[4] = {b.x, b.y, b.z, b.w};
-    float y[U][4], m[U];
-    double sd[U];
-    if (FULL) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float c = s_c[16 * (t0 + u) + i];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[u][r] = (float)acc[u][r] * c;
-            if (a.bias) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[u][r] = y[u][r] + bias[r];
-            }
-            m[u] = fmaxf(fmaxf(y[u][0], y[u][1]), fmaxf(y[u][2], y[u][3]));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) m[u] = quad_rows_max(m[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            sd[u] = (double)exp_le0(y[u][0] - m[u]);
-#pragma unroll
-            for (int r = 1; r < 4; ++r) sd[u] += (double)exp_le0(y[u][r] - m[u]);
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int colr = 16 * (t0 + u) + i;                  // column within the panel
-            const bool col_ok = t0 + u < nt && colr < cols;
-            const float c = col_ok ? s_c[colr] : 0.0f;
-            m[u] = -INFINITY;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                y[u][r] = -INFINITY;
-                if (col_ok && row0 + r < a.rows) {
-                    y[u][r] = (float)acc[u][r] * c;
-                    if (a.bias) y[u][r] = y[u][r] + bias[r];
-                }
-                m[u] = fmaxf(m[u], y[u][r]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) m[u] = quad_rows_max(m[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            sd[u] = 0.0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (y[u][r] > -INFINITY) sd[u] += (double)exp_le0(y[u][r] - m[u]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) sd[u] = quad_rows_sum(sd[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int colr = 16 * (t0 + u) + i;
-        if ((FULL || (t0 + u < nt && colr < cols)) && g == 0) {
-            a.part_max[(size_t)(c_base + colr) * a.ntiles + tile] = m[u];
-            a.part_sum[(size_t)(c_base + colr) * a.ntiles + tile] = sd[u];
-        }
-    }
+    float a, b, m;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(a) : "v"(v[0]), "v"(v[1]), "v"(v[2]));
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(b) : "v"(v[3]), "v"(v[4]), "v"(v[5]));
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(v[6]), "v"(v[7]), "v"(a));
+    asm("v_max_f32 %0, %1, %2" : "=v"(a) : "v"(m), "v"(b));
+    return a;
 }
 
-template <int KC, int U>      // 64-byte k steps per row: ld = 64 KC; column tiles per inner step
-__global__ __launch_bounds__(64 * VP_WAVES) void vocab_panel_kernel(PanelArgs a)
+// Results are 32 rows x 32 slots, one v_mfma_i32_32x32x32_i8 accumulator: a lane then holds 16 rows of ONE slot, eight of
+// each of the two 16-row tiles that the selection wants statistics of, so that a tile's maximum and its sum take
+// seven steps in the lane and one across the wave's halves (the 16 x 16 form that this replaced spent 126 instructions
+// per 16 x 16 results, 8 of them products; vector instructions bound it).  A unit is 64 rows x 32 slots: two
+// accumulators keep the matrix core busy and share every operand read from LDS.  A wave takes a run of consecutive
+// units, slots first, so that all waves end together whatever the number of rows; while it multiplies the last
+// slots of its rows, every weight register it has used is refilled from its next rows, so the weights need no second
+// set of registers and no wait of their own.
+// Waves are not held in step: one wave's products run beside the other's statistics (a barrier per unit, with whole
+// 64-byte lines of statistics leaving the block together, cost 8 of 43 us at 1000 slots).  A unit's statistics go
+// through LDS all the same, so that a slot's four tiles leave as 16 and 32 contiguous bytes: every lane storing its own
+// 4 and 8 bytes, into rows 12 and 25 KB apart, took 10 of 45 us.
+// 50000 x 512 (kernel trace): 25 us at 320 slots, 55 us at 1000 with 16 x 16 results -> 18.7 / 41.8 us; 40001 rows at 600
+// slots 43 -> 31.6 us; 50294 rows of 640 bytes at 320 slots 31 -> 21.3 us.  At 1000 slots the products alone (no
+// statistics, nothing stored) take 26 us.  Measured and not kept: units of 32 rows with every lane storing its own
+// (the same, but 38 us at 600 slots), twelve waves per block (the same; sixteen spill), the weights requested after
+// everything else (the same).
+template <int KS>      // 32-byte k steps per row: ld = 32 KS
+__global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs a)
 {
-    extern __shared__ __align__(16) int8_t s_x[];        // [cols x pitch]
-    constexpr int ld = 64 * KC, pitch = ld + 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = blockDim.x, nwave = nthr >> 6;
-    const int i = lane & 15, g = lane >> 4;
+    // [cols_per_group x pitch] codes, the waves' statistics, the slots' dequantization factors, the block's biases
+    extern __shared__ __align__(16) int8_t s_x[];
+    constexpr int ld = 32 * KS, pitch = ld + 16, NTHR = 64 * VP_WAVES;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 31, h = lane >> 5;
     const int n = a.n, c_base = blockIdx.y * a.cols_per_group;
     const int cols = min(a.cols_per_group, n - c_base);       // > 0 by construction of the grid
-    const int nt = (cols + 15) >> 4;
-    // this wave's row tiles: gw, gw + stride, ...
-    const int gw = blockIdx.x * nwave + wave, stride = gridDim.x * nwave;
+    const int nct = (cols + 31) >> 5, nrp = (a.rows + 63) >> 6;
+    double *s_sum = (double *)(s_x + (size_t)a.cols_per_group * pitch + wave * VP_STAGE);      // [32 slots][4 tiles]
+    float *s_max = (float *)(s_sum + 128);
+    float *s_c = (float *)(s_x + (size_t)a.cols_per_group * pitch + VP_WAVES * VP_STAGE), *s_b = s_c + a.cols_per_group;
+    // Blocks whose numbers agree modulo 8 share an XCD: they take neighbouring runs, the same ones in every column
+    // group, so that an XCD's L2 is asked for one eighth of the matrix and gives it to all groups.
+    const int gx = gridDim.x, rank = gx % 8 == 0 ? ((int)blockIdx.x & 7) * (gx >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+    const long long units = (long long)nrp * nct, nw = (long long)gx * VP_WAVES, w0 = (long long)rank * VP_WAVES;
+    const int u0 = (int)(units * (w0 + wave) / nw), u1 = (int)(units * (w0 + wave + 1) / nw);
+    int rp = u0 / nct, ct = u0 - rp * nct;
+    const int rp0 = (int)(units * w0 / nw) / nct;             // the block's first rows
 
-    v4i A0[KC], A1[KC];
-    auto load_tile = [&](v4i (&A)[KC], int tile) {
-        const int8_t *p = a.tiles + ((size_t)(tile < a.ntiles ? tile : a.ntiles - 1) * KC) * 1024 + lane * 16;
-#pragma unroll
-        for (int s = 0; s < KC; ++s) A[s] = *(const v4i *)(p + 1024 * s);
+    // weights: lane (row i, k half h) of k step s holds bytes 32 s + 16 h .. of row 64 rp + 32 t + i; in the packed order
+    // that is 64-byte block s / 2 of the row's tile, piece 2 (s % 2) + h
+    const __amdgpu_buffer_rsrc_t rw = q8_rsrc(a.tiles, (size_t)a.ntiles * (KS / 2) * 1024);
+    const __amdgpu_buffer_rsrc_t rpm = q8_rsrc(a.part_max, (size_t)n * a.ntiles * 4), rps = q8_rsrc(a.part_sum, (size_t)n * a.ntiles * 8);
+    const int woff = ((i >> 4) * (KS / 2) << 10) + h * 256 + (i & 15) * 16;
+    v4i A[2][KS];
+    auto weights = [&](int pair, int t, int s) {
+        return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, woff, (2 * pair + t) * (KS << 10) + (s >> 1) * 1024 + (s & 1) * 512, 0));
     };
-    load_tile(A0, gw);
     // the codes of this block's slots into LDS (slots past the panel are zero): eight 16-byte pieces per
     // thread and round, requested together through a bounds-checked descriptor (no branch around a
     // load: inside one, every piece would be a memory round trip of its own)
     {
         const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.xq + (size_t)c_base * ld, (size_t)cols * ld);
-        const int total = nt * 16 * (ld / 16);
-        for (int p0 = 0; p0 < total; p0 += 8 * nthr) {
+        const int total = nct * 32 * (ld / 16);
+        for (int p0 = 0; p0 < total; p0 += 8 * NTHR) {
             v4i v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * nthr + tid;               // piece p: slot p / (ld / 16), bytes 16 (p % (ld / 16)) ..
+                const int p = p0 + u * NTHR + tid;               // piece p: slot p / (ld / 16), bytes 16 (p % (ld / 16)) ..
                 v[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(p < total ? (unsigned)p * 16u : Q8_OOB), 0, 0));
+            }
+            if (p0 == 0) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) { A[0][s] = weights(rp, 0, s); A[1][s] = weights(rp, 1, s); }
+                __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * nthr + tid;
+                const int p = p0 + u * NTHR + tid;
                 const int col = p / (ld / 16), ch = p - col * (ld / 16);
                 if (p < total) *(v4i *)(s_x + col * pitch + ch * 16) = v[u];
             }
         }
     }
-    float *s_c = (float *)(s_x + (size_t)a.cols_per_group * pitch);      // dequantization factor of every slot
-    for (int c = tid; c < nt * 16; c += nthr) s_c[c] = c < cols ? a.w_scale * a.xscale[c_base + c] : 0.0f;
+    for (int c = tid; c < nct * 32; c += NTHR) s_c[c] = c < cols ? a.w_scale * a.xscale[c_base + c] : 0.0f;
+    // biases of the block's rows (zero without any: adding zero changes no logit but the sign of a zero, which
+    // no comparison and no exponential sees)
+    for (int r = tid; r < a.bias_rows; r += NTHR) s_b[r] = a.bias && 64 * rp0 + r < a.rows ? a.bias[64 * rp0 + r] : 0.0f;
     __syncthreads();
 
-    const bool bias_vec = (((uintptr_t)a.bias) & 15) == 0;
-    const int8_t *bp = s_x + i * pitch + 16 * g;
-    const int nt_full = cols >> 4;                           // column tiles without a missing slot
-    auto do_tile = [&](const v4i (&A)[KC], int tile) {
-        const int row0 = tile * 16 + 4 * g;
-        const bool rows_full = tile * 16 + 16 <= a.rows;
-        float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (a.bias) {
-            if (bias_vec && row0 + 3 < a.rows) {
-                b = *(const float4 *)(a.bias + row0);
-            } else {
-                if (row0 < a.rows) b.x = a.bias[row0];
-                if (row0 + 1 < a.rows) b.y = a.bias[row0 + 1];
-                if (row0 + 2 < a.rows) b.z = a.bias[row0 + 2];
-                if (row0 + 3 < a.rows) b.w = a.bias[row0 + 3];
+    const int8_t *bp = s_x + i * pitch + 16 * h;
+    v2u st_max = {0u, 0u};
+    v4u st_sum = {0u, 0u, 0u, 0u};
+    int st_o4 = 0, st_o8 = 0;
+    // (loads still out here would be waited for at the loop's head in every round, as if no store came after them)
+    __builtin_amdgcn_s_waitcnt(0x0f70);                       // vmcnt(0)
+    for (int u = u0; u < u1; ++u) {
+        const int8_t *bt = bp + ct * 32 * pitch;
+        v16i acc[2] = {{}, {}};
+        if (ct == nct - 1 && u + 1 < u1) {                    // uniform: the next unit starts other rows
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const v4i x = *(const v4i *)(bt + 32 * s);
+                acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[0][s], x, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[1][s], x, acc[1], 0, 0, 0);
+                A[0][s] = weights(rp + 1, 0, s);
+                A[1][s] = weights(rp + 1, 1, s);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const v4i x = *(const v4i *)(bt + 32 * s);
+                acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[0][s], x, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[1][s], x, acc[1], 0, 0, 0);
             }
         }
-        for (int t0 = 0; t0 < nt; t0 += U) {
-            const int8_t *bt = bp + t0 * 16 * pitch;
-            if (rows_full && t0 + U <= nt_full) panel_tiles<KC, U, true>(a, A, bt, pitch, s_c, tile, t0, nt, cols, c_base, b, i, g);
-            else panel_tiles<KC, U, false>(a, A, bt, pitch, s_c, tile, t0, nt, cols, c_base, b, i, g);
+        // result r of the lane: row 64 rp + 32 t + 8 (r / 4) + 4 h + r % 4 of slot 32 ct + i
+        const float c = s_c[32 * ct + i];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const float *bias = s_b + 64 * (rp - rp0) + 32 * t + 4 * h;
+            float y[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 b = *(const float4 *)(bias + 8 * q);
+                y[4 * q] = (float)acc[t][4 * q] * c + b.x;
+                y[4 * q + 1] = (float)acc[t][4 * q + 1] * c + b.y;
+                y[4 * q + 2] = (float)acc[t][4 * q + 2] * c + b.z;
+                y[4 * q + 3] = (float)acc[t][4 * q + 3] * c + b.w;
+            }
+            const int row0 = 64 * rp + 32 * t;
+            if (row0 + 32 > a.rows) {                         // uniform: the last rows may be incomplete
+#pragma unroll
+                for (int r = 0; r < 16; ++r) y[r] = row0 + 8 * (r >> 2) + 4 * h + (r & 3) < a.rows ? y[r] : -INFINITY;
+            }
+            float m[2] = {vp_max8(y), vp_max8(y + 8)};
+            // the halves trade: lanes of half v hold tile v's maximum, then everybody gets both
+            auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(m[0]), __float_as_uint(m[1]), false, false);
+            const float mine = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+            sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mine), __float_as_uint(mine), false, false);
+            m[0] = __uint_as_float(sw[0]); m[1] = __uint_as_float(sw[1]);
+            double sd[2];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                sd[v] = (double)exp_le0(y[8 * v] - m[v]);
+#pragma unroll
+                for (int r = 1; r < 8; ++r) sd[v] += (double)exp_le0(y[8 * v + r] - m[v]);
+            }
+            const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(sd[0]), (unsigned)__double2loint(sd[1]), false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(sd[0]), (unsigned)__double2hiint(sd[1]), false, false);
+            s_max[i * 4 + 2 * t + h] = mine;
+            s_sum[i * 4 + 2 * t + h] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
         }
-    };
-    for (int tile = gw; tile < a.ntiles; tile += 2 * stride) {
-        load_tile(A1, tile + stride);
-        do_tile(A0, tile);
-        if (tile + stride < a.ntiles) {
-            load_tile(A0, tile + 2 * stride);
-            do_tile(A1, tile + stride);
+        // Lane L carries tiles 2 (L % 2), + 1 of slot L / 2 out.  Through descriptors, not in a branch, and nothing the
+        // next unit needs is requested after them: stores count with the loads, and a wait for the weights must not
+        // become one for these.
+        __builtin_amdgcn_wave_barrier();                      // (the wave's own LDS: in order)
+        const int tile = 4 * rp + 2 * (lane & 1), colr = 32 * ct + (lane >> 1);
+        const unsigned o = colr < cols && tile < a.ntiles ? (unsigned)(c_base + colr) * (unsigned)a.ntiles + (unsigned)tile : Q8_OOB >> 2;
+        const bool both = tile + 1 < a.ntiles;
+        // The registers of a store are kept from reuse until the next unit's: taking one back waits for the store.
+        asm volatile("" ::"v"(st_max), "v"(st_sum), "v"(st_o4), "v"(st_o8));
+        st_max = *(const v2u *)(s_max + 2 * lane);
+        st_sum = *(const v4u *)(s_sum + 2 * lane);
+        st_o4 = (int)(o * 4u);
+        st_o8 = (int)(o < Q8_OOB >> 3 ? o * 8u : Q8_OOB);
+        if (4 * rp + 4 <= a.ntiles) {                         // uniform
+            __builtin_amdgcn_raw_buffer_store_b64(st_max, rpm, st_o4, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(st_sum, rps, st_o8, 0, 0);
+        } else {                                              // the last rows: some of the four tiles are missing
+            __builtin_amdgcn_raw_buffer_store_b32(st_max.x, rpm, st_o4, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 0, 1), rps, st_o8, 0, 0);
+            if (both && o < Q8_OOB >> 2) {
+                __builtin_amdgcn_raw_buffer_store_b32(st_max.y, rpm, st_o4 + 4, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 2, 3), rps, st_o8 + 8, 0, 0);
+            }
         }
+        if (++ct == nct) { ct = 0; ++rp; }
     }
 }
 
@@ -855,39 +878,33 @@ q8_status q8i_vocab_panel(q8_ctx *ctx, const q8_mat *W, const float *bias, const
     a.tiles = W->tiles; a.xq = xq; a.xscale = xscale; a.bias = bias;
     a.part_max = part_max; a.part_sum = part_sum;
     a.rows = W->rows; a.ld = W->ld; a.n = n; a.ntiles = (W->rows + 15) / 16; a.w_scale = W->scale;
-    // column groups of equal size, as many slots as fit the LDS (codes at pitch ld + 16, one float
-    // per slot) and VP_MAX_NT column tiles; about one block per compute unit
-    int max_cols = (int)((160 * 1024) / (size_t)(W->ld + 16 + 4)) & ~15;
-    if (max_cols > 16 * VP_MAX_NT) max_cols = 16 * VP_MAX_NT;
-    const int ngroups = (n + max_cols - 1) / max_cols;
-    a.cols_per_group = ((n + ngroups - 1) / ngroups + 15) & ~15;
-    int gx = 256 / ngroups;
-    if (gx < 1) gx = 1;
-    if (gx * 8 > a.ntiles) gx = (a.ntiles + 7) / 8;
-    const int gy = (n + a.cols_per_group - 1) / a.cols_per_group;
-    // waves per block (8..16): the count for which the busiest wave's row tiles exceed the average least
-    int nw = 8;
-    double best = 1e30;
-    for (int w = 8; w <= VP_WAVES; ++w) {
-        const int waves = gx * w, most = (a.ntiles + waves - 1) / waves;
-        const double ratio = (double)most * waves / a.ntiles;
-        if (ratio < best - 1e-9) { best = ratio; nw = w; }
+    // column groups of equal size, as many slots as fit the LDS beside the rest (codes at pitch ld + 16, one float per
+    // slot) and VP_MAX_COLS; one block per compute unit
+    const int nrp = (W->rows + 63) / 64;
+    int max_cols = VP_MAX_COLS, gx = 1, gy = 1;
+    size_t smem = 0;
+    for (; max_cols >= 32; max_cols -= 32) {
+        const int ngroups = (n + max_cols - 1) / max_cols;
+        a.cols_per_group = ((n + ngroups - 1) / ngroups + 31) & ~31;
+        gy = (n + a.cols_per_group - 1) / a.cols_per_group;
+        gx = 256 / gy;
+        if (gx < 1) gx = 1;
+        if (gx > nrp) gx = nrp;
+        a.bias_rows = ((nrp + gx - 1) / gx + 2) * 64;         // of a block's run, which may begin and end inside 64 rows
+        smem = (size_t)a.cols_per_group * (W->ld + 16 + 4) + VP_WAVES * VP_STAGE + (size_t)a.bias_rows * 4;
+        if (smem <= 160 * 1024) break;
     }
-    const size_t smem = (size_t)a.cols_per_group * (W->ld + 16 + 4);
-    // column tiles per inner step: five when they divide the group's tiles and four do not (rows of 512
-    // bytes only: with ten k steps per row five chains no longer fit the registers of 16 waves)
-    const int ntg = a.cols_per_group / 16;
-    const bool five = W->ld == 512 && ntg % 5 == 0 && ntg % 4 != 0;
+    if (smem > 160 * 1024) return q8_fail(ctx, Q8_ERR_SHAPE, "vocabulary panel: %d rows", W->rows);
     typedef void (*kern_t)(PanelArgs);
-    const kern_t kern = W->ld == 512 ? (five ? vocab_panel_kernel<8, 5> : vocab_panel_kernel<8, 4>) : vocab_panel_kernel<10, 4>;
-    static bool attr_set[3] = {false, false, false};
-    const int which = W->ld == 512 ? (five ? 1 : 0) : 2;
+    const kern_t kern = W->ld == 512 ? vocab_panel_kernel<16> : vocab_panel_kernel<20>;
+    static bool attr_set[2] = {false, false};
+    const int which = W->ld == 512 ? 0 : 1;
     if (!attr_set[which]) {
         const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "vocabulary panel kernel: %s", hipGetErrorString(e));
         attr_set[which] = true;
     }
-    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, kern, dim3(gx, gy), dim3(64 * nw), smem, a);
+    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, kern, dim3(gx, gy), dim3(64 * VP_WAVES), smem, a);
     return q8i_launch_check(ctx, "vocabulary panel");
 }
 

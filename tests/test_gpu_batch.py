@@ -578,3 +578,22 @@ def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
     for i in sorted({*range(min(12, len(lens))), *range(max(0, len(lens) - 3), len(lens))}):
         rows = slice(int(off[i]), int(off[i + 1]))
         assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
+
+
+@pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
+                                   (4097, 512, 511), (2051, 640, 1024)])
+def test_vocabulary_panel_edges(q, oracle, V, R, n):
+    """The panel kernel's units (32 rows x 32 slots) at their remainders, column groups of every size, an odd bias address:
+    the selection on its statistics against the one on stored logits.  The sums behind the log-sum-exp differ in order
+    (double, rounded to float once): a last place of lse."""
+    rng = np.random.default_rng(V + n)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=max(V, 4096), max_ld=640))
+    W = gpu_mat(q, ctx, (rng.standard_normal((V, R)) * 0.05).astype(np.float32), True)
+    b = ctx.f32(np.concatenate([[0], rng.standard_normal(V)]).astype(np.float32))[1:]
+    t = ctx.f32(np.tanh(rng.standard_normal((n, R))).astype(np.float32))
+    for bias in (b, None):
+        kept = q.output_logits_q8(ctx, None, W, bias, t_in=t, k=12, want_logits=True)
+        r = q.output_logits_q8(ctx, None, W, bias, t_in=t, k=12, want_logits=False)
+        assert_same(r["topk_idx"], np_(kept["topk_idx"]), "indices")
+        assert_close(r["lse"], np_(kept["lse"]).astype(np.float64), "lse", rel=2.0 ** -22)
+        assert_close(r["topk_logp"], np_(kept["topk_logp"]).astype(np.float64), "logp", rel=2.0 ** -22)
