@@ -529,6 +529,120 @@ __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_finish_kernel(AttAr
     att_finish<false>(a, b, l, enc_h, s_alpha);
 }
 
+// The same for NB hypotheses of a sentence in one block, which then reads every encoder state once for them: what a
+// compute unit takes in (some 77 GB/s) bounds these sums, and a block per hypothesis read a sentence's states beam
+// times, 280 KB each at 35 positions.  A thread owns two columns for the NB hypotheses; a state is converted once for
+// all of them, and since the product of two floats is exact in double, fma adds what a multiply and an add did.
+// Wave h derives the weights of hypothesis h while the first states are on their way.  Sums in order of the
+// positions, as att_finish forms them: the same bits.  NB is the smallest that gives at most one block per compute
+// unit: below that, more blocks side by side beat fewer reads (20 sentences, beam 8: 15.6 us with all eight in a block).
+// 64 / 200 sentences of 10 to 60 words at beam 5, C = 2048 (kernel trace): 17.0 / 31.0 us with the kernel above ->
+// 11.6 / 16.6 us.  C > 2048 and more positions than the weights' LDS holds keep the kernel above.  Block numbers as
+// there: the passes over a sentence fall on one XCD.
+#define ATTC_UN 8
+template <int NB>
+__global__ __launch_bounds__(ATT_MAX_THREADS) void attention_context_kernel(AttArgs a, int n_sent, int passes)
+{
+    extern __shared__ __align__(16) double s_al[];               // [positions, rounded up to ATTC_UN][NB], zeros past l
+    __shared__ float s_m[NB][ATT_MAX_THREADS / 64];
+    __shared__ float s_scale[NB][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, C = a.C;
+    const int q = (int)blockIdx.x >> 3, sent = q / passes * 8 + ((int)blockIdx.x & 7), h0 = q % passes * NB;
+    if (sent >= n_sent) return;
+    const int first = sent * a.beam + h0, own = min(NB, a.beam - h0);          // the hypotheses of this block
+    const int o = a.sent_off[sent], l = a.sent_off[sent + 1] - o, lup = (l + ATTC_UN - 1) / ATTC_UN * ATTC_UN;
+    const __amdgpu_buffer_rsrc_t rh = q8_rsrc(a.enc_h + (size_t)o * C, (size_t)l * C * sizeof(float));
+    const int c = tid * 2;
+    auto request = [&](float2 (&v)[ATTC_UN], int t0) {
+#pragma unroll
+        for (int u = 0; u < ATTC_UN; ++u)
+            v[u] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rh, (int)(c < C ? (unsigned)((t0 + u) * C + c) * 4u : Q8_OOB), 0, 0));
+    };
+    float2 v0[ATTC_UN], v1[ATTC_UN];
+    if (wave < NB) {
+        const int b = first + min(wave, own - 1);                // (past the beam: the last one again, not stored)
+        const float *e = a.e + (size_t)b * a.lde;
+        double *al = s_al + wave;
+        float mx = -INFINITY;
+        for (int t = lane; t < l; t += 64) {
+            const float ev = e[t];
+            al[t * NB] = (double)ev;
+            mx = fmaxf(mx, ev);
+        }
+        request(v0, 0);
+        mx = wave_max_f(mx);
+        double Z = 0.0, ex0 = 0.0;               // ex0: the lane's first term, kept for the division below
+        for (int t = lane; t < l; t += 64) {
+            const double ex = q8_exp_d(fmax(al[t * NB] - (double)mx, -700.0));
+            if (t == lane) ex0 = ex;
+            Z += ex;
+        }
+        Z = wave_sum_d(Z);
+        for (int t = lane; t < l; t += 64) {
+            const float w = (float)((t == lane ? ex0 : q8_exp_d(fmax(al[t * NB] - (double)mx, -700.0))) / Z);
+            al[t * NB] = (double)w;
+            if (a.alpha && wave < own) a.alpha[(size_t)b * a.lde + t] = w;
+        }
+        if (lane < lup - l) al[(l + lane) * NB] = 0.0;
+    } else {
+        request(v0, 0);
+    }
+    __syncthreads();
+    double acc[NB][2];
+#pragma unroll
+    for (int h = 0; h < NB; ++h) acc[h][0] = acc[h][1] = 0.0;
+    auto add = [&](const float2 (&v)[ATTC_UN], int t0) {
+#pragma unroll
+        for (int u = 0; u < ATTC_UN; ++u) {
+            const double x = (double)v[u].x, y = (double)v[u].y;
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                const double w = s_al[(t0 + u) * NB + h];
+                acc[h][0] = fma(w, x, acc[h][0]);
+                acc[h][1] = fma(w, y, acc[h][1]);
+            }
+        }
+    };
+    for (int t = 0; t < lup; t += 2 * ATTC_UN) {
+        if (t + ATTC_UN < lup) request(v1, t + ATTC_UN);
+        add(v0, t);
+        if (t + ATTC_UN < lup) {
+            if (t + 2 * ATTC_UN < lup) request(v0, t + 2 * ATTC_UN);
+            add(v1, t + ATTC_UN);
+        }
+    }
+    float f[NB][2];
+#pragma unroll
+    for (int h = 0; h < NB; ++h) {
+        f[h][0] = (float)acc[h][0];
+        f[h][1] = (float)acc[h][1];
+        if (c < C && h < own) *(float2 *)(a.ctx + (size_t)(first + h) * C + c) = make_float2(f[h][0], f[h][1]);
+    }
+    if (!a.ctx_q) return;
+    float m[NB];
+#pragma unroll
+    for (int h = 0; h < NB; ++h) m[h] = c < C ? fmaxf(fabsf(f[h][0]), fabsf(f[h][1])) : 0.0f;
+    wave_max_multi<NB>(m);
+#pragma unroll
+    for (int h = 0; h < NB; ++h)
+        if (lane == h) s_m[h][wave] = m[h];
+    __syncthreads();
+    if (tid < NB) {
+        float mx = 0.0f;
+#pragma unroll
+        for (int w = 0; w < ATT_MAX_THREADS / 64; ++w) mx = fmaxf(mx, s_m[tid][w]);
+        q8_scale_of(mx, s_scale[tid][0], s_scale[tid][1]);
+        if (tid < own) a.ctx_qscale[first + tid] = s_scale[tid][0];
+    }
+    __syncthreads();
+    if (c < a.ldq) {
+#pragma unroll
+        for (int h = 0; h < NB; ++h)                             // (zeros past C)
+            if (h < own)
+                *(short *)(a.ctx_q + (size_t)(first + h) * a.ldq + c) = (short)(c < C ? q8_pack2(f[h][0], f[h][1], s_scale[h][1]) : 0);
+    }
+}
+
 // ========================================================================== readout ==
 
 struct ReadoutArgs {
@@ -820,23 +934,36 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
     if (panel) {
         if (sent_off && beam > 1) {
             // hypotheses per pass: at most five share a block's exponentials (registers), wider beams go in two even passes
-            const int passes = beam > 5 ? 2 : 1, nb = (beam + passes - 1) / passes, n_sent = n / beam;
+            const int epasses = beam > 5 ? 2 : 1, enb = (beam + epasses - 1) / epasses, n_sent = n / beam;
             // three blocks per compute unit in all (256 / 512 / 768 / 1024 blocks: 16.9 / 17.0 / 16.2 / 18.3 us at 64 sentences,
             // 36.4 / 32.9 / 31.7 / 32.3 at 200: fewer hide less, more make the exponentials of a more often); no more than
             // there can be positions
             const long long most = (long long)n_sent * l;
-            const int runs = ATTE_BLOCKS / passes;
-            const dim3 grid(most < runs ? (unsigned)most : runs, passes);
-            if (nb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, grid, dim3(256), 0, t, n_sent);
-            else if (nb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, grid, dim3(256), 0, t, n_sent);
-            else if (nb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, grid, dim3(256), 0, t, n_sent);
+            const int runs = ATTE_BLOCKS / epasses;
+            const dim3 grid(most < runs ? (unsigned)most : runs, epasses);
+            if (enb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, grid, dim3(256), 0, t, n_sent);
+            else if (enb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, grid, dim3(256), 0, t, n_sent);
+            else if (enb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, grid, dim3(256), 0, t, n_sent);
             else Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<5>, grid, dim3(256), 0, t, n_sent);
         } else {
             Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_panel_kernel, dim3((l + ATTP_POS - 1) / ATTP_POS, n), dim3(256), 0, t);
         }
+        const int n_sent = sent_off ? n / beam : 0;
+        int nb = 1;                              // hypotheses per block of the context kernel
+        while (nb < beam && (long long)n_sent * ((beam + nb - 1) / nb) > 256) ++nb;
+        const int passes = (beam + nb - 1) / nb;
+        const size_t al_bytes = (size_t)(l + ATTC_UN - 1) / ATTC_UN * ATTC_UN * nb * sizeof(double);
+        if (sent_off && C % 2 == 0 && C <= 2 * ATT_MAX_THREADS && (!codes || ldq <= 2 * ATT_MAX_THREADS) && al_bytes <= 60 * 1024) {
+            const dim3 grid((n_sent + 7) / 8 * 8 * passes);
+#define ATTC(K) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_context_kernel<K>, grid, dim3(ATT_MAX_THREADS), al_bytes, t, n_sent, passes)
+            switch (nb) {
+            case 1: ATTC(1); break; case 2: ATTC(2); break; case 3: ATTC(3); break; case 4: ATTC(4); break;
+            case 5: ATTC(5); break; case 6: ATTC(6); break; case 7: ATTC(7); break; default: ATTC(8); break;
+            }
+            return q8i_launch_check(ctx, "attention context");
+        }
         // (block numbers are dealt to sentences in groups of eight, see the kernel: the grid covers whole groups)
-        const int nsent = sent_off ? (n + beam - 1) / beam : 0;
-        const int fin_blocks = sent_off ? (nsent + 7) / 8 * 8 * beam : n;
+        const int fin_blocks = sent_off ? (n_sent + 7) / 8 * 8 * beam : n;
         Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_finish_kernel, dim3(fin_blocks), dim3(ATT_MAX_THREADS), 0, t, n);
     } else {
         Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_kernel, dim3(l, n), dim3(ATT_THREADS), 0, t);

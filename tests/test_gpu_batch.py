@@ -597,3 +597,27 @@ def test_vocabulary_panel_edges(q, oracle, V, R, n):
         assert_same(r["topk_idx"], np_(kept["topk_idx"]), "indices")
         assert_close(r["lse"], np_(kept["lse"]).astype(np.float64), "lse", rel=2.0 ** -22)
         assert_close(r["topk_logp"], np_(kept["topk_logp"]).astype(np.float64), "logp", rel=2.0 ** -22)
+
+
+@pytest.mark.parametrize("beam,H,lens", [(1, 36, [3] * 9), (2, 36, [8, 9, 16, 17, 1, 5]), (3, 1000, [7] * 3 + [33]), (5, 1024, [1, 2, 3, 60, 8] * 14),
+                                         (5, 20, [4, 11] * 100), (7, 64, [5] * 40), (8, 36, [9, 2] * 64), (4, 36, [900, 3, 30]), (2, 1028, [6] * 5)])
+def test_context_of_several_hypotheses_per_block(q, beam, H, lens):
+    """The context kernel at every number of hypotheses per block, passes that end past the beam, positions at the edges
+    of a round of loads, widths it leaves to the other kernel (C = 2 H > 2048): the single-sentence step, bit for bit."""
+    E = A = 36
+    p = synth.cgru_step(seed=beam, E=E, H=H, A=A, l=1, n_beam=len(lens) * beam)
+    L, n = sum(lens), len(lens) * beam
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=max(lens), max_rows=3 * H, max_ld=2 * H + 64))
+    rng = np.random.default_rng(H)
+    P, enc = ctx.f32(rng.standard_normal((L, A)).astype(np.float32)), ctx.f32(rng.standard_normal((L, 2 * H)).astype(np.float32))
+    gru = lambda pre: gpu_gru(q, ctx, p, pre)
+    w = q.CgruWeights(gru("dec_r"), gpu_mat(q, ctx, p["att.U"], False), ctx.f32(p["att.v"]), gru("dec_q"))
+    off = np.array([0] + list(np.cumsum(lens)), dtype=np.int32)
+    y, s = ctx.f32(p["y_emb"]), ctx.f32(p["s_prev"])
+    r = q.cgru_decoder_step_batch_q8(ctx, w, P, enc, torch.as_tensor(off).to(ctx.device), beam, max(lens), y, s)
+    for i in sorted({0, 1, 3, len(lens) // 2, len(lens) - 1} & set(range(len(lens)))):
+        rows, sl = slice(int(off[i]), int(off[i + 1])), slice(i * beam, (i + 1) * beam)
+        one = q.cgru_decoder_step_q8(ctx, w, P[rows].contiguous(), enc[rows].contiguous(), y[sl].contiguous(), s[sl].contiguous())
+        assert_same(r["alpha"][sl, :lens[i]], np_(one["alpha"]), "alpha, sentence %d" % i)
+        assert_same(r["ctx"][sl], np_(one["ctx"]), "context, sentence %d" % i)
+        assert_same(r["s"][sl], np_(one["s"]), "state, sentence %d" % i)
