@@ -37,6 +37,9 @@ struct GemmJobs {          // products of one launch (blockIdx.z), all over the 
 #define GB_SMALL_RT 1
 #define GB_SMALL_NT 4
 #endif
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+#define TILE_FILL 144       // 128 x 128 tiles that are worth a launch
 #define GB_K 128           // k bytes per stage
 #define GB_PITCH 144       // LDS bytes per staged vector: 16 lanes x 16 bytes fall on 64 distinct banks
 
@@ -356,6 +359,117 @@ __global__ __launch_bounds__(256) void gemm_resident_kernel(GemmJobs jobs)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (row0 + r < rows) a.Y[(size_t)col * a.ldy + row0 + r] = y[r];
+        }
+    }
+}
+
+// ===================================================================== large panels ==
+// Plain products over many vectors: block tile 32 RW rows x 32 CW CT vectors, four waves (RW x CW), a wave 32 rows x 32 CT
+// vectors of v_mfma_i32_32x32x32_i8 results.  What a compute unit takes in (some 77 GB/s) bounds these products, so the
+// tile is as large as still gives every unit a block; k runs in stages of 256 bytes, and stages s + 1 and s + 2 are on
+// their way while s is multiplied: a vector piece's register is requested again once it is in LDS, a weight register
+// once its instruction has used it.  One barrier per stage (two LDS buffers).  Weights come tile-packed or row by row;
+// everything outside the matrix or the panel reads as zero through bounds-checked descriptors.
+// Measured (kernel trace), 1000 vectors: products of 512 + 1024 bytes and 3072 rows each 19.7 (K-resident) -> 17.4 us,
+// the readout's three 17.4 (staged) -> 11.9, rows of 2048 bytes times 3072 17.4 -> 17; 1024 x 2048 x 1024 12.8 -> 10.7.
+template <int RW, int CW, int CT>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmJobs jobs)
+{
+    static_assert(RW * CW == 4, "four waves");
+    constexpr int ROWS = 32 * RW, COLS = 32 * CW * CT, KB = 256, PITCH = KB + 16, PB = COLS * (KB / 16) / 256;
+    extern __shared__ __align__(16) int8_t s_t[];        // [2][COLS x PITCH]
+    const GemmArgs &a = jobs.j[blockIdx.z];
+    if ((int)blockIdx.x * ROWS >= a.rows) return;        // the grid is sized for the largest job
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 31, h = lane >> 5;
+    const int wr = wave / CW, wc = wave - wr * CW;
+    const int r0 = (int)blockIdx.x * ROWS + 32 * wr, c0 = (int)blockIdx.y * COLS;
+    const int ld = a.ld, n = a.n, rows = a.rows, nst = (ld + KB - 1) / KB;
+    const bool tiled = a.Wt != nullptr;
+    const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.xq, (size_t)n * ld);
+    const __amdgpu_buffer_rsrc_t rw = tiled ? q8_rsrc(a.Wt, (size_t)a.ntiles * 16 * ld) : q8_rsrc(a.W, (size_t)rows * ld);
+    // weights: lane (row i, k half h) of k step m of stage s holds bytes 256 s + 32 m + 16 h .. of row r0 + i
+    const int row = r0 + i;
+    const unsigned wbase = tiled ? (unsigned)(row >> 4) * (unsigned)(ld >> 6) * 1024u + (unsigned)h * 256u + (unsigned)(i & 15) * 16u
+                                 : (unsigned)row * (unsigned)ld + 16u * h;
+    auto load_a = [&](int st, int m) {
+        const int k = KB * st + 32 * m;
+        const unsigned off = row < rows && k + 16 * h < ld ? wbase + (tiled ? (unsigned)(k >> 6) * 1024u + (unsigned)((k >> 5) & 1) * 512u : (unsigned)k) : Q8_OOB;
+        return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
+    };
+    // vectors: thread's piece u of a stage is piece (tid % 16) of vector u * 16 + tid / 16
+    const int bcol = tid >> 4, bpc = (tid & 15) * 16;
+    auto load_b = [&](v4i (&b)[PB], int st) {
+        const int k = KB * st + bpc;
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+            const int col = c0 + u * 16 + bcol;
+            b[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(col < n && k < ld ? (unsigned)col * (unsigned)ld + (unsigned)k : Q8_OOB), 0, 0));
+        }
+    };
+    v4i A0[8], A1[8], B0[PB], B1[PB];
+    load_b(B0, 0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) A0[m] = load_a(0, m);
+    load_b(B1, 1);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) A1[m] = load_a(1, m);
+    v16i acc[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[t] = (v16i){};
+    auto step = [&](v4i (&A)[8], v4i (&B)[PB], int st) {
+        int8_t *buf = s_t + (st & 1) * COLS * PITCH;
+#pragma unroll
+        for (int u = 0; u < PB; ++u) *(v4i *)(buf + (u * 16 + bcol) * PITCH + bpc) = B[u];
+        load_b(B, st + 2);
+        __syncthreads();
+        const int8_t *bp = buf + (32 * CT * wc + i) * PITCH + 16 * h;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[m], *(const v4i *)(bp + 32 * t * PITCH + 32 * m), acc[t], 0, 0, 0);
+            A[m] = load_a(st + 2, m);
+        }
+    };
+    for (int st = 0; st < nst; st += 2) {
+        step(A0, B0, st);
+        if (st + 1 < nst) step(A1, B1, st + 1);
+    }
+    // result r of the lane: row r0 + 8 (r / 4) + 4 h + r % 4 of vector c0 + 32 (CT wc + t) + i
+    const __amdgpu_buffer_rsrc_t rs = q8_rsrc(a.xscale, (size_t)n * sizeof(float));
+    const __amdgpu_buffer_rsrc_t rb = q8_rsrc(a.bias, a.bias ? (size_t)rows * sizeof(float) : 0);
+    const __amdgpu_buffer_rsrc_t rr = q8_rsrc(a.row_scale, a.row_scale ? (size_t)rows * sizeof(float) : 0);
+    const bool vec_ok = ((a.ldy & 3) == 0) && (((uintptr_t)a.Y & 15) == 0);
+    float bias[16], xs[CT], rsv[16];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) xs[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (c0 + 32 * (CT * wc + t) + i) * 4, 0, 0));
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int off = (r0 + 8 * (r >> 2) + 4 * h + (r & 3)) * 4;
+        bias[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, off, 0, 0));
+        rsv[r] = a.row_scale ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, off, 0, 0)) : a.w_scale;
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const int col = c0 + 32 * (CT * wc + t) + i;
+        if (col >= n) continue;
+        float *y = a.Y + (size_t)col * a.ldy;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row4 = r0 + 8 * q + 4 * h;
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = (float)acc[t][4 * q + r] * (rsv[4 * q + r] * xs[t]);
+                if (a.bias) v[r] = v[r] + bias[4 * q + r];
+            }
+            if (vec_ok && row4 + 3 < rows) *(float4 *)(y + row4) = make_float4(v[0], v[1], v[2], v[3]);
+            else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (row4 + r < rows) y[row4 + r] = v[r];
+            }
         }
     }
 }
@@ -681,7 +795,6 @@ struct PanelArgs {
     float w_scale;
 };
 
-typedef int v16i __attribute__((ext_vector_type(16)));
 #define VP_WAVES 8
 #define VP_MAX_COLS 256
 #define VP_STAGE 1536      // bytes of LDS per wave: a unit's statistics on their way out
@@ -976,6 +1089,35 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         const GemmArgs &a = jobs.j[t];
         if (a.ld > 1024 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
         if (a.ld > max_ld) max_ld = a.ld;
+    }
+    // Large panels: 128 x 128 tiles where there are enough of them for most compute units (3072 x 1024 times 1024
+    // vectors, 192 tiles: 14.1 against 15.0 us K-resident; 2415 x 1860 x 903, 152 tiles: 19.6 against 20.1 us staged;
+    // 1024 x 2048 x 1024, 64 tiles: 16.5 against 13.0) and rows are longer than 512 bytes (two products of 3072 x 512 x
+    // 1024: 15.8 against 14.6 us K-resident); else 64 x 64 tiles for rows that a K-resident block does not take.  There
+    // the staged kernel keeps what its larger loads suit better: row-major weights against more than 512 vectors
+    // (1000 x 2000 x 1024: 12.4 against 13.0 us; x 500: 12.0 against 11.2), and more than 8192 rows.
+    bool tile_ok = !stats && n > 8, packed = true;
+    int big = 0;
+    for (int t = 0; t < njobs; ++t) {
+        const GemmArgs &a = jobs.j[t];
+        if (a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) tile_ok = false;
+        big += (a.rows + 127) / 128 * ((n + 127) / 128);
+        packed = packed && a.Wt;
+    }
+    if (tile_ok && big >= TILE_FILL && max_ld > 512) {
+        const size_t smem = (size_t)2 * 128 * (256 + 16);
+        static bool attr_set = false;
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_kernel<4, 1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "large panel kernel: %s", hipGetErrorString(e));
+            attr_set = true;
+        }
+        Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
+        return q8i_launch_check(ctx, "gemm");
+    }
+    if (tile_ok && !resident && max_rows <= 8192 && (packed || n <= 512)) {
+        Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<2, 2, 1>), dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)2 * 64 * (256 + 16), jobs);
+        return q8i_launch_check(ctx, "gemm");
     }
     if (resident) {
         const dim3 grid((max_rows + 63) / 64, (n + 63) / 64, njobs);

@@ -218,3 +218,31 @@ def test_rows_variant_argument_errors(q, ctx):
     with pytest.raises(q.Q8Error) as e:
         q.q8_gemm_narrow_rows(ctx, M, None, ctx.f32(np.ones((1, 16), np.float32)))
     assert e.value.code == 1
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled", [(17, 1100, 9, False), (64, 1088, 64, True), (65, 1040, 65, False), (1000, 2000, 513, False),
+                                               (1024, 2048, 513, True), (130, 2112, 33, True), (1537, 528, 1023, False), (3072, 576, 897, True),
+                                               (1553, 1024, 1024, False), (2049, 16, 1024, False)])
+@pytest.mark.parametrize("by_row", [False, True])
+def test_large_panels(q, oracle, rows, cols, n, tiled, by_row):
+    """The tiled products at the edges of their tiles, stages and k steps, packed and row by row, one scale and one per
+    row, results at an odd pitch: exact integer sums, one product of scales, one addition, so identical bits."""
+    rng = np.random.default_rng(rows + n)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
+    W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
+    M, rs = q.q8_quantize_matrix_rows(ctx, W) if by_row else (q.q8_quantize_matrix(ctx, W), None)
+    if tiled:
+        M = q.q8_pack_tiles(ctx, M)
+    pick = sorted({0, 1, n // 2, n - 2, n - 1})
+    codes = np_(M.data)[:, :cols].astype(np.int64)
+    for pitch, bias in ((rows, None), (rows + 3, b)):
+        Y = ctx.empty(n, pitch)[:, :rows]
+        if by_row: q.q8_gemm_narrow_rows(ctx, M, rs, ctx.f32(X), ctx.f32(bias), Y=Y)
+        else: q.q8_gemm_narrow(ctx, M, ctx.f32(X), ctx.f32(bias), Y=Y)
+        got = np_(Y)
+        for j in pick:
+            xq, xs = oracle.quantize(X[j])
+            acc = (codes @ xq[:cols].astype(np.int64)).astype(np.float32)
+            scale = (np_(rs) if by_row else np.float32(M.scale)) * np.float32(xs)
+            y = acc * scale
+            assert_same(got[j], y if bias is None else y + bias, "vector %d" % j)
