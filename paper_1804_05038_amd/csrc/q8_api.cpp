@@ -902,7 +902,6 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
     float *gxb = cv.take<float>((size_t)l * 3 * H);
     float *zero = cv.take<float>(H);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_encode: workspace too small");
-    TRY(q8i_fill_u32(ctx, zero, H, 0u));
 
     // input products for every position at once (the same per-vector quantization as l separate products)
     if (l <= kMaxNarrow) {
@@ -926,7 +925,8 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
             if (launched) return Q8_OK;
         }
     }
-    // ... else l sequential launches, both directions in each
+    // ... else l sequential launches, both directions in each, from a state of zeros
+    TRY(q8i_fill_u32(ctx, zero, H, 0u));
     for (int t = 0; t < l; ++t) {
         const int pf = t, pb = l - 1 - t;
         q8i_gru_desc d[2];
