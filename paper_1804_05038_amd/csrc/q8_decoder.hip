@@ -360,7 +360,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_split_kernel(AttArgs a)
 // (positions of the longest sentence, sentences) left some compute units with twice the work of others.  A run is
 // worked off in segments of at most ATTE_SEG positions of one sentence; each begins with the exponentials of its
 // hypotheses.  64 / 200 sentences of 10 to 60 words at beam 5, A = 1024 (kernel trace): 27.7 / 76.0 us with one tanh
-// each -> 16.2 / 31.7 us.  A beam of 1 shares nothing and stays with attention_panel_kernel.
+// each -> 16.2 / 31.7 us.  A beam of 1 shares no exponentials, but the reciprocals and the even runs: 600 sentences
+// 53 -> 40.5 us.
 #define ATTE_SEG 16
 #define ATTE_BLOCKS 768
 #define ATTE_RANGE 44.0f
@@ -463,40 +464,6 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
         __syncthreads();
         pos += np;
     }
-}
-
-// The same with one tanh per entry, for beams of one: block (g, b) of 256
-// threads takes source positions 8 g .. 8 g + 7 of hypothesis b; thread (p, c) =
-// (tid / 32, tid % 32) sums columns 4 c + 128 u, u = 0, 1, ..., of position 8 g + p, and the
-// 32 partial sums of a position are added across lanes.
-#define ATTP_POS 8
-__global__ __launch_bounds__(256) void attention_panel_kernel(AttArgs a)
-{
-    const int b = blockIdx.y, tid = threadIdx.x;
-    const float *P, *enc_h;
-    const int l = att_sentence(a, b, P, enc_h);
-    const int i0 = blockIdx.x * ATTP_POS;
-    if (i0 >= l) return;
-    const int p = tid >> 5, c = tid & 31, i = i0 + p;
-    double acc = 0.0;
-    if (i < l) {
-        const float *Pi = P + (size_t)i * a.A;
-        const float *ab = a.a + (size_t)b * a.A;
-        if ((a.A & 3) == 0) {
-            for (int j = 4 * c; j < a.A; j += 128) {
-                const float4 pv = *(const float4 *)(Pi + j), av = *(const float4 *)(ab + j), vv = *(const float4 *)(a.v + j);
-                acc += (double)vv.x * (double)tanh_rn(pv.x + av.x);
-                acc += (double)vv.y * (double)tanh_rn(pv.y + av.y);
-                acc += (double)vv.z * (double)tanh_rn(pv.z + av.z);
-                acc += (double)vv.w * (double)tanh_rn(pv.w + av.w);
-            }
-        } else {
-            for (int j = c; j < a.A; j += 32) acc += (double)a.v[j] * (double)tanh_rn(Pi[j] + ab[j]);
-        }
-    }
-#pragma unroll
-    for (int m = 16; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);     // within the position's 32 lanes
-    if (c == 0 && i < l) a.e[(size_t)b * a.lde + i] = (float)acc;
 }
 
 // Then softmax and context vector (Eq. 5) of every hypothesis: att_finish as a kernel of its own, one
@@ -931,29 +898,26 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
             return q8i_launch_check(ctx, "attention");
         }
     }
-    if (panel) {
-        if (sent_off && beam > 1) {
-            // hypotheses per pass: at most five share a block's exponentials (registers), wider beams go in two even passes
-            const int epasses = beam > 5 ? 2 : 1, enb = (beam + epasses - 1) / epasses, n_sent = n / beam;
-            // three blocks per compute unit in all (256 / 512 / 768 / 1024 blocks: 16.9 / 17.0 / 16.2 / 18.3 us at 64 sentences,
-            // 36.4 / 32.9 / 31.7 / 32.3 at 200: fewer hide less, more make the exponentials of a more often); no more than
-            // there can be positions
-            const long long most = (long long)n_sent * l;
-            const int runs = ATTE_BLOCKS / epasses;
-            const dim3 grid(most < runs ? (unsigned)most : runs, epasses);
-            if (enb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, grid, dim3(256), 0, t, n_sent);
-            else if (enb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, grid, dim3(256), 0, t, n_sent);
-            else if (enb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, grid, dim3(256), 0, t, n_sent);
-            else Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<5>, grid, dim3(256), 0, t, n_sent);
-        } else {
-            Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_panel_kernel, dim3((l + ATTP_POS - 1) / ATTP_POS, n), dim3(256), 0, t);
-        }
-        const int n_sent = sent_off ? n / beam : 0;
+    if (panel && sent_off) {
+        const int n_sent = n / beam;
+        // hypotheses per pass: at most five share a block's exponentials (registers), wider beams go in two even passes
+        const int epasses = beam > 5 ? 2 : 1, enb = (beam + epasses - 1) / epasses;
+        // three blocks per compute unit in all (256 / 512 / 768 / 1024 blocks: 16.9 / 17.0 / 16.2 / 18.3 us at 64 sentences,
+        // 36.4 / 32.9 / 31.7 / 32.3 at 200: fewer hide less, more make the exponentials of a more often); no more than
+        // there can be positions
+        const long long most = (long long)n_sent * l;
+        const int runs = ATTE_BLOCKS / epasses;
+        const dim3 egrid(most < runs ? (unsigned)most : runs, epasses);
+        if (enb == 1) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<1>, egrid, dim3(256), 0, t, n_sent);
+        else if (enb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, egrid, dim3(256), 0, t, n_sent);
+        else if (enb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, egrid, dim3(256), 0, t, n_sent);
+        else if (enb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, egrid, dim3(256), 0, t, n_sent);
+        else Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<5>, egrid, dim3(256), 0, t, n_sent);
         int nb = 1;                              // hypotheses per block of the context kernel
         while (nb < beam && (long long)n_sent * ((beam + nb - 1) / nb) > 256) ++nb;
         const int passes = (beam + nb - 1) / nb;
         const size_t al_bytes = (size_t)(l + ATTC_UN - 1) / ATTC_UN * ATTC_UN * nb * sizeof(double);
-        if (sent_off && C % 2 == 0 && C <= 2 * ATT_MAX_THREADS && (!codes || ldq <= 2 * ATT_MAX_THREADS) && al_bytes <= 60 * 1024) {
+        if (C % 2 == 0 && C <= 2 * ATT_MAX_THREADS && (!codes || ldq <= 2 * ATT_MAX_THREADS) && al_bytes <= 60 * 1024) {
             const dim3 grid((n_sent + 7) / 8 * 8 * passes);
 #define ATTC(K) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_context_kernel<K>, grid, dim3(ATT_MAX_THREADS), al_bytes, t, n_sent, passes)
             switch (nb) {
@@ -963,7 +927,7 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
             return q8i_launch_check(ctx, "attention context");
         }
         // (block numbers are dealt to sentences in groups of eight, see the kernel: the grid covers whole groups)
-        const int fin_blocks = sent_off ? (n_sent + 7) / 8 * 8 * beam : n;
+        const int fin_blocks = (n_sent + 7) / 8 * 8 * beam;
         Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_finish_kernel, dim3(fin_blocks), dim3(ATT_MAX_THREADS), 0, t, n);
     } else {
         Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_kernel, dim3(l, n), dim3(ATT_THREADS), 0, t);
