@@ -209,52 +209,57 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const 
 // branch around a load or a store: inside a branch the compiler waits for each of them on the
 // spot, and a thread's loads and stores become as many memory round trips in a row.
 // (Moved as plain 16-byte vectors: nothing here looks inside the values.)
+// (Everything arrives as a value of its own: a choice between fields of a structure behind a reference becomes a choice
+// between their addresses, the structure then lives in memory, and every field read is a memory round trip.)
 template <int ROWS, bool STATES>
-__device__ __forceinline__ void beam_gather_rows(const BeamUpdateArgs &a, const int *s_parent, const int *s_token)
+__device__ __forceinline__ void beam_gather_rows(int n, int H, int E, const float *s_step, float *s_next, const float *E_tgt, float *y_emb,
+                                                 const int8_t *Eq, const float *Es, const int8_t *sq_in, const float *ss_in,
+                                                 int8_t *yq_out, float *ys_out, int8_t *sq_out, float *ss_out, int ldy, int lds,
+                                                 const int *s_parent, const int *s_token)
 {
     const int tid = threadIdx.x;
-    const int H4 = a.H >> 2, E4 = a.E >> 2;
-    const v4i *s4 = (const v4i *)a.s_step;
-    v4i *sn4 = (v4i *)a.s_next;
+    const int H4 = H >> 2, E4 = E >> 2;
+    const v4i *s4 = (const v4i *)s_step;
+    v4i *sn4 = (v4i *)s_next;
     // The embedding rows are shorter than a pass of 256 pieces; the threads past their end move the rows'
     // codes instead (first pass only): pieces [E4, E4 + ldy / 16) of a "row" are the embedding row's codes,
     // the next lds / 16 the codes of the parent's state.  Each thread has one source and one destination
     // (base, pieces per row, piece) and, per row, the index its source is gathered by.
-    const int Y16 = a.Eq ? a.ldy >> 4 : 0, S16 = a.Eq ? a.lds >> 4 : 0;
+    const int Y16 = Eq ? ldy >> 4 : 0, S16 = Eq ? lds >> 4 : 0;
     const bool is_y = tid >= E4 && tid < E4 + Y16, is_s = tid >= E4 + Y16 && tid < E4 + Y16 + S16;
-    const v4i *src0 = is_y ? (const v4i *)a.Eq : is_s ? (const v4i *)a.sq_in : (const v4i *)a.E_tgt;
-    v4i *dst0 = is_y ? (v4i *)a.yq_out : is_s ? (v4i *)a.sq_out : (v4i *)a.y_emb;
+    const v4i *src0 = is_y ? (const v4i *)Eq : is_s ? (const v4i *)sq_in : (const v4i *)E_tgt;
+    v4i *dst0 = is_y ? (v4i *)yq_out : is_s ? (v4i *)sq_out : (v4i *)y_emb;
     const int pitch0 = is_y ? Y16 : is_s ? S16 : E4;
     const int piece0 = is_y ? tid - E4 : is_s ? tid - E4 - Y16 : min(tid, E4 - 1);
     // their scales: thread q & 7 of every wave fetches those of row q (the same words for all waves), thread q stores them
     // (unconditional loads: without codes they read the first floats of the tables and drop them)
-    const int qs = min(tid & 7, a.n - 1);
-    const float ys = *(a.Eq ? a.Es + s_token[qs] : a.E_tgt), ss = *(a.Eq && a.ss_in ? a.ss_in + s_parent[qs] : a.s_step);
+    const int qs = min(tid & 7, n - 1);
+    const float ys = *(Eq ? Es + s_token[qs] : E_tgt), ss = *(Eq && ss_in ? ss_in + s_parent[qs] : s_step);
     for (int c0 = 0; c0 < (STATES ? max(H4, E4) : E4); c0 += 256) {
         const int ch = min(c0 + tid, H4 - 1);
         const bool first = c0 == 0;
-        const v4i *src = first ? src0 : (const v4i *)a.E_tgt;
-        v4i *dst = first ? dst0 : (v4i *)a.y_emb;
+        const v4i *src = first ? src0 : (const v4i *)E_tgt;
+        v4i *dst = first ? dst0 : (v4i *)y_emb;
         const int pitch = first ? pitch0 : E4, piece = first ? piece0 : min(c0 + tid, E4 - 1);
         const bool by_parent = first && is_s;
         v4i vs[ROWS], ve[ROWS];
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
-            const int qq = min(q, a.n - 1);
+            const int qq = min(q, n - 1);
             const int par = s_parent[qq], tok = s_token[qq];
             if (STATES) vs[q] = s4[(size_t)par * H4 + ch];
             ve[q] = src[(size_t)(by_parent ? par : tok) * pitch + piece];
         }
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
-            const int qq = min(q, a.n - 1);
+            const int qq = min(q, n - 1);
             if (STATES) sn4[(size_t)qq * H4 + ch] = vs[q];
             dst[(size_t)qq * pitch + piece] = ve[q];
         }
     }
-    if (a.Eq && tid < a.n) {
-        a.ys_out[tid] = ys;
-        if (a.ss_out) a.ss_out[tid] = ss;
+    if (Eq && tid < n) {
+        ys_out[tid] = ys;
+        if (ss_out) ss_out[tid] = ss;
     }
 }
 
@@ -262,15 +267,19 @@ __device__ __forceinline__ void beam_gather(const BeamUpdateArgs &a, const int *
 {
     const int tid = threadIdx.x;
     if (((a.H | a.E) & 3) == 0) {
+#define GATHER(R, S)                                                                                                      \
+    beam_gather_rows<R, S>(a.n, a.H, a.E, a.s_step, a.s_next, a.E_tgt, a.y_emb, a.Eq, a.Es, a.sq_in, a.ss_in, a.yq_out, a.ys_out, \
+                           a.sq_out, a.ss_out, a.ldy, a.lds, s_parent, s_token)
         // (a compute unit moves these rows at about 50 GB/s: rows that only repeat the last one cost as much
         // as the others, so the row count follows the beam in three steps)
         if (!a.s_next) {
-            if (a.n <= 4) beam_gather_rows<4, false>(a, s_parent, s_token);
-            else if (a.n <= 6) beam_gather_rows<6, false>(a, s_parent, s_token);
-            else beam_gather_rows<Q8_MAX_BEAM, false>(a, s_parent, s_token);
-        } else if (a.n <= 4) beam_gather_rows<4, true>(a, s_parent, s_token);
-        else if (a.n <= 6) beam_gather_rows<6, true>(a, s_parent, s_token);
-        else beam_gather_rows<Q8_MAX_BEAM, true>(a, s_parent, s_token);
+            if (a.n <= 4) GATHER(4, false);
+            else if (a.n <= 6) GATHER(6, false);
+            else GATHER(Q8_MAX_BEAM, false);
+        } else if (a.n <= 4) GATHER(4, true);
+        else if (a.n <= 6) GATHER(6, true);
+        else GATHER(Q8_MAX_BEAM, true);
+#undef GATHER
     } else {
         for (int e = tid; a.s_next && e < a.n * a.H; e += blockDim.x) {
             const int q = e / a.H, c = e - q * a.H;

@@ -693,8 +693,8 @@ struct PanelSelectArgs {
 };
 
 // Tiles per wave whose weights are requested together.  Two keep the kernel at 128 registers and four blocks on a
-// compute unit, so that 1000 slots run in one round: 34.6 -> 26.3 us (320 slots, little more than one block per unit
-// either way: 17.8 -> 17.3); four (200 registers) save a round trip where a slot has more than eight tiles to look at.
+// compute unit (three for rows of 640 bytes), so that 1000 slots run in one round: 34.6 -> 26.3 us (320 slots, little
+// more than one block per unit either way: 17.8 -> 17.3; with the search step's arguments in registers 24.7 and 15.5); four (200 registers) save a round trip where a slot has more than eight tiles to look at.
 #define PSEL_BATCH 2
 
 // FUSE: the search step of every sentence runs here too, as in out_select_kernel: each block publishes its
@@ -704,7 +704,7 @@ struct PanelSelectArgs {
 // blocks it waits for have lower indices and were dispatched before it, so the wait ends whatever the
 // device holds at once; it is bounded all the same, and a wait that gives up sets wait_err.
 template <int KC, bool FUSE>
-__global__ __launch_bounds__(256, 4) void panel_select_kernel(PanelSelectArgs a)
+__global__ __launch_bounds__(256, KC <= 8 ? 4 : 3) void panel_select_kernel(PanelSelectArgs a)
 {
     __shared__ unsigned long long s_best[16];
     __shared__ unsigned short s_q[OUT_MAX_TILES];
