@@ -1041,6 +1041,37 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(QuantJobs jobs)
     __shared__ float s_red[4];
     const QuantJob &J = jobs.j[blockIdx.y];
     const int j = blockIdx.x;
+    // Vectors of at most 2048 floats in whole 16-byte pieces stay in registers between their maximum and their codes (read
+    // again after the barrier, they are a second round trip: 5.4 -> 4.6 us for 1024 vectors of 2048).
+    if (J.K <= 2048 && J.K % 4 == 0 && J.ld <= 2048) {
+        const int tid = threadIdx.x;
+        const __amdgpu_buffer_rsrc_t rx = q8_rsrc(J.X + (size_t)j * J.ldx, (size_t)J.K * sizeof(float));
+        float4 v[2];
+        float m = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) v[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rx, (t * 256 + tid) * 16, 0, 0));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[t].x), fabsf(v[t].y)), fmaxf(fabsf(v[t].z), fabsf(v[t].w))));
+        m = wave_max_f(m);
+        if ((tid & 63) == 0) s_red[tid >> 6] = m;
+        __syncthreads();
+        float scale, inv;
+        q8_scale_of(fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3])), scale, inv);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int k = (t * 256 + tid) * 4;                   // (zeros past K)
+            if (k < J.ld) *(int *)(J.xq + (size_t)j * J.ld + k) = q8_pack4(v[t].x, v[t].y, v[t].z, v[t].w, inv);
+        }
+        if (tid == 0) {
+            J.xscale[j] = scale;
+            if (J.tap_scale) J.tap_scale[j] = scale;
+        }
+        if (J.tap_xq) {
+            __syncthreads();
+            for (int k = tid; k < J.K; k += 256) J.tap_xq[(size_t)j * J.K + k] = J.xq[(size_t)j * J.ld + k];
+        }
+        return;
+    }
     block_quantize<1>(J.X + (size_t)j * J.ldx, 1, J.K, J.ldx, J.ld, J.xq + (size_t)j * J.ld, s_scale, s_red);
     if (threadIdx.x == 0) {
         J.xscale[j] = s_scale[0];
