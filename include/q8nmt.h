@@ -266,7 +266,8 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
  * Section 6 names).  Sentence s owns hypothesis slots [s beam, (s + 1) beam) of y_emb,
  * s_prev, s_out [n x H], ctx_out [n x C] (n = n_sent * beam <= 1024) and rows
  * [sent_off[s], sent_off[s + 1]) of P [L x A] and enc_h [L x C]; sent_off is a device
- * array of n_sent + 1 int32, max_l the longest sentence (<= 1024).  alpha_out
+ * array of n_sent + 1 int32 (its first need not be 0: a group of sentences out of a larger
+ * batch is stepped with sent_off + first), max_l the longest sentence (<= 1024).  alpha_out
  * [n x max_l] (row pitch max_l, entries past the sentence's length untouched) and
  * s_mid_out [n x H] may be NULL.  Per-vector quantization makes every slot's result
  * the one cgru_decoder_step_q8 gives for that slot alone. */

@@ -2,6 +2,7 @@
 // output network g of Eq. 2 ("Pieces of Eight: 8-bit Neural Machine Translation").
 #include "q8_internal.h"
 #include "q8_gemv_fast.h"
+#include "q8_index.h"
 
 // ======================================================================== attention ==
 
@@ -372,9 +373,8 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
     __shared__ int s_first;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h0 = blockIdx.y * NB, A = a.A;
-    const long long total = a.sent_off[n_sent];
-    const int pend = (int)(total * (blockIdx.x + 1) / gridDim.x);
-    int pos = (int)(total * blockIdx.x / gridDim.x);
+    int pos, pend;
+    q8_position_run(a.sent_off, n_sent, (int)blockIdx.x, (int)gridDim.x, &pos, &pend);
     if (pos >= pend) return;
     for (int s = tid; s < n_sent; s += 256)                  // the sentence of the run's first position
         if (a.sent_off[s] <= pos && pos < a.sent_off[s + 1]) s_first = s;

@@ -621,3 +621,24 @@ def test_context_of_several_hypotheses_per_block(q, beam, H, lens):
         assert_same(r["alpha"][sl, :lens[i]], np_(one["alpha"]), "alpha, sentence %d" % i)
         assert_same(r["ctx"][sl], np_(one["ctx"]), "context, sentence %d" % i)
         assert_same(r["s"][sl], np_(one["s"]), "state, sentence %d" % i)
+
+
+@pytest.mark.parametrize("beam,A,H,lens,s0", [(5, 64, 64, [30, 30, 30, 30, 30, 30], 3), (1, 36, 36, [4] * 30, 20), (8, 1028, 36, [9, 60, 2, 33, 1], 2)])
+def test_a_group_of_a_packed_batch_is_stepped_by_its_offsets(q, ctx, beam, A, H, lens, s0):
+    """A group of sentences out of a larger packed batch, stepped with the offsets from its first sentence on and the
+    batch's own P and encoder states (the first offset is not 0): bit for bit what the same group gives packed alone."""
+    E = 36
+    S = len(lens) - s0
+    p = synth.cgru_step(seed=7, E=E, H=H, A=A, l=1, n_beam=S * beam)
+    rng = np.random.default_rng(beam)
+    L = sum(lens)
+    P, enc = ctx.f32(rng.standard_normal((L, A)).astype(np.float32)), ctx.f32(rng.standard_normal((L, 2 * H)).astype(np.float32))
+    gru = lambda pre: gpu_gru(q, ctx, p, pre)
+    w = q.CgruWeights(gru("dec_r"), gpu_mat(q, ctx, p["att.U"], False), ctx.f32(p["att.v"]), gru("dec_q"))
+    off = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=ctx.device)
+    y, s = ctx.f32(p["y_emb"]), ctx.f32(p["s_prev"])
+    first, max_l = int(off[s0]), max(lens[s0:])
+    r = q.cgru_decoder_step_batch_q8(ctx, w, P, enc, off[s0:], beam, max_l, y, s)
+    alone = q.cgru_decoder_step_batch_q8(ctx, w, P[first:].contiguous(), enc[first:].contiguous(), (off[s0:] - first).contiguous(), beam, max_l, y, s)
+    for k in ("alpha", "ctx", "s"):
+        assert_same(r[k], np_(alone[k]), k)
