@@ -4,6 +4,7 @@
 // The arithmetic is that of the streaming kernels: per-vector activation codes, exact
 // int32 sums, one fp32 scale product, separate bias addition.
 #include "q8_internal.h"
+#include "q8_index.h"
 
 struct GemmArgs {
     const int8_t *W;       // [rows x ld] int8
@@ -844,19 +845,18 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
     // Blocks whose numbers agree modulo 8 share an XCD: they take neighbouring runs, the same ones in every column
     // group, so that an XCD's L2 is asked for one eighth of the matrix and gives it to all groups.
     const int gx = gridDim.x, rank = gx % 8 == 0 ? ((int)blockIdx.x & 7) * (gx >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
-    const long long units = (long long)nrp * nct, nw = (long long)gx * VP_WAVES, w0 = (long long)rank * VP_WAVES;
-    const int u0 = (int)(units * (w0 + wave) / nw), u1 = (int)(units * (w0 + wave + 1) / nw);
+    int u0, u1, rp0;                                          // the wave's units, the block's first rows
+    q8_panel_run(nrp, nct, gx, VP_WAVES, rank, wave, &u0, &u1, &rp0);
     int rp = u0 / nct, ct = u0 - rp * nct;
-    const int rp0 = (int)(units * w0 / nw) / nct;             // the block's first rows
 
     // weights: lane (row i, k half h) of k step s holds bytes 32 s + 16 h .. of row 64 rp + 32 t + i; in the packed order
-    // that is 64-byte block s / 2 of the row's tile, piece 2 (s % 2) + h
+    // that is 64-byte block s / 2 of the row's tile, piece 2 (s % 2) + h.  The whole offset is the vector offset and lies
+    // inside the packed weights (rows past the matrix come as -inf below); a scalar offset is not sure to be checked.
     const __amdgpu_buffer_rsrc_t rw = q8_rsrc(a.tiles, (size_t)a.ntiles * (KS / 2) * 1024);
     const __amdgpu_buffer_rsrc_t rpm = q8_rsrc(a.part_max, (size_t)n * a.ntiles * 4), rps = q8_rsrc(a.part_sum, (size_t)n * a.ntiles * 8);
-    const int woff = ((i >> 4) * (KS / 2) << 10) + h * 256 + (i & 15) * 16;
     v4i A[2][KS];
-    auto weights = [&](int pair, int t, int s) {
-        return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, woff, (2 * pair + t) * (KS << 10) + (s >> 1) * 1024 + (s & 1) * 512, 0));
+    auto weights = [&](unsigned at, int s) {
+        return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(at + q8_panel_step(s)), 0, 0));
     };
     // the codes of this block's slots into LDS (slots past the panel are zero): eight 16-byte pieces per
     // thread and round, requested together through a bounds-checked descriptor (no branch around a
@@ -872,8 +872,9 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
                 v[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(p < total ? (unsigned)p * 16u : Q8_OOB), 0, 0));
             }
             if (p0 == 0) {
+                const unsigned at0 = q8_panel_weight(2 * rp, lane, KS, a.ntiles), at1 = q8_panel_weight(2 * rp + 1, lane, KS, a.ntiles);
 #pragma unroll
-                for (int s = 0; s < KS; ++s) { A[0][s] = weights(rp, 0, s); A[1][s] = weights(rp, 1, s); }
+                for (int s = 0; s < KS; ++s) { A[0][s] = weights(at0, s); A[1][s] = weights(at1, s); }
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -900,13 +901,14 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
         const int8_t *bt = bp + ct * 32 * pitch;
         v16i acc[2] = {{}, {}};
         if (ct == nct - 1 && u + 1 < u1) {                    // uniform: the next unit starts other rows
+            const unsigned at0 = q8_panel_weight(2 * rp + 2, lane, KS, a.ntiles), at1 = q8_panel_weight(2 * rp + 3, lane, KS, a.ntiles);
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 const v4i x = *(const v4i *)(bt + 32 * s);
                 acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[0][s], x, acc[0], 0, 0, 0);
                 acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[1][s], x, acc[1], 0, 0, 0);
-                A[0][s] = weights(rp + 1, 0, s);
-                A[1][s] = weights(rp + 1, 1, s);
+                A[0][s] = weights(at0, s);
+                A[1][s] = weights(at1, s);
             }
         } else {
 #pragma unroll

@@ -18,3 +18,26 @@ Q8_INDEX_FN void q8_position_run(const int *off, int n_sent, int b, int blocks, 
     *pos = first + (int)(total * b / blocks);
     *end = first + (int)(total * (b + 1) / blocks);
 }
+
+// ---- the vocabulary panel (vocab_panel_kernel): units of 64 rows x 32 slots, dealt to the waves of a column group's blocks
+// in even runs, slots first ----
+
+// Units [*u0, *u1) of wave w of the block of rank b, and the 64-row group *rp0 that the block's first wave begins in.
+Q8_INDEX_FN void q8_panel_run(int row_groups, int slot_tiles, int blocks, int waves, int b, int w, int *u0, int *u1, int *rp0)
+{
+    const long long units = (long long)row_groups * slot_tiles, nw = (long long)blocks * waves, w0 = (long long)b * waves;
+    *u0 = (int)(units * (w0 + w) / nw);
+    *u1 = (int)(units * (w0 + w + 1) / nw);
+    *rp0 = (int)(units * w0 / nw) / slot_tiles;
+}
+
+// Byte offset, in tile-packed weights of ntiles tiles of ks / 2 blocks of 1 KiB, of what a lane multiplies in k step 0 of
+// the 32-row half `half` (two tiles): row lane % 32, k half lane / 32.  Step s lies q8_panel_step(s) bytes further on.
+// Tiles past the matrix (the last half's second tile, halves past the last, waves without a unit) are the last tile once
+// more: nothing is read outside the packed weights, whatever becomes of an offset in a bounds check.
+Q8_INDEX_FN unsigned q8_panel_weight(int half, int lane, int ks, int ntiles)
+{
+    const int i = lane & 31, t = 2 * half + (i >> 4), tile = t < ntiles ? t : ntiles - 1;
+    return ((unsigned)tile * (unsigned)(ks / 2) << 10) + (unsigned)(lane >> 5) * 256u + (unsigned)(i & 15) * 16u;
+}
+Q8_INDEX_FN unsigned q8_panel_step(int s) { return (unsigned)(s >> 1) * 1024u + (unsigned)(s & 1) * 512u; }

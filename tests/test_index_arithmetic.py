@@ -38,3 +38,32 @@ def test_position_runs_cover_the_sentences_of_a_group_once(lib, first, lens, blo
     assert (end >= pos).all() and np.ptp(end - pos) <= 1
     for p in pos[pos < end]:
         assert ((off[:-1] <= p) & (p < off[1:])).sum() == 1
+
+
+@pytest.mark.parametrize("row_groups,slot_tiles,blocks", [(1, 1, 1), (1, 8, 1), (782, 1, 256), (782, 8, 64), (995, 7, 51), (3, 5, 3), (1024, 8, 8)])
+def test_panel_runs_cover_the_units_once(lib, row_groups, slot_tiles, blocks):
+    waves = 8
+    u0, u1, rp0 = (_ints(blocks * waves) for _ in range(3))
+    lib.q8x_panel_runs(row_groups, slot_tiles, blocks, waves, u0, u1, rp0)
+    u0, u1, rp0 = (np.array(v[:]) for v in (u0, u1, rp0))
+    assert u0[0] == 0 and u1[-1] == row_groups * slot_tiles and (u0[1:] == u1[:-1]).all() and np.ptp(u1 - u0) <= 1
+    assert (rp0.reshape(blocks, waves) == (u0.reshape(blocks, waves)[:, :1] // slot_tiles)).all()
+
+
+@pytest.mark.parametrize("ks", [16, 20])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 64, 65, 1009, 50000, 50016, 50032, 50048])
+def test_panel_weights_lie_inside_the_packed_matrix(lib, ks, rows):
+    """Every byte that a wave asks for, for each half that it can come to (one group past the last: a wave without units),
+    is inside the rows / 16 tiles of 32 ks bytes times 16 that are there, and where the tile exists it is the right one:
+    row r's piece (k step s, half h) lies at tile r / 16, 64-byte block s / 2, piece 2 (s % 2) + h."""
+    ntiles = (rows + 15) // 16
+    groups = (rows + 63) // 64
+    at = (ctypes.c_uint * (64 * ks))()
+    lane, step = np.arange(64)[:, None], np.arange(ks)[None, :]
+    for half in {0, 1, *range(max(0, 2 * groups - 3), 2 * groups + 2)}:
+        lib.q8x_panel_weights(half, ks, ntiles, at)
+        got = np.array(at[:], dtype=np.int64).reshape(64, ks)
+        assert got.min() >= 0 and got.max() + 16 <= ntiles * 16 * 32 * ks
+        row = 32 * half + (lane & 31)
+        want = ((row >> 4) * (ks // 2) + (step >> 1)) * 1024 + (2 * (step & 1) + (lane >> 5)) * 256 + (row & 15) * 16
+        assert (got == want)[np.broadcast_to(row < 16 * ntiles, got.shape)].all()
