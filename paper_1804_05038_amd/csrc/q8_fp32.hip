@@ -49,7 +49,11 @@ __device__ __forceinline__ void f32_load(F32Regs<RW, UN> &R, const __amdgpu_buff
         }
 }
 
-// x: N vectors in LDS, pitch floats apart (pitch = cols rounded up to 4, zeros past cols).
+// LDS pitch of a vector: where a row's last chunk of 256 columns is incomplete, four zeros at least follow the vector.
+// The lanes past cols read those: their weights are zeros, and zero times an infinite entry of x would not be zero.
+__host__ __device__ constexpr int f32_pitch(int cols) { return cols % 256 == 0 ? cols : ((cols + 3) & ~3) + 4; }
+
+// x: N vectors in LDS, pitch floats apart (f32_pitch, zeros past cols).
 template <int N, int RW, int UN>
 __device__ __forceinline__ void f32_fma(const F32Regs<RW, UN> &R, const float *x, int pitch, int cols, int c0, int lane, double (&acc)[RW][N])
 {
@@ -104,8 +108,8 @@ __device__ __forceinline__ void f32_product(F32Regs<RW, UN> &R, const __amdgpu_b
 // N vectors into LDS at the pitch of f32_fma, by a block of 256 threads.  Loads come back in the order they were
 // issued, so the vectors are requested before the weights and stored to LDS behind the weights' requests: staging
 // them in one go after the requests made the block wait for the weights first (GRU r 11.7 us, readout 11.8 us).
-// flat (contiguous vectors of whole 16-byte pieces): they lie as they will in LDS, and XB pieces per thread are
-// requested at once; longer vectors and all other layouts follow in f32_x_store.
+// flat (contiguous vectors of whole 16-byte pieces): they lie as they will in LDS, but for the zeros between them, and XB
+// pieces per thread are requested at once; longer vectors and all other layouts follow in f32_x_store.
 template <int XB>
 struct F32X {
     float4 v[XB];
@@ -123,17 +127,28 @@ template <int N, int XB>
 __device__ __forceinline__ void f32_x_store(const F32X<XB> &R, float *s, const float *X, int cols, int ldx, int flat)
 {
     __builtin_amdgcn_sched_barrier(0);
+    const int pitch = f32_pitch(cols);
     if (flat) {
         const int total = N * cols;
+        auto store = [&](auto at) {                            // element k of the run goes to at(k)
 #pragma unroll
-        for (int i = 0; i < XB; ++i) {
-            const int k = (i * 256 + (int)threadIdx.x) * 4;
-            if (k < total) *(float4 *)(s + k) = R.v[i];
+            for (int i = 0; i < XB; ++i) {
+                const int k = (i * 256 + (int)threadIdx.x) * 4;
+                if (k < total) *(float4 *)(s + at(k)) = R.v[i];
+            }
+            for (int k = (XB * 256 + (int)threadIdx.x) * 4; k < total; k += 1024) *(float4 *)(s + at(k)) = *(const float4 *)(X + k);
+        };
+        if (pitch == cols) {
+            store([](int k) { return k; });
+        } else {
+            // four further on per vector before it; the quotient by a reciprocal: k < 2^16, so (k + 1/2) / cols lies further
+            // from an integer than the roundings move it
+            const float inv = __builtin_amdgcn_rcpf((float)cols);
+            store([&](int k) { return k + 4 * (int)(((float)k + 0.5f) * inv); });
+            if ((int)threadIdx.x < N) *(float4 *)(s + (size_t)threadIdx.x * pitch + cols) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        for (int k = (XB * 256 + (int)threadIdx.x) * 4; k < total; k += 1024) *(float4 *)(s + k) = *(const float4 *)(X + k);
         return;
     }
-    const int pitch = (cols + 3) & ~3;
     for (int j = 0; j < N; ++j)
         for (int k = threadIdx.x; k < pitch; k += 256) s[(size_t)j * pitch + k] = k < cols ? X[(size_t)j * ldx + k] : 0.0f;
 }
@@ -160,7 +175,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
     const F32Job &J = jobs.j[t];
     const int blk = blockIdx.x - jobs.nblk[t], nblk = jobs.nblk[t + 1] - jobs.nblk[t];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cols = J.cols, rows = J.rows, pitch = (cols + 3) & ~3;
+    const int cols = J.cols, rows = J.rows, pitch = f32_pitch(cols);
     __amdgpu_buffer_rsrc_t row[RW];
     F32Regs<RW, UN> R;
     auto request = [&](int r0) {
@@ -239,7 +254,7 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
     constexpr int UN = GH_PRE ? 4 : 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, H = a.H, I = a.I;
     const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave);
-    const int px = (I + 3) & ~3, ph = (H + 3) & ~3;
+    const int px = f32_pitch(I), ph = f32_pitch(H);
     __amdgpu_buffer_rsrc_t rx[3], rh[3];
     F32Regs<3, UN> X, Hh;
 #pragma unroll
@@ -317,7 +332,7 @@ __global__ __launch_bounds__(256) void readout_f32_kernel(F32ReadoutArgs a)
         row[m][0] = f32_row(a.W[m], unit, a.R, a.ld[m]);
         f32_load<1, 4>(R[m], row[m], a.cols[m], 0, lane);
     }
-    const int p0 = (a.cols[0] + 3) & ~3, p1 = (a.cols[1] + 3) & ~3;
+    const int p0 = f32_pitch(a.cols[0]), p1 = f32_pitch(a.cols[1]);
     f32_x_store<N, N>(x0, s_x, a.x[0], a.cols[0], a.cols[0], a.flat);
     f32_x_store<N, N>(x1, s_x + (size_t)N * p0, a.x[1], a.cols[1], a.cols[1], a.flat);
     f32_x_store<N, 2 * N>(x2, s_x + (size_t)N * (p0 + p1), a.x[2], a.cols[2], a.cols[2], a.flat);
@@ -326,7 +341,7 @@ __global__ __launch_bounds__(256) void readout_f32_kernel(F32ReadoutArgs a)
     float *s = s_x;
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-        const int pitch = (a.cols[m] + 3) & ~3;
+        const int pitch = f32_pitch(a.cols[m]);
         double acc[1][N];
 #pragma unroll
         for (int j = 0; j < N; ++j) acc[0][j] = 0.0;
@@ -372,7 +387,7 @@ q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n, floa
 {
     F32Jobs jobs;
     F32Stats st = {part_max, part_sum, q8i_out_tiles(d[0].W->rows)};
-    int blocks = 0, max_cols4 = 0;
+    int blocks = 0, max_pitch = 0;
     long long rows = 0;
     for (int t = 0; t < njobs; ++t) rows += d[t].W->rows;
     // Rows per wave: what fills the chip's 1024 SIMDs first (a wave's loads in flight are the same 8 either way),
@@ -387,19 +402,18 @@ q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n, floa
             // (more blocks than are resident together only stage the vectors more often)
             if (b > 1024) b = 1024;
             blocks += b;
-            const int c4 = (q.W->cols + 3) & ~3;
-            if (c4 > max_cols4) max_cols4 = c4;
+            if (f32_pitch(q.W->cols) > max_pitch) max_pitch = f32_pitch(q.W->cols);
         }
     }
     jobs.nblk[F32_MAX_JOBS] = blocks;
     for (int t = njobs; t < F32_MAX_JOBS; ++t) jobs.nblk[t] = blocks;
-    const size_t smem = (size_t)n * max_cols4 * sizeof(float);
+    const size_t smem = (size_t)n * max_pitch * sizeof(float);
 #define F32_GEMV(K)                                                                                                        \
     do {                                                                                                                   \
-        if (part_max) Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, (gemv_f32_kernel<K, 4, 2, true>), dim3(blocks), dim3(256), smem, jobs, st);  \
-        else if (rw == 4) Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, (gemv_f32_kernel<K, 4, 2, false>), dim3(blocks), dim3(256), smem, jobs, st); \
-        else if (rw == 2) Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, (gemv_f32_kernel<K, 2, 4, false>), dim3(blocks), dim3(256), smem, jobs, st); \
-        else Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, (gemv_f32_kernel<K, 1, 8, false>), dim3(blocks), dim3(256), smem, jobs, st);   \
+        void (*kern)(F32Jobs, F32Stats) = part_max ? gemv_f32_kernel<K, 4, 2, true> : rw == 4 ? gemv_f32_kernel<K, 4, 2, false> \
+                                          : rw == 2 ? gemv_f32_kernel<K, 2, 4, false> : gemv_f32_kernel<K, 1, 8, false>;   \
+        if (!f32_lds((const void *)kern, smem)) return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit product: %zu bytes of LDS refused", smem); \
+        Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, kern, dim3(blocks), dim3(256), smem, jobs, st);                                     \
     } while (0)
     F32_FOR_N(n, F32_GEMV)
     return q8i_launch_check(ctx, "gemv_f32");
@@ -423,7 +437,7 @@ q8_status q8i_gru_f32(q8_ctx *ctx, const q8_gru_weights_f32 *g, const float *x, 
     const int I = g->Wx.cols, H = g->Wh.cols;
     const bool flat = f32_flat(x, n, I, I) && (gh_pre || f32_flat(h_prev, n, H, H));
     const F32GruArgs a = {g->Wx.data, g->Wh.data, g->bx, g->bh, x, h_prev, gh_pre, h_out, I, H, g->Wx.ld, g->Wh.ld, flat};
-    const size_t smem = (size_t)n * (((I + 3) & ~3) + (gh_pre ? 0 : ((H + 3) & ~3))) * sizeof(float);
+    const size_t smem = (size_t)n * (f32_pitch(I) + (gh_pre ? 0 : f32_pitch(H))) * sizeof(float);
     const dim3 grid((H + 3) / 4);
 #define F32_GRU(K)                                                                                                          \
     do {                                                                                                                    \
@@ -453,7 +467,7 @@ q8_status q8i_readout_f32(q8_ctx *ctx, const q8_readout_weights_f32 *ro, const f
     for (int m = 0; m < 3; ++m) {
         a.W[m] = W[m]->data; a.x[m] = x[m]; a.cols[m] = W[m]->cols; a.ld[m] = W[m]->ld;
         a.flat &= f32_flat(x[m], n, W[m]->cols, W[m]->cols);
-        smem += (size_t)n * ((W[m]->cols + 3) & ~3) * sizeof(float);
+        smem += (size_t)n * f32_pitch(W[m]->cols) * sizeof(float);
     }
     a.b_t = ro->b_t; a.t_out = t_out; a.R = ro->W_s.rows;
     const dim3 grid((a.R + 3) / 4);

@@ -139,3 +139,47 @@ def test_cells_in_one_launch_equal_products_and_gates(q, ctx, oracle, E, H, A, C
         ctx.check(two.fn(*args))
         assert_same(sv, np_(one["t"]), "t")
         assert_same(two.out["logits"], np_(one["logits"]), "logits")
+
+
+@pytest.mark.parametrize("rows,cols,n", [(40, 620, 2), (2100, 1000, 5), (8200, 260, 8), (33, 7, 3), (64, 2048, 8), (20, 16384, 1), (17, 257, 1)])
+def test_gemv_f32_infinities_stay_in_their_column(q, ctx, rows, cols, n):
+    """An infinite entry of a vector, in its last columns too, gives +-inf by the sign of the row's weight there (not
+    NaN out of what lies past the columns), a row whose weight is 0 there gives NaN, and the other vectors are finite."""
+    rng = np.random.default_rng(rows + cols)
+    W, X = rng.standard_normal((rows, cols)).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
+    W[3, cols - 1] = 0.0
+    M = q.MatF(ctx, W)
+    for col in sorted({0, max(0, cols - 4), cols - 2, cols - 1}):
+        Xi = X.copy()
+        Xi[0, col] = np.inf
+        Y = np_(q.q8_gemv_f32(ctx, M, ctx.f32(Xi)))
+        want = np.where(W[:, col] > 0, np.inf, np.where(W[:, col] < 0, -np.inf, np.nan)).astype(np.float32)
+        np.testing.assert_array_equal(Y[0], want, "column %d" % col)
+        if n > 1:
+            assert_close(Y[1:], Xi[1:].astype(np.float64) @ W.T.astype(np.float64), "the other vectors", rel=3e-7)
+
+
+@pytest.mark.parametrize("E,H,C,n", [(620, 1000, 2000, 5), (36, 44, 88, 1)])
+def test_cells_of_the_32_bit_engine_with_an_infinite_input(q, ctx, E, H, C, n):
+    """The fused cell and readout with an infinite input in the last columns: gates saturate and states stay finite."""
+    p = synth.cgru_step(seed=5, E=E, H=H, A=H, l=3, n_beam=n)
+    gru = _fp32_weights(q, ctx, p)
+    w = q.CgruWeightsF32(gru("dec_r"), q.MatF(ctx, p["att.U"]), ctx.f32(p["att.v"]), gru("dec_q"))
+    y = p["y_emb"].copy()
+    y[0, E - 1] = np.inf
+    P = ctx.f32(np.random.default_rng(1).standard_normal((3, H)).astype(np.float32))
+    r = q.cgru_decoder_step_f32(ctx, w, P, ctx.f32(p["enc_h"]), ctx.f32(y), ctx.f32(p["s_prev"]))
+    with np.errstate(invalid="ignore", over="ignore"):
+        pre = y.astype(np.float64) @ p["dec_r.Wx"].T.astype(np.float64) + p["dec_r.bx"]
+        rec = p["s_prev"].astype(np.float64) @ p["dec_r.Wh"].T.astype(np.float64) + p["dec_r.bh"]
+        sig = lambda v: 1.0 / (1.0 + np.exp(-v))
+        z = sig(pre[:, H:2 * H] + rec[:, H:2 * H])
+        cand = np.tanh(pre[:, 2 * H:] + sig(pre[:, :H] + rec[:, :H]) * rec[:, 2 * H:])
+        ref = (1 - z) * cand + z * p["s_prev"]
+    assert np.isfinite(ref).all()
+    assert_close(r["s_mid"], ref, "s'")
+    assert np.isfinite(np_(r["s"])).all()
+    rng = np.random.default_rng(2)
+    ro = q.ReadoutWeightsF32(*[q.MatF(ctx, rng.standard_normal((H, d)).astype(np.float32) * 0.05) for d in (H, E, C)], ctx.f32(np.zeros(H)))
+    o = q.output_logits_f32(ctx, ro, q.MatF(ctx, rng.standard_normal((50, H)).astype(np.float32)), None, r["s"], ctx.f32(y), r["ctx"], k=12)
+    assert (np.abs(np_(o["t"])[0]) == 1).all() and np.isfinite(np_(o["logits"])).all()
