@@ -346,16 +346,10 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_split_kernel(AttArgs a)
 
 // Many hypotheses (sentences side by side): throughput matters, not the latency of one
 // energy, and the work is split over two kernels.  First the energies, bound by double-precision
-// instructions.  The hypotheses of a sentence attend over the same P, so the exponential of
-//   tanh(x) = 1 - 2 / (e^{2x} + 1),  x = fl(P_ij + a_bj)  (the fp32 sum that Eq. 6's tanh is taken of),
-// is put together from e^{2P} (once per entry of P, for all hypotheses) and e^{2a} (once per block, for all its
-// positions) as e^{2P} e^{2a} (1 + 2 (x - (P + a))): the sum's rounding error, at most half a last place, is
-// known exactly in double and its square is below 1e-15 of what it corrects.  The reciprocals of a thread's four
-// columns share one estimate (the reciprocal of their product, one third-order step: 2^-24.4 cubed) and part by
-// multiplications.  T is within 1e-15 of tanh(x), as q8_tanh_rn is, and rounded to float as there, so the
-// energies are the same but for a last place of T in some 1e-8 of the entries: 15 double-precision operations per
-// (hypothesis, entry) instead of 33.  Products of four e^{2x} + 1 stay inside the range while |P|, |a| <= 44; a
-// wave that sees larger (or non-finite) values takes q8_tanh_rn for that position.
+// instructions.  The hypotheses of a sentence attend over the same P, so the tanh of Eq. 6 is put together from e^{2P}
+// (once per entry of P, for all hypotheses) and e^{2a} (once per block, for all its positions): q8_tanh4_sums, 15
+// double-precision operations per (hypothesis, entry) instead of the 33 of q8_tanh_rn, and the same floats but for one in
+// some millions.  It takes |P|, |a| <= 44; a wave that sees larger (or non-finite) values takes q8_tanh_rn for that position.
 // A thread owns four columns, with a and e^{2a} of NB hypotheses in registers.  The positions of all sentences, back
 // to back, are dealt to the blocks in even runs (the host knows neither the lengths nor their sum): a grid over
 // (positions of the longest sentence, sentences) left some compute units with twice the work of others.  A run is
@@ -424,23 +418,10 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
 #pragma unroll
                     for (int h = 0; h < NB; ++h) {
                         const float af[4] = {av[h].x, av[h].y, av[h].z, av[h].w};
-                        double d[4];
+                        float T[4];
+                        q8_tanh4_sums(pf, af, ep, ea[h], T);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            // what the sum lost in rounding, exactly (Knuth's two-sum), with the sign turned
-                            const float x = pf[c] + af[c], t = x - pf[c], lost = (pf[c] - (x - t)) + (af[c] - t);
-                            const double e2 = ep[c] * ea[h][c];                    // 2 e^{2 (P + a)}
-                            d[c] = fma(e2, -(double)lost, fma(e2, 0.5, 1.0));
-                        }
-                        const double d01 = d[0] * d[1], d23 = d[2] * d[3], dd = d01 * d23;
-                        double y = __builtin_amdgcn_rcp(dd);
-                        const double e = fma(-dd, y, 1.0);
-                        y = fma(y, fma(e, e, e), y);
-                        const double y01 = y * d23, y23 = y * d01;
-                        acc[h] = fma(v[0], (double)(float)fma(-2.0, y01 * d[1], 1.0), acc[h]);
-                        acc[h] = fma(v[1], (double)(float)fma(-2.0, y01 * d[0], 1.0), acc[h]);
-                        acc[h] = fma(v[2], (double)(float)fma(-2.0, y23 * d[3], 1.0), acc[h]);
-                        acc[h] = fma(v[3], (double)(float)fma(-2.0, y23 * d[2], 1.0), acc[h]);
+                        for (int c = 0; c < 4; ++c) acc[h] = fma(v[c], (double)T[c], acc[h]);
                     }
                 } else {
 #pragma unroll

@@ -88,6 +88,38 @@ Q8_MATH_FN float q8_tanh_rn(float a)
     return (float)copysign(t, x);
 }
 
+// tanh of the four float sums x = fl(p + a), |p|, |a| <= 44, from ep = 2 e^{2 p} and ea = e^{2 a} that were made once for
+// many such sums: tanh(x) = 1 - 2 / (e^{2x} + 1) with e^{2x} = e^{2p} e^{2a} (1 + 2 (x - (p + a))).  What the sum lost in
+// rounding is known exactly (Knuth's two-sum); it is at most half a last place of x, and the square that the factor
+// leaves out moves the result by 2 lost^2 (1 - tanh^2) <= 1.5e-15, near |x| = 1.  The four reciprocals are parts of one,
+// that of the product of the four denominators (at most e^704): an estimate good to 2^-24 and one third-order step.
+// Measured on the host over 2^-34 <= |x| <= 64: 2.2e-15 from tanh(x) at most, 6e-16 below |x| = 1/8; an absolute bound,
+// unlike q8_tanh_rn's.  Where |x| < 2^-13, and an absolute bound says little about a float, tanh(x) is x but for less than
+// 0.34 of a last place, so the float nearest to it is x itself.  Above, 6e-16 is 1e-4 of a last place at most: the floats
+// are those of q8_tanh_rn but for one in some 10^5 near |x| = 2^-12, where tanh(x) lies that close to halfway between two.
+Q8_MATH_FN void q8_tanh4_sums(const float *p, const float *a, const double *ep, const double *ea, float *T)
+{
+    float x[4];
+    double d[4];
+    for (int c = 0; c < 4; ++c) {
+        x[c] = p[c] + a[c];
+        const float t = x[c] - p[c], lost = (p[c] - (x[c] - t)) + (a[c] - t);      // (with the sign turned)
+        const double e2 = ep[c] * ea[c];                                           // 2 e^{2 (p + a)}
+        d[c] = fma(e2, -(double)lost, fma(e2, 0.5, 1.0));
+    }
+    const double d01 = d[0] * d[1], d23 = d[2] * d[3], dd = d01 * d23;
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = __builtin_amdgcn_rcp(dd);
+#else
+    double y = 1.0 / dd * (1.0 + 0x1p-24);                                         // (as far off as the device's estimate)
+#endif
+    const double e = fma(-dd, y, 1.0);
+    y = fma(y, fma(e, e, e), y);
+    const double y01 = y * d23, y23 = y * d01;
+    const double r[4] = {y01 * d[1], y01 * d[0], y23 * d[3], y23 * d[2]};
+    for (int c = 0; c < 4; ++c) T[c] = fabsf(x[c]) < 0x1p-13f ? x[c] : (float)fma(-2.0, r[c], 1.0);
+}
+
 // sigmoid(a) = 1 / (1 + e^{-a}); with E = e^{-|a|} in (0, 1]: 1 / (1 + E) for a >= 0, E / (1 + E) below.
 Q8_MATH_FN float q8_sigmoid_rn(float a)
 {

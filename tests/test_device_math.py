@@ -79,3 +79,36 @@ def test_exp_double_accuracy(lib):
     rel = np.abs(got - ref) / ref
     assert rel.max() < 4.5e-16, rel.max()                 # two ulps of double
     assert got[x == 0].tolist() == [1.0] * int((x == 0).sum())
+
+
+def _tanh_of_sums(lib, p, a):
+    y = np.empty_like(p)
+    lib.q8m_tanh_sums.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_long]
+    lib.q8m_tanh_sums(p.ctypes.data, a.ctypes.data, y.ctypes.data, p.size)
+    return y
+
+
+def test_tanh_of_sums_from_the_parts_exponentials(lib):
+    """The attention energies' tanh, put together from e^{2p} and e^{2a}: sums of every magnitude from 2^-34 to 2^6, many
+    out of parts that cancel, next to sums of quite another size (four share a reciprocal).  The result is within 3e-15
+    of tanh(x) before its one rounding, 1e-4 of a last place at |x| = 2^-13 and less above: the float differs from the
+    correctly rounded one at most in the share of samples that lie so close to a tie (2e-4 of those at 2^-13, halved with
+    every octave), by one place; below 2^-13 not at all."""
+    rng = np.random.default_rng(3)
+    n = 1 << 21
+    x = np.ldexp(rng.uniform(1, 2, n), rng.integers(-34, 6, n)) * rng.choice([-1, 1], n)
+    p = np.where(rng.random(n) < 0.5, rng.standard_normal(n) * 2, x * rng.uniform(0, 1, n)).astype(np.float32)
+    a = (x - p).astype(np.float32)
+    p, a = np.clip(p, -44, 44), np.clip(a, -44, 44)
+    zero = rng.random(n) < 0.01
+    a[zero] = -p[zero]
+    s = (p + a).astype(np.float32)
+    got, ref64 = _tanh_of_sums(lib, p, a), np.tanh(s.astype(np.float64))
+    ref = ref64.astype(np.float32)
+    bad = got != ref
+    small = np.abs(s) < 2.0 ** -13
+    assert small.sum() > n // 3 and not bad[small].any(), (s[small & bad][:4], got[small & bad][:4])
+    assert bad.sum() <= 2e-4 * ((np.abs(s) >= 2.0 ** -13) & (np.abs(s) < 2.0 ** -11)).sum(), int(bad.sum())
+    assert (np.abs(got[bad].astype(np.float64) - ref[bad]) <= np.spacing(np.abs(ref[bad]))).all()
+    # (half a last place of a float, and the bound before it)
+    assert (np.abs(got - ref64) <= np.spacing(np.abs(ref)) * 0.5 * (1 + 2e-7) + 3e-15).all()
