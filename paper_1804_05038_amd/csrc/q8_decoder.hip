@@ -484,9 +484,11 @@ __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_finish_kernel(AttAr
 // Wave h derives the weights of hypothesis h while the first states are on their way.  Sums in order of the
 // positions, as att_finish forms them: the same bits.  NB is the smallest that gives at most one block per compute
 // unit: below that, more blocks side by side beat fewer reads (20 sentences, beam 8: 15.6 us with all eight in a block).
-// 64 / 200 sentences of 10 to 60 words at beam 5, C = 2048 (kernel trace): 17.0 / 31.0 us with the kernel above ->
-// 11.6 / 16.6 us.  C > 2048 and more positions than the weights' LDS holds keep the kernel above.  Block numbers as
-// there: the passes over a sentence fall on one XCD.
+// 64 / 200 sentences of 10 to 60 words at beam 5 (kernel trace), the kernel above -> this one: C = 2048 17.9 / 29.6 ->
+// 11.5 / 16.0 us, C = 1024 11.4 / 19.5 -> 8.0 / 10.7, C = 128 6.6 / 10.9 -> 5.2 / 7.6.  A position costs a wave some 20
+// instructions, which bound the sums where few columns are there (C = 128 took 10.8 / 13.5 us while waves without columns
+// went through them too).  C > 2048 and more positions than the weights' LDS holds keep the kernel above.  Block numbers
+// as there: the passes over a sentence fall on one XCD.
 #define ATTC_UN 8
 template <int NB>
 __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_context_kernel(AttArgs a, int n_sent, int passes)
@@ -501,10 +503,12 @@ __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_context_kernel(AttA
     const int o = a.sent_off[sent], l = a.sent_off[sent + 1] - o, lup = (l + ATTC_UN - 1) / ATTC_UN * ATTC_UN;
     const __amdgpu_buffer_rsrc_t rh = q8_rsrc(a.enc_h + (size_t)o * C, (size_t)l * C * sizeof(float));
     const int c = tid * 2;
-    auto request = [&](float2 (&v)[ATTC_UN], int t0) {
+    const bool busy = wave * 128 < C;                            // a wave without columns only joins in at the barriers
+    const unsigned col = c < C ? (unsigned)c * 4u : Q8_OOB, row = (unsigned)C * 4u;
+    auto request = [&](float2 (&v)[ATTC_UN], int t0) {           // (rows past l are past the descriptor)
 #pragma unroll
         for (int u = 0; u < ATTC_UN; ++u)
-            v[u] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rh, (int)(c < C ? (unsigned)((t0 + u) * C + c) * 4u : Q8_OOB), 0, 0));
+            v[u] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rh, (int)(col + (unsigned)(t0 + u) * row), 0, 0));
     };
     float2 v0[ATTC_UN], v1[ATTC_UN];
     if (wave < NB) {
@@ -551,12 +555,22 @@ __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_context_kernel(AttA
             }
         }
     };
-    for (int t = 0; t < lup; t += 2 * ATTC_UN) {
-        if (t + ATTC_UN < lup) request(v1, t + ATTC_UN);
-        add(v0, t);
-        if (t + ATTC_UN < lup) {
-            if (t + 2 * ATTC_UN < lup) request(v0, t + 2 * ATTC_UN);
+    // (no request behind a branch that its use is not behind: the compiler would wait as if it had not been made, for all
+    // that are out)
+    if (busy && lup > 0) {
+        int t = 0;
+        for (; t + 2 * ATTC_UN < lup; t += 2 * ATTC_UN) {
+            request(v1, t + ATTC_UN);
+            add(v0, t);
+            request(v0, t + 2 * ATTC_UN);
             add(v1, t + ATTC_UN);
+        }
+        if (t + ATTC_UN < lup) {
+            request(v1, t + ATTC_UN);
+            add(v0, t);
+            add(v1, t + ATTC_UN);
+        } else {
+            add(v0, t);
         }
     }
     float f[NB][2];
