@@ -345,28 +345,115 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_split_kernel(AttArgs a)
 }
 
 // Many hypotheses (sentences side by side): throughput matters, not the latency of one
-// energy, and the work is split over two kernels.  First the energies, bound by double-precision
-// instructions.  The hypotheses of a sentence attend over the same P, so the tanh of Eq. 6 is put together from e^{2P}
-// (once per entry of P, for all hypotheses) and e^{2a} (once per block, for all its positions): q8_tanh4_sums, 15
-// double-precision operations per (hypothesis, entry) instead of the 33 of q8_tanh_rn, and the same floats but for one in
-// some millions.  It takes |P|, |a| <= 44; a wave that sees larger (or non-finite) values takes q8_tanh_rn for that position.
-// A thread owns four columns, with a and e^{2a} of NB hypotheses in registers.  The positions of all sentences, back
-// to back, are dealt to the blocks in even runs (the host knows neither the lengths nor their sum): a grid over
-// (positions of the longest sentence, sentences) left some compute units with twice the work of others.  A run is
-// worked off in segments of at most ATTE_SEG positions of one sentence; each begins with the exponentials of its
-// hypotheses.  64 / 200 sentences of 10 to 60 words at beam 5, A = 1024 (kernel trace): 27.7 / 76.0 us with one tanh
-// each -> 16.2 / 31.7 us.  A beam of 1 shares no exponentials, but the reciprocals and the even runs: 600 sentences
-// 53 -> 40.5 us.
+// energy, and the work is split over two kernels.  First the energies, by one of three kernels.
+
+// Few columns or positions: block (g, b) of 256 threads takes source positions 8 g .. 8 g + 7 of hypothesis b; thread
+// (p, c) = (tid / 32, tid % 32) sums columns 4 c + 128 u, u = 0, 1, ..., of position 8 g + p, and the 32 partial sums of a
+// position are added across lanes.
+#define ATTP_POS 8
+// Where this kernel is the better one (kernel trace, us, this one against the two below): narrow positions leave most of a
+// wave's 256 columns idle there (A = 64, beam 5, 10 / 200 sentences of 10 to 60 words 3.4 / 16.4 against 5.7 / 17.5, 200 of
+// 3 to 8 words 4.3 against 10.1; A = 256 4.1 / 27.5 and 5.9 against 6.0 / 18.8 and 10.6), and few positions or a beam of 1
+// do not pay for their start at A = 512 and 768 (beam 5, 10 sentences 5.8 against 7.4 and 7.5 against 9.0, but 200
+// sentences 47 against 25 and 67 against 37; beam 1, 200 sentences of 200 to 300 words 41 against 46 and 58 against 65).
+// From A = 1000 on the other two are as fast or faster throughout.
+static bool att_panel_better(int A, int beam, long long positions) { return A <= 256 || (A <= 768 && (beam == 1 || positions < 3072)); }
+__global__ __launch_bounds__(256) void attention_panel_kernel(AttArgs a)
+{
+    const int b = blockIdx.y, tid = threadIdx.x;
+    const float *P, *enc_h;
+    const int l = att_sentence(a, b, P, enc_h);
+    const int i0 = blockIdx.x * ATTP_POS;
+    if (i0 >= l) return;
+    const int p = tid >> 5, c = tid & 31, i = i0 + p;
+    double acc = 0.0;
+    if (i < l) {
+        const float *Pi = P + (size_t)i * a.A;
+        const float *ab = a.a + (size_t)b * a.A;
+        for (int j = 4 * c; j < a.A; j += 128) {                 // A % 4 == 0
+            const float4 pv = *(const float4 *)(Pi + j), av = *(const float4 *)(ab + j), vv = *(const float4 *)(a.v + j);
+            acc = fma((double)vv.x, (double)tanh_rn(pv.x + av.x), acc);
+            acc = fma((double)vv.y, (double)tanh_rn(pv.y + av.y), acc);
+            acc = fma((double)vv.z, (double)tanh_rn(pv.z + av.z), acc);
+            acc = fma((double)vv.w, (double)tanh_rn(pv.w + av.w), acc);
+        }
+    }
+#pragma unroll
+    for (int m = 16; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);     // within the position's 32 lanes
+    if (c == 0 && i < l) a.e[(size_t)b * a.lde + i] = (float)acc;
+}
+
+// A beam of 1 shares no exponentials: one tanh per entry, and nothing is kept from one position to the next.  The
+// positions of all sentences, back to back, are dealt to the waves in even runs (the host knows neither the lengths nor
+// their sum; a grid over (positions of the longest sentence, sentences) left some compute units with twice the work of
+// others), and a wave sums all columns of a position before it adds up its lanes.  A = 1024, 200 / 600 / 1000 sentences of
+// 10 to 60 words (kernel trace) 22.8 / 55.4 / 90 us with the kernel above -> 15.2 / 36.3 / 57, the same of 200 to 300 words
+// 75.5 / 226 / 393 -> 74.8 / 227 / 394 (1024 blocks there: 78.6 and 464); half waves per position, whose first search takes
+// twice as long, 16.9 us at 200 and 66.6 at 1000.
+// Four waves per SIMD where there are positions for them, eight where each still gets more than a few.
+static unsigned att_greedy_blocks(long long positions) { return positions < 4096 ? (unsigned)(positions + 3) / 4 : positions < 32768 ? 1024 : 2048; }
+__global__ __launch_bounds__(256) void attention_greedy_kernel(AttArgs a, int n_sent)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), A = a.A;
+    int pos, pend;
+    q8_position_run(a.sent_off, n_sent, (int)blockIdx.x * 4 + wave, (int)gridDim.x * 4, &pos, &pend);
+    if (pos >= pend) return;
+    int found = -1;                                          // the sentence of the run's first position: one lane finds it
+    for (int s = lane; s < n_sent; s += 64)
+        if (a.sent_off[s] <= pos && pos < a.sent_off[s + 1]) found = s;
+    int sent = __builtin_amdgcn_readlane(found, __builtin_ctzll(__ballot(found >= 0)));
+    for (; pos < pend; ++pos) {
+        while (a.sent_off[sent + 1] <= pos) ++sent;
+        // (columns past A read as zero, and count for nothing; four chunks of 256 are requested together)
+        const size_t bytes = (size_t)A * sizeof(float);
+        const __amdgpu_buffer_rsrc_t rp = q8_rsrc(a.P + (size_t)pos * A, bytes), ra = q8_rsrc(a.a + (size_t)sent * A, bytes), rv = q8_rsrc(a.v, bytes);
+        double acc = 0.0;
+        for (int j0 = 0; j0 < A; j0 += 1024) {
+            float4 pv[4], av[4], vv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int at = (j0 + 256 * u + 4 * lane) * 4;
+                pv[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rp, at, 0, 0));
+                av[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(ra, at, 0, 0));
+                vv[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rv, at, 0, 0));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (j0 + 256 * u >= A) break;                // uniform
+                acc = fma((double)vv[u].x, (double)tanh_rn(pv[u].x + av[u].x), acc);
+                acc = fma((double)vv[u].y, (double)tanh_rn(pv[u].y + av[u].y), acc);
+                acc = fma((double)vv[u].z, (double)tanh_rn(pv[u].z + av[u].z), acc);
+                acc = fma((double)vv[u].w, (double)tanh_rn(pv[u].w + av[u].w), acc);
+            }
+        }
+        acc = wave_sum_d(acc);
+        if (lane == 0) a.e[(size_t)sent * a.lde + (pos - a.sent_off[sent])] = (float)acc;
+    }
+}
+
+// Beams of 2 and more: bound by double-precision instructions, and the hypotheses of a sentence attend over the same P, so
+// the tanh of Eq. 6 is put together from e^{2P} (once per entry of P, for all hypotheses) and e^{2a} (once per block, for
+// all its positions): q8_tanh4_sums, 15 double-precision operations per (hypothesis, entry) instead of the 33 of
+// q8_tanh_rn, and the same floats but for one in some millions.  It takes |P|, |a| <= 44; a wave that sees larger (or
+// non-finite) values takes q8_tanh_rn for that position.
+// A thread owns four columns, with a and e^{2a} of NB hypotheses in registers; as many waves as the columns fill work on a
+// position, and a block on one or two positions at a time.  Positions are dealt to the blocks in even runs.  A run
+// is worked off in segments of at most ATTE_SEG positions per group of waves, of one sentence; each begins with the
+// exponentials of its hypotheses.  Kernel trace, 64 / 200 sentences of 10 to 60 words at beam 5, one tanh per entry ->
+// this kernel: A = 1024 31.3 / 87 -> 18.2 / 38 us, A = 512 17.9 / 47 -> 15.1 / 25.
 #define ATTE_SEG 16
 #define ATTE_BLOCKS 768
 #define ATTE_RANGE 44.0f
 template <int NB>
 __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int n_sent)
 {
-    __shared__ double s_part[4][ATTE_SEG][NB];
+    __shared__ double s_part[4 * ATTE_SEG * NB];             // [waves of a group][positions of a segment][NB]
     __shared__ int s_first;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h0 = blockIdx.y * NB, A = a.A;
+    // waves per position, groups of that many waves, positions of a segment
+    const int wp = A > 512 ? 4 : 2, groups = 4 / wp, seg = ATTE_SEG * groups;                  // (A > 256, see att_panel_better)
+    const int g = wave / wp, wg = wave - g * wp, parts = min(wp, (A + 255) / 256);
     int pos, pend;
     q8_position_run(a.sent_off, n_sent, (int)blockIdx.x, (int)gridDim.x, &pos, &pend);
     if (pos >= pend) return;
@@ -376,20 +463,22 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
     int sent = __builtin_amdgcn_readfirstlane(s_first);
     while (pos < pend) {
         while (a.sent_off[sent + 1] <= pos) ++sent;
-        const int o = a.sent_off[sent], np = min(min(pend, a.sent_off[sent + 1]) - pos, ATTE_SEG);
+        const int o = a.sent_off[sent], np = min(min(pend, a.sent_off[sent + 1]) - pos, seg);
         const __amdgpu_buffer_rsrc_t rp = q8_rsrc(a.P + (size_t)pos * A, (size_t)np * A * sizeof(float));
-        for (int j0 = 0; j0 < A; j0 += 1024) {
-            const int j = j0 + tid * 4;
+        for (int j0 = 0; j0 + 256 * wg < A; j0 += 256 * wp) {    // (a wave without columns has nothing to add)
+            const int j = j0 + (64 * wg + lane) * 4;
             const unsigned col = j < A ? (unsigned)j * 4u : Q8_OOB;
             auto load4 = [&](__amdgpu_buffer_rsrc_t r, unsigned off) {
                 return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
             };
-            float4 av[NB], pv;
+            float4 av[NB];
 #pragma unroll
             for (int h = 0; h < NB; ++h)         // (a pass past the beam repeats its last hypothesis and stores nothing for it)
                 av[h] = load4(q8_rsrc(a.a + (size_t)(sent * a.beam + min(h0 + h, a.beam - 1)) * A, (size_t)A * sizeof(float)), col);
             const float4 vv = load4(q8_rsrc(a.v, (size_t)A * sizeof(float)), col);
-            pv = load4(rp, col);
+            // the group's positions g, g + groups, .., the next on its way (past the last: zeros)
+            auto position = [&](int p) { return load4(rp, col + (unsigned)p * (unsigned)A * 4u); };
+            float4 pv = position(g);
             double ea[NB][4];
             bool far = false;
 #pragma unroll
@@ -402,9 +491,9 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
                 }
             }
             const double v[4] = {(double)vv.x, (double)vv.y, (double)vv.z, (double)vv.w};
-            for (int p = 0; p < np; ++p) {
+            for (int p = g; p < np; p += groups) {
                 const float pf[4] = {pv.x, pv.y, pv.z, pv.w};
-                pv = load4(rp, j < A ? (unsigned)((p + 1) * A + j) * 4u : Q8_OOB);          // (past the last position: zeros)
+                pv = position(p + groups);
                 double acc[NB];
 #pragma unroll
                 for (int h = 0; h < NB; ++h) acc[h] = 0.0;
@@ -432,15 +521,19 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
                 }
                 const double tot = wave_sums_d<NB>(acc, lane);
                 const int h = wave_sums_index<NB>(lane);
-                if ((lane & 15) < (NB + 3) / 4 && h < NB) s_part[wave][p][h] = j0 ? s_part[wave][p][h] + tot : tot;
+                if ((lane & 15) < (NB + 3) / 4 && h < NB) {
+                    double &to = s_part[(wg * seg + p) * NB + h];
+                    to = j0 ? to + tot : tot;
+                }
             }
         }
         __syncthreads();
-        if (tid < np * NB) {
-            const int p = tid / NB, h = tid - p * NB;
-            if (h0 + h < a.beam)
-                a.e[(size_t)(sent * a.beam + h0 + h) * a.lde + (pos - o) + p] =
-                    (float)((s_part[0][p][h] + s_part[1][p][h]) + (s_part[2][p][h] + s_part[3][p][h]));
+        for (int e = tid; e < np * NB; e += 256) {
+            const int p = e / NB, h = e - p * NB;
+            const double *part = s_part + e;
+            double sum = part[0];
+            for (int u = 1; u < parts; ++u) sum += part[u * seg * NB];
+            if (h0 + h < a.beam) a.e[(size_t)(sent * a.beam + h0 + h) * a.lde + (pos - o) + p] = (float)sum;
         }
         __syncthreads();
         pos += np;
@@ -903,7 +996,8 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
         const long long most = (long long)n_sent * l;
         const int runs = ATTE_BLOCKS / epasses;
         const dim3 egrid(most < runs ? (unsigned)most : runs, epasses);
-        if (enb == 1) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<1>, egrid, dim3(256), 0, t, n_sent);
+        if (att_panel_better(A, beam, most)) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_panel_kernel, dim3((l + ATTP_POS - 1) / ATTP_POS, n), dim3(256), 0, t);
+        else if (beam == 1) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_greedy_kernel, dim3(att_greedy_blocks(most)), dim3(256), 0, t, n_sent);
         else if (enb == 2) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<2>, egrid, dim3(256), 0, t, n_sent);
         else if (enb == 3) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<3>, egrid, dim3(256), 0, t, n_sent);
         else if (enb == 4) Q8_LAUNCH(ctx, Q8_KERNEL_ATTENTION, attention_energy_kernel<4>, egrid, dim3(256), 0, t, n_sent);
