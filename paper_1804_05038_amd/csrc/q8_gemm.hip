@@ -366,8 +366,10 @@ __global__ __launch_bounds__(256) void gemm_resident_kernel(GemmJobs jobs)
 
 // ===================================================================== large panels ==
 // Plain products over many vectors: block tile 32 RW rows x 32 CW CT vectors, four waves (RW x CW), a wave 32 rows x 32 CT
-// vectors of v_mfma_i32_32x32x32_i8 results.  What a compute unit takes in (some 77 GB/s) bounds these products, so the
-// tile is as large as still gives every unit a block; k runs in stages of 256 bytes, and stages s + 1 and s + 2 are on
+// vectors of v_mfma_i32_32x32x32_i8 results.  The tile is as large as still gives most compute units a block, so that a
+// unit, which takes in some 77 GB/s, asks for few bytes (that is not all of it: 1024 x 2048 x 1024 with 64 x 64 tiles asks
+// for 256 KB per unit, 3.4 us, and multiplies for 1.8 of its 10.7 us; what the rest goes into is not known).  k runs in
+// stages of 256 bytes, and stages s + 1 and s + 2 are on
 // their way while s is multiplied: a vector piece's register is requested again once it is in LDS, a weight register
 // once its instruction has used it.  One barrier per stage (two LDS buffers).  Weights come tile-packed or row by row;
 // everything outside the matrix or the panel reads as zero through bounds-checked descriptors.
@@ -1123,21 +1125,25 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.ld > 1024 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
         if (a.ld > max_ld) max_ld = a.ld;
     }
-    // Large panels: 128 x 128 tiles where there are enough of them for most compute units (3072 x 1024 times 1024
-    // vectors, 192 tiles: 14.1 against 15.0 us K-resident; 2415 x 1860 x 903, 152 tiles: 19.6 against 20.1 us staged;
-    // 1024 x 2048 x 1024, 64 tiles: 16.5 against 13.0) and rows are longer than 512 bytes (two products of 3072 x 512 x
-    // 1024: 15.8 against 14.6 us K-resident); else 64 x 64 tiles for rows that a K-resident block does not take.  There
-    // the staged kernel keeps what its larger loads suit better: row-major weights against more than 512 vectors
-    // (1000 x 2000 x 1024: 12.4 against 13.0 us; x 500: 12.0 against 11.2), and more than 8192 rows.
-    bool tile_ok = !stats && n > 8, packed = true;
+    // Large panels (kernel trace, us, this form against the one that it takes the place of).  128 x 128 tiles where there
+    // are enough of them for most compute units (3072 x 1024 times 1000 vectors, 192 tiles: 14.3 against 14.9 K-resident;
+    // 2415 x 1860 x 903, 152 tiles: 19.6 against 20.1 staged; 1024 x 2048 x 1024, 64 tiles: 16.5 against 13.0) and rows are
+    // longer than 512 bytes (two products of 3072 x 512 x 1024: 15.8 against 14.6 K-resident); rows that a K-resident
+    // block takes have to be whole 64-byte steps (3000 rows of 1008 bytes x 900: 13.6 against 12.8).  Else 64 x 64 tiles for
+    // packed rows that a K-resident block does not take (1024 x 2048 x 1024 10.7 against 12.8): with row-major weights the
+    // staged kernel, which requests a whole 128 bytes of each row at a time, is the faster one at every size (1024 x 2048
+    // times 9 / 130 / 512 vectors 9.8 / 11.0 / 11.4 against 12.1 / 12.1 / 12.4, 8192 rows x 130 15.3 against 21.6), as it is
+    // beyond 8192 rows.
+    bool tile_ok = !stats && n > 8, packed = true, steps = true;
     int big = 0;
     for (int t = 0; t < njobs; ++t) {
         const GemmArgs &a = jobs.j[t];
         if (a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) tile_ok = false;
         big += (a.rows + 127) / 128 * ((n + 127) / 128);
         packed = packed && a.Wt;
+        steps = steps && a.ld % 64 == 0;
     }
-    if (tile_ok && big >= TILE_FILL && max_ld > 512) {
+    if (tile_ok && big >= TILE_FILL && (max_ld > 1024 || (max_ld > 512 && steps))) {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
         static bool attr_set = false;
         if (!attr_set) {
@@ -1148,7 +1154,7 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }
-    if (tile_ok && !resident && max_rows <= 8192 && (packed || n <= 512)) {
+    if (tile_ok && !resident && max_rows <= 8192 && packed) {
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<2, 2, 1>), dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)2 * 64 * (256 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
     }

@@ -220,20 +220,37 @@ def test_rows_variant_argument_errors(q, ctx):
     assert e.value.code == 1
 
 
-@pytest.mark.parametrize("rows,cols,n,tiled", [(17, 1100, 9, False), (64, 1088, 64, True), (65, 1040, 65, False), (1000, 2000, 513, False),
-                                               (1024, 2048, 513, True), (130, 2112, 33, True), (1537, 528, 1023, False), (3072, 576, 897, True),
-                                               (1553, 1024, 1024, False), (2049, 16, 1024, False)])
+def _panel_route(rows, ld, n, packed):
+    """The kernel that a plain product of more than 8 vectors is dispatched to."""
+    if -(-rows // 128) * -(-n // 128) >= 144 and (ld > 1024 or (ld > 512 and ld % 64 == 0)):
+        return "tiles of 128"
+    if ld <= 1024:
+        return "resident"
+    return "tiles of 64" if packed and rows <= 8192 else "staged"
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled,route", [
+    # 128 x 128 tiles: rows and vectors at the remainders of a tile (1, 127, 47), k steps and stages at theirs, row by row and packed
+    (2415, 1860, 903, False, "tiles of 128"), (2945, 1040, 769, False, "tiles of 128"), (2303, 576, 1023, False, "tiles of 128"),
+    (3000, 1088, 895, True, "tiles of 128"), (2433, 2112, 897, True, "tiles of 128"), (3072, 576, 897, True, "tiles of 128"),
+    # 64 x 64 tiles
+    (64, 1088, 64, True, "tiles of 64"), (1024, 2048, 513, True, "tiles of 64"), (130, 2112, 33, True, "tiles of 64"),
+    (65, 1088, 65, True, "tiles of 64"), (127, 1152, 9, True, "tiles of 64"),
+    # the forms on the other side of the rule
+    (3000, 1000, 900, False, "resident"), (1553, 1024, 1024, False, "resident"), (1537, 528, 1023, False, "resident"), (2049, 16, 1024, False, "resident"),
+    (17, 1100, 9, False, "staged"), (65, 1040, 65, False, "staged"), (1000, 2000, 513, False, "staged"), (8200, 1088, 33, True, "staged")])
 @pytest.mark.parametrize("by_row", [False, True])
-def test_large_panels(q, oracle, rows, cols, n, tiled, by_row):
+def test_large_panels(q, oracle, rows, cols, n, tiled, route, by_row):
     """The tiled products at the edges of their tiles, stages and k steps, packed and row by row, one scale and one per
     row, results at an odd pitch: exact integer sums, one product of scales, one addition, so identical bits."""
+    assert _panel_route(rows, (cols + 15) // 16 * 16, n, tiled) == route
     rng = np.random.default_rng(rows + n)
     ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
     W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
     M, rs = q.q8_quantize_matrix_rows(ctx, W) if by_row else (q.q8_quantize_matrix(ctx, W), None)
     if tiled:
         M = q.q8_pack_tiles(ctx, M)
-    pick = sorted({0, 1, n // 2, n - 2, n - 1})
+    pick = sorted({0, 1, 127, 128, n // 2, n - 2, n - 1} & set(range(n)))
     codes = np_(M.data)[:, :cols].astype(np.int64)
     for pitch, bias in ((rows, None), (rows + 3, b)):
         Y = ctx.empty(n, pitch)[:, :rows]
