@@ -40,7 +40,7 @@ struct GemmJobs {          // products of one launch (blockIdx.z), all over the 
 #endif
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-#define TILE_FILL 144       // 128 x 128 tiles that are worth a launch
+#define TILE_FILL (128LL * 128 * 128)       // results that are worth a launch of 128 x 128 tiles: 128 full ones
 #define GB_K 128           // k bytes per stage
 #define GB_PITCH 144       // LDS bytes per staged vector: 16 lanes x 16 bytes fall on 64 distinct banks
 
@@ -1125,9 +1125,10 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.ld > 1024 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
         if (a.ld > max_ld) max_ld = a.ld;
     }
-    // Large panels (kernel trace, us, this form against the one that it takes the place of).  128 x 128 tiles where there
-    // are enough of them for most compute units (3072 x 1024 times 1000 vectors, 192 tiles: 14.3 against 14.9 K-resident;
-    // 2415 x 1860 x 903, 152 tiles: 19.6 against 20.1 staged; 1024 x 2048 x 1024, 64 tiles: 16.5 against 13.0) and rows are
+    // Large panels (kernel trace, us, this form against the one that it takes the place of).  128 x 128 tiles where the
+    // results fill enough of them (3072 x 1024 times 1000 vectors: 14.3 against 14.9 K-resident; two such products times 384
+    // vectors 15.6 against 16.0, but times 257, whose last vector tile holds one, 15.0 against 11.1, and of 2304 rows times 448
+    // 14.3 against 12.6; 2415 x 1860 x 903: 19.6 against 20.1 staged; 1024 x 2048 x 1024: 16.5 against 13.0) and rows are
     // longer than 512 bytes (two products of 3072 x 512 x 1024: 15.8 against 14.6 K-resident); rows that a K-resident
     // block takes have to be whole 64-byte steps (3000 rows of 1008 bytes x 900: 13.6 against 12.8).  Else 64 x 64 tiles for
     // packed rows that a K-resident block does not take (1024 x 2048 x 1024 10.7 against 12.8): with row-major weights the
@@ -1135,15 +1136,15 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
     // times 9 / 130 / 512 vectors 9.8 / 11.0 / 11.4 against 12.1 / 12.1 / 12.4, 8192 rows x 130 15.3 against 21.6), as it is
     // beyond 8192 rows.
     bool tile_ok = !stats && n > 8, packed = true, steps = true;
-    int big = 0;
+    long long results = 0;
     for (int t = 0; t < njobs; ++t) {
         const GemmArgs &a = jobs.j[t];
         if (a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) tile_ok = false;
-        big += (a.rows + 127) / 128 * ((n + 127) / 128);
+        results += (long long)a.rows * n;
         packed = packed && a.Wt;
         steps = steps && a.ld % 64 == 0;
     }
-    if (tile_ok && big >= TILE_FILL && (max_ld > 1024 || (max_ld > 512 && steps))) {
+    if (tile_ok && results >= TILE_FILL && (max_ld > 1024 || (max_ld > 512 && steps))) {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
         static bool attr_set = false;
         if (!attr_set) {

@@ -222,7 +222,7 @@ def test_rows_variant_argument_errors(q, ctx):
 
 def _panel_route(rows, ld, n, packed):
     """The kernel that a plain product of more than 8 vectors is dispatched to."""
-    if -(-rows // 128) * -(-n // 128) >= 144 and (ld > 1024 or (ld > 512 and ld % 64 == 0)):
+    if rows * n >= 128 ** 3 and (ld > 1024 or (ld > 512 and ld % 64 == 0)):
         return "tiles of 128"
     if ld <= 1024:
         return "resident"
