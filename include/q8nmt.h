@@ -255,8 +255,8 @@ q8_status output_logits_q8(q8_ctx *ctx, const q8_readout_weights *ro, const q8_m
  * vectors back to back, sentence s in rows [sent_off[s], sent_off[s + 1]) (sent_off: device
  * int32 [n_sent + 1]; sent_off_host: the same values on the host, sent_off_host[0] = 0);
  * enc_h [L x 2H] as q8_encode.  All input products run as matrix-core panels; time step t
- * of every sentence that has one, in both directions, runs in one launch (H <= 1024; beyond
- * that a quantize / product / gates triple).  Values are those of q8_encode sentence by sentence.  Needs
+ * of every sentence that has one, in both directions, runs in one launch (H <= 1024 and, at
+ * H = 1024, up to 256 sentences; beyond, mostly a quantize / product / gates triple).  Values are those of q8_encode sentence by sentence.  Needs
  * q8_encode_batch_bytes(fwd, L, n_sent) bytes of workspace. */
 size_t q8_encode_batch_bytes(const q8_gru_weights *fwd, int total_l, int n_sent);
 q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X,

@@ -806,11 +806,28 @@ q8_status q8i_gru_gates(q8_ctx *ctx, const float *gx, const float *gh, const flo
 }
 
 
+// Tiles of 16 slots per block of the one-launch step, 0 where three launches are faster.  A round of at most one block
+// per compute unit takes about 5, 8 and 12 us with 1, 2 and 4 tiles (every group of slots reads the weights again, every
+// block reads and quantizes its slots' states, 4 KB each), so the fewest that need one round; beyond 256 blocks of 4
+// tiles, two rounds if the second is at least half full.  Per position (a panel of 12 words less one of 2), us, three launches against
+// this rule: H = 1024 13.4 / 5.9 at 64 sentences, 15.7 / 10.4 at 128, 22.4 / 17.1 at 256, 35.2 / 33.7 at 512 (and without
+// it 23.3 / 28.7 at 257, 61.6 / 71.8 at 1024); H = 512 12.9 / 7.1 at 128, 22.7 / 16.8 at 512, 23.1 / 27.1 without it at 513;
+// H = 256 11.3 / 6.3 at 128 (12.1 with 4 tiles), 26.7 / 20.5 at 1024.
+static int enc_cell_tiles(int H, int S)
+{
+    const int units = (H + EC_UNITS - 1) / EC_UNITS;
+    auto blocks = [&](int nt) { return units * 2 * ((S + 16 * nt - 1) / (16 * nt)); };
+    for (int nt = 1; nt <= 4; nt *= 2)
+        if (blocks(nt) <= 256) return nt;
+    return blocks(4) >= 384 && blocks(4) <= 512 ? 4 : 0;
+}
+
 bool q8i_enc_cell_ok(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S)
 {
     const int H = fwd->Wh.cols;
     // (the states of all sentences are addressed with 32-bit byte offsets)
-    return H % 4 == 0 && H <= 1024 && fwd->Wh.ld <= 1024 && bwd->Wh.ld == fwd->Wh.ld && (size_t)S * H * 4 < (1u << 31);
+    return H % 4 == 0 && H <= 1024 && fwd->Wh.ld <= 1024 && bwd->Wh.ld == fwd->Wh.ld && (size_t)S * H * 4 < (1u << 31) &&
+           enc_cell_tiles(H, S) > 0;
 }
 
 q8_status q8i_enc_cell(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, int t,
@@ -820,9 +837,7 @@ q8_status q8i_enc_cell(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weig
     const int H = fwd->Wh.cols, ld = fwd->Wh.ld;
     EncCellArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {gxf, gxb}, sent_off, enc_h,
                      h_in, h_out, pm_in, pm_out, S, t, H, ld, {fwd->Wh.scale, bwd->Wh.scale}};
-    // Slots per block: as few as keep the grid at one block per compute unit (64 blocks per 16 NT slots at H = 1024):
-    // a block reads and quantizes its slots' states, 4 KB each, while every group of slots reads the weights again.
-    const int nt = S <= 64 ? 1 : S <= 128 ? 2 : 4;
+    const int nt = enc_cell_tiles(H, S);
     const size_t smem = (size_t)16 * nt * EC_PITCH + (size_t)12 * nt * 1024;
     const dim3 grid((H + EC_UNITS - 1) / EC_UNITS * ((S + 16 * nt - 1) / (16 * nt)) * 2);
     if (smem > 65536) {

@@ -571,9 +571,12 @@ def test_energies_of_a_batch(q, ctx, beam, A, lens):
 
 
 @pytest.mark.parametrize("E,H,lens,tiled", [(36, 4, [3, 1], False), (64, 64, [2] * 9 + [5], True), (620, 1000, [4, 9, 1], False), (64, 256, [1, 2, 3] * 6, True),
-                                            (48, 96, [3, 1, 4] * 22, False), (48, 100, [2, 1] * 65, False), (32, 1024, [1, 3] * 130, True)])
+                                            (48, 96, [3, 1, 4] * 22, False), (48, 100, [2, 1] * 65, False),
+                                            # 32 and 64 slots per block, two rounds of blocks, three launches instead
+                                            (16, 100, [1, 2, 2] * 190, False), (32, 1000, [2, 1, 3] * 33, False), (32, 1024, [1, 3] * 97, True),
+                                            (64, 512, [2, 1] * 200, True), (32, 1024, [2, 1] * 200, True), (32, 1024, [1, 3] * 130, True)])
 def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
-    """The batched encoder's one launch per position at the edges of its blocks (32 units, 16 / 32 / 64 slots, one slot
+    """The batched encoder's launches per position at the edges of their blocks (32 units, 16 / 32 / 64 slots, one slot
     group and more), sentences that end at different steps: the states of q8_encode, which runs another kernel per
     position, bit for bit; with the workspace that q8_encode_batch_bytes asks for, and no more than it."""
     rng = np.random.default_rng(H + len(lens))
