@@ -169,6 +169,7 @@ q8_status q8_create(q8_ctx **out, void *hip_stream, void *workspace, size_t work
     c->att_split = 1;
     c->att_spin_limit = Q8_ENC_SPIN_DEFAULT;
     c->att_capacity = -1;
+    c->grup_capacity[0] = c->grup_capacity[1] = -1;
     c->att_words_set = 0;
     c->grup_used[0] = c->grup_used[1] = 0;
     c->gate_pause = Q8_GATE_PAUSE_DEFAULT;

@@ -639,12 +639,9 @@ q8_status q8i_gemm_ksplit3(q8_ctx *ctx, const q8i_gemm_job *d, int n)
     }
     a.R = d[0].W->rows; a.n = n; a.ldy = d[0].ldy;
     const size_t smem = (size_t)KS3_SLOTS * (1024 + 16 + 512 + 16 + 2048 + 16) + (size_t)KS3_WAVES * 2 * 1024;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute((const void *)gemm_ksplit3_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "three-product kernel: %s", hipGetErrorString(e));
-        attr_set = true;
-    }
+    static Q8OncePerDevice asked;
+    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_ksplit3_kernel, smem, "three-product kernel");
+    if (st) return st;
     Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_ksplit3_kernel, dim3(a.R / KS3_ROWS, (n + KS3_SLOTS - 1) / KS3_SLOTS), dim3(64 * KS3_WAVES), smem, a);
     return q8i_launch_check(ctx, "three products");
 }
@@ -769,12 +766,9 @@ q8_status q8i_gemm_ksplit2(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.rows > max_rows) max_rows = a.rows;
     }
     const size_t smem = (size_t)KS2_SLOTS * (1024 + 16) + (size_t)16 * 3 * 1024;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute((const void *)gemm_ksplit2_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "k-split product kernel: %s", hipGetErrorString(e));
-        attr_set = true;
-    }
+    static Q8OncePerDevice asked;
+    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_ksplit2_kernel, smem, "k-split product kernel");
+    if (st) return st;
     Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_ksplit2_kernel, dim3(max_rows / KS2_ROWS, (n + KS2_SLOTS - 1) / KS2_SLOTS, njobs), dim3(1024), smem, jobs);
     return q8i_launch_check(ctx, "k-split products");
 }
@@ -1014,13 +1008,9 @@ q8_status q8i_vocab_panel(q8_ctx *ctx, const q8_mat *W, const float *bias, const
     if (smem > 160 * 1024) return q8_fail(ctx, Q8_ERR_SHAPE, "vocabulary panel: %d rows", W->rows);
     typedef void (*kern_t)(PanelArgs);
     const kern_t kern = W->ld == 512 ? vocab_panel_kernel<16> : vocab_panel_kernel<20>;
-    static bool attr_set[2] = {false, false};
-    const int which = W->ld == 512 ? 0 : 1;
-    if (!attr_set[which]) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "vocabulary panel kernel: %s", hipGetErrorString(e));
-        attr_set[which] = true;
-    }
+    static Q8OncePerDevice asked[2];
+    const q8_status st = q8i_lds(ctx, asked[W->ld == 512 ? 0 : 1], (const void *)kern, 160 * 1024, "vocabulary panel kernel");
+    if (st) return st;
     Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, kern, dim3(gx, gy), dim3(64 * VP_WAVES), smem, a);
     return q8i_launch_check(ctx, "vocabulary panel");
 }
@@ -1146,12 +1136,9 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
     }
     if (tile_ok && results >= TILE_FILL && (max_ld > 1024 || (max_ld > 512 && steps))) {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
-        static bool attr_set = false;
-        if (!attr_set) {
-            const hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_kernel<4, 1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "large panel kernel: %s", hipGetErrorString(e));
-            attr_set = true;
-        }
+        static Q8OncePerDevice asked;
+        const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_tile_kernel<4, 1, 4>, smem, "large panel kernel");
+        if (st) return st;
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }
@@ -1161,17 +1148,11 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
     }
     if (resident) {
         const dim3 grid((max_rows + 63) / 64, (n + 63) / 64, njobs);
-        static bool attr_set[2] = {false, false};
-        const int which = max_ld <= 512 ? 0 : 1;
-        const size_t smem = (size_t)64 * (which == 0 ? 64 * 8 + 16 : 64 * 16 + 16);
-        if (!attr_set[which]) {
-            const hipError_t e = which == 0
-                ? hipFuncSetAttribute((const void *)gemm_resident_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)
-                : hipFuncSetAttribute((const void *)gemm_resident_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "resident product kernel: %s", hipGetErrorString(e));
-            attr_set[which] = true;
-        }
-        if (which == 0) Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<8>, grid, dim3(256), smem, jobs);
+        static Q8OncePerDevice asked;
+        const size_t smem = (size_t)64 * (max_ld <= 512 ? 64 * 8 + 16 : 64 * 16 + 16);
+        const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_resident_kernel<16>, smem, "resident product kernel");      // (<8>: 33 KB)
+        if (st) return st;
+        if (max_ld <= 512) Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<8>, grid, dim3(256), smem, jobs);
         else Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<16>, grid, dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }

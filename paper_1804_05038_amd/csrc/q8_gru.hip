@@ -840,10 +840,9 @@ q8_status q8i_enc_cell(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weig
     const int nt = enc_cell_tiles(H, S);
     const size_t smem = (size_t)16 * nt * EC_PITCH + (size_t)12 * nt * 1024;
     const dim3 grid((H + EC_UNITS - 1) / EC_UNITS * ((S + 16 * nt - 1) / (16 * nt)) * 2);
-    if (smem > 65536) {
-        const hipError_t e = hipFuncSetAttribute((const void *)enc_cell_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "encoder step kernel: %s", hipGetErrorString(e));
-    }
+    static Q8OncePerDevice asked;
+    const q8_status st = q8i_lds(ctx, asked, (const void *)enc_cell_kernel<4>, smem, "encoder step kernel");      // (<1>, <2>: less than 64 KB)
+    if (st) return st;
     if (nt == 1) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<1>, grid, dim3(EC_THREADS), smem, a);
     else if (nt == 2) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<2>, grid, dim3(EC_THREADS), smem, a);
     else Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<4>, grid, dim3(EC_THREADS), smem, a);
@@ -1121,6 +1120,13 @@ __global__ __launch_bounds__(64 * GP_WAVES) void gru_panel_kernel(GruPanelArgs a
     }
 }
 
+static q8_status gru_panel_lds(q8_ctx *ctx, bool gh_pre, size_t bytes)
+{
+    static Q8OncePerDevice asked[2];
+    return gh_pre ? q8i_lds(ctx, asked[1], (const void *)gru_panel_kernel<16, 16, true>, bytes, "panel GRU kernel")
+                  : q8i_lds(ctx, asked[0], (const void *)gru_panel_kernel<8, 16, false>, bytes, "panel GRU kernel");
+}
+
 // Whether the one-launch panel GRU takes this shape (rows of 512 + 1024 bytes for both products, or rows of
 // 2048 bytes for the input product alone; H a multiple of 32, at most 1024; code rows of exactly H bytes), and,
 // where codes are wanted (its blocks then wait for each other), whether the context allows such kernels
@@ -1136,22 +1142,19 @@ bool q8i_gru_panel_ok(q8_ctx *ctx, const q8_gru_weights *g, bool gh_pre, int n, 
     if (ld1 != H || (have_q2 && ld2 != H) || !ctx->att_split) return false;
     const int ncg = (n + GP_SLOTS - 1) / GP_SLOTS;
     if (ncg > GP_MAX_CG) return false;
-    static int capacity[2] = {-1, -1};
     const int v = gh_pre ? 1 : 0;
-    if (capacity[v] < 0) {
+    if (ctx->grup_capacity[v] < 0) {
         int per_cu = 0, dev = 0, cus = 0;
         const size_t smem = (size_t)GP_SLOTS * (gh_pre ? 2048 + 16 : 512 + 16 + 1024 + 16) + (size_t)GP_WAVES * 3 * 256 * sizeof(int);
-        hipError_t e = gh_pre ? hipFuncSetAttribute((const void *)gru_panel_kernel<16, 16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)
-                              : hipFuncSetAttribute((const void *)gru_panel_kernel<8, 16, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e == hipSuccess)
-            e = gh_pre ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gru_panel_kernel<16, 16, true>, 64 * GP_WAVES, smem)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gru_panel_kernel<8, 16, false>, 64 * GP_WAVES, smem);
+        if (gru_panel_lds(ctx, gh_pre, smem)) return false;
+        hipError_t e = gh_pre ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gru_panel_kernel<16, 16, true>, 64 * GP_WAVES, smem)
+                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gru_panel_kernel<8, 16, false>, 64 * GP_WAVES, smem);
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) { (void)hipGetLastError(); return false; }
-        capacity[v] = per_cu * cus;
+        ctx->grup_capacity[v] = per_cu * cus;
     }
-    return (H / GP_UNITS) * ncg <= capacity[v];
+    return (H / GP_UNITS) * ncg <= ctx->grup_capacity[v];
 }
 
 // region: which of the two sets of exchange words this launch uses (0: GRU r of a decoder step and single
@@ -1184,24 +1187,11 @@ q8_status q8i_gru_panel(q8_ctx *ctx, const q8_gru_weights *g, const int8_t *xq, 
         ctx->grup_used[r] = ugs;
     }
     const size_t e_bytes = (size_t)GP_WAVES * 3 * 256 * sizeof(int);
-    static bool attr_set[2] = {false, false};
-    if (gh_pre) {
-        const size_t smem = (size_t)GP_SLOTS * (a.ldx + 16) + e_bytes;
-        if (!attr_set[1]) {
-            const hipError_t e = hipFuncSetAttribute((const void *)gru_panel_kernel<16, 16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "panel GRU kernel: %s", hipGetErrorString(e));
-            attr_set[1] = true;
-        }
-        Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_panel_kernel<16, 16, true>), grid, dim3(64 * GP_WAVES), smem, a);
-    } else {
-        const size_t smem = (size_t)GP_SLOTS * (a.ldx + 16 + a.ldh + 16) + e_bytes;
-        if (!attr_set[0]) {
-            const hipError_t e = hipFuncSetAttribute((const void *)gru_panel_kernel<8, 16, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return q8_fail(ctx, Q8_ERR_DEVICE, "panel GRU kernel: %s", hipGetErrorString(e));
-            attr_set[0] = true;
-        }
-        Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_panel_kernel<8, 16, false>), grid, dim3(64 * GP_WAVES), smem, a);
-    }
+    const size_t smem = (size_t)GP_SLOTS * (a.ldx + 16 + (gh_pre ? 0 : a.ldh + 16)) + e_bytes;
+    const q8_status st = gru_panel_lds(ctx, gh_pre != nullptr, smem);
+    if (st) return st;
+    if (gh_pre) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_panel_kernel<16, 16, true>), grid, dim3(64 * GP_WAVES), smem, a);
+    else Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_panel_kernel<8, 16, false>), grid, dim3(64 * GP_WAVES), smem, a);
     return q8i_launch_check(ctx, "panel GRU");
 }
 

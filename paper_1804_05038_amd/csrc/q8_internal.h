@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include "q8nmt.h"
+#include "q8_once.h"
 #ifdef __HIPCC__
 #include "q8_device.h"
 #endif
@@ -60,6 +61,8 @@ struct q8_ctx {
     // one-launch panel GRU: unit groups whose exchange words a launch has left set in each of the two regions
     // (0: the region is clear); the launch after it clears them, see q8i_gru_panel
     int grup_used[2];
+    // and how many of its blocks the device holds at once, per form (-1: not asked yet)
+    int grup_capacity[2];
     // the decoding loop whose GRU r runs ahead (output_logits_beam_ahead_q8): short sleeps of the blocks that
     // wait for the search step's decision before their first poll
     int gate_pause;
@@ -89,6 +92,18 @@ static inline q8_status q8_fail(q8_ctx *ctx, q8_status code, const char *fmt, ..
         va_end(ap);
     }
     return code;
+}
+
+// Dynamic LDS above 64 KB has to be asked for before a kernel's first launch on a device; `once` is the kernel's own.
+static inline q8_status q8i_lds(q8_ctx *ctx, Q8OncePerDevice &once, const void *kernel, size_t bytes, const char *what)
+{
+    if (bytes <= 65536) return Q8_OK;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess && once(dev, [&] { return (e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes)) == hipSuccess; }))
+        return Q8_OK;
+    (void)hipGetLastError();
+    return q8_fail(ctx, Q8_ERR_DEVICE, "%s: %zu bytes of LDS refused: %s", what, bytes, hipGetErrorString(e));
 }
 
 struct q8i_gemv_desc {
