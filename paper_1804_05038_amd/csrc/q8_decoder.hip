@@ -9,8 +9,7 @@
 struct AttArgs {
     const float *P, *enc_h, *a, *v;
     float *e, *alpha, *ctx;
-    unsigned *counters;     // one arrival counter per hypothesis (cstride words apart), zero on entry and on exit
-    int cstride;
+    unsigned *counters;     // one arrival counter per hypothesis (Q8_COUNTER_STRIDE words apart), zero on entry and on exit
     int l, A, C;
     // several sentences side by side: hypothesis b belongs to sentence b / beam, whose rows of
     // P and enc_h are [sent_off[s], sent_off[s + 1]); NULL = one sentence of l positions
@@ -75,7 +74,7 @@ __device__ __forceinline__ void att_finish(const AttArgs &a, int b, int l, const
             s_alpha[t] = (double)al;          // the weight as the context sum uses it: converted once, not per column
             if (a.alpha) a.alpha[(size_t)b * a.lde + t] = al;
         }
-        if (HANDOFF && lane == 0) __hip_atomic_store(&a.counters[b * a.cstride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (HANDOFF && lane == 0) __hip_atomic_store(&a.counters[b * Q8_COUNTER_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (a.ctx_q) {
@@ -168,7 +167,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttArgs a)
         // count can read every energy with device-coherent loads, no cache flush needed.
         __hip_atomic_store(&a.e[(size_t)b * a.lde + i], (float)tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         q8_stores_performed();
-        const unsigned prev = __hip_atomic_fetch_add(&a.counters[b * a.cstride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned prev = __hip_atomic_fetch_add(&a.counters[b * Q8_COUNTER_STRIDE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_last = (prev == (unsigned)l - 1u);
     }
     __syncthreads();
@@ -559,11 +558,7 @@ __global__ __launch_bounds__(256, 2) void attention_energy_kernel(AttArgs a, int
 __global__ __launch_bounds__(ATT_MAX_THREADS) void attention_finish_kernel(AttArgs a, int n)
 {
     __shared__ double s_alpha[1024];
-    int b = blockIdx.x;
-    if (a.sent_off) {
-        const int xcd = b & 7, q = b >> 3;
-        b = ((q / a.beam) * 8 + xcd) * a.beam + q % a.beam;
-    }
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3, b = ((q / a.beam) * 8 + xcd) * a.beam + q % a.beam;
     if (b >= n) return;
     const float *P, *enc_h;
     const int l = att_sentence(a, b, P, enc_h);
@@ -947,10 +942,9 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
     AttArgs t;
     t.P = P; t.enc_h = enc_h; t.a = a; t.v = v; t.e = e; t.alpha = alpha; t.ctx = cvec;
     t.counters = (unsigned *)ctx->ws;
-    t.cstride = n <= Q8_MAX_BEAM ? Q8_COUNTER_STRIDE : 1;        // header: 1024 words of counters
     t.l = l; t.A = A; t.C = C;
     t.sent_off = sent_off; t.beam = beam; t.lde = l;
-    const bool panel = n > Q8_MAX_BEAM;
+    const bool panel = n > Q8_MAX_BEAM;                          // (hypotheses of several sentences: sent_off is there)
     const bool codes = ctx_q && ctx_qscale && C % 2 == 0 && ldq >= C && ldq % 2 == 0 && ldq <= 2 * ATT_PAIRS * ATT_THREADS;
     t.ctx_q = codes ? ctx_q : nullptr; t.ctx_qscale = ctx_qscale; t.ldq = ldq;
     t.xchg = nullptr; t.wait_err = nullptr; t.spin_limit = 0; t.ppb = 0; t.inv_ppb = 0.0f;
@@ -986,7 +980,7 @@ q8_status q8i_attention(q8_ctx *ctx, const float *P, const float *enc_h, int l, 
             return q8i_launch_check(ctx, "attention");
         }
     }
-    if (panel && sent_off) {
+    if (panel) {
         const int n_sent = n / beam;
         // hypotheses per pass: at most five share a block's exponentials (registers), wider beams go in two even passes
         const int epasses = beam > 5 ? 2 : 1, enb = (beam + epasses - 1) / epasses;

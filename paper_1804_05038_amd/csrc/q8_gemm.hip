@@ -792,9 +792,8 @@ struct PanelArgs {
     float w_scale;
 };
 
-#define VP_WAVES 8
-#define VP_MAX_COLS 256
-#define VP_STAGE 1536      // bytes of LDS per wave: a unit's statistics on their way out
+#define VP_WAVES Q8_PANEL_WAVES
+#define VP_STAGE Q8_PANEL_STAGE
 
 // max of eight values (the plain form costs a canonicalization of every operand)
 __device__ __forceinline__ float vp_max8(const float *v)
@@ -989,27 +988,12 @@ q8_status q8i_vocab_panel(q8_ctx *ctx, const q8_mat *W, const float *bias, const
     a.tiles = W->tiles; a.xq = xq; a.xscale = xscale; a.bias = bias;
     a.part_max = part_max; a.part_sum = part_sum;
     a.rows = W->rows; a.ld = W->ld; a.n = n; a.ntiles = (W->rows + 15) / 16; a.w_scale = W->scale;
-    // column groups of equal size, as many slots as fit the LDS beside the rest (codes at pitch ld + 16, one float per
-    // slot) and VP_MAX_COLS; one block per compute unit
-    const int nrp = (W->rows + 63) / 64;
-    int max_cols = VP_MAX_COLS, gx = 1, gy = 1;
-    size_t smem = 0;
-    for (; max_cols >= 32; max_cols -= 32) {
-        const int ngroups = (n + max_cols - 1) / max_cols;
-        a.cols_per_group = ((n + ngroups - 1) / ngroups + 31) & ~31;
-        gy = (n + a.cols_per_group - 1) / a.cols_per_group;
-        gx = 256 / gy;
-        if (gx < 1) gx = 1;
-        if (gx > nrp) gx = nrp;
-        a.bias_rows = ((nrp + gx - 1) / gx + 2) * 64;         // of a block's run, which may begin and end inside 64 rows
-        smem = (size_t)a.cols_per_group * (W->ld + 16 + 4) + VP_WAVES * VP_STAGE + (size_t)a.bias_rows * 4;
-        if (smem <= 160 * 1024) break;
-    }
-    if (smem > 160 * 1024) return q8_fail(ctx, Q8_ERR_SHAPE, "vocabulary panel: %d rows", W->rows);
+    int gx, gy;
+    const size_t smem = q8_panel_plan(W->rows, W->ld, n, &a.cols_per_group, &gx, &gy, &a.bias_rows);
     typedef void (*kern_t)(PanelArgs);
     const kern_t kern = W->ld == 512 ? vocab_panel_kernel<16> : vocab_panel_kernel<20>;
     static Q8OncePerDevice asked[2];
-    const q8_status st = q8i_lds(ctx, asked[W->ld == 512 ? 0 : 1], (const void *)kern, 160 * 1024, "vocabulary panel kernel");
+    const q8_status st = q8i_lds(ctx, asked[W->ld == 512 ? 0 : 1], (const void *)kern, Q8_PANEL_LDS, "vocabulary panel kernel");
     if (st) return st;
     Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, kern, dim3(gx, gy), dim3(64 * VP_WAVES), smem, a);
     return q8i_launch_check(ctx, "vocabulary panel");

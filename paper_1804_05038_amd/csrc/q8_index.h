@@ -22,6 +22,32 @@ Q8_INDEX_FN void q8_position_run(const int *off, int n_sent, int b, int blocks, 
 // ---- the vocabulary panel (vocab_panel_kernel): units of 64 rows x 32 slots, dealt to the waves of a column group's blocks
 // in even runs, slots first ----
 
+#define Q8_PANEL_WAVES 8
+#define Q8_PANEL_STAGE 1536      // bytes of LDS per wave: a unit's statistics on their way out
+#define Q8_PANEL_LDS (160 * 1024)
+
+// Grid and LDS bytes of `rows` rows of ld bytes (512 or 640) times n slots.  Column groups of equal size, as many slots as fit
+// the LDS beside the rest (codes at pitch ld + 16, one float per slot) and 256; one block per compute unit.  A block's LDS
+// also holds the biases of its run's rows, which may begin and end inside 64 rows: *bias_rows of them.  For the 65536 rows
+// and 1024 slots that callers may ask for at most, a size always fits.
+Q8_INDEX_FN unsigned long long q8_panel_plan(int rows, int ld, int n, int *cols_per_group, int *gx, int *gy, int *bias_rows)
+{
+    const int groups = (rows + 63) / 64;
+    unsigned long long lds = 0;
+    for (int most = 256; most >= 32; most -= 32) {
+        const int ngroups = (n + most - 1) / most;
+        *cols_per_group = ((n + ngroups - 1) / ngroups + 31) & ~31;
+        *gy = (n + *cols_per_group - 1) / *cols_per_group;
+        *gx = 256 / *gy;
+        if (*gx < 1) *gx = 1;
+        if (*gx > groups) *gx = groups;
+        *bias_rows = ((groups + *gx - 1) / *gx + 2) * 64;
+        lds = (unsigned long long)*cols_per_group * (ld + 16 + 4) + Q8_PANEL_WAVES * Q8_PANEL_STAGE + (unsigned long long)*bias_rows * 4;
+        if (lds <= Q8_PANEL_LDS) break;
+    }
+    return lds;
+}
+
 // Units [*u0, *u1) of wave w of the block of rank b, and the 64-row group *rp0 that the block's first wave begins in.
 Q8_INDEX_FN void q8_panel_run(int row_groups, int slot_tiles, int blocks, int waves, int b, int w, int *u0, int *u1, int *rp0)
 {

@@ -18,3 +18,28 @@ void q8x_panel_weights(int half, int ks, int ntiles, unsigned *at)
     for (int lane = 0; lane < 64; ++lane)
         for (int s = 0; s < ks; ++s) at[lane * ks + s] = q8_panel_weight(half, lane, ks, ntiles) + q8_panel_step(s);
 }
+
+/* Plans every height in [1, rows] (step apart) times n slots: the largest LDS and the most rows of biases that a block's run
+ * needs beyond what the plan gives it (<= 0: enough); 0 in *worst_lds if a plan's groups do not cover the slots */
+void q8x_panel_plans(int rows, int step, int ld, int n, unsigned long long *worst_lds, int *worst_bias)
+{
+    *worst_lds = 1;
+    *worst_bias = -1000000;
+    for (int r = 1; r <= rows; r += step) {
+        int cols, gx, gy, bias_rows;
+        const unsigned long long lds = q8_panel_plan(r, ld, n, &cols, &gx, &gy, &bias_rows);
+        if ((long long)cols * gy < n || cols * (gy - 1) >= n || cols % 32 || gx * gy > 256) { *worst_lds = 0; return; }
+        if (lds > *worst_lds) *worst_lds = lds;
+        const int groups = (r + 63) / 64;
+        for (int g = 0; g < gy; g += gy > 1 ? gy - 1 : 1) {           /* the first group, and the last, which may be narrower */
+            const int own = n - g * cols < cols ? n - g * cols : cols, tiles = (own + 31) / 32;
+            for (int b = 0; b < gx; b += gx > 7 ? gx / 7 : 1) {
+                int u0, u1, rp0, first;
+                q8_panel_run(groups, tiles, gx, Q8_PANEL_WAVES, b, 0, &first, &u1, &rp0);
+                q8_panel_run(groups, tiles, gx, Q8_PANEL_WAVES, b, Q8_PANEL_WAVES - 1, &u0, &u1, &rp0);
+                const int need = u1 > first ? ((u1 - 1) / tiles - rp0 + 1) * 64 - bias_rows : -bias_rows;
+                if (need > *worst_bias) *worst_bias = need;
+            }
+        }
+    }
+}

@@ -67,3 +67,13 @@ def test_panel_weights_lie_inside_the_packed_matrix(lib, ks, rows):
         row = 32 * half + (lane & 31)
         want = ((row >> 4) * (ks // 2) + (step >> 1)) * 1024 + (2 * (step & 1) + (lane >> 5)) * 256 + (row & 15) * 16
         assert (got == want)[np.broadcast_to(row < 16 * ntiles, got.shape)].all()
+
+
+@pytest.mark.parametrize("ld", [512, 640])
+def test_panel_plans_fit_the_lds(lib, ld):
+    """Every vocabulary of up to 65536 rows times every panel of 9 to 1024 slots has a plan whose LDS is there, whose
+    groups cover the slots, and whose blocks hold the biases of all rows that their runs touch."""
+    lds, bias = ctypes.c_ulonglong(), ctypes.c_int()
+    for n in [*range(9, 70), *range(95, 1024, 31), 256, 257, 288, 289, 320, 512, 1000, 1023, 1024]:
+        lib.q8x_panel_plans(65536, 97 if n % 8 else 63, ld, n, ctypes.byref(lds), ctypes.byref(bias))
+        assert 0 < lds.value <= 160 * 1024 and bias.value <= 0, (n, lds.value, bias.value)
