@@ -601,9 +601,9 @@ def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
 @pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
                                    (4097, 512, 511), (2051, 640, 1024)])
 def test_vocabulary_panel_edges(q, oracle, V, R, n):
-    """The panel kernel's units (32 rows x 32 slots) at their remainders, column groups of every size, an odd bias address:
-    the selection on its statistics against the one on stored logits.  The sums behind the log-sum-exp differ in order
-    (double, rounded to float once): a last place of lse."""
+    """The panel kernel's units (64 rows x 32 slots) at their remainders, rows past the last packed tile, column groups of
+    every size, an odd bias address: the selection on its statistics against the one on stored logits.  The sums behind
+    the log-sum-exp differ in order (double, rounded to float once): a last place of lse."""
     rng = np.random.default_rng(V + n)
     ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=max(V, 4096), max_ld=640))
     W = gpu_mat(q, ctx, (rng.standard_normal((V, R)) * 0.05).astype(np.float32), True)
