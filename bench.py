@@ -570,7 +570,7 @@ def main():
                          "to back on one matrix and on 24 copies in turn, the two matrix-core products of a sentence, 20 batched steps")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on one GPU only (translation shards by sentence, one sentence per GPU, "
+        print("bench.py: runs on one GPU only (translation shards by sentence, one sentence per GPU, "
               "with no exchange); --gpus %d is not supported" % args.gpus, file=sys.stderr)
         sys.exit(2)
 

@@ -2,7 +2,7 @@
 import numpy as np
 import torch
 
-REL = 1e-5   # spec tolerance on dequantized fp32 values
+REL = 1e-5   # tolerance on dequantized fp32 values
 
 
 def assert_close(gpu, ref, what="", rel=REL):

@@ -25,7 +25,7 @@ def declared_functions():
     return sorted(set(names))
 
 
-def test_header_declares_the_north_star_entry_points():
+def test_header_declares_the_entry_points():
     names = declared_functions()
     for f in ("q8_quantize_matrix", "q8_gemv", "q8_gemm_narrow", "gru_step_q8", "cgru_decoder_step_q8",
               "output_logits_q8", "q8_encode", "q8_beam_update", "q8_translate", "q8_create", "q8_destroy"):

@@ -1,7 +1,7 @@
 """Pins for the oracle's search rules.  Section 3 of the paper only says that the beam is
 smaller than 8; pruning to the live beam, the shrink on end-of-sentence, the candidate order
 (score descending, parent ascending, token ascending), the stopping rule and "the best
-finished hypothesis wins" are this build's reading, and these tests fix them from outside the
+finished hypothesis wins" are this implementation's reading, and these tests fix them from outside the
 oracle's own code:
 
 * a model whose weight matrices are all zero has logits = the output bias at every step,
