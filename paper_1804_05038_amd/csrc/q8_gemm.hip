@@ -1100,16 +1100,18 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.ld > max_ld) max_ld = a.ld;
     }
     // Large panels (kernel trace, us, this form against the one that it takes the place of).  128 x 128 tiles where the
-    // results fill enough of them (3072 x 1024 times 1000 vectors: 14.3 against 14.9 K-resident; two such products times 384
-    // vectors 15.6 against 16.0, but times 257, whose last vector tile holds one, 15.0 against 11.1, and of 2304 rows times 448
-    // 14.3 against 12.6; 2415 x 1860 x 903: 19.6 against 20.1 staged; 1024 x 2048 x 1024: 16.5 against 13.0) and rows are
-    // longer than 512 bytes (two products of 3072 x 512 x 1024: 15.8 against 14.6 K-resident); rows that a K-resident
-    // block takes have to be whole 64-byte steps (3000 rows of 1008 bytes x 900: 13.6 against 12.8).  Else 64 x 64 tiles for
-    // packed rows that a K-resident block does not take (1024 x 2048 x 1024 10.7 against 12.8): with row-major weights the
+    // results fill enough of them (2415 x 1860 x 903: 19.6 against 20.1 staged; 1024 x 2048 x 1024: 16.5 against 13.0): for
+    // rows that a K-resident block does not take, but packed ones times at most 64 vectors, where 64 x 64 tiles are as fast
+    // or faster (33658 x 1088 x 64: 21.8 against 19.5); and for rows of more than 512 bytes that it takes, in whole 64-byte
+    // steps (3000 rows of 1008 bytes x 900: 13.6 against 12.8), more than 64 vectors (50000 x 1024 x 43 / 65: 19.8 against 17.8,
+    // 20.6 against 26.5) and results that leave in whole 16-byte pieces (33658 x 640 x 100, rows of results 4 bytes off:
+    // 24.3 against 21.0).  3072 x 1024 times 1000 vectors: 14.3 against 14.9 K-resident; two such products times 384 vectors 15.6
+    // against 16.0, but times 257, whose last vector tile holds one, 15.0 against 11.1; two products of 3072 x 512 x 1024: 15.8
+    // against 14.6.  Else 64 x 64 tiles for packed rows that a K-resident block does not take (1024 x 2048 x 1024 10.7 against
+    // 12.8 staged, 8200 x 2048 times 9 / 64 / 200 vectors 9.2 / 9.7 / 19.2 against 17.3 / 18.8 / 22.5): with row-major weights the
     // staged kernel, which requests a whole 128 bytes of each row at a time, is the faster one at every size (1024 x 2048
-    // times 9 / 130 / 512 vectors 9.8 / 11.0 / 11.4 against 12.1 / 12.1 / 12.4, 8192 rows x 130 15.3 against 21.6), as it is
-    // beyond 8192 rows.
-    bool tile_ok = !stats && n > 8, packed = true, steps = true;
+    // times 9 / 130 / 512 vectors 9.8 / 11.0 / 11.4 against 12.1 / 12.1 / 12.4, 8192 rows x 130 15.3 against 21.6).
+    bool tile_ok = !stats && n > 8, packed = true, steps = true, whole = true;
     long long results = 0;
     for (int t = 0; t < njobs; ++t) {
         const GemmArgs &a = jobs.j[t];
@@ -1117,8 +1119,9 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         results += (long long)a.rows * n;
         packed = packed && a.Wt;
         steps = steps && a.ld % 64 == 0;
+        whole = whole && a.ldy % 4 == 0 && ((uintptr_t)a.Y & 15) == 0;
     }
-    if (tile_ok && results >= TILE_FILL && (max_ld > 1024 || (max_ld > 512 && steps))) {
+    if (tile_ok && results >= TILE_FILL && (max_ld > 1024 ? n > 64 || !packed : max_ld > 512 && n > 64 && steps && whole)) {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
         static Q8OncePerDevice asked;
         const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_tile_kernel<4, 1, 4>, smem, "large panel kernel");
@@ -1126,7 +1129,7 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }
-    if (tile_ok && !resident && max_rows <= 8192 && packed) {
+    if (tile_ok && !resident && packed) {
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<2, 2, 1>), dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)2 * 64 * (256 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
     }

@@ -220,30 +220,30 @@ def test_rows_variant_argument_errors(q, ctx):
     assert e.value.code == 1
 
 
-def _panel_route(rows, ld, n, packed):
-    """The kernel that a plain product of more than 8 vectors is dispatched to."""
-    if rows * n >= 128 ** 3 and (ld > 1024 or (ld > 512 and ld % 64 == 0)):
+def _panel_route(rows, ld, n, packed, pitch):
+    """The kernel that a plain product of more than 8 vectors is dispatched to (results at `pitch` floats per vector)."""
+    resident = ld <= 1024
+    if rows * n >= 128 ** 3 and (ld > 512 and ld % 64 == 0 and n > 64 and pitch % 4 == 0 if resident else n > 64 or not packed):
         return "tiles of 128"
-    if ld <= 1024:
-        return "resident"
-    return "tiles of 64" if packed and rows <= 8192 else "staged"
+    return "resident" if resident else "tiles of 64" if packed else "staged"
 
 
 @pytest.mark.parametrize("rows,cols,n,tiled,route", [
     # 128 x 128 tiles: rows and vectors at the remainders of a tile (1, 127, 47), k steps and stages at theirs, row by row and packed
-    (2415, 1860, 903, False, "tiles of 128"), (2945, 1040, 769, False, "tiles of 128"), (2303, 576, 1023, False, "tiles of 128"),
+    (2415, 1860, 903, False, "tiles of 128"), (2945, 1040, 769, False, "tiles of 128"), (2324, 576, 1023, False, "tiles of 128"), (33000, 1100, 64, False, "tiles of 128"),
     (3000, 1088, 895, True, "tiles of 128"), (2433, 2112, 897, True, "tiles of 128"), (3072, 576, 897, True, "tiles of 128"),
     # 64 x 64 tiles
     (64, 1088, 64, True, "tiles of 64"), (1024, 2048, 513, True, "tiles of 64"), (130, 2112, 33, True, "tiles of 64"),
-    (65, 1088, 65, True, "tiles of 64"), (127, 1152, 9, True, "tiles of 64"),
+    (65, 1088, 65, True, "tiles of 64"), (127, 1152, 9, True, "tiles of 64"), (8200, 1088, 33, True, "tiles of 64"), (33001, 1088, 64, True, "tiles of 64"),
     # the forms on the other side of the rule
     (3000, 1000, 900, False, "resident"), (1553, 1024, 1024, False, "resident"), (1537, 528, 1023, False, "resident"), (2049, 16, 1024, False, "resident"),
-    (17, 1100, 9, False, "staged"), (65, 1040, 65, False, "staged"), (1000, 2000, 513, False, "staged"), (8200, 1088, 33, True, "staged")])
+    (17, 1100, 9, False, "staged"), (65, 1040, 65, False, "staged"), (1000, 2000, 513, False, "staged"), (8201, 1088, 33, False, "staged"),
+    (33658, 640, 65, True, "resident"), (33000, 640, 64, False, "resident")])
 @pytest.mark.parametrize("by_row", [False, True])
 def test_large_panels(q, oracle, rows, cols, n, tiled, route, by_row):
     """The tiled products at the edges of their tiles, stages and k steps, packed and row by row, one scale and one per
     row, results at an odd pitch: exact integer sums, one product of scales, one addition, so identical bits."""
-    assert _panel_route(rows, (cols + 15) // 16 * 16, n, tiled) == route
+    assert _panel_route(rows, (cols + 15) // 16 * 16, n, tiled, rows) == route
     rng = np.random.default_rng(rows + n)
     ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
     W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
