@@ -51,21 +51,25 @@ __device__ __forceinline__ void f32_load(F32Regs<RW, UN> &R, const __amdgpu_buff
 
 // LDS pitch of a vector: where a row's last chunk of 256 columns is incomplete, four zeros at least follow the vector.
 // The lanes past cols read those: their weights are zeros, and zero times an infinite entry of x would not be zero.
+// GAP is false in kernels whose vectors are all whole chunks: nothing is masked and nothing lies between them (in one
+// kernel for both, a decoder step and output layer of such vectors took 75.5 us instead of 72.8).
 __host__ __device__ constexpr int f32_pitch(int cols) { return cols % 256 == 0 ? cols : ((cols + 3) & ~3) + 4; }
+template <bool GAP>
+__device__ __forceinline__ int f32_pitch_of(int cols) { return GAP ? f32_pitch(cols) : cols; }
 
 // x: N vectors in LDS, pitch floats apart (f32_pitch, zeros past cols).
-template <int N, int RW, int UN>
+template <int N, int RW, int UN, bool GAP>
 __device__ __forceinline__ void f32_fma(const F32Regs<RW, UN> &R, const float *x, int pitch, int cols, int c0, int lane, double (&acc)[RW][N])
 {
 #pragma unroll
     for (int t = 0; t < UN; ++t) {
         if ((c0 + t) * 256 >= cols) break;                      // uniform
-        const int k = ((c0 + t) * 64 + lane) * 4, kx = min(k, pitch - 4);
+        const int k = ((c0 + t) * 64 + lane) * 4, kx = GAP ? min(k, pitch - 4) : k;
         double w[RW][4];
 #pragma unroll
         for (int u = 0; u < RW; ++u) {
             float4 v = R.w[u][t];
-            if (cols & 3) {                                     // what lies past cols in the row counts for nothing
+            if (GAP && (cols & 3)) {                                     // what lies past cols in the row counts for nothing
                 v.x = k < cols ? v.x : 0.0f; v.y = k + 1 < cols ? v.y : 0.0f;
                 v.z = k + 2 < cols ? v.z : 0.0f; v.w = k + 3 < cols ? v.w : 0.0f;
             }
@@ -87,21 +91,21 @@ __device__ __forceinline__ void f32_fma(const F32Regs<RW, UN> &R, const float *x
 }
 
 // The rest of a product whose first UN chunks are on their way in R.
-template <int N, int RW, int UN>
+template <int N, int RW, int UN, bool GAP>
 __device__ __forceinline__ void f32_product(F32Regs<RW, UN> &R, const __amdgpu_buffer_rsrc_t (&row)[RW], const float *x, int pitch,
                                             int cols, int lane, double (&acc)[RW][N])
 {
     const int nchunk = (cols + 255) >> 8;
     if (nchunk <= UN) {
-        f32_fma<N, RW, UN>(R, x, pitch, cols, 0, lane, acc);
+        f32_fma<N, RW, UN, GAP>(R, x, pitch, cols, 0, lane, acc);
         return;
     }
     for (int c0 = 0; c0 < nchunk; c0 += 2 * UN) {
         F32Regs<RW, UN> S;
         f32_load<RW, UN>(S, row, cols, c0 + UN, lane);
-        f32_fma<N, RW, UN>(R, x, pitch, cols, c0, lane, acc);
+        f32_fma<N, RW, UN, GAP>(R, x, pitch, cols, c0, lane, acc);
         f32_load<RW, UN>(R, row, cols, c0 + 2 * UN, lane);
-        f32_fma<N, RW, UN>(S, x, pitch, cols, c0 + UN, lane, acc);
+        f32_fma<N, RW, UN, GAP>(S, x, pitch, cols, c0 + UN, lane, acc);
     }
 }
 
@@ -123,11 +127,11 @@ __device__ __forceinline__ void f32_x_load(F32X<XB> &R, const float *X, int tota
         R.v[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rx, (i * 256 + (int)threadIdx.x) * 16, 0, 0));
     __builtin_amdgcn_sched_barrier(0);
 }
-template <int N, int XB>
+template <int N, int XB, bool GAP>
 __device__ __forceinline__ void f32_x_store(const F32X<XB> &R, float *s, const float *X, int cols, int ldx, int flat)
 {
     __builtin_amdgcn_sched_barrier(0);
-    const int pitch = f32_pitch(cols);
+    const int pitch = f32_pitch_of<GAP>(cols);
     if (flat) {
         const int total = N * cols;
         auto store = [&](auto at) {                            // element k of the run goes to at(k)
@@ -138,7 +142,7 @@ __device__ __forceinline__ void f32_x_store(const F32X<XB> &R, float *s, const f
             }
             for (int k = (XB * 256 + (int)threadIdx.x) * 4; k < total; k += 1024) *(float4 *)(s + at(k)) = *(const float4 *)(X + k);
         };
-        if (pitch == cols) {
+        if (!GAP || pitch == cols) {
             store([](int k) { return k; });
         } else {
             // four further on per vector before it; the quotient by a reciprocal: k < 2^16, so (k + 1/2) / cols lies further
@@ -159,13 +163,13 @@ __device__ __forceinline__ void f32_x_store(const F32X<XB> &R, float *s, const f
 // Measured (5 vectors, kernel trace): 50000 x 512 with the statistics 22.6 us (102 MB, 4.5 TB/s), the two products of
 // s' (4096 x 1024) 6.3 us.  The five product launches of a decoder step and output layer took 130 us of 176 before (a
 // row pair per wave without a second round in flight; a multiply, an add and a conversion of x per entry; 10
-// reductions of 18 instructions per row pair), the statistics a launch of 4.8 us; now 76 us for all of it.
+// reductions of 18 instructions per row pair), the statistics a launch of 4.8 us; now 73 us for all of it.
 struct F32Stats {
     float *part_max;
     double *part_sum;
     int ntiles;
 };
-template <int N, int RW, int UN, bool STATS>
+template <int N, int RW, int UN, bool STATS, bool GAP>
 __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st)
 {
     extern __shared__ __align__(16) float s_x[];
@@ -175,7 +179,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
     const F32Job &J = jobs.j[t];
     const int blk = blockIdx.x - jobs.nblk[t], nblk = jobs.nblk[t + 1] - jobs.nblk[t];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cols = J.cols, rows = J.rows, pitch = f32_pitch(cols);
+    const int cols = J.cols, rows = J.rows, pitch = f32_pitch_of<GAP>(cols);
     __amdgpu_buffer_rsrc_t row[RW];
     F32Regs<RW, UN> R;
     auto request = [&](int r0) {
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
     F32X<N> X;
     f32_x_load<N>(X, J.X, N * cols, J.flat);
     request(r0);
-    f32_x_store<N, N>(X, s_x, J.X, cols, J.ldx, J.flat);
+    f32_x_store<N, N, GAP>(X, s_x, J.X, cols, J.ldx, J.flat);
     __syncthreads();
     // (the trip count is the block's, so that STATS can meet inside: a wave past the last row works on zeros)
     for (int b0 = blk * 4 * RW; b0 < rows; b0 += nblk * 4 * RW) {
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
         const int idx = wave_sums_index<RW * N>(lane), u = idx / N, j = idx - u * N, rw = r0 + u;
         const bool mine = (lane & 15) < (RW * N + 3) / 4 && idx < RW * N;
         const float bias = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(mine && rw < rows ? (unsigned)rw * 4u : Q8_OOB), 0, 0));
-        f32_product<N, RW, UN>(R, row, s_x, pitch, cols, lane, acc);
+        f32_product<N, RW, UN, GAP>(R, row, s_x, pitch, cols, lane, acc);
         r0 += nblk * 4 * RW;
         request(r0);                                           // the next group's first round, behind the reduction
         double v[RW * N];
@@ -239,14 +243,14 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(F32Jobs jobs, F32Stats st
 
 // A whole GRU cell (Eq. 1): a wave owns one hidden unit, its three rows of Wx and, unless the recurrent
 // pre-activations are given (gh_pre, [n x 3H], bias included), of Wh; the gates follow in the lanes.  Was a
-// launch of products, 2 x n x 3H floats written and read back, and a launch of gates: 20.8 + 4.5 us -> 8.2 us
-// (512 / 1024 columns, 1024 units, 5 vectors), 9.1 us for 2048 columns with gh_pre.
+// launch of products, 2 x n x 3H floats written and read back, and a launch of gates: 20.8 + 4.5 us -> 7.3 us
+// (512 / 1024 columns, 1024 units, 5 vectors), 7.8 us for 2048 columns with gh_pre.
 struct F32GruArgs {
     const float *Wx, *Wh, *bx, *bh, *x, *h_prev, *gh_pre;
     float *h_out;
     int I, H, ldx_w, ldh_w, flat;
 };
-template <int N, bool GH_PRE>
+template <int N, bool GH_PRE, bool GAP>
 __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
 {
     extern __shared__ __align__(16) float s_x[];
@@ -254,7 +258,7 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
     constexpr int UN = GH_PRE ? 4 : 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, H = a.H, I = a.I;
     const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave);
-    const int px = f32_pitch(I), ph = f32_pitch(H);
+    const int px = f32_pitch_of<GAP>(I), ph = f32_pitch_of<GAP>(H);
     __amdgpu_buffer_rsrc_t rx[3], rh[3];
     F32Regs<3, UN> X, Hh;
 #pragma unroll
@@ -269,8 +273,8 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
     if (!GH_PRE) f32_x_load<N>(hv, a.h_prev, N * H, a.flat);
     f32_load<3, UN>(X, rx, I, 0, lane);
     if (!GH_PRE) f32_load<3, UN>(Hh, rh, H, 0, lane);
-    f32_x_store<N, XB>(xv, s_x, a.x, I, I, a.flat);
-    if (!GH_PRE) f32_x_store<N, N>(hv, s_x + (size_t)N * px, a.h_prev, H, H, a.flat);
+    f32_x_store<N, XB, GAP>(xv, s_x, a.x, I, I, a.flat);
+    if (!GH_PRE) f32_x_store<N, N, GAP>(hv, s_x + (size_t)N * px, a.h_prev, H, H, a.flat);
     __syncthreads();
     double acc[3][N];
     auto finish = [&](int base, const float *bias) {
@@ -286,12 +290,12 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
     };
 #pragma unroll
     for (int e = 0; e < 3 * N; ++e) acc[e / N][e % N] = 0.0;
-    f32_product<N, 3, UN>(X, rx, s_x, px, I, lane, acc);
+    f32_product<N, 3, UN, GAP>(X, rx, s_x, px, I, lane, acc);
     finish(0, a.bx);
     if (!GH_PRE) {
 #pragma unroll
         for (int e = 0; e < 3 * N; ++e) acc[e / N][e % N] = 0.0;
-        f32_product<N, 3, UN>(Hh, rh, s_x + (size_t)N * px, ph, H, lane, acc);
+        f32_product<N, 3, UN, GAP>(Hh, rh, s_x + (size_t)N * px, ph, H, lane, acc);
         finish(3 * N, a.bh);
     }
     __builtin_amdgcn_wave_barrier();                           // a wave reads back its own sums
@@ -307,13 +311,13 @@ __global__ __launch_bounds__(256) void gru_f32_kernel(F32GruArgs a)
 }
 
 // t = tanh(((W_s s + W_y y) + W_c c) + b_t) (first layer of g, Eq. 2): a wave owns one unit and the three
-// rows that meet in it.  Was a launch of three products and a launch that added them up: 20.8 + 4.8 us -> 7.9 us.
+// rows that meet in it.  Was a launch of three products and a launch that added them up: 20.8 + 4.8 us -> 7.3 us.
 struct F32ReadoutArgs {
     const float *W[3], *x[3], *b_t;
     float *t_out;
     int cols[3], ld[3], R, flat;
 };
-template <int N>
+template <int N, bool GAP>
 __global__ __launch_bounds__(256) void readout_f32_kernel(F32ReadoutArgs a)
 {
     extern __shared__ __align__(16) float s_x[];
@@ -332,20 +336,20 @@ __global__ __launch_bounds__(256) void readout_f32_kernel(F32ReadoutArgs a)
         row[m][0] = f32_row(a.W[m], unit, a.R, a.ld[m]);
         f32_load<1, 4>(R[m], row[m], a.cols[m], 0, lane);
     }
-    const int p0 = f32_pitch(a.cols[0]), p1 = f32_pitch(a.cols[1]);
-    f32_x_store<N, N>(x0, s_x, a.x[0], a.cols[0], a.cols[0], a.flat);
-    f32_x_store<N, N>(x1, s_x + (size_t)N * p0, a.x[1], a.cols[1], a.cols[1], a.flat);
-    f32_x_store<N, 2 * N>(x2, s_x + (size_t)N * (p0 + p1), a.x[2], a.cols[2], a.cols[2], a.flat);
+    const int p0 = f32_pitch_of<GAP>(a.cols[0]), p1 = f32_pitch_of<GAP>(a.cols[1]);
+    f32_x_store<N, N, GAP>(x0, s_x, a.x[0], a.cols[0], a.cols[0], a.flat);
+    f32_x_store<N, N, GAP>(x1, s_x + (size_t)N * p0, a.x[1], a.cols[1], a.cols[1], a.flat);
+    f32_x_store<N, 2 * N, GAP>(x2, s_x + (size_t)N * (p0 + p1), a.x[2], a.cols[2], a.cols[2], a.flat);
     __syncthreads();
     double v[3 * N];
     float *s = s_x;
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-        const int pitch = f32_pitch(a.cols[m]);
+        const int pitch = f32_pitch_of<GAP>(a.cols[m]);
         double acc[1][N];
 #pragma unroll
         for (int j = 0; j < N; ++j) acc[0][j] = 0.0;
-        f32_product<N, 1, 4>(R[m], row[m], s, pitch, a.cols[m], lane, acc);
+        f32_product<N, 1, 4, GAP>(R[m], row[m], s, pitch, a.cols[m], lane, acc);
 #pragma unroll
         for (int j = 0; j < N; ++j) v[m * N + j] = acc[0][j];
         s += (size_t)N * pitch;
@@ -388,6 +392,7 @@ q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n, floa
     F32Jobs jobs;
     F32Stats st = {part_max, part_sum, q8i_out_tiles(d[0].W->rows)};
     int blocks = 0, max_pitch = 0;
+    bool gap = false;
     long long rows = 0;
     for (int t = 0; t < njobs; ++t) rows += d[t].W->rows;
     // Rows per wave: what fills the chip's 1024 SIMDs first (a wave's loads in flight are the same 8 either way),
@@ -403,15 +408,18 @@ q8_status q8i_gemv_f32(q8_ctx *ctx, const q8i_f32_job *d, int njobs, int n, floa
             if (b > 1024) b = 1024;
             blocks += b;
             if (f32_pitch(q.W->cols) > max_pitch) max_pitch = f32_pitch(q.W->cols);
+            gap = gap || q.W->cols % 256;
         }
     }
     jobs.nblk[F32_MAX_JOBS] = blocks;
     for (int t = njobs; t < F32_MAX_JOBS; ++t) jobs.nblk[t] = blocks;
     const size_t smem = (size_t)n * max_pitch * sizeof(float);
+#define F32_GEMV_G(K, G)                                                                                                    \
+    (part_max ? gemv_f32_kernel<K, 4, 2, true, G> : rw == 4 ? gemv_f32_kernel<K, 4, 2, false, G>                            \
+     : rw == 2 ? gemv_f32_kernel<K, 2, 4, false, G> : gemv_f32_kernel<K, 1, 8, false, G>)
 #define F32_GEMV(K)                                                                                                        \
     do {                                                                                                                   \
-        void (*kern)(F32Jobs, F32Stats) = part_max ? gemv_f32_kernel<K, 4, 2, true> : rw == 4 ? gemv_f32_kernel<K, 4, 2, false> \
-                                          : rw == 2 ? gemv_f32_kernel<K, 2, 4, false> : gemv_f32_kernel<K, 1, 8, false>;   \
+        void (*kern)(F32Jobs, F32Stats) = gap ? F32_GEMV_G(K, true) : F32_GEMV_G(K, false);                                \
         if (!f32_lds((const void *)kern, smem)) return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit product: %zu bytes of LDS refused", smem); \
         Q8_LAUNCH(ctx, Q8_KERNEL_GEMV, kern, dim3(blocks), dim3(256), smem, jobs, st);                                     \
     } while (0)
@@ -439,12 +447,13 @@ q8_status q8i_gru_f32(q8_ctx *ctx, const q8_gru_weights_f32 *g, const float *x, 
     const F32GruArgs a = {g->Wx.data, g->Wh.data, g->bx, g->bh, x, h_prev, gh_pre, h_out, I, H, g->Wx.ld, g->Wh.ld, flat};
     const size_t smem = (size_t)n * (f32_pitch(I) + (gh_pre ? 0 : f32_pitch(H))) * sizeof(float);
     const dim3 grid((H + 3) / 4);
+    const bool gap = I % 256 || (!gh_pre && H % 256);
 #define F32_GRU(K)                                                                                                          \
     do {                                                                                                                    \
-        if (!f32_lds(gh_pre ? (const void *)gru_f32_kernel<K, true> : (const void *)gru_f32_kernel<K, false>, smem))        \
-            return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit GRU kernel: %zu bytes of LDS refused", smem);                         \
-        if (gh_pre) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_f32_kernel<K, true>), grid, dim3(256), smem, a);                      \
-        else Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (gru_f32_kernel<K, false>), grid, dim3(256), smem, a);                            \
+        void (*kern)(F32GruArgs) = gap ? (gh_pre ? gru_f32_kernel<K, true, true> : gru_f32_kernel<K, false, true>)          \
+                                       : (gh_pre ? gru_f32_kernel<K, true, false> : gru_f32_kernel<K, false, false>);       \
+        if (!f32_lds((const void *)kern, smem)) return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit GRU kernel: %zu bytes of LDS refused", smem); \
+        Q8_LAUNCH(ctx, Q8_KERNEL_GRU, kern, grid, dim3(256), smem, a);                                                      \
     } while (0)
     F32_FOR_N(n, F32_GRU)
     return q8i_launch_check(ctx, "gru_f32");
@@ -463,19 +472,21 @@ q8_status q8i_readout_f32(q8_ctx *ctx, const q8_readout_weights_f32 *ro, const f
     const float *x[3] = {s, y, c};
     F32ReadoutArgs a;
     size_t smem = 0;
+    bool gap = false;
     a.flat = 1;
     for (int m = 0; m < 3; ++m) {
         a.W[m] = W[m]->data; a.x[m] = x[m]; a.cols[m] = W[m]->cols; a.ld[m] = W[m]->ld;
         a.flat &= f32_flat(x[m], n, W[m]->cols, W[m]->cols);
+        gap = gap || W[m]->cols % 256;
         smem += (size_t)n * f32_pitch(W[m]->cols) * sizeof(float);
     }
     a.b_t = ro->b_t; a.t_out = t_out; a.R = ro->W_s.rows;
     const dim3 grid((a.R + 3) / 4);
 #define F32_READOUT(K)                                                                                                      \
     do {                                                                                                                    \
-        if (!f32_lds((const void *)readout_f32_kernel<K>, smem))                                                            \
-            return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit readout kernel: %zu bytes of LDS refused", smem);                     \
-        Q8_LAUNCH(ctx, Q8_KERNEL_READOUT, (readout_f32_kernel<K>), grid, dim3(256), smem, a);                               \
+        void (*kern)(F32ReadoutArgs) = gap ? readout_f32_kernel<K, true> : readout_f32_kernel<K, false>;                    \
+        if (!f32_lds((const void *)kern, smem)) return q8_fail(ctx, Q8_ERR_DEVICE, "32-bit readout kernel: %zu bytes of LDS refused", smem); \
+        Q8_LAUNCH(ctx, Q8_KERNEL_READOUT, kern, grid, dim3(256), smem, a);                                                  \
     } while (0)
     F32_FOR_N(n, F32_READOUT)
     return q8i_launch_check(ctx, "readout_f32");
