@@ -254,9 +254,12 @@ q8_status output_logits_q8(q8_ctx *ctx, const q8_readout_weights *ro, const q8_m
 /* The encoder of Eq. 1 for n_sent sentences side by side: X [L x E] holds their embedding
  * vectors back to back, sentence s in rows [sent_off[s], sent_off[s + 1]) (sent_off: device
  * int32 [n_sent + 1]; sent_off_host: the same values on the host, sent_off_host[0] = 0);
- * enc_h [L x 2H] as q8_encode.  All input products run as matrix-core panels; time step t
- * of every sentence that has one, in both directions, runs in one launch (H <= 1024 and, at
- * H = 1024, up to 256 sentences; beyond, mostly a quantize / product / gates triple).  Values are those of q8_encode sentence by sentence.  Needs
+ * enc_h [L x 2H] as q8_encode.  All input products run as matrix-core panels; the recurrences of all
+ * sentences, both directions, are one launch for H <= 1024 (rows of Wh of at most 1024 bytes), else a
+ * quantize / product / gates triple per time step.  Blocks of that launch wait for each other's states, but
+ * nothing depends on them running side by side: a wait that takes too long (some milliseconds, or the bound
+ * of q8_encoder_options if that is smaller) ends in one block working its sentences off alone, which is
+ * slow and gives the same states.  Values are those of q8_encode sentence by sentence.  Needs
  * q8_encode_batch_bytes(fwd, L, n_sent) bytes of workspace. */
 size_t q8_encode_batch_bytes(const q8_gru_weights *fwd, int total_l, int n_sent);
 q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X,

@@ -598,6 +598,30 @@ def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
         assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
 
 
+@pytest.mark.parametrize("E,H,lens,tiled", [(16, 36, [5, 1, 9], False), (16, 4, [3] * 129, False), (32, 1024, [4] * 64 + [7], True),
+                                            (32, 1000, [1, 6, 2] * 23, False), (16, 100, [3, 2] * 70, False), (16, 256, [2, 5, 3] * 340, True)])
+def test_encoder_of_a_batch_whatever_its_blocks_wait_for(q, oracle, E, H, lens, tiled):
+    """The recurrences in one launch at the edges of their sets and groups (one sentence per set, 16 and 17 of them, several
+    groups, units and rows past H), with room for their words only: q8_encode's states, bit for bit; and the same with a
+    bound of one poll, where members leave and the last of each set works it off by itself.  Neither reports a wait."""
+    rng = np.random.default_rng(H + len(lens))
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=len(lens) + (k == "b"), I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], False), gpu_mat(q, big, p[k + "Wh"], tiled), big.f32(p[k + "bx"]), big.f32(p[k + "bh"]))
+         for k in ("f", "b")]
+    L = sum(lens)
+    X = big.f32(rng.standard_normal((L, E)).astype(np.float32))
+    ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], L, len(lens)))
+    enc = np_(q.q8_encode_batch(ctx, G[0], G[1], X, list(lens)))
+    off = [0] + list(np.cumsum(lens))
+    for i in sorted({*range(min(20, len(lens))), *range(max(0, len(lens) - 5), len(lens))}):
+        rows = slice(int(off[i]), int(off[i + 1]))
+        assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
+    q.q8_encoder_options(ctx, True, 1)
+    assert_same(q.q8_encode_batch(ctx, G[0], G[1], X, list(lens)), enc, "a bound of one poll")
+    q.q8_encode_check(ctx)
+
+
 @pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
                                    (4097, 512, 511), (2051, 640, 1024)])
 def test_vocabulary_panel_edges(q, oracle, V, R, n):
