@@ -818,9 +818,13 @@ __device__ __forceinline__ float vp_max8(const float *v)
 // 64-byte lines of statistics leaving the block together, cost 8 of 43 us at 1000 slots).  A unit's statistics go
 // through LDS all the same, so that a slot's four tiles leave as 16 and 32 contiguous bytes: every lane storing its own
 // 4 and 8 bytes, into rows 12 and 25 KB apart, took 10 of 45 us.
-// 50000 x 512 (kernel trace): 25 us at 320 slots, 55 us at 1000 with 16 x 16 results -> 18.7 / 41.8 us; 40001 rows at 600
-// slots 43 -> 31.6 us; 50294 rows of 640 bytes at 320 slots 31 -> 21.3 us.  At 1000 slots the products alone (no
-// statistics, nothing stored) take 26 us.  Measured and not kept: units of 32 rows with every lane storing its own
+// 50000 x 512 (kernel trace): 25 us at 320 slots, 55 us at 1000 with 16 x 16 results -> 18.5 / 41.2 us -> 17.8 / 38.0 with
+// everything that goes to LDS requested at once, rows past the matrix masked by their biases instead of sixteen selects
+// (the block that has them ended 3 us after the others) and longer runs for the waves that are served first; 40001 rows at
+// 600 slots 43 -> 31.6 us; 50294 rows of 640 bytes at 320 slots 31 -> 21.3 us.  At 1000 slots, us after the first block
+// starts: codes and weights there 5.6 (256 KB per compute unit), waves done 31 to 38; a unit of 2000 clocks per SIMD is 1024 of
+// products and some 390 vector instructions, which take 1.4 times as long beside products; the clock is at 1.8 GHz there.
+// (Products of one half beside the statistics of the other in one wave: the same, 39.8 against 40.4.)  Measured and not kept: units of 32 rows with every lane storing its own
 // (the same, but 38 us at 600 slots), twelve waves per block (the same; sixteen spill), the weights requested after
 // everything else (the same).
 template <int KS>      // 32-byte k steps per row: ld = 32 KS
@@ -841,7 +845,12 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
     // group, so that an XCD's L2 is asked for one eighth of the matrix and gives it to all groups.
     const int gx = gridDim.x, rank = gx % 8 == 0 ? ((int)blockIdx.x & 7) * (gx >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
     int u0, u1, rp0;                                          // the wave's units, the block's first rows
-    q8_panel_run(nrp, nct, gx, VP_WAVES, rank, wave, &u0, &u1, &rp0);
+    {
+        int first, end, skip;
+        q8_panel_run(nrp, nct, gx, VP_WAVES, rank, 0, &first, &skip, &rp0);
+        q8_panel_run(nrp, nct, gx, VP_WAVES, rank, VP_WAVES - 1, &skip, &end, &u1);
+        q8_panel_wave_run(first, end, wave, &u0, &u1);
+    }
     int rp = u0 / nct, ct = u0 - rp * nct;
 
     // weights: lane (row i, k half h) of k step s holds bytes 32 s + 16 h .. of row 64 rp + 32 t + i; in the packed order
@@ -853,37 +862,50 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
     auto weights = [&](unsigned at, int s) {
         return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(at + q8_panel_step(s)), 0, 0));
     };
-    // the codes of this block's slots into LDS (slots past the panel are zero): eight 16-byte pieces per
-    // thread and round, requested together through a bounds-checked descriptor (no branch around a
-    // load: inside one, every piece would be a memory round trip of its own)
+    // Everything the block keeps in LDS is requested before the first wait, through descriptors and not in branches, what is
+    // needed first first: factors, biases, codes (16-byte pieces; slots past the panel are zero), then the weights.  (Biases
+    // zero without any: adding zero changes no logit but the sign of a zero, which no comparison and no exponential sees.
+    // Rows past the matrix have -inf, which makes their logits that.)
     {
+        constexpr int PB = 4, PX = (256 * (ld / 16) + NTHR - 1) / NTHR < 18 ? (256 * (ld / 16) + NTHR - 1) / NTHR : 18;
+        const __amdgpu_buffer_rsrc_t rc = q8_rsrc(a.xscale + c_base, (size_t)cols * 4);
+        const __amdgpu_buffer_rsrc_t rb = q8_rsrc(a.bias, a.bias ? (size_t)a.rows * 4 : 0);
         const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.xq + (size_t)c_base * ld, (size_t)cols * ld);
         const int total = nct * 32 * (ld / 16);
-        for (int p0 = 0; p0 < total; p0 += 8 * NTHR) {
-            v4i v[8];
+        const float xs = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, tid * 4, 0, 0));
+        float bv[PB];
+        v4i xv[PX];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * NTHR + tid;               // piece p: slot p / (ld / 16), bytes 16 (p % (ld / 16)) ..
-                v[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(p < total ? (unsigned)p * 16u : Q8_OOB), 0, 0));
-            }
-            if (p0 == 0) {
-                const unsigned at0 = q8_panel_weight(2 * rp, lane, KS, a.ntiles), at1 = q8_panel_weight(2 * rp + 1, lane, KS, a.ntiles);
+        for (int u = 0; u < PB; ++u) bv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (64 * rp0 + u * NTHR + tid) * 4, 0, 0));
 #pragma unroll
-                for (int s = 0; s < KS; ++s) { A[0][s] = weights(at0, s); A[1][s] = weights(at1, s); }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * NTHR + tid;
-                const int col = p / (ld / 16), ch = p - col * (ld / 16);
-                if (p < total) *(v4i *)(s_x + col * pitch + ch * 16) = v[u];
-            }
+        for (int u = 0; u < PX; ++u) {
+            const int p = u * NTHR + tid;                        // piece p: slot p / (ld / 16), bytes 16 (p % (ld / 16)) ..
+            xv[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(p < total ? (unsigned)p * 16u : Q8_OOB), 0, 0));
         }
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned at0 = q8_panel_weight(2 * rp, lane, KS, a.ntiles), at1 = q8_panel_weight(2 * rp + 1, lane, KS, a.ntiles);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) A[0][s] = weights(at0, s);
+        __builtin_amdgcn_sched_barrier(0);
+        if (tid < a.cols_per_group) s_c[tid] = a.w_scale * xs;
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+            if (u * NTHR + tid < a.bias_rows) s_b[u * NTHR + tid] = 64 * rp0 + u * NTHR + tid < a.rows ? bv[u] : -INFINITY;
+#pragma unroll
+        for (int u = 0; u < PX; ++u) {
+            const int p = u * NTHR + tid, col = p / (ld / 16), ch = p - col * (ld / 16);
+            if (p < total) *(v4i *)(s_x + col * pitch + ch * 16) = xv[u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) A[1][s] = weights(at1, s);
+        // (the last pieces and biases of widths and heights that need more than the registers above)
+        for (int p = PX * NTHR + tid; p < total; p += NTHR) {
+            const int col = p / (ld / 16), ch = p - col * (ld / 16);
+            *(v4i *)(s_x + col * pitch + ch * 16) = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, p * 16, 0, 0));
+        }
+        for (int r = PB * NTHR + tid; r < a.bias_rows; r += NTHR) s_b[r] = 64 * rp0 + r < a.rows ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (64 * rp0 + r) * 4, 0, 0)) : -INFINITY;
     }
-    for (int c = tid; c < nct * 32; c += NTHR) s_c[c] = c < cols ? a.w_scale * a.xscale[c_base + c] : 0.0f;
-    // biases of the block's rows (zero without any: adding zero changes no logit but the sign of a zero, which
-    // no comparison and no exponential sees)
-    for (int r = tid; r < a.bias_rows; r += NTHR) s_b[r] = a.bias && 64 * rp0 + r < a.rows ? a.bias[64 * rp0 + r] : 0.0f;
     __syncthreads();
 
     const int8_t *bp = s_x + i * pitch + 16 * h;
@@ -927,11 +949,6 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
                 y[4 * q + 2] = (float)acc[t][4 * q + 2] * c + b.z;
                 y[4 * q + 3] = (float)acc[t][4 * q + 3] * c + b.w;
             }
-            const int row0 = 64 * rp + 32 * t;
-            if (row0 + 32 > a.rows) {                         // uniform: the last rows may be incomplete
-#pragma unroll
-                for (int r = 0; r < 16; ++r) y[r] = row0 + 8 * (r >> 2) + 4 * h + (r & 3) < a.rows ? y[r] : -INFINITY;
-            }
             float m[2] = {vp_max8(y), vp_max8(y + 8)};
             // the halves trade: lanes of half v hold tile v's maximum, then everybody gets both
             auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(m[0]), __float_as_uint(m[1]), false, false);
@@ -961,17 +978,17 @@ __global__ __launch_bounds__(64 * VP_WAVES, 2) void vocab_panel_kernel(PanelArgs
         asm volatile("" ::"v"(st_max), "v"(st_sum), "v"(st_o4), "v"(st_o8));
         st_max = *(const v2u *)(s_max + 2 * lane);
         st_sum = *(const v4u *)(s_sum + 2 * lane);
-        st_o4 = (int)(o * 4u);
-        st_o8 = (int)(o < Q8_OOB >> 3 ? o * 8u : Q8_OOB);
-        if (4 * rp + 4 <= a.ntiles) {                         // uniform
-            __builtin_amdgcn_raw_buffer_store_b64(st_max, rpm, st_o4, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(st_sum, rps, st_o8, 0, 0);
-        } else {                                              // the last rows: some of the four tiles are missing
-            __builtin_amdgcn_raw_buffer_store_b32(st_max.x, rpm, st_o4, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 0, 1), rps, st_o8, 0, 0);
-            if (both && o < Q8_OOB >> 2) {
-                __builtin_amdgcn_raw_buffer_store_b32(st_max.y, rpm, st_o4 + 4, 0, 0);
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 2, 3), rps, st_o8 + 8, 0, 0);
+        const bool whole = 4 * rp + 4 <= a.ntiles;            // uniform
+        st_o4 = (int)(whole ? o * 4u : Q8_OOB);
+        st_o8 = (int)(whole && o < Q8_OOB >> 3 ? o * 8u : Q8_OOB);
+        __builtin_amdgcn_raw_buffer_store_b64(st_max, rpm, st_o4, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(st_sum, rps, st_o8, 0, 0);
+        if (!whole && o < Q8_OOB >> 2) {                      // the last rows: some of the four tiles are missing
+            __builtin_amdgcn_raw_buffer_store_b32(st_max.x, rpm, (int)(o * 4u), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 0, 1), rps, (int)(o * 8u), 0, 0);
+            if (both) {
+                __builtin_amdgcn_raw_buffer_store_b32(st_max.y, rpm, (int)(o * 4u) + 4, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(st_sum, st_sum, 2, 3), rps, (int)(o * 8u) + 8, 0, 0);
             }
         }
         if (++ct == nct) { ct = 0; ++rp; }

@@ -12,6 +12,11 @@ void q8x_panel_runs(int row_groups, int slot_tiles, int blocks, int waves, int *
         for (int w = 0; w < waves; ++w) q8_panel_run(row_groups, slot_tiles, blocks, waves, b, w, u0 + b * waves + w, u1 + b * waves + w, rp0 + b * waves + w);
 }
 
+void q8x_panel_wave_runs(int first, int end, int *u0, int *u1)
+{
+    for (int w = 0; w < Q8_PANEL_WAVES; ++w) q8_panel_wave_run(first, end, w, u0 + w, u1 + w);
+}
+
 /* [64 lanes][ks] byte offsets that a wave reads for a half */
 void q8x_panel_weights(int half, int ks, int ntiles, unsigned *at)
 {

@@ -50,6 +50,16 @@ def test_panel_runs_cover_the_units_once(lib, row_groups, slot_tiles, blocks):
     assert (rp0.reshape(blocks, waves) == (u0.reshape(blocks, waves)[:, :1] // slot_tiles)).all()
 
 
+@pytest.mark.parametrize("first,units", [(0, 0), (7, 1), (3, 7), (100, 8), (5, 15), (0, 16), (11, 97), (40000, 131072)])
+def test_panel_wave_runs_cover_a_blocks_units_once(lib, first, units):
+    """Back to back from the block's first unit to its last, the first four waves' share of all 9 / 16 to within a unit."""
+    u0, u1 = _ints(8), _ints(8)
+    lib.q8x_panel_wave_runs(first, first + units, u0, u1)
+    u0, u1 = np.array(u0[:]), np.array(u1[:])
+    assert u0[0] == first and u1[-1] == first + units and (u0[1:] == u1[:-1]).all() and (u1 >= u0).all()
+    assert abs((u1[:4] - u0[:4]).sum() - units * 9 / 16) <= 1 and (u1 - u0).max() <= units * 9 / 64 + 1
+
+
 @pytest.mark.parametrize("ks", [16, 20])
 @pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 64, 65, 1009, 50000, 50016, 50032, 50048])
 def test_panel_weights_lie_inside_the_packed_matrix(lib, ks, rows):
