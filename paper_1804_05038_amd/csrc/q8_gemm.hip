@@ -5,28 +5,7 @@
 // int32 sums, one fp32 scale product, separate bias addition.
 #include "q8_internal.h"
 #include "q8_index.h"
-
-struct GemmArgs {
-    const int8_t *W;       // [rows x ld] int8
-    const int8_t *Wt;      // the same matrix tile-packed (q8_pack_tiles), or NULL: every matrix-core operand of 16 rows x 64 k
-                           // bytes is then one contiguous KiB instead of 16 pieces of rows that lie ld bytes apart, which the
-                           // memory system delivers about 2.5 times as fast (measured: 192 KB per block, 2.1 against 5.3 us)
-    const int8_t *xq;      // [n x ld] int8 codes of the n vectors
-    const float *xscale;   // [n]
-    const float *bias;     // [rows] or NULL
-    float *Y;              // [n x ldy]
-    int32_t *tap_acc;      // [n x rows] or NULL
-    float *part_max;       // STATS: [n x ntiles] maximum of each 16-row tile
-    double *part_sum;      // STATS: [n x ntiles] sum of exp(y - maximum)
-    int rows, ld, n, ldy, ntiles;
-    int tiled;             // Y as [ntiles][n][16]: every 16 x 16 result tile is one contiguous KiB
-    float w_scale;
-    const float *row_scale; // NULL, or one weight scale per row in place of w_scale
-};
-#define GEMM_MAX_JOBS 3
-struct GemmJobs {          // products of one launch (blockIdx.z), all over the same number of vectors
-    GemmArgs j[GEMM_MAX_JOBS];
-};
+#include "q8_gemm_jobs.h"
 
 // Block tiles (row tiles per wave, vector tiles): matrices of more than 8192 rows (the
 // vocabulary) and the rest.
@@ -265,16 +244,16 @@ __global__ __launch_bounds__(256) void gemm_block_kernel(GemmJobs jobs)
 }
 
 // ============================================================== K-resident blocks ==
-// Rows of at most 64 KS bytes (KS = 8 or 16): nothing is staged.  A block of four waves takes
+// Rows of at most 512 bytes: nothing is staged.  A block of four waves takes
 // 64 rows x 64 vectors; every wave requests its 16 rows whole (KS operands per lane), the block
-// requests the 64 vectors' codes whole (one vector row per wave-wide load) and parks them in LDS
+// requests the 64 vectors' codes whole (two vector rows per wave-wide load) and parks them in LDS
 // at pitch 64 KS + 16 (16 lanes x 16 bytes then fall on distinct banks); one barrier; 4 KS
 // matrix-core instructions per wave in four independent chains.  All loads go through
 // bounds-checked descriptors without branches (what lies outside reads as zero), so they are all
 // in flight before the first wait.  Matrices and panels below 2 GiB, no taps, no statistics.
-template <int KS>
 __global__ __launch_bounds__(256) void gemm_resident_kernel(GemmJobs jobs)
 {
+    constexpr int KS = 8;
     extern __shared__ __align__(16) int8_t s_v[];        // [64 x pitch]
     const GemmArgs &a = jobs.j[blockIdx.z];
     if ((int)blockIdx.x * 64 >= a.rows) return;          // the grid is sized for the largest job
@@ -646,133 +625,6 @@ q8_status q8i_gemm_ksplit3(q8_ctx *ctx, const q8i_gemm_job *d, int n)
     return q8i_launch_check(ctx, "three products");
 }
 
-// ============================================ rows of 1024 bytes, k split over two waves ==
-// Products with rows of exactly 1024 bytes over a panel of at most 336 slots (u(s') of Eq. 6 and the
-// recurrent product of GRU q, which share a launch): block (rg, cg, job) owns 128 rows and 48 slots;
-// wave (row tile, half) multiplies 16 rows over 512 k bytes against the three slot tiles, the two exact
-// int32 halves meet in LDS and are dequantized once, and a slot's 128 results leave as 512 contiguous
-// bytes.  Against the 64 x 64 blocks of gemm_resident_kernel a compute unit takes in 178 KB instead of
-// 2 x 128 KB, and the results leave in whole lines.
-#define KS2_ROWS 128
-#define KS2_SLOTS 48
-struct Ksplit2Args {
-    GemmArgs j[2];
-};
-
-__global__ __launch_bounds__(1024) void gemm_ksplit2_kernel(Ksplit2Args jobs)
-{
-    extern __shared__ __align__(16) int8_t s_k2[];
-    constexpr int NT = 1024, LD = 1024, PITCH = LD + 16;
-    const GemmArgs &a = jobs.j[blockIdx.z];
-    if ((int)blockIdx.x * KS2_ROWS >= a.rows) return;            // the grid is sized for the larger job
-    int8_t *s_x = s_k2;
-    int *s_e = (int *)(s_k2 + KS2_SLOTS * PITCH);                // [16 waves][3 slot tiles][16 slots][16 rows]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i = lane & 15, g = lane >> 4;
-    const int n = a.n, c0 = (int)blockIdx.y * KS2_SLOTS, r0 = (int)blockIdx.x * KS2_ROWS;
-
-    // ---- all loads up front ----
-    constexpr int UX = KS2_SLOTS * (LD / 16) / NT;              // 3 pieces per thread
-    static_assert(KS2_SLOTS * (LD / 16) % NT == 0, "pieces divide among the threads");
-    const __amdgpu_buffer_rsrc_t rq = q8_rsrc(a.xq, (size_t)n * LD);
-    v4i bq[UX];
-#pragma unroll
-    for (int u = 0; u < UX; ++u) {
-        const int p = u * NT + tid, slot = p / (LD / 16), piece = p - slot * (LD / 16);
-        const unsigned off = c0 + slot < n ? (unsigned)(c0 + slot) * LD + 16u * piece : Q8_OOB;
-        bq[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rq, (int)off, 0, 0));
-    }
-    const int rt = wave >> 1, half = wave & 1, kbase = 512 * half;
-    const __amdgpu_buffer_rsrc_t rw = q8_rsrc(a.Wt ? a.Wt : a.W, (size_t)a.rows * LD);      // rows % 128 == 0
-    const int row0 = r0 + 16 * rt;
-    v4i av[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        unsigned off = (unsigned)(row0 + i) * (unsigned)LD + (unsigned)(kbase + 64 * s + 16 * g);
-        if (a.Wt) off = (((unsigned)(row0 >> 4) * (unsigned)(LD >> 6) + (unsigned)((kbase >> 6) + s)) << 10) + 16u * lane;
-        av[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
-    }
-    // per (slot, row) pair tid + 1024 e, e = 0..5: row = pair % 128 is the same for all six
-    const int row = r0 + (tid & 127);
-    const __amdgpu_buffer_rsrc_t rs = q8_rsrc(a.xscale, (size_t)n * 4), rb = q8_rsrc(a.bias, a.bias ? (size_t)a.rows * 4 : 0);
-    const float bias = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (int)((unsigned)row * 4u), 0, 0));
-    float xs[6];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const int col = c0 + ((e * NT + tid) >> 7);
-        xs[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(col < n ? (unsigned)col * 4u : Q8_OOB), 0, 0));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-
-#pragma unroll
-    for (int u = 0; u < UX; ++u) {
-        const int p = u * NT + tid, slot = p / (LD / 16), piece = p - slot * (LD / 16);
-        *(v4i *)(s_x + slot * PITCH + 16 * piece) = bq[u];
-    }
-    __syncthreads();
-
-    v4i acc[3] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}};
-    {
-        const int8_t *bp = s_x + i * PITCH + kbase + 16 * g;
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                const v4i bv = *(const v4i *)(bp + t * 16 * PITCH + 64 * s);
-                acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[s], bv, acc[t], 0, 0, 0);
-            }
-    }
-#pragma unroll
-    for (int t = 0; t < 3; ++t) *(v4i *)(s_e + (((wave * 3 + t) * 16 + i) * 16 + 4 * g)) = acc[t];
-    __syncthreads();
-
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const int pr = e * NT + tid, c = pr >> 7, r = pr & 127, col = c0 + c;
-        const int at = ((c >> 4) * 16 + (c & 15)) * 16 + (r & 15), w0 = (r >> 4) * 2;        // wave (row tile, half) = 2 rt + half
-        const int sum = s_e[w0 * 768 + at] + s_e[(w0 + 1) * 768 + at];
-        float y = (float)sum * (a.w_scale * xs[e]);
-        if (a.bias) y = y + bias;
-        if (col < n) a.Y[(size_t)col * a.ldy + row] = y;
-    }
-}
-
-// Whether the products d[0 .. njobs) (njobs <= 2; plain output, no taps) take the kernel above.
-bool q8i_gemm_ksplit2_ok(const q8i_gemm_job *d, int njobs, int n)
-{
-    if (njobs < 1 || njobs > 2 || n < 1 || (n + KS2_SLOTS - 1) / KS2_SLOTS > 7) return false;
-    int blocks = 0;
-    for (int u = 0; u < njobs; ++u) {
-        if (d[u].W->ld != 1024 || d[u].W->rows % KS2_ROWS || d[u].tap_acc || d[u].part_max || d[u].tiled || d[u].row_scale ||
-            (size_t)d[u].W->rows * 1024 >= (1u << 31))
-            return false;
-        blocks += d[u].W->rows / KS2_ROWS;
-    }
-    return blocks * ((n + KS2_SLOTS - 1) / KS2_SLOTS) <= 256;
-}
-
-q8_status q8i_gemm_ksplit2(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
-{
-    Ksplit2Args jobs;
-    int max_rows = 0;
-    for (int t = 0; t < 2; ++t) {
-        const q8i_gemm_job &q = d[t < njobs ? t : 0];
-        GemmArgs &a = jobs.j[t];
-        a.W = q.W->data; a.Wt = q.W->tiles; a.xq = q.xq; a.xscale = q.xscale; a.bias = q.bias; a.Y = q.Y; a.tap_acc = nullptr;
-        a.part_max = nullptr; a.part_sum = nullptr;
-        a.rows = q.W->rows; a.ld = q.W->ld; a.n = n; a.ldy = q.ldy; a.ntiles = (q.W->rows + 15) / 16; a.tiled = 0;
-        a.w_scale = q.W->scale; a.row_scale = nullptr;
-        if (a.rows > max_rows) max_rows = a.rows;
-    }
-    const size_t smem = (size_t)KS2_SLOTS * (1024 + 16) + (size_t)16 * 3 * 1024;
-    static Q8OncePerDevice asked;
-    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_ksplit2_kernel, smem, "k-split product kernel");
-    if (st) return st;
-    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_ksplit2_kernel, dim3(max_rows / KS2_ROWS, (n + KS2_SLOTS - 1) / KS2_SLOTS, njobs), dim3(1024), smem, jobs);
-    return q8i_launch_check(ctx, "k-split products");
-}
-
 // ================================================================ vocabulary panel ==
 // The vocabulary product for a panel of hypothesis slots (many sentences side by side).  Unlike
 // the block kernel above, a block keeps its share of the vectors' codes in LDS for its whole
@@ -1108,26 +960,32 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.rows > max_rows) max_rows = a.rows;
     }
     const bool stats = d[0].part_max != nullptr;
-    // K-resident blocks: every product with rows of at most 1024 bytes, plain output, no taps
+    // K-resident blocks: products with rows of at most 512 bytes, plain output, no taps
     bool resident = !stats && n > 8;
-    int max_ld = 0;
+    int max_ld = 0, min_ld = 1 << 30;
     for (int t = 0; t < njobs; ++t) {
         const GemmArgs &a = jobs.j[t];
-        if (a.ld > 1024 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
+        if (a.ld < min_ld) min_ld = a.ld;
+        if (a.ld > 512 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
         if (a.ld > max_ld) max_ld = a.ld;
     }
-    // Large panels (kernel trace, us, this form against the one that it takes the place of).  128 x 128 tiles where the
-    // results fill enough of them (2415 x 1860 x 903: 19.6 against 20.1 staged; 1024 x 2048 x 1024: 16.5 against 13.0): for
-    // rows that a K-resident block does not take, but packed ones times at most 64 vectors, where 64 x 64 tiles are as fast
-    // or faster (33658 x 1088 x 64: 21.8 against 19.5); and for rows of more than 512 bytes that it takes, in whole 64-byte
-    // steps (3000 rows of 1008 bytes x 900: 13.6 against 12.8), more than 64 vectors (50000 x 1024 x 43 / 65: 19.8 against 17.8,
-    // 20.6 against 26.5) and results that leave in whole 16-byte pieces (33658 x 640 x 100, rows of results 4 bytes off:
-    // 24.3 against 21.0).  3072 x 1024 times 1000 vectors: 14.3 against 14.9 K-resident; two such products times 384 vectors 15.6
-    // against 16.0, but times 257, whose last vector tile holds one, 15.0 against 11.1; two products of 3072 x 512 x 1024: 15.8
-    // against 14.6.  Else 64 x 64 tiles for packed rows that a K-resident block does not take (1024 x 2048 x 1024 10.7 against
-    // 12.8 staged, 8200 x 2048 times 9 / 64 / 200 vectors 9.2 / 9.7 / 19.2 against 17.3 / 18.8 / 22.5): with row-major weights the
-    // staged kernel, which requests a whole 128 bytes of each row at a time, is the faster one at every size (1024 x 2048
-    // times 9 / 130 / 512 vectors 9.8 / 11.0 / 11.4 against 12.1 / 12.1 / 12.4, 8192 rows x 130 15.3 against 21.6).
+    // Plain products with longer rows (kernel trace, us, each form beside the one that would run without it):
+    // rows of 513-1024 bytes: whole tiles at once, 128 rows x 32 vectors while these give a compute unit at most one block, else
+    //   x 64 (3072 x 1024 times 9 / 200 / 400 / 1000 vectors 4.6 / 5.3 / 7.2 / 10.4 against 5.3 / 6.6 / 8.7 K-resident and 13.8
+    //   in 128 x 128 tiles, 4096 x 1024 x 1000 11.4 against 15.5, 3000 rows of 1008 bytes, row-major, x 1000 11.2 against 14.6;
+    //   two such products of a decoder step times 100 / 320 4.8 / 7.2 against 6.2 / 7.5 with k split over two waves; x 32
+    //   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some three rounds of
+    //   blocks: beyond, 128 x 128 tiles read less (50000 x 1024 x 65 18.3 against 21.2, 20000 x 1024 x 300 22.0 against 23.6;
+    //   8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps and results in whole 16-byte pieces;
+    // rows of 1025-2048 bytes: 64 rows x 64 vectors at once where these nearly fill one round (1024 x 2048 x 1024 8.4 against
+    //   11.0 in 64 x 64 tiles, 9.6 streamed; 3000 x 2000 x 300, row-major, 9.0 against 13.0 staged, 9.9 streamed), else the weights
+    //   kept for a stream of vectors (1024 x 2048 times 30 / 130 6.3 / 6.5 against 9.0 / 9.1, 6.7 / 7.0 at once; 3072 x 2048 times
+    //   400 / 700 10.9 / 14.8 against 13.6 / 17.3; 2000 x 1500 x 700, row-major, 11.9 against 14.4), unless the rows' last
+    //   parts are mostly padding or a launch has many rounds (3072 x 1280 x 1000 17.7 against 15.9 in 128 x 128 tiles,
+    //   3072 x 2048 x 1000 18.2 in a decoder step against 17.4; 33658 x 2048 x 64 30.7 against 23.3 in 64 x 64 tiles);
+    // longer rows, and what is left: 128 x 128 tiles where the results fill enough of them (TILE_FILL), 64 x 64 tiles for packed
+    //   rows (8200 x 2048 times 9 / 64 / 200 9.2 / 9.7 / 19.2 against 17.3 / 18.8 / 22.5 staged), the staged kernel for row-major
+    //   ones, of which it requests a whole 128 bytes at a time.
     bool tile_ok = !stats && n > 8, packed = true, steps = true, whole = true;
     long long results = 0;
     for (int t = 0; t < njobs; ++t) {
@@ -1138,7 +996,20 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         steps = steps && a.ld % 64 == 0;
         whole = whole && a.ldy % 4 == 0 && ((uintptr_t)a.Y & 15) == 0;
     }
-    if (tile_ok && results >= TILE_FILL && (max_ld > 1024 ? n > 64 || !packed : max_ld > 512 && n > 64 && steps && whole)) {
+    auto blocks = [&](int rw, int cw) {
+        long long b = 0;
+        for (int t = 0; t < njobs; ++t) b += (long long)((jobs.j[t].rows + rw - 1) / rw) * ((n + cw - 1) / cw);
+        return b;
+    };
+    if (tile_ok && min_ld > 1024 && max_ld <= 2048) {
+        const long long b = blocks(64, 64), rb = blocks(64, n);
+        if (b > 150 && b <= 256) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 64, 64);
+        if (rb <= 256 && b * 2048 <= 640LL * max_ld) return q8i_gemm_stream(ctx, jobs, max_rows, n, njobs, (int)rb);
+    } else if (tile_ok && max_ld > 512 && max_ld <= 1024) {
+        if (blocks(128, 32) <= 256) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 32);
+        if (blocks(128, 64) <= 800 || n <= 64 || !steps || !whole || results < TILE_FILL) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 64);
+    }
+    if (tile_ok && results >= TILE_FILL && max_ld > 512 && (max_ld <= 1024 || n > 64 || !packed)) {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
         static Q8OncePerDevice asked;
         const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_tile_kernel<4, 1, 4>, smem, "large panel kernel");
@@ -1146,18 +1017,12 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }
-    if (tile_ok && !resident && packed) {
+    if (tile_ok && max_ld > 512 && packed) {
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<2, 2, 1>), dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)2 * 64 * (256 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
     }
     if (resident) {
-        const dim3 grid((max_rows + 63) / 64, (n + 63) / 64, njobs);
-        static Q8OncePerDevice asked;
-        const size_t smem = (size_t)64 * (max_ld <= 512 ? 64 * 8 + 16 : 64 * 16 + 16);
-        const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_resident_kernel<16>, smem, "resident product kernel");      // (<8>: 33 KB)
-        if (st) return st;
-        if (max_ld <= 512) Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<8>, grid, dim3(256), smem, jobs);
-        else Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<16>, grid, dim3(256), smem, jobs);
+        Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel, dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)64 * (512 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
     }
     if (max_rows > 8192) {

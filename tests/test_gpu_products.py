@@ -263,3 +263,37 @@ def test_large_panels(q, oracle, rows, cols, n, tiled, route, by_row):
             scale = (np_(rs) if by_row else np.float32(M.scale)) * np.float32(xs)
             y = acc * scale
             assert_same(got[j], y if bias is None else y + bias, "vector %d" % j)
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled", [
+    # rows of 513-1024 bytes: 128 rows x 32 and x 64 vectors, at the remainders of both, of the k parts and of a matrix-core step
+    (1, 516, 9, False), (129, 1024, 31, True), (127, 1000, 33, False), (128, 576, 64, True), (3072, 1024, 320, True), (3073, 720, 353, False), (4096, 1024, 1000, True),
+    (300, 528, 1024, False), (33000, 1024, 50, True),
+    # rows of 1025-2048 bytes: 64 rows x 64 vectors at once
+    (1024, 2048, 1024, True), (1000, 1100, 1009, False), (2999, 2000, 300, False), (2880, 1600, 255, True),
+    # the same streamed: one share of the vectors and several, a last group of one vector, an odd number of groups
+    (1, 1028, 9, False), (65, 2048, 33, True), (64, 1536, 64, True), (3071, 2000, 61, False), (1500, 2048, 700, True), (8200, 2048, 97, True), (2000, 1500, 641, False)])
+@pytest.mark.parametrize("by_row", [False, True])
+def test_panels_requested_whole(q, oracle, rows, cols, n, tiled, by_row):
+    """The products whose blocks request all they need at once, and the ones that keep their weights for a stream of vectors,
+    at the edges of their tiles, parts and groups, with one scale and one per row, results at an odd pitch: the same integer
+    sums, product of scales and addition as everywhere, so the same bits."""
+    rng = np.random.default_rng(rows + n + cols)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
+    W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
+    M, rs = q.q8_quantize_matrix_rows(ctx, W) if by_row else (q.q8_quantize_matrix(ctx, W), None)
+    if tiled:
+        M = q.q8_pack_tiles(ctx, M)
+    codes = np_(M.data)[:, :cols].astype(np.int64)
+    for pitch, bias in ((rows, b), (rows + 3, None)):
+        Y = ctx.empty(n, pitch)
+        Y.fill_(7.0)
+        if by_row: q.q8_gemm_narrow_rows(ctx, M, rs, ctx.f32(X), ctx.f32(bias), Y=Y[:, :rows])
+        else: q.q8_gemm_narrow(ctx, M, ctx.f32(X), ctx.f32(bias), Y=Y[:, :rows])
+        got = np_(Y)
+        assert (got[:, rows:] == 7.0).all()
+        for j in sorted({0, 1, 31, 32, 63, 64, n // 2, n - 2, n - 1} & set(range(n))):
+            xq, xs = oracle.quantize(X[j])
+            acc = (codes @ xq[:cols].astype(np.int64)).astype(np.float32)
+            y = acc * ((np_(rs) if by_row else np.float32(M.scale)) * np.float32(xs))
+            assert_same(got[j, :rows], y if bias is None else y + bias, "vector %d" % j)
