@@ -69,7 +69,7 @@ __device__ __forceinline__ BeamStateRead beam_state_read(const BeamState *st, in
 
 __device__ __forceinline__ void beam_gather(const BeamUpdateArgs &a, const int *s_parent, const int *s_token);
 template <bool GIVEN>
-__device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const float (&lp_in)[2], const int (&tk_in)[2],
+__device__ __forceinline__ int beam_update_body(const BeamUpdateArgs &a, const float (&lp_in)[2], const int (&tk_in)[2],
                                                  const BeamStateRead &pre);
 // The tables as they lie in memory (written by an earlier kernel).
 __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a)
@@ -89,13 +89,14 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a)
 // embeddings of the new tokens.  GIVEN: lanes of the first wave bring their two candidates (entries
 // lane and lane + 64 of the top-k tables, the last entry repeated past the end) in lp_in / tk_in
 // and what beam_state_read returned (requested while they waited for the candidates), and
-// neither the tables nor the state are read here.
+// neither the tables nor the state are read here.  Returns, in the first wave, what st->done is now.
 template <bool GIVEN>
-__device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const float (&lp_in)[2], const int (&tk_in)[2],
+__device__ __forceinline__ int beam_update_body(const BeamUpdateArgs &a, const float (&lp_in)[2], const int (&tk_in)[2],
                                                  const BeamStateRead &pre)
 {
     __shared__ int s_parent[Q8_MAX_BEAM], s_token[Q8_MAX_BEAM];
     __shared__ int s_skip;
+    int done = 0;
     BeamState *st = a.st;
     const int tid = threadIdx.x;
     if (tid < 64) {
@@ -114,6 +115,7 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const 
         const float sc_slot = sr.sc_slot;                                // lane q < 8: score of slot q
         const int n_live = sr.n_live, b_live = sr.b_live, step = sr.step, max_steps = sr.max_steps;
         const bool skip = sr.done != 0;
+        done = sr.done;
         const int have_fin0 = sr.have_fin;
         const float fin_score0 = sr.fin_score;
         const int ncand = skip ? 0 : n_live * a.k;
@@ -161,6 +163,7 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const 
         const int token0 = n_new ? __builtin_amdgcn_readlane(token, first_alive) : 0;
         __builtin_amdgcn_wave_barrier();
         if (!skip) {
+            done = b_left == 0 || n_new == 0 || step + 1 >= max_steps;
             // slot q of the new state, lane q: its score and last token come from the survivor that took slot q
             if (kept && token != 0) {
                 st->score[slot] = sc;
@@ -173,7 +176,7 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const 
                     st->have_fin = 1; st->fin_score = end_sc; st->fin_len = step; st->fin_parent = end_parent;
                 }
                 st->n_live = n_new; st->b_live = b_left; st->step = step + 1;
-                if (b_left == 0 || n_new == 0 || step + 1 >= max_steps) st->done = 1;
+                if (done) st->done = 1;
             }
         }
         if (lane == 0) { st->gathered = skip ? 0 : 1; s_skip = skip; }
@@ -196,8 +199,8 @@ __device__ __forceinline__ void beam_update_body(const BeamUpdateArgs &a, const 
         }
     }
     __syncthreads();
-    if (s_skip) return;
-    beam_gather(a, s_parent, s_token);
+    if (!s_skip) beam_gather(a, s_parent, s_token);
+    return done;
 }
 
 // Gathers the surviving decoder states and the embeddings of the new tokens: slot q of the

@@ -470,6 +470,38 @@ __device__ __forceinline__ void ahead_gates_block(const SelectArgs &a)
 }
           // survivors held in LDS
 
+// The statistics of thread tid's tiles tid, tid + 256, ...: all maxima are requested before the first sum, which is needed only
+// when the threshold is known; without branches (a tile past the end: -inf, 0).  50000 x 512, five hypotheses: vocabulary layer
+// 12.72 -> 12.55 us with this and sel_list.
+__device__ __forceinline__ void sel_partials(float (&pm)[OUT_SB], double (&ps)[OUT_SB], const float *part_max, const double *part_sum, int j, int ntiles)
+{
+    const __amdgpu_buffer_rsrc_t rm = q8_rsrc(part_max + (size_t)j * ntiles, (size_t)ntiles * sizeof(float));
+    const __amdgpu_buffer_rsrc_t rs = q8_rsrc(part_sum + (size_t)j * ntiles, (size_t)ntiles * sizeof(double));
+    const int tid = (int)threadIdx.x;
+#pragma unroll
+    for (int t = 0; t < OUT_SB; ++t) pm[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, (tid + 256 * t) * 4, 0, 0));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < OUT_SB; ++t) ps[t] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, (tid + 256 * t) * 8, 0, 0));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < OUT_SB; ++t)
+        if (tid + 256 * t >= ntiles) pm[t] = -INFINITY;
+}
+
+// Appends the thread's tiles whose maximum reaches T (one atomic for all of them; most threads have none).
+__device__ __forceinline__ void sel_list(const float (&pm)[OUT_SB], float T, int ntiles, unsigned short *s_q, int *s_nq)
+{
+    const int tid = (int)threadIdx.x;
+    unsigned hit = 0;
+#pragma unroll
+    for (int t = 0; t < OUT_SB; ++t) hit |= (tid + 256 * t < ntiles && pm[t] >= T) ? 1u << t : 0u;
+    if (hit) {
+        int at = atomicAdd(s_nq, __popc(hit));
+        for (; hit; hit &= hit - 1) s_q[at++] = (unsigned short)(tid + 256 * (__ffs(hit) - 1));
+    }
+}
+
 // One block of 256 threads per hypothesis; thread t owns tiles t, t + 256, ... (up to 16).
 // (1) log-sum-exp from the tile partials.  (2) Each wave sorts its 64 threads' maxima; the
 // wave's k-th largest has at least k logits at or above it, and T is the largest of the four
@@ -503,16 +535,7 @@ __global__ __launch_bounds__(256) void out_select_kernel(SelectArgs a)
 
     float pm[OUT_SB];
     double ps[OUT_SB];
-#pragma unroll
-    for (int t = 0; t < OUT_SB; ++t) {
-        const int tile = tid + 256 * t;            // consecutive threads, consecutive tiles
-        pm[t] = -INFINITY;
-        ps[t] = 0.0;
-        if (tile < ntiles) {
-            pm[t] = a.part_max[(size_t)j * ntiles + tile];
-            ps[t] = a.part_sum[(size_t)j * ntiles + tile];
-        }
-    }
+    sel_partials(pm, ps, a.part_max, a.part_sum, j, ntiles);
     float bm = -INFINITY;
 #pragma unroll
     for (int t = 0; t < OUT_SB; ++t) bm = fmaxf(bm, pm[t]);
@@ -525,9 +548,7 @@ __global__ __launch_bounds__(256) void out_select_kernel(SelectArgs a)
     const float T = fmaxf(fmaxf(s_t4[0], s_t4[1]), fmaxf(s_t4[2], s_t4[3]));   // -inf: everything qualifies
 
     // ---- tiles that can hold a logit >= T
-#pragma unroll
-    for (int t = 0; t < OUT_SB; ++t)
-        if (tid + 256 * t < ntiles && pm[t] >= T) s_q[atomicAdd(&s_nq, 1)] = (unsigned short)(tid + 256 * t);
+    sel_list(pm, T, ntiles, s_q, &s_nq);
     __syncthreads();
     const int total = s_nq * OUT_TILE;
     // logit of vocabulary row r of this hypothesis, in either layout
@@ -693,8 +714,11 @@ struct PanelSelectArgs {
 };
 
 // Tiles per wave whose weights are requested together.  Two keep the kernel at 128 registers and four blocks on a
-// compute unit (three for rows of 640 bytes), so that 1000 slots run in one round: 34.6 -> 26.3 us (320 slots, little
-// more than one block per unit either way: 17.8 -> 17.3; with the search step's arguments in registers 24.7 and 15.5); four (200 registers) save a round trip where a slot has more than eight tiles to look at.
+// compute unit (three for rows of 640 bytes), so that 1000 slots run in one round (34.6 -> 26.3 us when they came down to
+// that).  Three (212 registers), the sum formed while they are on their way, save a round trip where a slot has 9 to 12 tiles to
+// look at, and are the slower ones also where there is little more than one block per unit (320 slots: 16.5 against 14.8 us).
+// Kernel trace, 320 / 1000 slots, 12 entries each: 15.4 / 24.3 -> 14.8 / 23.9 us by one atomic per thread for the list of
+// tiles instead of a branch per tile, and by the search step saying whether it ended instead of reading that back.
 #define PSEL_BATCH 2
 
 // FUSE: the search step of every sentence runs here too, as in out_select_kernel: each block publishes its
@@ -726,16 +750,16 @@ __global__ __launch_bounds__(256, KC <= 8 ? 4 : 3) void panel_select_kernel(Pane
     // the slot's codes as second operand: column 0 carries them, columns 1..15 are zero
     v4i bv[KC];
     {
-        const int8_t *xj = a.xq + (size_t)j * ld + 16 * g;
+        const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.xq + (size_t)j * ld, ld);
 #pragma unroll
-        for (int s = 0; s < KC; ++s) bv[s] = i == 0 ? *(const v4i *)(xj + 64 * s) : (v4i){0, 0, 0, 0};
+        for (int s = 0; s < KC; ++s) bv[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(i == 0 ? 16u * g + 64u * s : Q8_OOB), 0, 0));
     }
     const float c = a.w_scale * a.xscale[j];
 
     float pm[OUT_SB];
     double ps[OUT_SB];
 #pragma unroll
-    for (int t = 0; t < OUT_SB; ++t) {
+    for (int t = 0; t < OUT_SB; ++t) {                   // (with the loads of sel_partials: 23.9 -> 25.0 us at 1000 slots, 14.8 -> 14.7 at 320)
         const int tile = tid + 256 * t;
         pm[t] = -INFINITY;
         ps[t] = 0.0;
@@ -763,9 +787,7 @@ __global__ __launch_bounds__(256, KC <= 8 ? 4 : 3) void panel_select_kernel(Pane
     __syncthreads();
     const float T = s_T;
 
-#pragma unroll
-    for (int t = 0; t < OUT_SB; ++t)
-        if (tid + 256 * t < ntiles && pm[t] >= T) s_q[atomicAdd(&s_nq, 1)] = (unsigned short)(tid + 256 * t);
+    sel_list(pm, T, ntiles, s_q, &s_nq);
     __syncthreads();
     const int nq = s_nq;
 
@@ -947,9 +969,8 @@ __global__ __launch_bounds__(256, KC <= 8 ? 4 : 3) void panel_select_kernel(Pane
         if (lane < nk) xw[lane] = 0ull;
         if (lane + 64 < nk) xw[lane + 64] = 0ull;
     }
-    beam_update_body<true>(bu, lp, tk, sr);
-    __syncthreads();
-    if (tid == 0) a.bb.done[sent] = bu.st->done;
+    const int done = beam_update_body<true>(bu, lp, tk, sr);
+    if (tid == 0) a.bb.done[sent] = done;
 }
 
 // =================================================================== host launcher ==
