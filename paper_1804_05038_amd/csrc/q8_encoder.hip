@@ -13,6 +13,13 @@
 // With several groups, the next group's words are requested before this one's products.  Arithmetic of
 // enc_quantize_kernel, the panel product and enc_gates_kernel, value for value.
 //
+// What orders the accesses to LDS: two barriers per group, behind the codes and behind the products.  Codes are written in front of
+// the first and read between the two, sums written between the two and read behind the second, states belong to one thread.
+// Scales are written in front of the first barrier and read behind the second, where the waves without gates are on the next
+// group's scales already; so two sets of them take turns (q8_enc_scale), and the next write to a set lies behind a
+// barrier that every reader has passed.  (With one group the words polled are this block's own as well, whose gates come
+// first; with several they are another group's, and nothing but the sets' turn orders the two.)
+//
 // Exchange.  A word is the float itself, or ENCG_ABSENT (a NaN pattern that is never published) while it is not there.
 // Three buffers take turns.  A block that has read the words of step t - 1 knows that every member has read those of
 // step t - 2 (it published t - 1 after that), so it puts its own words of that buffer back to ENCG_ABSENT, for step
@@ -24,7 +31,8 @@
 //
 // Nobody has to be resident for the result to be right.  A wait is bounded; a member that gives up says so in the set's
 // flag, at which the others leave as well, and the last member to leave works the whole set off by itself, from the
-// first position on, without waiting for anybody.
+// first position on, without waiting for anybody.  Words that are not there make no codes: whatever a member stores or
+// publishes before it leaves is what the last one stores again.
 //
 // The chain of a step bounds it (1024 units, 16 slots, in us: words there 1.1, codes 0.35, products 0.45, gates 0.6), with
 // several groups the instructions of the codes and the gates (2.0 us per group).  A launch per position, whose blocks read
@@ -60,7 +68,7 @@ struct EncGroupArgs {
 __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 {
     extern __shared__ __align__(16) int8_t s_codes[];                  // [16][ENCG_PITCH], sums, states, offsets, lengths
-    __shared__ float s_scale[ENCG_SLOTS];
+    __shared__ float s_scale[2 * ENCG_SLOTS];
     __shared__ int s_flag, s_max;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, gq = lane >> 4;
@@ -102,8 +110,8 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
             av[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
         }
     };
-    // one wave: the codes and the scale of its slot's state, floats 4 (lane + 64 c) .. (zero past H)
-    auto codes = [&](const float4 (&v)[4]) {
+    // one wave, iteration it (groups of time steps, counted): the codes and the scale of its slot's state, floats 4 (lane + 64 c) .. (zero past H)
+    auto codes = [&](const float4 (&v)[4], int it) {
         float m = 0.0f;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
         m = wave_max_f(m);
         float scale, inv;
         q8_scale_of(m, scale, inv);
-        if (lane == 0) s_scale[wave] = scale;
+        if (lane == 0) s_scale[q8_enc_scale(it, wave)] = scale;
 #pragma unroll
         for (int c = 0; c < 4; ++c) *(int *)(s_codes + wave * ENCG_PITCH + 4 * (lane + 64 * c)) = q8_pack4(v[c].x, v[c].y, v[c].z, v[c].w, inv);
     };
@@ -130,8 +138,8 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
         }
     };
     const int sl = tid >> 5, u = tid & 31;                             // this thread's (slot, unit) pair, below 16 x 32
-    auto gates = [&](const float (&gx)[3], const float (&bias)[3], float h_prev) {
-        const float ch = a.wh_scale[d] * s_scale[sl];
+    auto gates = [&](const float (&gx)[3], const float (&bias)[3], float h_prev, int it) {
+        const float ch = a.wh_scale[d] * s_scale[q8_enc_scale(it, sl)];
         float gh[3];
 #pragma unroll
         for (int gt = 0; gt < 3; ++gt) {
@@ -176,8 +184,9 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
         };
         const unsigned mine = (unsigned)((c0 + sl) * H + unit) * 4u;
         bool gave_up = false;
+        int it = 0;
         for (int t = 0; t < max_l && !gave_up; ++t) {
-            for (int g = 0; g < ng; ++g) {
+            for (int g = 0; g < ng; ++g, ++it) {
                 const int e0 = g * ENCG_SLOTS, e = min(e0 + sl, ng * ENCG_SLOTS - 1), l = s_len[e], pos = row(s_off[e], l, t);
                 const bool on = pair && t < l;
                 const float *gp = a.gx[d] + (size_t)(on ? pos : 0) * 3 * H + (on ? unit : 0);
@@ -186,6 +195,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                 for (int gt = 0; gt < 3; ++gt) gx[gt] = gp[gt * H];
                 if (t < s_len[e0 + wave]) {                            // wave-uniform
                     float4 v[4];
+                    bool there = true;
                     if (t > 0) {
                         if (ng == 1) {
                             if (a.spin_limit > 1)
@@ -203,6 +213,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                                     s_flag = 1;
                                     __hip_atomic_store(a.ctl + 2 * set + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                                 }
+                                there = false;
                                 break;
                             }
                             request(was + g * group);
@@ -213,7 +224,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 #pragma unroll
                         for (int c = 0; c < 4; ++c) v[c] = make_float4(0.f, 0.f, 0.f, 0.f);
                     }
-                    codes(v);
+                    if (there) codes(v, it);
                 }
                 __syncthreads();
                 if (s_flag) { gave_up = true; break; }
@@ -225,7 +236,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                 products();
                 __syncthreads();
                 if (tid < ENCG_SLOTS * ENCG_UNITS) {
-                    const float hn = gates(gx, bias, s_h[e0 * ENCG_UNITS + tid]);
+                    const float hn = gates(gx, bias, s_h[e0 * ENCG_UNITS + tid], it);
                     if (on) {
                         unsigned word = __float_as_uint(hn);
                         word = word == ENCG_ABSENT ? 0x7fffffffu : word;
@@ -263,7 +274,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                     const int k = 4 * (lane + 64 * c);
                     v[c] = t > 0 && k < H ? *(const float4 *)(h + k) : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
-                codes(v);
+                codes(v, 0);
             }
             for (int m = 0; m < members; ++m) {
                 const int unit = m * ENCG_UNITS + u, at = min(e0 + sl, ng * ENCG_SLOTS - 1), l = s_len[at], pos = row(s_off[at], l, t);
@@ -276,7 +287,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                     biases(unit, bias);
                     const float *gp = a.gx[d] + (size_t)pos * 3 * H + unit;
                     const float gx[3] = {gp[0], gp[H], gp[2 * H]};
-                    a.enc_h[(size_t)pos * 2 * H + col0 + unit] = gates(gx, bias, t > 0 ? a.enc_h[(size_t)(pos + back) * 2 * H + col0 + unit] : 0.0f);
+                    a.enc_h[(size_t)pos * 2 * H + col0 + unit] = gates(gx, bias, t > 0 ? a.enc_h[(size_t)(pos + back) * 2 * H + col0 + unit] : 0.0f, 0);
                 }
             }
             __syncthreads();

@@ -79,3 +79,9 @@ Q8_INDEX_FN unsigned q8_panel_weight(int half, int lane, int ks, int ntiles)
     return ((unsigned)tile * (unsigned)(ks / 2) << 10) + (unsigned)(lane >> 5) * 256u + (unsigned)(i & 15) * 16u;
 }
 Q8_INDEX_FN unsigned q8_panel_step(int s) { return (unsigned)(s >> 1) * 1024u + (unsigned)(s & 1) * 512u; }
+
+// ---- the batched encoder (enc_group_kernel) ----
+
+// Where iteration `it` of a block (one group of slots at one time step, counted from the launch's first) keeps the scale of its
+// slot: two sets of 16 in turn, because an iteration's scales are read while other waves write the next one's.
+Q8_INDEX_FN int q8_enc_scale(int it, int slot) { return 16 * (it & 1) + slot; }

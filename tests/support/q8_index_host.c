@@ -48,3 +48,5 @@ void q8x_panel_plans(int rows, int step, int ld, int n, unsigned long long *wors
         }
     }
 }
+
+int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }

@@ -622,6 +622,26 @@ def test_encoder_of_a_batch_whatever_its_blocks_wait_for(q, oracle, E, H, lens, 
     q.q8_encode_check(ctx)
 
 
+@pytest.mark.parametrize("H,S,group", [(1024, 200, 64), (1000, 90, 60), (516, 1024, 64)])
+def test_encoder_groups_of_a_set_keep_their_scales_apart(q, H, S, group):
+    """Sets of several groups, whose states lie orders of magnitude apart (so that another sentence's scale would show): every
+    sentence's states are those of batches small enough for one group per set, every time."""
+    rng = np.random.default_rng(H)
+    E, lens = 16, [int(v) for v in rng.integers(1, 9, size=S)]
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=S + (k == "b"), I=E, H=H).items()}
+    off = np.concatenate([[0], np.cumsum(lens)])
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], False), gpu_mat(q, big, p[k + "Wh"], H % 64 == 0), big.f32(p[k + "bx"] * 0), big.f32(p[k + "bh"] * 0))
+         for k in ("f", "b")]
+    ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], int(off[-1]), S))
+    X = rng.standard_normal((int(off[-1]), E)) * np.repeat(10.0 ** -rng.integers(0, 4, size=S), lens)[:, None]
+    X = big.f32(X.astype(np.float32))
+    want = np.concatenate([np_(q.q8_encode_batch(ctx, G[0], G[1], X[int(off[s]):int(off[min(s + group, S)])].contiguous(), lens[s:s + group]))
+                           for s in range(0, S, group)])
+    for _ in range(5):
+        assert_same(q.q8_encode_batch(ctx, G[0], G[1], X, lens), want, "states")
+
+
 @pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
                                    (4097, 512, 511), (2051, 640, 1024)])
 def test_vocabulary_panel_edges(q, oracle, V, R, n):

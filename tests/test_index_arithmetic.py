@@ -87,3 +87,36 @@ def test_panel_plans_fit_the_lds(lib, ld):
     for n in [*range(9, 70), *range(95, 1024, 31), 256, 257, 288, 289, 320, 512, 1000, 1023, 1024]:
         lib.q8x_panel_plans(65536, 97 if n % 8 else 63, ld, n, ctypes.byref(lds), ctypes.byref(bias))
         assert 0 < lds.value <= 160 * 1024 and bias.value <= 0, (n, lds.value, bias.value)
+
+
+def _enc_accesses(scale_at, it):
+    """What the sixteen waves of the batched encoder's block do in LDS in iteration `it` (a group of slots at a time step), as
+    (interval between barriers, wave, array, index, is a write): codes in front of the first of its two barriers, products
+    between them, gates behind the second, where the waves without any are in front of the next iteration's first."""
+    for w in range(16):
+        yield 2 * it, w, "scale", scale_at(it, w), True
+        yield 2 * it, w, "codes", w, True
+    for w in range(12):
+        for slot in range(16):
+            yield 2 * it + 1, w, "codes", slot, False
+        yield 2 * it + 1, w, "sums", w, True
+    for w in range(8):
+        for slot in (2 * w, 2 * w + 1):
+            yield 2 * it + 2, w, "scale", scale_at(it, slot), False
+        for tile in range(12):
+            yield 2 * it + 2, w, "sums", tile, False
+
+
+def test_no_two_waves_of_the_batched_encoder_meet_in_lds(lib):
+    """With several groups of slots nothing but the barriers orders the waves: between two of them, what one wave writes no
+    other touches, over any run of iterations (an array of one set of scales fails this)."""
+    seen, written = {}, {}
+    for it in range(9):
+        assert all(0 <= lib.q8x_enc_scale(it, s) < 32 for s in range(16))
+        for interval, wave, array, at, write in _enc_accesses(lib.q8x_enc_scale, it):
+            key = interval, array, at
+            assert not (write and seen.get(key, {wave}) - {wave}), (key, wave)
+            assert not (written.get(key, {wave}) - {wave}), (key, wave)
+            seen.setdefault(key, set()).add(wave)
+            if write:
+                written.setdefault(key, set()).add(wave)
