@@ -2,6 +2,7 @@
 // recurrent weights in registers for all positions and hand the states to each other through memory.
 #include "q8_internal.h"
 #include "q8_index.h"
+#include <mutex>
 
 // Block `member` of a set owns hidden units 32 member .. + 31 of one direction, for the set's sentences ("slots"), in
 // groups of up to 16, one group after the other at every time step.  A time step of a group:
@@ -32,7 +33,11 @@
 // Nobody has to be resident for the result to be right.  A wait is bounded; a member that gives up says so in the set's
 // flag, at which the others leave as well, and the last member to leave works the whole set off by itself, from the
 // first position on, without waiting for anybody.  Words that are not there make no codes: whatever a member stores or
-// publishes before it leaves is what the last one stores again.
+// publishes before it leaves is what the last one stores again.  That is slow (4 ms at 64 sentences), so the blocks of two
+// encoders don't compete for the compute units: the launch that clears the words also waits for its turn on the device, and
+// the encoder's last block to start passes it on, when all of them are on their units and wait for nobody else.  Four
+// streams with a batch of 64 sentences each, us per batch: 2110 without turns (an encoder that ends makes room for part of
+// the next two, which wait for each other's room until both give up), 215 with them (a launch per position, before: 358).
 //
 // The chain of a step bounds it (1024 units, 16 slots, in us: words there 1.1, codes 0.35, products 0.45, gates 0.6), with
 // several groups the instructions of the codes and the gates (2.0 us per group).  A launch per position, whose blocks read
@@ -54,6 +59,36 @@
 #define ENCG_LDS_GROUP (ENCG_SLOTS * ENCG_UNITS * 4 + ENCG_SLOTS * 8)
 #define ENCG_AGENT_LOAD 0x10            // cache policy of a device-coherent load or store (sc1)
 
+// The turn on a device (a module's variable, so one per device and process): how many of the last eight blocks (one per XCD;
+// blocks of lower index start earlier) of the encoder whose turn it is have started.  Whoever takes an eight from it has the
+// next turn; fewer are put back.  The wait ends after ENCG_TURN of the 100 MHz clock (an encoder that failed to launch, or
+// whose blocks wait for room behind long kernels): whoever goes on then passes on an eight of its own, so nobody else
+// waits for what never comes.
+#define ENCG_TURN 400000ull
+__device__ unsigned enc_group_turn = 8;
+
+// Clears [words, words + n) and waits for the turn.
+__global__ __launch_bounds__(256) void enc_group_clear_kernel(unsigned *words, int n)
+{
+    if (blockIdx.x > 0) {
+        const int e = ((int)blockIdx.x - 1) * 256 + (int)threadIdx.x;
+        if (e < n) words[e] = ENCG_ABSENT;
+        return;
+    }
+    if (threadIdx.x > 0) return;
+    auto take = [] {
+        const unsigned had = __hip_atomic_exchange(&enc_group_turn, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (had < 8 && had > 0) __hip_atomic_fetch_add(&enc_group_turn, had, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return had >= 8;
+    };
+    if (take()) return;
+    const unsigned long long begin = wall_clock64();
+    while (wall_clock64() - begin < ENCG_TURN) {
+        __builtin_amdgcn_s_sleep(16);
+        if (__hip_atomic_load(&enc_group_turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 8 && take()) return;
+    }
+}
+
 struct EncGroupArgs {
     const int8_t *Wh[2], *Wht[2];        // [3H x ld], the same tile-packed or NULL
     const float *bh[2], *gx[2];          // [3H] or NULL; [L x 3H]
@@ -74,6 +109,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
     const int i = lane & 15, gq = lane >> 4;
     const int H = a.H, S = a.S, ld = a.ld, members = a.members;
     const int round = (int)blockIdx.x >> 3, member = round % members, set = ((int)blockIdx.x & 7) + 8 * (round / members);
+    if (blockIdx.x + 8 >= gridDim.x && tid == 0) __hip_atomic_fetch_add(&enc_group_turn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (set >= 2 * a.sets_per_dir) return;
     // the set's slots, in groups of gs
     const int d = set & 1, c0 = S * (set >> 1) / a.sets_per_dir, ns = S * ((set >> 1) + 1) / a.sets_per_dir - c0;
@@ -316,7 +352,12 @@ q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_wei
 {
     const int H = fwd->Wh.cols, spd = enc_group_sets(H, S), members = (H + ENCG_UNITS - 1) / ENCG_UNITS;
     const int ns = (S + spd - 1) / spd, ng = (ns + ENCG_SLOTS - 1) / ENCG_SLOTS, gs = (ns + ng - 1) / ng;
-    const q8_status st = q8i_fill_u32(ctx, words, 4 * spd + 2 * S * H, ENCG_ABSENT);
+    const int clear = 4 * spd + 2 * S * H;
+    // (the two launches side by side on their queue: a stream that shares it cannot wait for the turn between them)
+    static std::mutex pair;
+    std::lock_guard<std::mutex> hold(pair);
+    hipLaunchKernelGGL(enc_group_clear_kernel, dim3(1 + (clear + 255) / 256), dim3(256), 0, ctx->stream, words, clear);
+    const q8_status st = q8i_launch_check(ctx, "clear");
     if (st) return st;
     EncGroupArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {gxf, gxb}, sent_off, enc_h,
                       words + 4 * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,

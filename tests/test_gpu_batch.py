@@ -5,6 +5,8 @@ Per-vector quantization makes a panel's result for vector j the result of the si
 call, so each case is checked twice: against the oracle (codes and sums bit-exact through the
 taps, floats to 1e-5) and against this library's own streaming kernels (bit for bit).
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -640,6 +642,46 @@ def test_encoder_groups_of_a_set_keep_their_scales_apart(q, H, S, group):
                            for s in range(0, S, group)])
     for _ in range(5):
         assert_same(q.q8_encode_batch(ctx, G[0], G[1], X, lens), want, "states")
+
+
+def test_encoders_on_several_streams_take_turns(q):
+    """Four streams with a batch each, whose blocks all wait for each other: the states of one stream alone, and no batch takes
+    as long as the blocks that give up on each other would (5 ms and more; half a millisecond is ordinary)."""
+    E, H, S = 64, 1024, 64
+    rng = np.random.default_rng(7)
+    lens = [int(v) for v in rng.integers(10, 61, size=S)]
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=k == "b", I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], True), gpu_mat(q, big, p[k + "Wh"], True), big.f32(p[k + "bx"]), big.f32(p[k + "bh"]))
+         for k in ("f", "b")]
+    X = big.f32(rng.standard_normal((sum(lens), E)).astype(np.float32))
+    torch.cuda.synchronize()
+    lanes = []
+    for _ in range(4):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], sum(lens), S), stream=st)
+            lanes.append((st, ctx, ctx.empty(sum(lens), 2 * H)))
+
+    def run(n, times):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(times):
+            for st, ctx, out in lanes[:n]:
+                with torch.cuda.stream(st):
+                    q.q8_encode_batch(ctx, G[0], G[1], X, lens, enc_h=out)
+        torch.cuda.synchronize()
+        return (time.perf_counter() - t) / times / n
+
+    run(4, 2)
+    want = np_(lanes[0][2])
+    for _, _, out in lanes:
+        out.fill_(7.0)
+    together = min(run(4, 10) for _ in range(3))
+    for st, ctx, out in lanes:
+        assert_same(out, want, "states")
+        q.q8_encode_check(ctx)
+    assert together < 1e-3, together
 
 
 @pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
