@@ -259,8 +259,12 @@ q8_status output_logits_q8(q8_ctx *ctx, const q8_readout_weights *ro, const q8_m
  * quantize / product / gates triple per time step.  Blocks of that launch wait for each other's states, but
  * nothing depends on them running side by side: a wait that takes too long (some milliseconds, or the bound
  * of q8_encoder_options if that is smaller) ends in one block working its sentences off alone, which is
- * slow and gives the same states.  Values are those of q8_encode sentence by sentence.  Needs
- * q8_encode_batch_bytes(fwd, L, n_sent) bytes of workspace. */
+ * slow and gives the same states.  Batched encoders of one process take turns on a device while their blocks
+ * start, whatever their streams; beside other kernels whose blocks wait (q8_attention_options names them) and
+ * other processes' encoders such a wait is possible, and q8_encoder_options with one_launch = 0 takes it out:
+ * a launch per time step, without any wait (at H = 1024 for up to 256 sentences; beyond, mostly the triple).
+ * Values are those of q8_encode sentence by sentence.  Needs q8_encode_batch_bytes(fwd, L, n_sent) bytes of
+ * workspace. */
 size_t q8_encode_batch_bytes(const q8_gru_weights *fwd, int total_l, int n_sent);
 q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X,
                           const int32_t *sent_off, const int32_t *sent_off_host, int n_sent, float *enc_h);
@@ -286,7 +290,7 @@ q8_status cgru_decoder_step_batch_q8(q8_ctx *ctx, const q8_cgru_weights *w, cons
 q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd,
                     const float *X, int l, float *enc_h);
 
-/* How q8_encode runs the recurrence.  one_launch != 0 (the default): all positions in one
+/* How q8_encode and q8_encode_batch (see there) run the recurrence.  q8_encode, one_launch != 0 (the default): all positions in one
  * launch where the shape is covered (H % 8 == 0, H <= 2048, rows of Wh of at most 2048 bytes,
  * not under stream capture) and the device can hold 2 H / 8 blocks of 512 threads at once;
  * otherwise, and with one_launch == 0, one launch per position.  Both give the same bits.
@@ -320,7 +324,10 @@ q8_status q8_encode_check(q8_ctx *ctx);
  * together must fit the device together (l n_beam blocks of 1024 threads each, two per compute
  * unit); give the contexts beyond that exchange = 0.  The same holds for q8_encoder_options'
  * one-launch recurrence (2 H / 8 blocks of 512 threads) and for the batched step's one-kernel
- * GRU (H / 32 x ceil(slots / 48) blocks of 768 threads, one per compute unit).  The waits inside the
+ * GRU (H / 32 x ceil(slots / 48) blocks of 768 threads, one per compute unit).  q8_encode_batch's
+ * one-launch recurrences fill the device (up to 256 blocks of 1024 threads, one per compute unit): beside
+ * any of these each may wait for the other's room until the encoder's bound (some milliseconds) has
+ * passed, which costs time and nothing else; one_launch = 0 there avoids it.  The waits inside the
  * selection kernels (output_logits_beam_q8 and its forms, output_logits_beam_ahead_q8's blocks that
  * compute the next GRU r, output_logits_beam_batch_q8) are for blocks of lower index in the same
  * launch, which the device has started before the block that waits: they end whatever else runs. */

@@ -1028,12 +1028,23 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
         TRY(q8i_gemm_jobs(ctx, gj, 2, cnt));
     }
     // the recurrences: all positions of all sentences in one launch ...
-    const size_t words = q8i_enc_group_words(fwd, bwd, n_sent);
+    // (this and the next form in the room of the last one's codes, scales and pre-activations, which is more)
+    const size_t words = ctx->enc_one_launch ? q8i_enc_group_words(fwd, bwd, n_sent) : 0;
     if (words) {
-        // (in the room of the other form's codes, scales and pre-activations, which is more)
         cv.off = mark;
         unsigned *w = cv.take<unsigned>(words);
         if (w) return q8i_enc_group(ctx, fwd, bwd, sent_off, n_sent, enc_h, gxf, gxb, w);
+    }
+    // ... or a launch per time step, whose blocks wait for nobody ...
+    if (q8i_enc_cell_ok(fwd, bwd, n_sent)) {
+        cv.off = mark;
+        const size_t nm = (size_t)2 * n_sent * ((H + 31) / 32);
+        float *h[2], *pm[2];
+        for (int u = 0; u < 2; ++u) { h[u] = cv.take<float>((size_t)2 * n_sent * H); pm[u] = cv.take<float>(nm); }
+        if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_encode_batch: workspace too small");
+        for (int t = 0; t < max_l; ++t)
+            TRY(q8i_enc_cell(ctx, fwd, bwd, sent_off, n_sent, t, enc_h, gxf, gxb, h[(t + 1) & 1], h[t & 1], pm[(t + 1) & 1], pm[t & 1]));
+        return Q8_OK;
     }
     // ... or, all sentences and both directions per time step, codes, products and gates
     for (int t = 0; t < max_l; ++t) {

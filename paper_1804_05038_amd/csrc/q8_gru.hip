@@ -443,6 +443,193 @@ __global__ __launch_bounds__(256) void enc_gates_kernel(EncStepArgs a, int S)
     a.enc_h[(size_t)pos * 2 * H + col] = gru_gates(xv, hv, hp);
 }
 
+// ---- one time step of many sentences, both directions, in one launch (where all steps are not to be one launch) ----
+// Products, gates and the next step's quantization without a launch of their own: a step leaves its states in fp32
+// (the output, and a compact copy in slot order whose addresses need no look-up) with each block's largest
+// magnitudes, and the blocks of the next step quantize what they multiply themselves.  Block (ug, cg, d) of twelve
+// waves owns hidden units 32 ug .. + 31 and slots 16 NT cg .. of direction d; wave (rt, kp), rt = 2 gate + unit tile,
+// multiplies its 16 rows of W_h over one half of the k range (at most 512 bytes) against the slots' codes in LDS.
+// The step is bound by its chain (states and maxima arrive, codes, products, gates, stores: about 5 us) and not by what
+// it moves; before, quantization, product and gates were three such chains: 13.2 us per position at 64 sentences of
+// hidden size 1024 (kernel trace), 5.75 us now.  Block numbers deal the (slots, direction) groups out first: with up to
+// eight of them the blocks of a group fall on one XCD and find its weights (3 MB) and last states in that L2 (6.0 us
+// with the unit groups first).  Nothing waits inside the kernel, so it is as free to be captured or to
+// run beside others as the three launches were.
+// Arithmetic of the three launches (max-abs codes, exact sums, one scale product, bias, gates), value for value.
+// H % 4 == 0, H <= 1024 and rows of at most 1024 bytes; everything past H or past the slots reads as zero.
+struct EncCellArgs {
+    const int8_t *Wh[2], *Wht[2];        // [3H x ld], the same tile-packed or NULL
+    const float *bh[2], *gx[2];          // [3H] or NULL; [L x 3H]
+    const int *sent_off;
+    float *enc_h;                        // [L x 2H]
+    const float *h_in;                   // [2][S][H] states of the step before (unused at t = 0)
+    float *h_out;
+    const float *pm_in;                  // [2][S][units / 32] largest magnitudes per block
+    float *pm_out;
+    int S, t, H, ld;
+    float wh_scale[2];
+};
+#define EC_UNITS 32
+#define EC_THREADS 768
+#define EC_PITCH (1024 + 16)
+template <int NT>
+__global__ __launch_bounds__(EC_THREADS) void enc_cell_kernel(EncCellArgs a)
+{
+    constexpr int SLOTS = 16 * NT, ROUNDS = (SLOTS + 2) / 3, PAIRS = (SLOTS * EC_UNITS + EC_THREADS - 1) / EC_THREADS;
+    extern __shared__ __align__(16) int8_t s_codes[];                  // [SLOTS][EC_PITCH], then the exchange of the sums
+    __shared__ float s_inv[SLOTS], s_scale[SLOTS];
+    int *s_e = (int *)(s_codes + SLOTS * EC_PITCH);                    // [12 waves][NT tiles][16 slots][16 units]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4;
+    const int H = a.H, S = a.S, ld = a.ld, nblk = (H + EC_UNITS - 1) / EC_UNITS;
+    const int groups = gridDim.x / nblk, ug = blockIdx.x / groups, cgd = blockIdx.x - ug * groups;
+    const int d = cgd & 1, c0 = (cgd >> 1) * SLOTS, u0 = ug * EC_UNITS;
+    const bool first = a.t == 0;
+
+    // ---- requests, in the order in which they are needed: where the slots' rows are, maxima, states, weights, what
+    // the gates take ----
+    const __amdgpu_buffer_rsrc_t ro = q8_rsrc(a.sent_off, (size_t)(S + 1) * 4);
+    int so[PAIRS], sn[PAIRS];
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+        const int pr = e * EC_THREADS + tid, slot = c0 + (pr >> 5);
+        const bool ok = (pr >> 5) < SLOTS && slot < S;
+        so[e] = __builtin_amdgcn_raw_buffer_load_b32(ro, (int)(ok ? (unsigned)slot * 4u : Q8_OOB), 0, 0);
+        sn[e] = __builtin_amdgcn_raw_buffer_load_b32(ro, (int)(ok ? (unsigned)slot * 4u + 4u : Q8_OOB), 0, 0);
+    }
+    const __amdgpu_buffer_rsrc_t rm = q8_rsrc(a.pm_in + (size_t)d * S * nblk, first ? 0 : (size_t)S * nblk * 4);
+    const __amdgpu_buffer_rsrc_t rh = q8_rsrc(a.h_in + (size_t)d * S * H, first ? 0 : (size_t)S * H * 4);
+    constexpr int MR = (SLOTS * 32 + EC_THREADS - 1) / EC_THREADS;
+    float mx[MR];
+#pragma unroll
+    for (int e = 0; e < MR; ++e) {
+        const int w = e * EC_THREADS + tid, slot = c0 + (w >> 5), b = w & 31;
+        const bool ok = (w >> 5) < SLOTS && slot < S && b < nblk;
+        mx[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, (int)(ok ? (unsigned)(slot * nblk + b) * 4u : Q8_OOB), 0, 0));
+    }
+    float4 hv[ROUNDS];                                                  // slot 3 r + tid / 256, floats 4 (tid % 256) ..
+    const int hk = (tid & 255) * 4;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int sl = 3 * r + (tid >> 8), slot = c0 + sl;
+        const bool ok = sl < SLOTS && slot < S && hk < H;
+        hv[r] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(ok ? (unsigned)(slot * H + hk) * 4u : Q8_OOB), 0, 0));
+    }
+    const int rt = wave % 6, kp = wave / 6, gate = rt >> 1, ut = rt & 1;
+    const int unit0 = u0 + 16 * ut;
+    const bool tiled = a.Wht[d] != nullptr && H % 16 == 0;              // (a tile of 16 rows then belongs to one gate)
+    const __amdgpu_buffer_rsrc_t rw = q8_rsrc(tiled ? a.Wht[d] : a.Wh[d], (size_t)(tiled ? (3 * H + 15) / 16 * 16 : 3 * H) * ld);
+    v4i av[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int k = kp * 512 + 64 * s + 16 * g;
+        unsigned off = (unit0 + i < H && k < ld) ? (unsigned)(gate * H + unit0 + i) * (unsigned)ld + (unsigned)k : Q8_OOB;
+        if (tiled)
+            off = (unit0 < H && kp * 512 + 64 * s < ld)
+                      ? (((unsigned)((gate * H + unit0) >> 4) * (unsigned)(ld >> 6) + (unsigned)(kp * 8 + s)) << 10) + 16u * lane : Q8_OOB;
+        av[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
+    }
+    const __amdgpu_buffer_rsrc_t rb = q8_rsrc(a.bh[d], a.bh[d] ? (size_t)3 * H * 4 : 0);
+    float hp[PAIRS], bv[PAIRS][3];
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+        const int pr = e * EC_THREADS + tid, slot = c0 + (pr >> 5), unit = u0 + (pr & 31);
+        const bool ok = (pr >> 5) < SLOTS && slot < S && unit < H;
+        hp[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rh, (int)(ok ? (unsigned)(slot * H + unit) * 4u : Q8_OOB), 0, 0));
+#pragma unroll
+        for (int gt = 0; gt < 3; ++gt)
+            bv[e][gt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(ok ? (unsigned)(gt * H + unit) * 4u : Q8_OOB), 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // the input pre-activations, whose rows are known by now
+    int pos[PAIRS];
+    float gxv[PAIRS][3];
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+        const int unit = u0 + ((e * EC_THREADS + tid) & 31), l = sn[e] - so[e];
+        const bool on = a.t < l && unit < H;                            // (l = 0 where there is no slot)
+        pos[e] = on ? (d == 0 ? so[e] + a.t : so[e] + l - 1 - a.t) : -1;
+        const float *gx = a.gx[d] + (size_t)(on ? pos[e] : 0) * 3 * H + (on ? unit : 0);
+#pragma unroll
+        for (int gt = 0; gt < 3; ++gt) gxv[e][gt] = gx[gt * H];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- scales: the 32 lanes of a slot reduce its blocks' maxima ----
+#pragma unroll
+    for (int e = 0; e < MR; ++e) {
+        float m = mx[e];
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_XOR1>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_XOR2>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_HALF_MIRROR>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_MIRROR>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(m), SWZ_XOR16)));
+        const int sl = (e * EC_THREADS + tid) >> 5;
+        if ((lane & 31) == 0 && sl < SLOTS) q8_scale_of(m, s_scale[sl], s_inv[sl]);
+    }
+    __syncthreads();
+    // ---- codes ----
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int sl = 3 * r + (tid >> 8);
+        if (sl < SLOTS) *(int *)(s_codes + sl * EC_PITCH + hk) = q8_pack4(hv[r].x, hv[r].y, hv[r].z, hv[r].w, s_inv[sl]);
+    }
+    __syncthreads();
+
+    // ---- products ----
+    v4i acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = (v4i){0, 0, 0, 0};
+    {
+        const int8_t *bp = s_codes + i * EC_PITCH + kp * 512 + 16 * g;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            if (kp * 512 + 64 * s < ld) {                               // wave-uniform
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const v4i x = *(const v4i *)(bp + t * 16 * EC_PITCH + 64 * s);
+                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[s], x, acc[t], 0, 0, 0);
+                }
+            }
+    }
+    // lane (i, g) holds units 4 g + r, r = 0..3, of slot i of each tile
+#pragma unroll
+    for (int t = 0; t < NT; ++t) *(v4i *)(s_e + (((wave * NT + t) * 16 + i) * 16 + 4 * g)) = acc[t];
+    __syncthreads();
+
+    // ---- gates ----
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+        const int pr = e * EC_THREADS + tid, sl = pr >> 5, u = pr & 31, unit = u0 + u, slot = c0 + sl;
+        const bool in = sl < SLOTS;
+        const float ch = a.wh_scale[d] * s_scale[in ? sl : 0];
+        float gh[3];
+#pragma unroll
+        for (int gt = 0; gt < 3; ++gt) {
+            const int at = (((gt * 2 + (u >> 4)) * NT + ((in ? sl : 0) >> 4)) * 16 + (sl & 15)) * 16 + (u & 15);
+            float y = (float)(s_e[at] + s_e[at + 6 * NT * 256]) * ch;
+            if (a.bh[d]) y = y + bv[e][gt];
+            gh[gt] = y;
+        }
+        float hn = gru_gates(gxv[e], gh, hp[e]);
+        const bool on = pos[e] >= 0;
+        if (!on) hn = 0.0f;
+        if (on) {
+            a.enc_h[(size_t)pos[e] * 2 * H + (d == 0 ? H : 0) + unit] = hn;
+            a.h_out[((size_t)d * S + slot) * H + unit] = hn;
+        }
+        float m = fabsf(hn);
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_XOR1>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_XOR2>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_HALF_MIRROR>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp_mov_i<DPP_MIRROR>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(m), SWZ_XOR16)));
+        if (u == 0 && in && slot < S) a.pm_out[((size_t)d * S + slot) * nblk + ug] = m;
+    }
+}
+
 // ============================================= encoder recurrence in one launch ==
 // Eq. 1 for one sentence, both directions, all l positions in ONE launch whose blocks are all
 // resident at once (the launcher checks that the device can hold them; otherwise the caller
@@ -618,6 +805,49 @@ q8_status q8i_gru_gates(q8_ctx *ctx, const float *gx, const float *gh, const flo
     return q8i_launch_check(ctx, "gru gates");
 }
 
+
+// Tiles of 16 slots per block of the one-launch step, 0 where three launches are faster.  A round of at most one block
+// per compute unit takes about 5, 8 and 12 us with 1, 2 and 4 tiles (every group of slots reads the weights again, every
+// block reads and quantizes its slots' states, 4 KB each), so the fewest that need one round; beyond 256 blocks of 4
+// tiles, two rounds if the second is at least half full.  Per position (a panel of 12 words less one of 2), us, three launches against
+// this rule: H = 1024 13.4 / 5.9 at 64 sentences, 15.7 / 10.4 at 128, 22.4 / 17.1 at 256, 35.2 / 33.7 at 512 (and without
+// it 23.3 / 28.7 at 257, 61.6 / 71.8 at 1024); H = 512 12.9 / 7.1 at 128, 22.7 / 16.8 at 512, 23.1 / 27.1 without it at 513;
+// H = 256 11.3 / 6.3 at 128 (12.1 with 4 tiles), 26.7 / 20.5 at 1024.
+static int enc_cell_tiles(int H, int S)
+{
+    const int units = (H + EC_UNITS - 1) / EC_UNITS;
+    auto blocks = [&](int nt) { return units * 2 * ((S + 16 * nt - 1) / (16 * nt)); };
+    for (int nt = 1; nt <= 4; nt *= 2)
+        if (blocks(nt) <= 256) return nt;
+    return blocks(4) >= 384 && blocks(4) <= 512 ? 4 : 0;
+}
+
+bool q8i_enc_cell_ok(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S)
+{
+    const int H = fwd->Wh.cols;
+    // (the states of all sentences are addressed with 32-bit byte offsets)
+    return H % 4 == 0 && H <= 1024 && fwd->Wh.ld <= 1024 && bwd->Wh.ld == fwd->Wh.ld && (size_t)S * H * 4 < (1u << 31) &&
+           enc_cell_tiles(H, S) > 0;
+}
+
+q8_status q8i_enc_cell(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, int t,
+                       float *enc_h, const float *gxf, const float *gxb, const float *h_in, float *h_out, const float *pm_in,
+                       float *pm_out)
+{
+    const int H = fwd->Wh.cols, ld = fwd->Wh.ld;
+    EncCellArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {gxf, gxb}, sent_off, enc_h,
+                     h_in, h_out, pm_in, pm_out, S, t, H, ld, {fwd->Wh.scale, bwd->Wh.scale}};
+    const int nt = enc_cell_tiles(H, S);
+    const size_t smem = (size_t)16 * nt * EC_PITCH + (size_t)12 * nt * 1024;
+    const dim3 grid((H + EC_UNITS - 1) / EC_UNITS * ((S + 16 * nt - 1) / (16 * nt)) * 2);
+    static Q8OncePerDevice asked;
+    const q8_status st = q8i_lds(ctx, asked, (const void *)enc_cell_kernel<4>, smem, "encoder step kernel");      // (<1>, <2>: less than 64 KB)
+    if (st) return st;
+    if (nt == 1) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<1>, grid, dim3(EC_THREADS), smem, a);
+    else if (nt == 2) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<2>, grid, dim3(EC_THREADS), smem, a);
+    else Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_cell_kernel<4>, grid, dim3(EC_THREADS), smem, a);
+    return q8i_launch_check(ctx, "encoder step");
+}
 
 // gates + codes of the new states; false if the shape is not covered (the caller then runs the
 // gates and the quantization as two launches)

@@ -256,6 +256,12 @@ q8_status q8i_enc_step(q8_ctx *ctx, int phase, const int *sent_off, int S, int t
 size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S);
 q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
                         const float *gxf, const float *gxb, unsigned *words);
+// one time step of the batched encoder in one launch whose blocks wait for nobody: states [2][S][H] and their blocks' largest
+// magnitudes [2][S][ceil(H / 32)] of the step before (unused at t = 0) in h_in / pm_in, of this one in h_out / pm_out
+bool q8i_enc_cell_ok(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S);
+q8_status q8i_enc_cell(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, int t,
+                       float *enc_h, const float *gxf, const float *gxb, const float *h_in, float *h_out, const float *pm_in,
+                       float *pm_out);
 q8_status q8i_readout_combine(q8_ctx *ctx, const float *ts, const float *ty, const float *tc, const float *b_t, int R,
                               int n, float *t_out, int ld, int8_t *tq, float *tscale, const q8_taps *tap);
 q8_status q8i_output_codes(q8_ctx *ctx, const q8_mat *W, const float *bias, const int8_t *tq, const float *tscale, int n,

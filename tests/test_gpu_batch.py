@@ -574,13 +574,14 @@ def test_energies_of_a_batch(q, ctx, beam, A, lens):
 
 @pytest.mark.parametrize("E,H,lens,tiled", [(36, 4, [3, 1], False), (64, 64, [2] * 9 + [5], True), (620, 1000, [4, 9, 1], False), (64, 256, [1, 2, 3] * 6, True),
                                             (48, 96, [3, 1, 4] * 22, False), (48, 100, [2, 1] * 65, False),
-                                            # 32 and 64 slots per block, two rounds of blocks, three launches instead
+                                            # 32 and 64 slots per block, two rounds of blocks, three launches per position instead
                                             (16, 100, [1, 2, 2] * 190, False), (32, 1000, [2, 1, 3] * 33, False), (32, 1024, [1, 3] * 97, True),
                                             (64, 512, [2, 1] * 200, True), (32, 1024, [2, 1] * 200, True), (32, 1024, [1, 3] * 130, True)])
 def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
-    """The batched encoder's launches per position at the edges of their blocks (32 units, 16 / 32 / 64 slots, one slot
-    group and more), sentences that end at different steps: the states of q8_encode, which runs another kernel per
-    position, bit for bit; with the workspace that q8_encode_batch_bytes asks for, and no more than it."""
+    """The batched encoder's launches per position (one_launch = 0) at the edges of their blocks (32 units, 16 / 32 / 64 slots,
+    one slot group and more), sentences that end at different steps: the states of q8_encode, which runs another kernel per
+    position, and of the batch in one launch, bit for bit; with the workspace that q8_encode_batch_bytes asks for, and no
+    more than it."""
     rng = np.random.default_rng(H + len(lens))
     p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=len(lens) + (k == "b"), I=E, H=H).items()}
     big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
@@ -591,13 +592,53 @@ def test_encoder_step_in_one_launch(q, oracle, E, H, lens, tiled):
     from paper_1804_05038_amd import binding
     header = 256 * 1024
     ctx = q.Context(workspace_bytes=header + binding.q8_encode_batch_bytes(G[0], L, len(lens)))
+    q.q8_encoder_options(ctx, False)
     for _ in range(2):
         enc = q.q8_encode_batch(ctx, G[0], G[1], X, list(lens))
+    q.q8_encoder_options(ctx, True)
+    assert_same(q.q8_encode_batch(ctx, G[0], G[1], X, list(lens)), np_(enc), "in one launch")
     q.q8_encoder_options(big, False)
     off = [0] + list(np.cumsum(lens))
     for i in sorted({*range(min(12, len(lens))), *range(max(0, len(lens) - 3), len(lens))}):
         rows = slice(int(off[i]), int(off[i + 1]))
         assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
+
+
+def test_encoder_options_choose_the_launches_of_a_batch(q):
+    """one_launch = 0 takes the kernel whose blocks wait for each other out of q8_encode_batch as out of q8_encode: a launch per
+    position in its place."""
+    E, H, lens = 16, 64, [3, 5, 2]
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=k == "b", I=E, H=H).items()}
+    ctx = q.Context()
+    G = [q.GruWeights(gpu_mat(q, ctx, p[k + "Wx"]), gpu_mat(q, ctx, p[k + "Wh"]), ctx.f32(p[k + "bx"]), ctx.f32(p[k + "bh"])) for k in ("f", "b")]
+    X = ctx.f32(np.random.default_rng(0).standard_normal((sum(lens), E)).astype(np.float32))
+    for one_launch, launches in ((True, 1), (False, max(lens)), (True, 1)):
+        q.q8_encoder_options(ctx, one_launch)
+        q.q8_profile_begin(ctx, "gru", 16)
+        q.q8_encode_batch(ctx, G[0], G[1], X, lens)
+        assert q.q8_profile_end(ctx)[1] == launches
+
+
+@pytest.mark.parametrize("E,H,ld,lens", [(16, 1028, None, [3, 1, 5, 2, 4, 1, 2]), (16, 1028, None, [2, 1, 3, 1, 2, 1, 4, 2]), (16, 1028, None, [1, 4, 2] * 3),
+                                         (16, 1056, None, [2, 3] * 35), (20, 64, 1040, [2, 1, 3]), (20, 64, 1040, [1, 2, 3] * 6)])
+def test_encoder_of_a_batch_in_three_launches_per_position(q, E, H, ld, lens):
+    """What neither launch takes (more than 1024 hidden units, rows of W_h of more than 1024 bytes): codes, products and gates
+    per position, at 7, 8, 9 and more sentences (products of up to 8 vectors are other kernels'), against q8_encode bit for
+    bit."""
+    rng = np.random.default_rng(H + len(lens))
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=len(lens) + (k == "b"), I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1088))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"]), q.q8_quantize_matrix(big, p[k + "Wh"], ld), big.f32(p[k + "bx"]), big.f32(p[k + "bh"]))
+         for k in ("f", "b")]
+    off = np.concatenate([[0], np.cumsum(lens)])
+    X = big.f32(rng.standard_normal((int(off[-1]), E)).astype(np.float32))
+    ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], int(off[-1]), len(lens)))
+    for one_launch in (True, False):
+        q.q8_encoder_options(ctx, one_launch)
+        enc = q.q8_encode_batch(ctx, G[0], G[1], X, list(lens))
+        for i in range(len(lens)):
+            rows = slice(int(off[i]), int(off[i + 1]))
+            assert_same(enc[rows], np_(q.q8_encode(big, G[0], G[1], X[rows].contiguous())), "sentence %d" % i)
 
 
 @pytest.mark.parametrize("E,H,lens,tiled", [(16, 36, [5, 1, 9], False), (16, 4, [3] * 129, False), (32, 1024, [4] * 64 + [7], True),
