@@ -48,15 +48,13 @@
 // more sums to add up: 1 us faster in nothing, 5 slower where a poll comes early); all floats of a step exchanged as
 // (float, tag) pairs (twice the bytes).  The pause before the first poll: too early costs another 64 KB per block and slows
 // the stores that are waited for (64 sentences, 4 / 8 / 12 / 16 times 64 clocks: 263 / 242 / 240 / 242 us; 16: 196 / 173 / 173 / 180).
-#define ENCG_UNITS 32
-#define ENCG_SLOTS 16
+#define ENCG_UNITS Q8_ENC_UNITS
+#define ENCG_SLOTS Q8_ENC_SLOTS
 #define ENCG_THREADS 1024
-#define ENCG_PITCH (1024 + 16)
-#define ENCG_TILE (16 * 16 + 32)       // ints per exchanged tile of sums: the unit tiles of a slot fall on different banks
+#define ENCG_PITCH Q8_ENC_PITCH
+#define ENCG_TILE Q8_ENC_TILE
 #define ENCG_ABSENT 0xffffffffu
 #define ENCG_SPINS 4096                // polls of a wait at most (some 5 ms): what follows is slow, not wrong
-#define ENCG_LDS (ENCG_SLOTS * ENCG_PITCH + 12 * ENCG_TILE * 4)
-#define ENCG_LDS_GROUP (ENCG_SLOTS * ENCG_UNITS * 4 + ENCG_SLOTS * 8)
 #define ENCG_AGENT_LOAD 0x10            // cache policy of a device-coherent load or store (sc1)
 
 // The turn on a device (a module's variable, so one per device and process): how many of the last eight blocks (one per XCD;
@@ -332,26 +330,21 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 
 // =================================================================== host launchers ==
 
-// Sets per direction: as many as there are slots for, and as leave a compute unit at most one block.
-static int enc_group_sets(int H, int S)
-{
-    const int members = (H + ENCG_UNITS - 1) / ENCG_UNITS, most = 4 * (32 / members);
-    return S < most ? S : most;
-}
-
 // 4-byte words of scratch (0: the shape is not covered): the members' words and the sets' counters and flags.
 size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S)
 {
     const int H = fwd->Wh.cols;
-    if (H % 4 || H > 1024 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld) return 0;
-    return (size_t)6 * S * H + 4 * enc_group_sets(H, S);
+    int members, sets, groups, slots;
+    if (H % 4 || H > 1024 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || q8_enc_plan(H, S, &members, &sets, &groups, &slots) > Q8_ENC_LDS) return 0;
+    return (size_t)6 * S * H + 4 * sets;
 }
 
 q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
                         const float *gxf, const float *gxb, unsigned *words)
 {
-    const int H = fwd->Wh.cols, spd = enc_group_sets(H, S), members = (H + ENCG_UNITS - 1) / ENCG_UNITS;
-    const int ns = (S + spd - 1) / spd, ng = (ns + ENCG_SLOTS - 1) / ENCG_SLOTS, gs = (ns + ng - 1) / ng;
+    const int H = fwd->Wh.cols;
+    int members, spd, ng, gs;
+    const size_t lds = q8_enc_plan(H, S, &members, &spd, &ng, &gs);
     const int clear = 4 * spd + 2 * S * H;
     // (the two launches side by side on their queue: a stream that shares it cannot wait for the turn between them)
     static std::mutex pair;
@@ -362,7 +355,6 @@ q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_wei
     EncGroupArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {gxf, gxb}, sent_off, enc_h,
                       words + 4 * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,
                       (size_t)gs * H > 8192 ? 11 : 8, {fwd->Wh.scale, bwd->Wh.scale}};
-    Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_group_kernel, dim3(8 * members * ((2 * spd + 7) / 8)), dim3(ENCG_THREADS),
-              (size_t)ENCG_LDS + (size_t)ng * ENCG_LDS_GROUP, a);
+    Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_group_kernel, dim3(8 * members * ((2 * spd + 7) / 8)), dim3(ENCG_THREADS), lds, a);
     return q8i_launch_check(ctx, "encoder recurrences");
 }

@@ -82,6 +82,26 @@ Q8_INDEX_FN unsigned q8_panel_step(int s) { return (unsigned)(s >> 1) * 1024u + 
 
 // ---- the batched encoder (enc_group_kernel) ----
 
+#define Q8_ENC_UNITS 32
+#define Q8_ENC_SLOTS 16
+#define Q8_ENC_PITCH (1024 + 16)
+#define Q8_ENC_TILE (16 * 16 + 32)      // ints per exchanged tile of sums: the unit tiles of a slot fall on different banks
+#define Q8_ENC_LDS (64 * 1024 - 256)     // what a launch may have without asking for more, less the kernel's own variables
+
+// S sentences of H units: members of a set, sets per direction (as many as there are slots for, and as leave a compute unit at
+// most one block), groups of a set with the most sentences and slots per group.  Returns the bytes of LDS, which grow with
+// the groups (65280 at the 1024 sentences that callers may ask for at most).
+Q8_INDEX_FN unsigned q8_enc_plan(int H, int S, int *members, int *sets, int *groups, int *slots)
+{
+    *members = (H + Q8_ENC_UNITS - 1) / Q8_ENC_UNITS;
+    const int most = 4 * (32 / *members);
+    *sets = S < most ? S : most;
+    const int ns = (S + *sets - 1) / *sets;
+    *groups = (ns + Q8_ENC_SLOTS - 1) / Q8_ENC_SLOTS;
+    *slots = (ns + *groups - 1) / *groups;
+    return Q8_ENC_SLOTS * Q8_ENC_PITCH + 12 * Q8_ENC_TILE * 4 + (unsigned)*groups * (Q8_ENC_SLOTS * Q8_ENC_UNITS * 4 + Q8_ENC_SLOTS * 8);
+}
+
 // Where iteration `it` of a block (one group of slots at one time step, counted from the launch's first) keeps the scale of its
 // slot: two sets of 16 in turn, because an iteration's scales are read while other waves write the next one's.
 Q8_INDEX_FN int q8_enc_scale(int it, int slot) { return 16 * (it & 1) + slot; }

@@ -49,4 +49,19 @@ void q8x_panel_plans(int rows, int step, int ld, int n, unsigned long long *wors
     }
 }
 
+/* The most LDS of [1, S] sentences of H units, and 0 if some plan's groups don't cover a set, or its blocks the device */
+unsigned q8x_enc_lds(int H, int S)
+{
+    unsigned worst = 0;
+    for (int s = 1; s <= S; ++s) {
+        int members, sets, groups, slots;
+        const unsigned lds = q8_enc_plan(H, s, &members, &sets, &groups, &slots);
+        for (int i = 0; i < sets; ++i)
+            if (s * (i + 1) / sets - s * i / sets > groups * slots || s * (i + 1) / sets == s * i / sets) return 0;
+        if (members * 32 < H || slots > 16 || 2 * sets * members > 256) return 0;
+        if (lds > worst) worst = lds;
+    }
+    return worst;
+}
+
 int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }

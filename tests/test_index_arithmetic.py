@@ -89,6 +89,13 @@ def test_panel_plans_fit_the_lds(lib, ld):
         assert 0 < lds.value <= 160 * 1024 and bias.value <= 0, (n, lds.value, bias.value)
 
 
+@pytest.mark.parametrize("H", [4, 32, 36, 100, 256, 512, 516, 1000, 1024])
+def test_batched_encoder_plans_fit_the_lds_of_a_plain_launch(lib, H):
+    """All numbers of sentences that the entry point takes (1024): no block needs more than 64 KB with the kernel's own
+    variables (144 bytes), every sentence has a slot, and there is at most a block per compute unit."""
+    assert 0 < lib.q8x_enc_lds(H, 1024) <= 64 * 1024 - 256
+
+
 def _enc_accesses(scale_at, it):
     """What the sixteen waves of the batched encoder's block do in LDS in iteration `it` (a group of slots at a time step), as
     (interval between barriers, wave, array, index, is a write): codes in front of the first of its two barriers, products
