@@ -6,6 +6,7 @@
 #include "q8_internal.h"
 #include "q8_index.h"
 #include "q8_gemm_jobs.h"
+#include "q8_route.h"
 
 // Block tiles (row tiles per wave, vector tiles): matrices of more than 8192 rows (the
 // vocabulary) and the rest.
@@ -19,7 +20,6 @@
 #endif
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-#define TILE_FILL (128LL * 128 * 128)       // results that are worth a launch of 128 x 128 tiles: 128 full ones
 #define GB_K 128           // k bytes per stage
 #define GB_PITCH 144       // LDS bytes per staged vector: 16 lanes x 16 bytes fall on 64 distinct banks
 
@@ -960,56 +960,22 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.rows > max_rows) max_rows = a.rows;
     }
     const bool stats = d[0].part_max != nullptr;
-    // K-resident blocks: products with rows of at most 512 bytes, plain output, no taps
-    bool resident = !stats && n > 8;
-    int max_ld = 0, min_ld = 1 << 30;
+    q8_panel_shape shape = {njobs, {jobs.j[0].rows, jobs.j[1].rows, jobs.j[2].rows}, n, jobs.j[0].ld, jobs.j[0].ld, !stats, 1, 1, 1};
     for (int t = 0; t < njobs; ++t) {
         const GemmArgs &a = jobs.j[t];
-        if (a.ld < min_ld) min_ld = a.ld;
-        if (a.ld > 512 || a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) resident = false;
-        if (a.ld > max_ld) max_ld = a.ld;
+        if (a.ld < shape.min_ld) shape.min_ld = a.ld;
+        if (a.ld > shape.max_ld) shape.max_ld = a.ld;
+        if (a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) shape.plain = 0;
+        if (!a.Wt) shape.packed = 0;
+        if (a.ld % 64) shape.steps = 0;
+        if (a.ldy % 4 || ((uintptr_t)a.Y & 15)) shape.whole = 0;
     }
-    // Plain products with longer rows (kernel trace, us, each form beside the one that would run without it):
-    // rows of 513-1024 bytes: whole tiles at once, 128 rows x 32 vectors while these give a compute unit at most one block, else
-    //   x 64 (3072 x 1024 times 9 / 200 / 400 / 1000 vectors 4.6 / 5.3 / 7.2 / 10.4 against 5.3 / 6.6 / 8.7 K-resident and 13.8
-    //   in 128 x 128 tiles, 4096 x 1024 x 1000 11.4 against 15.5, 3000 rows of 1008 bytes, row-major, x 1000 11.2 against 14.6;
-    //   two such products of a decoder step times 100 / 320 4.8 / 7.2 against 6.2 / 7.5 with k split over two waves; x 32
-    //   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some three rounds of
-    //   blocks: beyond, 128 x 128 tiles read less (50000 x 1024 x 65 18.3 against 21.2, 20000 x 1024 x 300 22.0 against 23.6;
-    //   8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps and results in whole 16-byte pieces;
-    // rows of 1025-2048 bytes: 64 rows x 64 vectors at once where these nearly fill one round (1024 x 2048 x 1024 8.4 against
-    //   11.0 in 64 x 64 tiles, 9.6 streamed; 3000 x 2000 x 300, row-major, 9.0 against 13.0 staged, 9.9 streamed), else the weights
-    //   kept for a stream of vectors (1024 x 2048 times 30 / 130 6.3 / 6.5 against 9.0 / 9.1, 6.7 / 7.0 at once; 3072 x 2048 times
-    //   400 / 700 10.9 / 14.8 against 13.6 / 17.3; 2000 x 1500 x 700, row-major, 11.9 against 14.4), unless the rows' last
-    //   parts are mostly padding or a launch has many rounds (3072 x 1280 x 1000 17.7 against 15.9 in 128 x 128 tiles,
-    //   3072 x 2048 x 1000 18.2 in a decoder step against 17.4; 33658 x 2048 x 64 30.7 against 23.3 in 64 x 64 tiles);
-    // longer rows, and what is left: 128 x 128 tiles where the results fill enough of them (TILE_FILL), 64 x 64 tiles for packed
-    //   rows (8200 x 2048 times 9 / 64 / 200 9.2 / 9.7 / 19.2 against 17.3 / 18.8 / 22.5 staged), the staged kernel for row-major
-    //   ones, of which it requests a whole 128 bytes at a time.
-    bool tile_ok = !stats && n > 8, packed = true, steps = true, whole = true;
-    long long results = 0;
-    for (int t = 0; t < njobs; ++t) {
-        const GemmArgs &a = jobs.j[t];
-        if (a.tap_acc || a.tiled || (size_t)a.ntiles * 16 * a.ld >= (1u << 31) || (size_t)n * a.ld >= (1u << 31)) tile_ok = false;
-        results += (long long)a.rows * n;
-        packed = packed && a.Wt;
-        steps = steps && a.ld % 64 == 0;
-        whole = whole && a.ldy % 4 == 0 && ((uintptr_t)a.Y & 15) == 0;
-    }
-    auto blocks = [&](int rw, int cw) {
-        long long b = 0;
-        for (int t = 0; t < njobs; ++t) b += (long long)((jobs.j[t].rows + rw - 1) / rw) * ((n + cw - 1) / cw);
-        return b;
-    };
-    if (tile_ok && min_ld > 1024 && max_ld <= 2048) {
-        const long long b = blocks(64, 64), rb = blocks(64, n);
-        if (b > 150 && b <= 256) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 64, 64);
-        if (rb <= 256 && b * 2048 <= 640LL * max_ld) return q8i_gemm_stream(ctx, jobs, max_rows, n, njobs, (int)rb);
-    } else if (tile_ok && max_ld > 512 && max_ld <= 1024) {
-        if (blocks(128, 32) <= 256) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 32);
-        if (blocks(128, 64) <= 800 || n <= 64 || !steps || !whole || results < TILE_FILL) return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 64);
-    }
-    if (tile_ok && results >= TILE_FILL && max_ld > 512 && (max_ld <= 1024 || n > 64 || !packed)) {
+    switch (q8_panel_route(&shape)) {
+    case Q8_ROUTE_ONCE_64X64: return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 64, 64);
+    case Q8_ROUTE_ONCE_128X32: return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 32);
+    case Q8_ROUTE_ONCE_128X64: return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 64);
+    case Q8_ROUTE_STREAM: return q8i_gemm_stream(ctx, jobs, max_rows, n, njobs, (int)q8_panel_blocks(&shape, 64, n));
+    case Q8_ROUTE_TILES_128: {
         const size_t smem = (size_t)2 * 128 * (256 + 16);
         static Q8OncePerDevice asked;
         const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_tile_kernel<4, 1, 4>, smem, "large panel kernel");
@@ -1017,13 +983,13 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<4, 1, 4>), dim3((max_rows + 127) / 128, (n + 127) / 128, njobs), dim3(256), smem, jobs);
         return q8i_launch_check(ctx, "gemm");
     }
-    if (tile_ok && max_ld > 512 && packed) {
+    case Q8_ROUTE_TILES_64:
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_tile_kernel<2, 2, 1>), dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)2 * 64 * (256 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
-    }
-    if (resident) {
+    case Q8_ROUTE_RESIDENT:
         Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel, dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), (size_t)64 * (512 + 16), jobs);
         return q8i_launch_check(ctx, "gemm");
+    default: break;                                      // staged
     }
     if (max_rows > 8192) {
         const dim3 grid((max_rows + 64 * GB_BIG_RT - 1) / (64 * GB_BIG_RT), (n + 16 * GB_BIG_NT - 1) / (16 * GB_BIG_NT), njobs);

@@ -1,0 +1,70 @@
+// q8_route.h -- which kernel a panel product (q8i_gemm_jobs) takes: plain integer arithmetic on its sizes, the same in a host
+// build, so that the tests of the kernels can be checked against the rule that the library follows.
+#pragma once
+
+enum q8_panel_kernel {
+    Q8_ROUTE_STAGED,           // gemm_block_kernel
+    Q8_ROUTE_RESIDENT,         // gemm_resident_kernel: rows of at most 512 bytes
+    Q8_ROUTE_TILES_64,         // gemm_tile_kernel, 64 x 64 and 128 x 128
+    Q8_ROUTE_TILES_128,
+    Q8_ROUTE_ONCE_64X64,       // gemm_once_kernel, rows x vectors of a block
+    Q8_ROUTE_ONCE_128X32,
+    Q8_ROUTE_ONCE_128X64,
+    Q8_ROUTE_STREAM            // gemm_stream_kernel
+};
+
+struct q8_panel_shape {
+    int njobs, rows[3];        // products of the launch
+    int n;                     // vectors
+    int min_ld, max_ld;        // bytes per row of the products
+    int plain;                 // no taps, no statistics, results vector by vector, operands below 2 GiB
+    int packed;                // all weights tile-packed
+    int steps;                 // all rows whole 64-byte steps
+    int whole;                 // all results in whole 16-byte pieces
+};
+typedef struct q8_panel_shape q8_panel_shape;
+
+#define Q8_TILE_FILL (128LL * 128 * 128)       // results that are worth a launch of 128 x 128 tiles: 128 full ones
+
+// blocks of rw rows x cw vectors that the launch's results touch
+static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
+{
+    long long b = 0;
+    for (int t = 0; t < s->njobs; ++t) b += (long long)((s->rows[t] + rw - 1) / rw) * ((s->n + cw - 1) / cw);
+    return b;
+}
+
+// Plain products with longer rows (kernel trace, us, each form beside the one that would run without it):
+// rows of 513-1024 bytes: whole tiles at once, 128 rows x 32 vectors while these give a compute unit at most one block, else
+//   x 64 (3072 x 1024 times 9 / 200 / 400 / 1000 vectors 4.6 / 5.3 / 7.2 / 10.4 against 5.3 / 6.6 / 8.7 K-resident and 13.8
+//   in 128 x 128 tiles, 4096 x 1024 x 1000 11.4 against 15.5, 3000 rows of 1008 bytes, row-major, x 1000 11.2 against 14.6;
+//   two such products of a decoder step times 100 / 320 4.8 / 7.2 against 6.2 / 7.5 with k split over two waves; x 32
+//   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some three rounds of
+//   blocks: beyond, 128 x 128 tiles read less (50000 x 1024 x 65 18.3 against 21.2, 20000 x 1024 x 300 22.0 against 23.6;
+//   8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps and results in whole 16-byte pieces;
+// rows of 1025-2048 bytes: 64 rows x 64 vectors at once where these nearly fill one round (1024 x 2048 x 1024 8.4 against
+//   11.0 in 64 x 64 tiles, 9.6 streamed; 3000 x 2000 x 300, row-major, 9.0 against 13.0 staged, 9.9 streamed), else the weights
+//   kept for a stream of vectors (1024 x 2048 times 30 / 130 6.3 / 6.5 against 9.0 / 9.1, 6.7 / 7.0 at once; 3072 x 2048 times
+//   400 / 700 10.9 / 14.8 against 13.6 / 17.3; 2000 x 1500 x 700, row-major, 11.9 against 14.4), unless the rows' last
+//   parts are mostly padding or a launch has many rounds (3072 x 1280 x 1000 17.7 against 15.9 in 128 x 128 tiles,
+//   3072 x 2048 x 1000 18.2 in a decoder step against 17.4; 33658 x 2048 x 64 30.7 against 23.3 in 64 x 64 tiles);
+// longer rows, and what is left: 128 x 128 tiles where the results fill enough of them (Q8_TILE_FILL), 64 x 64 tiles for packed
+//   rows (8200 x 2048 times 9 / 64 / 200 9.2 / 9.7 / 19.2 against 17.3 / 18.8 / 22.5 staged), the staged kernel for row-major
+//   ones, of which it requests a whole 128 bytes at a time.
+static inline int q8_panel_route(const q8_panel_shape *s)
+{
+    long long results = 0;
+    if (!s->plain || s->n <= 8) return Q8_ROUTE_STAGED;
+    if (s->max_ld <= 512) return Q8_ROUTE_RESIDENT;
+    for (int t = 0; t < s->njobs; ++t) results += (long long)s->rows[t] * s->n;
+    if (s->min_ld > 1024 && s->max_ld <= 2048) {
+        const long long b = q8_panel_blocks(s, 64, 64);
+        if (b > 150 && b <= 256) return Q8_ROUTE_ONCE_64X64;
+        if (q8_panel_blocks(s, 64, s->n) <= 256 && b * 2048 <= 640LL * s->max_ld) return Q8_ROUTE_STREAM;
+    } else if (s->max_ld <= 1024) {
+        if (q8_panel_blocks(s, 128, 32) <= 256) return Q8_ROUTE_ONCE_128X32;
+        if (q8_panel_blocks(s, 128, 64) <= 800 || s->n <= 64 || !s->steps || !s->whole || results < Q8_TILE_FILL) return Q8_ROUTE_ONCE_128X64;
+    }
+    if (results >= Q8_TILE_FILL && (s->max_ld <= 1024 || s->n > 64 || !s->packed)) return Q8_ROUTE_TILES_128;
+    return s->packed ? Q8_ROUTE_TILES_64 : Q8_ROUTE_STAGED;
+}

@@ -1,5 +1,6 @@
 /* Host build of the index arithmetic that the kernels share (plain C). */
 #include "q8_index.h"
+#include "q8_route.h"
 
 void q8x_position_runs(const int *off, int n_sent, int blocks, int *pos, int *end)
 {
@@ -62,6 +63,13 @@ unsigned q8x_enc_lds(int H, int S)
         if (lds > worst) worst = lds;
     }
     return worst;
+}
+
+/* one product of n vectors (codes of ld bytes, results at `pitch` floats per vector) */
+int q8x_panel_route(int rows, int ld, int n, int packed, int pitch)
+{
+    const q8_panel_shape s = {1, {rows, 0, 0}, n, ld, ld, 1, packed, ld % 64 == 0, pitch % 4 == 0};
+    return q8_panel_route(&s);
 }
 
 int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }

@@ -220,32 +220,41 @@ def test_rows_variant_argument_errors(q, ctx):
     assert e.value.code == 1
 
 
-def _panel_route(rows, ld, n, packed, pitch):
-    """The kernel that a plain product of more than 8 vectors is dispatched to (results at `pitch` floats per vector)."""
-    resident = ld <= 1024
-    if rows * n >= 128 ** 3 and (ld > 512 and ld % 64 == 0 and n > 64 and pitch % 4 == 0 if resident else n > 64 or not packed):
-        return "tiles of 128"
-    return "resident" if resident else "tiles of 64" if packed else "staged"
+# rows, columns, vectors, tile-packed, the kernel that the product takes with results at a pitch of `rows` floats (checked against the
+# library's rule on the host)
+LARGE_PANELS = [
+    # 128 x 128 tiles: rows and vectors at the remainders of a tile, k steps and stages at theirs, row by row and packed; rows of 513-1024 bytes on both sides of 800 blocks
+    (2945, 1040, 769, False, "tiles of 128"), (33000, 1100, 64, False, "tiles of 128"), (3000, 1088, 895, True, "tiles of 128"),
+    (2433, 2112, 897, True, "tiles of 128"), (12804, 576, 512, False, "tiles of 128"), (13068, 1024, 500, True, "tiles of 128"),
+    (12800, 576, 512, True, "once 128 x 64"),
+    # 64 x 64 tiles, and the line to the streamed form
+    (130, 2112, 33, True, "tiles of 64"), (33001, 1088, 64, True, "tiles of 64"), (65, 2112, 65, True, "tiles of 64"),
+    (1472, 1088, 960, True, "tiles of 64"), (1400, 1088, 960, True, "stream"),
+    # staged, and the line to the streamed form
+    (17, 2500, 9, False, "staged"), (65, 2064, 65, False, "staged"), (1000, 2064, 513, False, "staged"), (130, 4096, 33, False, "staged"),
+    (1400, 1040, 960, False, "staged"), (1300, 1040, 960, False, "stream"),
+    # rows of at most 512 bytes
+    (2049, 16, 1024, False, "resident"), (1537, 512, 1023, True, "resident"), (33, 500, 9, False, "resident"), (64, 512, 64, True, "resident"),
+    # rows of 513-1024 bytes, 128 rows x 32 and x 64 vectors at once, and the line between them
+    (4096, 576, 256, False, "once 128 x 32"), (4100, 576, 256, True, "once 128 x 64"), (2324, 576, 1023, False, "once 128 x 64"),
+    (3072, 576, 897, True, "once 128 x 64"), (3000, 1000, 900, False, "once 128 x 64"), (1553, 1024, 1024, False, "once 128 x 64"),
+    (1537, 528, 1023, False, "once 128 x 64"), (33658, 640, 65, True, "once 128 x 64"), (33000, 640, 64, False, "once 128 x 64"),
+    # rows of 1025-2048 bytes, 64 x 64 at once and streamed, and the lines between them
+    (641, 1104, 960, False, "once 64 x 64"), (640, 1104, 960, False, "stream"), (1024, 1088, 1024, True, "once 64 x 64"),
+    (1025, 2048, 1024, True, "stream"), (2415, 1860, 903, False, "stream"), (64, 1088, 64, True, "stream"), (1024, 2048, 513, True, "stream"),
+    (65, 1088, 65, True, "stream"), (127, 1152, 9, True, "stream"), (8200, 1088, 33, True, "stream"), (17, 1100, 9, False, "stream"),
+    (65, 1040, 65, False, "stream"), (1000, 2000, 513, False, "stream"), (8201, 1088, 33, False, "stream"),
+]
 
 
-@pytest.mark.parametrize("rows,cols,n,tiled,route", [
-    # 128 x 128 tiles: rows and vectors at the remainders of a tile (1, 127, 47), k steps and stages at theirs, row by row and packed
-    (2415, 1860, 903, False, "tiles of 128"), (2945, 1040, 769, False, "tiles of 128"), (2324, 576, 1023, False, "tiles of 128"), (33000, 1100, 64, False, "tiles of 128"),
-    (3000, 1088, 895, True, "tiles of 128"), (2433, 2112, 897, True, "tiles of 128"), (3072, 576, 897, True, "tiles of 128"),
-    # 64 x 64 tiles
-    (64, 1088, 64, True, "tiles of 64"), (1024, 2048, 513, True, "tiles of 64"), (130, 2112, 33, True, "tiles of 64"),
-    (65, 1088, 65, True, "tiles of 64"), (127, 1152, 9, True, "tiles of 64"), (8200, 1088, 33, True, "tiles of 64"), (33001, 1088, 64, True, "tiles of 64"),
-    # the forms on the other side of the rule
-    (3000, 1000, 900, False, "resident"), (1553, 1024, 1024, False, "resident"), (1537, 528, 1023, False, "resident"), (2049, 16, 1024, False, "resident"),
-    (17, 1100, 9, False, "staged"), (65, 1040, 65, False, "staged"), (1000, 2000, 513, False, "staged"), (8201, 1088, 33, False, "staged"),
-    (33658, 640, 65, True, "resident"), (33000, 640, 64, False, "resident")])
+@pytest.mark.parametrize("rows,cols,n,tiled,route", LARGE_PANELS)
 @pytest.mark.parametrize("by_row", [False, True])
 def test_large_panels(q, oracle, rows, cols, n, tiled, route, by_row):
-    """The tiled products at the edges of their tiles, stages and k steps, packed and row by row, one scale and one per
-    row, results at an odd pitch: exact integer sums, one product of scales, one addition, so identical bits."""
-    assert _panel_route(rows, (cols + 15) // 16 * 16, n, tiled, rows) == route
+    """Every kernel of the plain panel products at the edges of its tiles, stages and k steps and on both sides of the rule's
+    lines, packed and row by row, one scale and one per row, results at an odd pitch: exact integer sums, one product of
+    scales, one addition, so identical bits."""
     rng = np.random.default_rng(rows + n)
-    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=4096))
     W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
     M, rs = q.q8_quantize_matrix_rows(ctx, W) if by_row else (q.q8_quantize_matrix(ctx, W), None)
     if tiled:
@@ -265,16 +274,23 @@ def test_large_panels(q, oracle, rows, cols, n, tiled, route, by_row):
             assert_same(got[j], y if bias is None else y + bias, "vector %d" % j)
 
 
-@pytest.mark.parametrize("rows,cols,n,tiled", [
+WHOLE_PANELS = [
     # rows of 513-1024 bytes: 128 rows x 32 and x 64 vectors, at the remainders of both, of the k parts and of a matrix-core step
-    (1, 516, 9, False), (129, 1024, 31, True), (127, 1000, 33, False), (128, 576, 64, True), (3072, 1024, 320, True), (3073, 720, 353, False), (4096, 1024, 1000, True),
-    (300, 528, 1024, False), (33000, 1024, 50, True),
+    (1, 516, 9, False, "once 128 x 32"), (129, 1024, 31, True, "once 128 x 32"), (127, 1000, 33, False, "once 128 x 32"),
+    (128, 576, 64, True, "once 128 x 32"), (3072, 1024, 320, True, "once 128 x 32"), (3073, 720, 353, False, "once 128 x 64"),
+    (4096, 1024, 1000, True, "once 128 x 64"), (300, 528, 1024, False, "once 128 x 32"), (33000, 1024, 50, True, "once 128 x 64"),
     # rows of 1025-2048 bytes: 64 rows x 64 vectors at once
-    (1024, 2048, 1024, True), (1000, 1100, 1009, False), (2999, 2000, 300, False), (2880, 1600, 255, True),
+    (1024, 2048, 1024, True, "once 64 x 64"), (1000, 1100, 1009, False, "once 64 x 64"), (2999, 2000, 300, False, "once 64 x 64"),
+    (2880, 1600, 255, True, "once 64 x 64"),
     # the same streamed: one share of the vectors and several, a last group of one vector, an odd number of groups
-    (1, 1028, 9, False), (65, 2048, 33, True), (64, 1536, 64, True), (3071, 2000, 61, False), (1500, 2048, 700, True), (8200, 2048, 97, True), (2000, 1500, 641, False)])
+    (1, 1028, 9, False, "stream"), (65, 2048, 33, True, "stream"), (64, 1536, 64, True, "stream"), (3071, 2000, 61, False, "stream"),
+    (1500, 2048, 700, True, "stream"), (8200, 2048, 97, True, "stream"), (2000, 1500, 641, False, "stream"),
+]
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled,route", WHOLE_PANELS)
 @pytest.mark.parametrize("by_row", [False, True])
-def test_panels_requested_whole(q, oracle, rows, cols, n, tiled, by_row):
+def test_panels_requested_whole(q, oracle, rows, cols, n, tiled, route, by_row):
     """The products whose blocks request all they need at once, and the ones that keep their weights for a stream of vectors,
     at the edges of their tiles, parts and groups, with one scale and one per row, results at an odd pitch: the same integer
     sums, product of scales and addition as everywhere, so the same bits."""

@@ -127,3 +127,20 @@ def test_no_two_waves_of_the_batched_encoder_meet_in_lds(lib):
             seen.setdefault(key, set()).add(wave)
             if write:
                 written.setdefault(key, set()).add(wave)
+
+
+ROUTES = ["staged", "resident", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "stream"]
+
+
+def test_panel_products_take_the_kernels_that_their_tests_name(lib):
+    """The rule that q8i_gemm_jobs follows, on the shapes of the device tests: each takes the kernel it is listed for, and every
+    kernel has shapes."""
+    from test_gpu_products import LARGE_PANELS, WHOLE_PANELS
+    seen = set()
+    for rows, cols, n, tiled, route in LARGE_PANELS + WHOLE_PANELS:
+        assert ROUTES[lib.q8x_panel_route(rows, (cols + 15) // 16 * 16, n, int(tiled), rows)] == route, (rows, cols, n, tiled)
+        seen.add((route, tiled))
+    assert {r for r, _ in seen} == set(ROUTES)
+    assert {r for r, t in seen if t} == set(ROUTES) - {"staged"} and {r for r, t in seen if not t} == set(ROUTES) - {"tiles of 64"}
+    for n in (1, 8):                                                   # (other kernels' work, or the staged kernel's with taps)
+        assert ROUTES[lib.q8x_panel_route(3072, 1024, n, 1, 3072)] == "staged"
