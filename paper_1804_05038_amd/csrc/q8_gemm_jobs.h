@@ -27,8 +27,9 @@ struct GemmJobs {          // products of one launch (blockIdx.z), all over the 
 };
 
 // q8_gemm_once.hip; rows: of one block of gemm_once_kernel's three forms (64: 64 rows x 64 vectors, k of at most 2048 bytes;
-// 128: 128 rows x cols vectors (32 or 64), k of at most 1024)
-q8_status q8i_gemm_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int rows, int cols);
+// 128: 128 rows x cols vectors (32 or 64), k of at most 1024; x 64 with trade: see there)
+q8_status q8i_gemm_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int rows, int cols, bool trade);
+q8_status q8i_gemm_resident_1024(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs);
 // row_blocks: of all products; each has as many shares of the vectors as give every compute unit a block
 q8_status q8i_gemm_stream(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int row_blocks);
 

@@ -1,7 +1,7 @@
 // q8_gemm_once.hip -- panel products (see q8_gemm.hip) whose blocks request everything that they need before their first
 // wait: rows of 513 to 2048 bytes, plain output.  In a file of its own: with these kernels in q8_gemm.hip's code object the
 // others there, unchanged, took longer (a decoder step of 64 sentences 0.4 us of 107).
-#include "q8_gemm_jobs.h"
+#include "q8_gemm_resident.h"
 #include "q8_index.h"
 #include <type_traits>
 
@@ -15,8 +15,15 @@
 // (us after the first block starts): all requested 3.0, first 32 vectors in LDS 3.6, last products 5.5, sums exchanged 6.0,
 // stores done 6.7; the kernel with stages of 256 bytes, two of them on their way, took in 44 GB/s (a stage per 0.74 us)
 // and ended at 9.2, of which 1.7 were biases requested behind the last products.  Kernel trace: 11.0 -> 8.4 us.
-template <int RP, int KP, int CG>
-__global__ __launch_bounds__(512, 2) void gemm_once_kernel(GemmJobs jobs)
+//
+// TRADE: row-major weights whose rows are whole 128 bytes.  The 64 bytes that 16 rows have in a step then lie in the same half
+// of their lines, and a compute unit takes such requests in at a lower rate than ones that fall on both halves, as those of
+// other rows do; so odd rows request the two steps of a line the other way round, and what has arrived trades places before
+// the products (64 selects for a wave's 64 operand registers).  3072 rows x 1000 and 8192 x 320 vectors: 640 bytes 13.7 and
+// 13.9 -> 11.8 and 11.4, 1024 bytes 16.1 and 15.3 -> 12.6 and 12.1 (kernel trace).  A form of its own, so that the others keep
+// their registers, in 128 registers, so that two blocks share a compute unit (with 130: 15.1 in place of 12.6).
+template <int RP, int KP, int CG, bool TRADE>
+__global__ __launch_bounds__(512, TRADE ? 4 : 2) void gemm_once_kernel(GemmJobs jobs)
 {
     static_assert(RP * KP == 8 && 2 * CG % KP == 0, "eight waves, even shares of the vector tiles");
     constexpr int ROWS = 32 * RP, COLS = 32 * CG, KB = 512 * KP, PITCH = KB + 16, PPC = KB / 16, PT = PPC / 16, CT = 2 * CG, KEEP = CT / KP;
@@ -39,6 +46,7 @@ __global__ __launch_bounds__(512, 2) void gemm_once_kernel(GemmJobs jobs)
     };
     vectors(0);
     const bool tiled = a.Wt != nullptr;
+    const int flip = TRADE && !tiled ? i & 1 : 0;
     const __amdgpu_buffer_rsrc_t rw = tiled ? q8_rsrc(a.Wt, (size_t)a.ntiles * 16 * ld) : q8_rsrc(a.W, (size_t)rows * ld);
     v4i av[2][8];
 #pragma unroll
@@ -49,7 +57,7 @@ __global__ __launch_bounds__(512, 2) void gemm_once_kernel(GemmJobs jobs)
         const bool ok = (tiled ? row0 : row0 + i) < rows;
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int ks = kp * 8 + s;
+            const int ks = kp * 8 + (s ^ flip);
             av[u][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(ok && 64 * ks + (tiled ? 0 : 16 * g) < ld ? base + step * ks : Q8_OOB), 0, 0));
         }
     }
@@ -76,6 +84,16 @@ __global__ __launch_bounds__(512, 2) void gemm_once_kernel(GemmJobs jobs)
             *(v4i *)(s_g + (32 * c + e / PPC) * PITCH + 16 * (e & (PPC - 1))) = xv[c][u];
         }
         __syncthreads();
+        if (TRADE && c == 0) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int s = 0; s < 8; s += 2) {
+                    const v4i even = flip ? av[u][s + 1] : av[u][s], odd = flip ? av[u][s] : av[u][s + 1];
+                    av[u][s] = even;
+                    av[u][s + 1] = odd;
+                }
+        }
         const int8_t *bp = s_g + (32 * c + i) * PITCH + kp * 512 + 16 * g;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -259,22 +277,23 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmJobs jobs, int 
     }
 }
 
-template <int RP, int KP, int CG>
+template <int RP, int KP, int CG, bool TRADE>
 static q8_status launch_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs)
 {
     constexpr size_t smem = (size_t)32 * CG * (512 * KP + 16);
     static Q8OncePerDevice asked;
-    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_once_kernel<RP, KP, CG>, smem, "panel product kernel");
+    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_once_kernel<RP, KP, CG, TRADE>, smem, "panel product kernel");
     if (st) return st;
     const dim3 grid((max_rows + 32 * RP - 1) / (32 * RP), (n + 32 * CG - 1) / (32 * CG), njobs);
-    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_once_kernel<RP, KP, CG>), grid, dim3(512), smem, jobs);
+    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_once_kernel<RP, KP, CG, TRADE>), grid, dim3(512), smem, jobs);
     return q8i_launch_check(ctx, "gemm");
 }
 
-q8_status q8i_gemm_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int rows, int cols)
+q8_status q8i_gemm_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int rows, int cols, bool trade)
 {
-    if (rows == 64) return launch_once<2, 4, 2>(ctx, jobs, max_rows, n, njobs);
-    return cols == 32 ? launch_once<4, 2, 1>(ctx, jobs, max_rows, n, njobs) : launch_once<4, 2, 2>(ctx, jobs, max_rows, n, njobs);
+    if (rows == 64) return launch_once<2, 4, 2, false>(ctx, jobs, max_rows, n, njobs);
+    if (cols == 32) return launch_once<4, 2, 1, false>(ctx, jobs, max_rows, n, njobs);
+    return trade ? launch_once<4, 2, 2, true>(ctx, jobs, max_rows, n, njobs) : launch_once<4, 2, 2, false>(ctx, jobs, max_rows, n, njobs);
 }
 
 q8_status q8i_gemm_stream(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int row_blocks)
@@ -285,5 +304,15 @@ q8_status q8i_gemm_stream(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n
     const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_stream_kernel<2, 4>, smem, "streaming panel product kernel");
     if (st) return st;
     Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_stream_kernel<2, 4>), dim3((max_rows + 63) / 64, shares, njobs), dim3(512), smem, jobs, shares);
+    return q8i_launch_check(ctx, "gemm");
+}
+
+q8_status q8i_gemm_resident_1024(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs)
+{
+    constexpr size_t smem = (size_t)64 * (1024 + 16);
+    static Q8OncePerDevice asked;
+    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_resident_kernel<16>, smem, "resident product kernel");
+    if (st) return st;
+    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_resident_kernel<16>, dim3((max_rows + 63) / 64, (n + 63) / 64, njobs), dim3(256), smem, jobs);
     return q8i_launch_check(ctx, "gemm");
 }

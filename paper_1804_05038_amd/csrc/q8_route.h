@@ -4,12 +4,14 @@
 
 enum q8_panel_kernel {
     Q8_ROUTE_STAGED,           // gemm_block_kernel
-    Q8_ROUTE_RESIDENT,         // gemm_resident_kernel: rows of at most 512 bytes
+    Q8_ROUTE_RESIDENT,         // gemm_resident_kernel: rows of at most 512, and of at most 1024 bytes
+    Q8_ROUTE_RESIDENT_1024,
     Q8_ROUTE_TILES_64,         // gemm_tile_kernel, 64 x 64 and 128 x 128
     Q8_ROUTE_TILES_128,
     Q8_ROUTE_ONCE_64X64,       // gemm_once_kernel, rows x vectors of a block
     Q8_ROUTE_ONCE_128X32,
     Q8_ROUTE_ONCE_128X64,
+    Q8_ROUTE_ONCE_128X64_TRADE,
     Q8_ROUTE_STREAM            // gemm_stream_kernel
 };
 
@@ -19,7 +21,7 @@ struct q8_panel_shape {
     int min_ld, max_ld;        // bytes per row of the products
     int plain;                 // no taps, no statistics, results vector by vector, operands below 2 GiB
     int packed;                // all weights tile-packed
-    int steps;                 // all rows whole 64-byte steps
+    int steps, lines;          // all rows whole 64-byte steps, whole 128 bytes
     int whole;                 // all results in whole 16-byte pieces
 };
 typedef struct q8_panel_shape q8_panel_shape;
@@ -42,6 +44,9 @@ static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
 //   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some three rounds of
 //   blocks: beyond, 128 x 128 tiles read less (50000 x 1024 x 65 18.3 against 21.2, 20000 x 1024 x 300 22.0 against 23.6;
 //   8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps and results in whole 16-byte pieces;
+//   row-major rows of whole 128 bytes, which a compute unit takes in more slowly: 64 x 64 K-resident blocks, of half the
+//   bytes, in place of x 32 where they are one round (3072 rows of 640 / 768 / 1024 bytes times 9 5.3 / 5.1 / 5.6 against 6.2 / 6.2 / 7.1,
+//   times 64 6.2 / 6.2 / 6.6 against 6.4 / 6.6 / 7.4; 20000 x 640 x 9, two rounds, 7.4 against 6.4), x 64 with the trade;
 // rows of 1025-2048 bytes: 64 rows x 64 vectors at once where these nearly fill one round (1024 x 2048 x 1024 8.4 against
 //   11.0 in 64 x 64 tiles, 9.6 streamed; 3000 x 2000 x 300, row-major, 9.0 against 13.0 staged, 9.9 streamed), else the weights
 //   kept for a stream of vectors (1024 x 2048 times 30 / 130 6.3 / 6.5 against 9.0 / 9.1, 6.7 / 7.0 at once; 3072 x 2048 times
@@ -62,8 +67,9 @@ static inline int q8_panel_route(const q8_panel_shape *s)
         if (b > 150 && b <= 256) return Q8_ROUTE_ONCE_64X64;
         if (q8_panel_blocks(s, 64, s->n) <= 256 && b * 2048 <= 640LL * s->max_ld) return Q8_ROUTE_STREAM;
     } else if (s->max_ld <= 1024) {
-        if (q8_panel_blocks(s, 128, 32) <= 256) return Q8_ROUTE_ONCE_128X32;
-        if (q8_panel_blocks(s, 128, 64) <= 800 || s->n <= 64 || !s->steps || !s->whole || results < Q8_TILE_FILL) return Q8_ROUTE_ONCE_128X64;
+        if (q8_panel_blocks(s, 128, 32) <= 256) return !s->packed && s->lines && q8_panel_blocks(s, 64, 64) <= 256 ? Q8_ROUTE_RESIDENT_1024 : Q8_ROUTE_ONCE_128X32;
+        if (q8_panel_blocks(s, 128, 64) <= 800 || s->n <= 64 || !s->steps || !s->whole || results < Q8_TILE_FILL)
+            return !s->packed && s->lines ? Q8_ROUTE_ONCE_128X64_TRADE : Q8_ROUTE_ONCE_128X64;
     }
     if (results >= Q8_TILE_FILL && (s->max_ld <= 1024 || s->n > 64 || !s->packed)) return Q8_ROUTE_TILES_128;
     return s->packed ? Q8_ROUTE_TILES_64 : Q8_ROUTE_STAGED;

@@ -68,7 +68,7 @@ unsigned q8x_enc_lds(int H, int S)
 /* one product of n vectors (codes of ld bytes, results at `pitch` floats per vector) */
 int q8x_panel_route(int rows, int ld, int n, int packed, int pitch)
 {
-    const q8_panel_shape s = {1, {rows, 0, 0}, n, ld, ld, 1, packed, ld % 64 == 0, pitch % 4 == 0};
+    const q8_panel_shape s = {1, {rows, 0, 0}, n, ld, ld, 1, packed, ld % 64 == 0, ld % 128 == 0, pitch % 4 == 0};
     return q8_panel_route(&s);
 }
 

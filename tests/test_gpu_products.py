@@ -223,7 +223,8 @@ def test_rows_variant_argument_errors(q, ctx):
 # rows, columns, vectors, tile-packed, the kernel that the product takes with results at a pitch of `rows` floats (checked against the
 # library's rule on the host)
 LARGE_PANELS = [
-    # 128 x 128 tiles: rows and vectors at the remainders of a tile, k steps and stages at theirs, row by row and packed; rows of 513-1024 bytes on both sides of 800 blocks
+    # 128 x 128 tiles: rows and vectors at the remainders of a tile, k steps and stages at theirs, row by row and packed; rows of 513-1024
+    # bytes on both sides of 800 blocks
     (2945, 1040, 769, False, "tiles of 128"), (33000, 1100, 64, False, "tiles of 128"), (3000, 1088, 895, True, "tiles of 128"),
     (2433, 2112, 897, True, "tiles of 128"), (12804, 576, 512, False, "tiles of 128"), (13068, 1024, 500, True, "tiles of 128"),
     (12800, 576, 512, True, "once 128 x 64"),
@@ -237,13 +238,18 @@ LARGE_PANELS = [
     (2049, 16, 1024, False, "resident"), (1537, 512, 1023, True, "resident"), (33, 500, 9, False, "resident"), (64, 512, 64, True, "resident"),
     # rows of 513-1024 bytes, 128 rows x 32 and x 64 vectors at once, and the line between them
     (4096, 576, 256, False, "once 128 x 32"), (4100, 576, 256, True, "once 128 x 64"), (2324, 576, 1023, False, "once 128 x 64"),
-    (3072, 576, 897, True, "once 128 x 64"), (3000, 1000, 900, False, "once 128 x 64"), (1553, 1024, 1024, False, "once 128 x 64"),
-    (1537, 528, 1023, False, "once 128 x 64"), (33658, 640, 65, True, "once 128 x 64"), (33000, 640, 64, False, "once 128 x 64"),
+    (3072, 576, 897, True, "once 128 x 64"), (3000, 1000, 900, False, "once 128 x 64"), (1553, 1024, 1024, False, "once 128 x 64 trade"),
+    (1537, 528, 1023, False, "once 128 x 64"), (33658, 640, 65, True, "once 128 x 64"), (33000, 640, 64, False, "once 128 x 64 trade"),
     # rows of 1025-2048 bytes, 64 x 64 at once and streamed, and the lines between them
     (641, 1104, 960, False, "once 64 x 64"), (640, 1104, 960, False, "stream"), (1024, 1088, 1024, True, "once 64 x 64"),
     (1025, 2048, 1024, True, "stream"), (2415, 1860, 903, False, "stream"), (64, 1088, 64, True, "stream"), (1024, 2048, 513, True, "stream"),
     (65, 1088, 65, True, "stream"), (127, 1152, 9, True, "stream"), (8200, 1088, 33, True, "stream"), (17, 1100, 9, False, "stream"),
     (65, 1040, 65, False, "stream"), (1000, 2000, 513, False, "stream"), (8201, 1088, 33, False, "stream"),
+    # row by row in rows of whole 128 bytes: K-resident, at the edges of its blocks and on both sides of one round of them, and 128 x 64 with the trade
+    (1, 640, 9, False, "resident 1024"), (65, 896, 65, False, "resident 1024"), (127, 1024, 64, False, "resident 1024"),
+    (300, 640, 1024, False, "resident 1024"), (8192, 640, 128, False, "resident 1024"), (20000, 640, 20, False, "once 128 x 32"),
+    (2324, 640, 1023, False, "once 128 x 64 trade"), (3073, 768, 353, False, "once 128 x 64 trade"), (8200, 1024, 260, False, "once 128 x 64 trade"),
+    (20001, 896, 100, False, "once 128 x 64 trade"),
 ]
 
 

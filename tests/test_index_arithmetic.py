@@ -129,7 +129,7 @@ def test_no_two_waves_of_the_batched_encoder_meet_in_lds(lib):
                 written.setdefault(key, set()).add(wave)
 
 
-ROUTES = ["staged", "resident", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "stream"]
+ROUTES = ["staged", "resident", "resident 1024", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "once 128 x 64 trade", "stream"]
 
 
 def test_panel_products_take_the_kernels_that_their_tests_name(lib):
@@ -141,6 +141,13 @@ def test_panel_products_take_the_kernels_that_their_tests_name(lib):
         assert ROUTES[lib.q8x_panel_route(rows, (cols + 15) // 16 * 16, n, int(tiled), rows)] == route, (rows, cols, n, tiled)
         seen.add((route, tiled))
     assert {r for r, _ in seen} == set(ROUTES)
-    assert {r for r, t in seen if t} == set(ROUTES) - {"staged"} and {r for r, t in seen if not t} == set(ROUTES) - {"tiles of 64"}
+    assert {r for r, t in seen if t} == set(ROUTES) - {"staged", "resident 1024", "once 128 x 64 trade"}
+    assert {r for r, t in seen if not t} == set(ROUTES) - {"tiles of 64"}
+    # row by row in rows of whole 128 bytes: the K-resident blocks while they are one round, for any number of vectors
+    for ld in (640, 768, 896, 1024):
+        for rows, n in ((64, 9), (3072, 9), (3072, 64), (3072, 320), (8192, 33), (8192, 128)):
+            assert ROUTES[lib.q8x_panel_route(rows, ld, n, 0, rows)] == "resident 1024"
+            assert ROUTES[lib.q8x_panel_route(rows, ld, n, 1, rows)] == ROUTES[lib.q8x_panel_route(rows, ld - 16, n, 0, rows)] == "once 128 x 32"
+        assert ROUTES[lib.q8x_panel_route(20000, ld, 9, 0, 20000)] == "once 128 x 32"
     for n in (1, 8):                                                   # (other kernels' work, or the staged kernel's with taps)
         assert ROUTES[lib.q8x_panel_route(3072, 1024, n, 1, 3072)] == "staged"
