@@ -41,9 +41,11 @@ static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
 //   x 64 (3072 x 1024 times 9 / 200 / 400 / 1000 vectors 4.6 / 5.3 / 7.2 / 10.4 against 5.3 / 6.6 / 8.7 K-resident and 13.8
 //   in 128 x 128 tiles, 4096 x 1024 x 1000 11.4 against 15.5, 3000 rows of 1008 bytes, row-major, x 1000 11.2 against 14.6;
 //   two such products of a decoder step times 100 / 320 4.8 / 7.2 against 6.2 / 7.5 with k split over two waves; x 32
-//   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some three rounds of
-//   blocks: beyond, 128 x 128 tiles read less (50000 x 1024 x 65 18.3 against 21.2, 20000 x 1024 x 300 22.0 against 23.6;
-//   8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps and results in whole 16-byte pieces;
+//   beside x 64 vectors at 200 / 350 / 1000: 5.3 / 7.2 / 11.2 against 6.8 / 7.0 / 10.4), up to some 800 blocks, 700 of matrices
+//   of more than 16384 rows: beyond, 128 x 128 tiles read less (50000 x 640 x 100 18.0 against 22.2, 20000 x 1024 x 300 22.0
+//   against 23.6; 20000 x 640 x 200, 628 blocks, 18.0 against 18.1; two products of 3072 x 512 and x 1024 times 1000, 768 blocks,
+//   17.4 against 14.2; 8192 x 1024 x 512 11.9 against 14.8), for more than 64 vectors, whole k steps, results in whole
+//   16-byte pieces and no third of a tile past the vectors (33660 x 768 x 130 23.2 against 25.4, 50000 x 1024 x 130 31.6 against 34.5);
 //   row-major rows of whole 128 bytes, which a compute unit takes in more slowly: 64 x 64 K-resident blocks, of half the
 //   bytes, in place of x 32 where they are one round (3072 rows of 640 / 768 / 1024 bytes times 9 5.3 / 5.1 / 5.6 against 6.2 / 6.2 / 7.1,
 //   times 64 6.2 / 6.2 / 6.6 against 6.4 / 6.6 / 7.4; 20000 x 640 x 9, two rounds, 7.4 against 6.4), x 64 with the trade;
@@ -58,17 +60,18 @@ static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
 //   ones, of which it requests a whole 128 bytes at a time.
 static inline int q8_panel_route(const q8_panel_shape *s)
 {
-    long long results = 0;
+    long long rows = 0, results;
     if (!s->plain || s->n <= 8) return Q8_ROUTE_STAGED;
     if (s->max_ld <= 512) return Q8_ROUTE_RESIDENT;
-    for (int t = 0; t < s->njobs; ++t) results += (long long)s->rows[t] * s->n;
+    for (int t = 0; t < s->njobs; ++t) rows += s->rows[t];
+    results = rows * s->n;
     if (s->min_ld > 1024 && s->max_ld <= 2048) {
         const long long b = q8_panel_blocks(s, 64, 64);
         if (b > 150 && b <= 256) return Q8_ROUTE_ONCE_64X64;
         if (q8_panel_blocks(s, 64, s->n) <= 256 && b * 2048 <= 640LL * s->max_ld) return Q8_ROUTE_STREAM;
     } else if (s->max_ld <= 1024) {
         if (q8_panel_blocks(s, 128, 32) <= 256) return !s->packed && s->lines && q8_panel_blocks(s, 64, 64) <= 256 ? Q8_ROUTE_RESIDENT_1024 : Q8_ROUTE_ONCE_128X32;
-        if (q8_panel_blocks(s, 128, 64) <= 800 || s->n <= 64 || !s->steps || !s->whole || results < Q8_TILE_FILL)
+        if (q8_panel_blocks(s, 128, 64) <= (rows > 16384 ? 700 : 800) || s->n <= 64 || (s->n > 128 && s->n <= 192) || !s->steps || !s->whole || results < Q8_TILE_FILL)
             return !s->packed && s->lines ? Q8_ROUTE_ONCE_128X64_TRADE : Q8_ROUTE_ONCE_128X64;
     }
     if (results >= Q8_TILE_FILL && (s->max_ld <= 1024 || s->n > 64 || !s->packed)) return Q8_ROUTE_TILES_128;

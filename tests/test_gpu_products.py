@@ -224,10 +224,11 @@ def test_rows_variant_argument_errors(q, ctx):
 # library's rule on the host)
 LARGE_PANELS = [
     # 128 x 128 tiles: rows and vectors at the remainders of a tile, k steps and stages at theirs, row by row and packed; rows of 513-1024
-    # bytes on both sides of 800 blocks
+    # bytes on both sides of 800 and 700 blocks and of 192 vectors
     (2945, 1040, 769, False, "tiles of 128"), (33000, 1100, 64, False, "tiles of 128"), (3000, 1088, 895, True, "tiles of 128"),
     (2433, 2112, 897, True, "tiles of 128"), (12804, 576, 512, False, "tiles of 128"), (13068, 1024, 500, True, "tiles of 128"),
-    (12800, 576, 512, True, "once 128 x 64"),
+    (12800, 576, 512, True, "once 128 x 64"), (22272, 576, 256, True, "once 128 x 64"), (22404, 576, 256, False, "tiles of 128"),
+    (30000, 576, 160, True, "once 128 x 64"), (30000, 576, 193, True, "tiles of 128"),
     # 64 x 64 tiles, and the line to the streamed form
     (130, 2112, 33, True, "tiles of 64"), (33001, 1088, 64, True, "tiles of 64"), (65, 2112, 65, True, "tiles of 64"),
     (1472, 1088, 960, True, "tiles of 64"), (1400, 1088, 960, True, "stream"),
