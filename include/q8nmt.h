@@ -255,14 +255,15 @@ q8_status output_logits_q8(q8_ctx *ctx, const q8_readout_weights *ro, const q8_m
  * vectors back to back, sentence s in rows [sent_off[s], sent_off[s + 1]) (sent_off: device
  * int32 [n_sent + 1]; sent_off_host: the same values on the host, sent_off_host[0] = 0);
  * enc_h [L x 2H] as q8_encode.  All input products run as matrix-core panels; the recurrences of all
- * sentences, both directions, are one launch for H <= 1024 (rows of Wh of at most 1024 bytes), else a
- * quantize / product / gates triple per time step.  Blocks of that launch wait for each other's states, but
+ * sentences, both directions, are one launch for H <= 1024 (rows of Wh of at most 1024 bytes), up to 512
+ * sentences of H = 1024 and, mostly, 3 words and more; else one launch per time step (at H = 1024 for up
+ * to 256 sentences) or a quantize / product / gates triple.  Blocks of that launch wait for each other's states, but
  * nothing depends on them running side by side: a wait that takes too long (some milliseconds, or the bound
  * of q8_encoder_options if that is smaller) ends in one block working its sentences off alone, which is
  * slow and gives the same states.  Batched encoders of one process take turns on a device while their blocks
  * start, whatever their streams; beside other kernels whose blocks wait (q8_attention_options names them) and
  * other processes' encoders such a wait is possible, and q8_encoder_options with one_launch = 0 takes it out:
- * a launch per time step, without any wait (at H = 1024 for up to 256 sentences; beyond, mostly the triple).
+ * a launch per time step or the triple, without any wait.
  * Values are those of q8_encode sentence by sentence.  Needs q8_encode_batch_bytes(fwd, L, n_sent) bytes of
  * workspace. */
 size_t q8_encode_batch_bytes(const q8_gru_weights *fwd, int total_l, int n_sent);

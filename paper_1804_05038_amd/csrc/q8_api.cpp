@@ -1029,7 +1029,7 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
     }
     // the recurrences: all positions of all sentences in one launch ...
     // (this and the next form in the room of the last one's codes, scales and pre-activations, which is more)
-    const size_t words = ctx->enc_one_launch ? q8i_enc_group_words(fwd, bwd, n_sent) : 0;
+    const size_t words = ctx->enc_one_launch ? q8i_enc_group_words(fwd, bwd, n_sent, max_l) : 0;
     if (words) {
         cv.off = mark;
         unsigned *w = cv.take<unsigned>(words);

@@ -330,12 +330,13 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 
 // =================================================================== host launchers ==
 
-// 4-byte words of scratch (0: the shape is not covered): the members' words and the sets' counters and flags.
-size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S)
+// 4-byte words of scratch (0: not for this shape): the members' words and the sets' counters and flags.
+size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S, int max_l)
 {
     const int H = fwd->Wh.cols;
     int members, sets, groups, slots;
-    if (H % 4 || H > 1024 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || q8_enc_plan(H, S, &members, &sets, &groups, &slots) > Q8_ENC_LDS) return 0;
+    if (H % 4 || H > 1024 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || !q8_enc_one_launch(H, S, max_l)) return 0;
+    q8_enc_plan(H, S, &members, &sets, &groups, &slots);
     return (size_t)6 * S * H + 4 * sets;
 }
 

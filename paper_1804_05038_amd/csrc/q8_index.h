@@ -86,11 +86,10 @@ Q8_INDEX_FN unsigned q8_panel_step(int s) { return (unsigned)(s >> 1) * 1024u + 
 #define Q8_ENC_SLOTS 16
 #define Q8_ENC_PITCH (1024 + 16)
 #define Q8_ENC_TILE (16 * 16 + 32)      // ints per exchanged tile of sums: the unit tiles of a slot fall on different banks
-#define Q8_ENC_LDS (64 * 1024 - 256)     // what a launch may have without asking for more, less the kernel's own variables
 
 // S sentences of H units: members of a set, sets per direction (as many as there are slots for, and as leave a compute unit at
 // most one block), groups of a set with the most sentences and slots per group.  Returns the bytes of LDS, which grow with
-// the groups (65280 at the 1024 sentences that callers may ask for at most).
+// the groups (47872 for eight).
 Q8_INDEX_FN unsigned q8_enc_plan(int H, int S, int *members, int *sets, int *groups, int *slots)
 {
     *members = (H + Q8_ENC_UNITS - 1) / Q8_ENC_UNITS;
@@ -100,6 +99,19 @@ Q8_INDEX_FN unsigned q8_enc_plan(int H, int S, int *members, int *sets, int *gro
     *groups = (ns + Q8_ENC_SLOTS - 1) / Q8_ENC_SLOTS;
     *slots = (ns + *groups - 1) / *groups;
     return Q8_ENC_SLOTS * Q8_ENC_PITCH + 12 * Q8_ENC_TILE * 4 + (unsigned)*groups * (Q8_ENC_SLOTS * Q8_ENC_UNITS * 4 + Q8_ENC_SLOTS * 8);
+}
+
+// Whether S sentences of H units and up to max_l words run in that launch (else in one per time step, or three).  It costs 8 us
+// more than the first of those, which a time step gains back 3 us of: q8_encode_batch in us per batch, sentences of equal length,
+// H = 1024, 9 sentences of 1 / 2 / 3 / 4 words 17.5 / 20.3 / 24 / 26.5 against 11.1 / 16.9 / 24 / 29.5.  A group of a set takes 4 us of
+// a time step, so more than eight lose to the three launches (600 / 800 / 1024 sentences of 10 words 1.05 / 1.04 / 1.15 times as
+// long, 400, seven groups, 0.81), and at H <= 512 four, whose launches per time step are of half the blocks, need 7 words
+// (H = 512, 400 sentences of 3 / 4 / 6 / 8 words 1.10 / 1.07 / 1.02 / 0.98; H = 256, 1024 sentences 1.07 / 1.03 / 1.01 / 0.99).
+Q8_INDEX_FN int q8_enc_one_launch(int H, int S, int max_l)
+{
+    int members, sets, groups, slots;
+    q8_enc_plan(H, S, &members, &sets, &groups, &slots);
+    return groups <= 8 && max_l >= (H <= 512 && groups >= 4 ? 7 : 3);
 }
 
 // Where iteration `it` of a block (one group of slots at one time step, counted from the launch's first) keeps the scale of its

@@ -252,8 +252,8 @@ q8_status q8i_encode_persistent(q8_ctx *ctx, const q8_gru_weights *fwd, const q8
 q8_status q8i_enc_step(q8_ctx *ctx, int phase, const int *sent_off, int S, int t, int H, int ld, float *enc_h,
                        const float *gxf, const float *gxb, float *ghf, float *ghb, int8_t *hqf, int8_t *hqb, float *hsf,
                        float *hsb);
-// the recurrences of many sentences in one launch: words of scratch it takes (0: shape not covered), and the launch
-size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S);
+// the recurrences of many sentences in one launch: words of scratch it takes (0: not for this shape), and the launch
+size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S, int max_l);
 q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
                         const float *gxf, const float *gxb, unsigned *words);
 // one time step of the batched encoder in one launch whose blocks wait for nobody: states [2][S][H] and their blocks' largest

@@ -50,7 +50,9 @@ void q8x_panel_plans(int rows, int step, int ld, int n, unsigned long long *wors
     }
 }
 
-/* The most LDS of [1, S] sentences of H units, and 0 if some plan's groups don't cover a set, or its blocks the device */
+int q8x_enc_one_launch(int H, int S, int max_l) { return q8_enc_one_launch(H, S, max_l); }
+
+/* The most LDS of those of [1, S] sentences of H units that are one launch, and 0 if some plan's groups don't cover a set, or its blocks the device */
 unsigned q8x_enc_lds(int H, int S)
 {
     unsigned worst = 0;
@@ -60,7 +62,7 @@ unsigned q8x_enc_lds(int H, int S)
         for (int i = 0; i < sets; ++i)
             if (s * (i + 1) / sets - s * i / sets > groups * slots || s * (i + 1) / sets == s * i / sets) return 0;
         if (members * 32 < H || slots > 16 || 2 * sets * members > 256) return 0;
-        if (lds > worst) worst = lds;
+        if (lds > worst && q8_enc_one_launch(H, s, 1024)) worst = lds;
     }
     return worst;
 }

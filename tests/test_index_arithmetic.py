@@ -96,6 +96,14 @@ def test_batched_encoder_plans_fit_the_lds_of_a_plain_launch(lib, H):
     assert 0 < lib.q8x_enc_lds(H, 1024) <= 64 * 1024 - 256
 
 
+def test_batches_that_one_launch_of_the_encoder_pays_for(lib):
+    one = lib.q8x_enc_one_launch
+    for H in (4, 64, 256, 512, 516, 1000, 1024):
+        assert not one(H, 1, 1) and not one(H, 64, 2) and one(H, 1, 3) and one(H, 64, 3) and one(H, 200, 60)
+    assert one(1024, 512, 3) and not one(1024, 513, 60) and not one(1024, 1024, 1024) and not one(516, 1024, 1024)
+    assert one(512, 384, 3) and not one(512, 385, 6) and one(512, 385, 7) and one(512, 1024, 7) and not one(256, 1024, 6) and one(256, 1024, 7)
+
+
 def _enc_accesses(scale_at, it):
     """What the sixteen waves of the batched encoder's block do in LDS in iteration `it` (a group of slots at a time step), as
     (interval between barriers, wave, array, index, is a write): codes in front of the first of its two barriers, products
