@@ -25,7 +25,7 @@
 template <int RP, int KP, int CG, bool TRADE>
 __global__ __launch_bounds__(512, TRADE ? 4 : 2) void gemm_once_kernel(GemmJobs jobs)
 {
-    static_assert(RP * KP == 8 && 2 * CG % KP == 0, "eight waves, even shares of the vector tiles");
+    static_assert(RP * KP == 8 && (KP == 2 || KP == 4) && 2 * CG % KP == 0, "eight waves, even shares of the vector tiles");
     constexpr int ROWS = 32 * RP, COLS = 32 * CG, KB = 512 * KP, PITCH = KB + 16, PPC = KB / 16, PT = PPC / 16, CT = 2 * CG, KEEP = CT / KP;
     extern __shared__ __align__(16) int8_t s_g[];                      // [COLS x PITCH] codes, then the parts' sums
     const GemmArgs &a = jobs.j[blockIdx.z];
@@ -112,28 +112,24 @@ __global__ __launch_bounds__(512, TRADE ? 4 : 2) void gemm_once_kernel(GemmJobs 
     const __amdgpu_buffer_rsrc_t rr = q8_rsrc(a.row_scale, a.row_scale ? (size_t)rows * sizeof(float) : 0);
     auto finish = [&](auto part) {
         constexpr int PART = decltype(part)::value;
-        if constexpr (KP > 1) {
-            __syncthreads();                                           // (every wave has read its codes)
+        __syncthreads();                                               // (every wave has read its codes)
 #pragma unroll
-            for (int to = 0; to < KP; ++to) {
-                if (to == PART) continue;
-                v4i *out = (v4i *)s_g + (size_t)((rp * KP + to) * (KP - 1) + (PART < to ? PART : PART - 1)) * 2 * KEEP * 64 + lane;
+        for (int to = 0; to < KP; ++to) {
+            if (to == PART) continue;
+            v4i *out = (v4i *)s_g + (size_t)((rp * KP + to) * (KP - 1) + (PART < to ? PART : PART - 1)) * 2 * KEEP * 64 + lane;
 #pragma unroll
-                for (int j = 0; j < KEEP; ++j) { out[(2 * j) * 64] = acc[0][to * KEEP + j]; out[(2 * j + 1) * 64] = acc[1][to * KEEP + j]; }
-            }
-            __syncthreads();
+            for (int j = 0; j < KEEP; ++j) { out[(2 * j) * 64] = acc[0][to * KEEP + j]; out[(2 * j + 1) * 64] = acc[1][to * KEEP + j]; }
         }
+        __syncthreads();
 #pragma unroll
         for (int j = 0; j < KEEP; ++j) {
             const int col = c0 + 16 * (PART * KEEP + j) + i;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 v4i sum = acc[u][PART * KEEP + j];
-                if constexpr (KP > 1) {
 #pragma unroll
-                    for (int from = 0; from < KP - 1; ++from)
-                        sum += ((const v4i *)s_g)[(size_t)((rp * KP + PART) * (KP - 1) + from) * 2 * KEEP * 64 + (2 * j + u) * 64 + lane];
-                }
+                for (int from = 0; from < KP - 1; ++from)
+                    sum += ((const v4i *)s_g)[(size_t)((rp * KP + PART) * (KP - 1) + from) * 2 * KEEP * 64 + (2 * j + u) * 64 + lane];
                 if (col >= n) continue;
                 const int row4 = r0 + 16 * u + 4 * g;
                 float *y = a.Y + (size_t)col * a.ldy, v[4];
@@ -152,8 +148,7 @@ __global__ __launch_bounds__(512, TRADE ? 4 : 2) void gemm_once_kernel(GemmJobs 
             }
         }
     };
-    if constexpr (KP == 1) finish(std::integral_constant<int, 0>{});
-    else if constexpr (KP == 2) {
+    if constexpr (KP == 2) {
         if (kp == 0) finish(std::integral_constant<int, 0>{});
         else finish(std::integral_constant<int, 1>{});
     } else {
@@ -168,11 +163,9 @@ __global__ __launch_bounds__(512, TRADE ? 4 : 2) void gemm_once_kernel(GemmJobs 
 // requested two ahead, two of them take turns in LDS.  With 64 rows of 2048 bytes a group takes 1.6 us: 64 KB in, and 256 KB
 // through LDS (codes written, read by two row pairs, four parts' sums out and in), which is what bounds it.  (Four row
 // tiles per wave instead of two would halve the reads and do not fit the registers.)
-template <int RP, int KP>
 __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmJobs jobs, int shares)
 {
-    static_assert(RP * KP == 8 && KP > 1 && 4 % KP == 0, "eight waves, even shares of the tiles");
-    constexpr int ROWS = 32 * RP, KB = 512 * KP, PPC = KB / 16, PT = PPC / 16, OWN = 4 / KP;
+    constexpr int RP = 2, KP = 4, ROWS = 32 * RP, KB = 512 * KP, PPC = KB / 16, PT = PPC / 16, OWN = 4 / KP;
     extern __shared__ __align__(16) int8_t s_g[];                      // [2][32 x KB] codes, [8 waves][4 tiles] sums
     const GemmArgs &a = jobs.j[blockIdx.z];
     if ((int)blockIdx.x * ROWS >= a.rows) return;                      // the grid is sized for the largest job
@@ -301,9 +294,9 @@ q8_status q8i_gemm_stream(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n
     const int groups = (n + 31) / 32, most = 256 / row_blocks, shares = most < 1 ? 1 : most < groups ? most : groups;
     constexpr size_t smem = (size_t)2 * 32 * 2048 + (size_t)8 * 4 * 1024;
     static Q8OncePerDevice asked;
-    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_stream_kernel<2, 4>, smem, "streaming panel product kernel");
+    const q8_status st = q8i_lds(ctx, asked, (const void *)gemm_stream_kernel, smem, "streaming panel product kernel");
     if (st) return st;
-    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_stream_kernel<2, 4>), dim3((max_rows + 63) / 64, shares, njobs), dim3(512), smem, jobs, shares);
+    Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, gemm_stream_kernel, dim3((max_rows + 63) / 64, shares, njobs), dim3(512), smem, jobs, shares);
     return q8i_launch_check(ctx, "gemm");
 }
 
