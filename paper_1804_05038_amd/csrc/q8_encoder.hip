@@ -61,8 +61,9 @@
 // blocks of lower index start earlier) of the encoder whose turn it is have started.  Whoever takes an eight from it has the
 // next turn; fewer are put back.  The wait ends after ENCG_TURN of the 100 MHz clock (an encoder that failed to launch, or
 // whose blocks wait for room behind long kernels): whoever goes on then passes on an eight of its own, so nobody else
-// waits for what never comes.
-#define ENCG_TURN 400000ull
+// waits for what never comes.  40 ms: an encoder whose blocks wait for room waits for another to end, and 512 sentences of
+// 1024 words, the most that one launch takes, are 28 ms.
+#define ENCG_TURN 4000000ull
 __device__ unsigned enc_group_turn = 8;
 
 // Clears [words, words + n) and waits for the turn.

@@ -5,6 +5,7 @@ Per-vector quantization makes a panel's result for vector j the result of the si
 call, so each case is checked twice: against the oracle (codes and sums bit-exact through the
 taps, floats to 1e-5) and against this library's own streaming kernels (bit for bit).
 """
+import ctypes
 import time
 
 import numpy as np
@@ -728,6 +729,46 @@ def test_encoders_on_several_streams_take_turns(q):
         assert_same(out, want, "states")
         q.q8_encode_check(ctx)
     assert together < 1e-3, together
+
+
+@pytest.mark.parametrize("one_launch", [True, False])
+def test_encoder_of_a_batch_replayed_from_a_graph(q, one_launch):
+    """Captured with its clearing launch, which waits for a turn on the device: every replay, with eager batches and new inputs
+    between them, gives the eager states."""
+    from paper_1804_05038_amd import binding
+    E, H, lens = 16, 256, [5, 9, 1, 7] * 40
+    rng, L, S = np.random.default_rng(3), sum(lens), len(lens)
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=k == "b", I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], False), gpu_mat(q, big, p[k + "Wh"], True), big.f32(p[k + "bx"]), big.f32(p[k + "bh"]))
+         for k in ("f", "b")]
+    eager = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], L, S))
+    xs = [eager.f32(rng.standard_normal((L, E)).astype(np.float32)) for _ in range(3)]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    off_dev, X = torch.as_tensor(off).cuda(), xs[0].clone()
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], L, S), stream=st)
+        q.q8_encoder_options(ctx, one_launch)
+        out = ctx.empty(L, 2 * H)
+        run = lambda: ctx.check(ctx.lib.q8_encode_batch(ctx.handle, ctypes.byref(G[0].c), ctypes.byref(G[1].c), binding._ptr(X), binding._ptr(off_dev),
+                                                        off.ctypes.data_as(ctypes.POINTER(ctypes.c_int)), S, binding._ptr(out)))
+        run()
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            run()
+    torch.cuda.synchronize()
+    for i in range(6):
+        X.copy_(xs[i % 3])
+        out.fill_(7.0)
+        want = np_(q.q8_encode_batch(eager, G[0], G[1], xs[i % 3], lens))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert_same(out, want, "replay %d" % i)
 
 
 @pytest.mark.parametrize("V,R,n", [(17, 512, 9), (31, 512, 33), (33, 640, 224), (65, 512, 225), (1000, 512, 257), (1009, 640, 289),
