@@ -49,6 +49,8 @@ static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
 //   row-major rows of whole 128 bytes, which a compute unit takes in more slowly: 64 x 64 K-resident blocks, of half the
 //   bytes, in place of x 32 where they are one round (3072 rows of 640 / 768 / 1024 bytes times 9 5.3 / 5.1 / 5.6 against 6.2 / 6.2 / 7.1,
 //   times 64 6.2 / 6.2 / 6.6 against 6.4 / 6.6 / 7.4; 20000 x 640 x 9, two rounds, 7.4 against 6.4), x 64 with the trade;
+//   the same for up to 8 vectors, which the batched step of few slots has (the staged kernel elsewhere; step of 1 / 4 / 8 slots, H = 1024,
+//   packed, 37.8 / 40.7 / 41.7 against 39.3 / 43.0 / 43.9 staged and 39.2 / 41.6 / 42.6 with k split over two waves);
 // rows of 1025-2048 bytes: 64 rows x 64 vectors at once where these nearly fill one round (1024 x 2048 x 1024 8.4 against
 //   11.0 in 64 x 64 tiles, 9.6 streamed; 3000 x 2000 x 300, row-major, 9.0 against 13.0 staged, 9.9 streamed), else the weights
 //   kept for a stream of vectors (1024 x 2048 times 30 / 130 6.3 / 6.5 against 9.0 / 9.1, 6.7 / 7.0 at once; 3072 x 2048 times
@@ -61,7 +63,7 @@ static inline long long q8_panel_blocks(const q8_panel_shape *s, int rw, int cw)
 static inline int q8_panel_route(const q8_panel_shape *s)
 {
     long long rows = 0, results;
-    if (!s->plain || s->n <= 8) return Q8_ROUTE_STAGED;
+    if (!s->plain || (s->n <= 8 && (s->min_ld <= 512 || s->max_ld > 1024))) return Q8_ROUTE_STAGED;
     if (s->max_ld <= 512) return Q8_ROUTE_RESIDENT;
     for (int t = 0; t < s->njobs; ++t) rows += s->rows[t];
     results = rows * s->n;

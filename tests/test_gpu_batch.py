@@ -163,6 +163,27 @@ def _translate_all(q, ctx, m_gpu, m_ref, sents, beam, k, max_steps):
     return finished
 
 
+@pytest.mark.parametrize("H,A,lens,beam,tiled", [(1024, 1024, (9,), 1, True), (1024, 1024, (5, 3), 4, True), (1024, 1024, (5, 3), 3, False),
+                                                 (768, 640, (4, 7, 2), 2, True), (768, 640, (4, 7), 4, False), (1000, 1000, (6, 2), 2, False)])
+def test_batched_step_of_up_to_eight_slots(q, H, A, lens, beam, tiled):
+    """Its products of rows of 513-1024 bytes run in the panel kernels: the states and contexts that cgru_decoder_step_q8 gives for
+    each sentence, bit for bit."""
+    E, rng = 512, np.random.default_rng(H + beam)
+    p = synth.cgru_step(seed=beam, E=E, H=H, A=A, l=1, n_beam=1)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=16, max_rows=3 * H, max_ld=2048))
+    gru = lambda pre: q.GruWeights(gpu_mat(q, ctx, p[pre + ".Wx"], tiled), gpu_mat(q, ctx, p[pre + ".Wh"], tiled), ctx.f32(p[pre + ".bx"]), ctx.f32(p[pre + ".bh"]))
+    w = q.CgruWeights(gru("dec_r"), gpu_mat(q, ctx, p["att.U"], tiled), ctx.f32(p["att.v"]), gru("dec_q"))
+    off, n = np.concatenate([[0], np.cumsum(lens)]), len(lens) * beam
+    f = lambda *s: ctx.f32(rng.standard_normal(s).astype(np.float32))
+    P, enc, y, s = f(int(off[-1]), A), f(int(off[-1]), 2 * H), f(n, E), torch.tanh(f(n, H))
+    r = q.cgru_decoder_step_batch_q8(ctx, w, P, enc, torch.as_tensor(off.astype(np.int32)).cuda(), beam, max(lens), y, s)
+    for i in range(len(lens)):
+        rows, sl = slice(int(off[i]), int(off[i + 1])), slice(i * beam, (i + 1) * beam)
+        one = q.cgru_decoder_step_q8(ctx, w, P[rows].contiguous(), enc[rows].contiguous(), y[sl].contiguous(), s[sl].contiguous())
+        assert_same(r["s"][sl], np_(one["s"]), "s of sentence %d" % i)
+        assert_same(r["ctx"][sl], np_(one["ctx"]), "context of sentence %d" % i)
+
+
 @pytest.mark.parametrize("V,E,H,A,R,beam,k,S", [(13, 16, 24, 20, 12, 5, 6, 4), (50, 32, 48, 40, 24, 3, 5, 7),
                                                 (200, 64, 64, 32, 48, 5, 12, 3), (40, 36, 40, 28, 20, 8, 12, 2),
                                                 (13, 16, 24, 20, 12, 1, 4, 11)])

@@ -157,5 +157,7 @@ def test_panel_products_take_the_kernels_that_their_tests_name(lib):
             assert ROUTES[lib.q8x_panel_route(rows, ld, n, 0, rows)] == "resident 1024"
             assert ROUTES[lib.q8x_panel_route(rows, ld, n, 1, rows)] == ROUTES[lib.q8x_panel_route(rows, ld - 16, n, 0, rows)] == "once 128 x 32"
         assert ROUTES[lib.q8x_panel_route(20000, ld, 9, 0, 20000)] == "once 128 x 32"
-    for n in (1, 8):                                                   # (other kernels' work, or the staged kernel's with taps)
-        assert ROUTES[lib.q8x_panel_route(3072, 1024, n, 1, 3072)] == "staged"
+    for n in (1, 8):                                                   # the batched step of few slots has such products
+        assert ROUTES[lib.q8x_panel_route(3072, 1024, n, 1, 3072)] == ROUTES[lib.q8x_panel_route(3072, 1008, n, 0, 3072)] == "once 128 x 32"
+        assert ROUTES[lib.q8x_panel_route(3072, 1024, n, 0, 3072)] == "resident 1024"
+        assert ROUTES[lib.q8x_panel_route(3072, 512, n, 1, 3072)] == ROUTES[lib.q8x_panel_route(3072, 2048, n, 1, 3072)] == "staged"
