@@ -1018,7 +1018,15 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
     float *hsf = cv.take<float>(n_sent), *hsb = cv.take<float>(n_sent);
     float *ghf = cv.take<float>((size_t)n_sent * 3 * H), *ghb = cv.take<float>((size_t)n_sent * 3 * H);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_encode_batch: workspace too small");
-    // input products of every position of every sentence, both directions per launch
+    // all positions of all sentences in one launch, which multiplies X as well (in the room of the products and of the last form's arrays) ...
+    const size_t words = ctx->enc_one_launch ? q8i_enc_group_words(fwd, bwd, n_sent, max_l) : 0;
+    if (words && q8i_enc_group_takes_x(fwd, n_sent)) {
+        Carver own(ctx);
+        unsigned *w = own.take<unsigned>(words);
+        q8i_enc_input in = {nullptr, nullptr, X, total_l, own.take<int8_t>((size_t)total_l * fwd->Wx.ld), own.take<float>(total_l)};
+        if (own.ok) return q8i_enc_group(ctx, fwd, bwd, sent_off, n_sent, enc_h, &in, w);
+    }
+    // ... else input products of every position of every sentence, both directions per launch
     for (int o = 0; o < total_l; o += kMaxMfmaN) {
         const int cnt = total_l - o < kMaxMfmaN ? total_l - o : kMaxMfmaN;
         const q8i_quant_job qj = {X + (size_t)o * E, E, E, fwd->Wx.ld, xq, xs, nullptr};
@@ -1027,13 +1035,14 @@ q8_status q8_encode_batch(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_w
                                     {&bwd->Wx, xq, xs, bwd->bx, gxb + (size_t)o * 3 * H, 3 * H, nullptr, nullptr, nullptr, 0}};
         TRY(q8i_gemm_jobs(ctx, gj, 2, cnt));
     }
-    // the recurrences: all positions of all sentences in one launch ...
+    // the recurrences: in one launch ...
     // (this and the next form in the room of the last one's codes, scales and pre-activations, which is more)
-    const size_t words = ctx->enc_one_launch ? q8i_enc_group_words(fwd, bwd, n_sent, max_l) : 0;
     if (words) {
-        cv.off = mark;
-        unsigned *w = cv.take<unsigned>(words);
-        if (w) return q8i_enc_group(ctx, fwd, bwd, sent_off, n_sent, enc_h, gxf, gxb, w);
+        Carver own = cv;
+        own.off = mark;
+        unsigned *w = own.take<unsigned>(words);
+        const q8i_enc_input in = {gxf, gxb, nullptr, 0, nullptr, nullptr};
+        if (w) return q8i_enc_group(ctx, fwd, bwd, sent_off, n_sent, enc_h, &in, w);
     }
     // ... or a launch per time step, whose blocks wait for nobody ...
     if (q8i_enc_cell_ok(fwd, bwd, n_sent)) {

@@ -3,32 +3,46 @@
 #include "q8_internal.h"
 #include "q8_index.h"
 #include <mutex>
+#include <type_traits>
 
 // Block `member` of a set owns hidden units 32 member .. + 31 of one direction, for the set's sentences ("slots"), in
 // groups of up to 16, one group after the other at every time step.  A time step of a group:
-//   wave w polls the states that the members of the set published for slot w at the step before (one wave, so that the
+//   a wave polls the states that the members of the set published for a slot at the step before (one wave, so that the
 //   slot's maximum needs no other wave), quantizes them and leaves the codes in LDS;
 //   wave (rt, kp), rt = 2 gate + unit tile, of the first twelve multiplies its 16 weight rows by one half of the k range
 //   (at most 512 bytes), the sums cross to the (slot, unit) threads through LDS;
-//   eight waves apply the gates, store the new states and publish them.
-// With several groups, the next group's words are requested before this one's products.  Arithmetic of
-// enc_quantize_kernel, the panel product and enc_gates_kernel, value for value.
+//   the first eight waves apply the gates, store the new states and publish them.
+// Arithmetic of quantize_rows_kernel, the panel products and enc_gates_kernel, value for value.
 //
-// What orders the accesses to LDS: two barriers per group, behind the codes and behind the products.  Codes are written in front of
-// the first and read between the two, sums written between the two and read behind the second, states belong to one thread.
-// Scales are written in front of the first barrier and read behind the second, where the waves without gates are on the next
-// group's scales already; so two sets of them take turns (q8_enc_scale), and the next write to a set lies behind a
-// barrier that every reader has passed.  (With one group the words polled are this block's own as well, whose gates come
-// first; with several they are another group's, and nothing but the sets' turn orders the two.)
+// ONE: one group per set (up to 64 sentences of 1024 units).  Every wave has one slot, those without gates the first eight, and
+// with XS > 0 the twelve also multiply the rows of X, whose codes and scales the launch in front made, by the block's rows of
+// Wx, which lie in LDS (XS k steps of 64 bytes per half): a step's products of X are made while the words of the step before
+// travel.  Else (rows of more than 640 bytes) they come from a product launch.  64 sentences of E = 512: 217 us with the
+// products given, 182 so (product launches and their 55 MB of results: 41 us).
+// Several groups: eight waves take two slots each, eight apply the gates, and the next group's words are requested before this
+// one's products; bound by instructions and LDS traffic, so the products of X stay outside (200 sentences: 614 us, 717 with
+// them inside).
 //
-// Exchange.  A word is the float itself, or ENCG_ABSENT (a NaN pattern that is never published) while it is not there.
-// Three buffers take turns.  A block that has read the words of step t - 1 knows that every member has read those of
-// step t - 2 (it published t - 1 after that), so it puts its own words of that buffer back to ENCG_ABSENT, for step
-// t + 1 to be published there, and waits for those stores before it publishes step t: whoever polls for step t + 1 has
-// seen step t, and so no word of step t - 2.  Only the first buffer has to be clear on entry.  All of it with
-// agent-scope loads and stores, so it does not matter where the blocks run; but the members of a set are block numbers
-// that agree modulo 8, which are dealt to one XCD, and 1024 words exchanged by 32 blocks within an XCD arrive in 0.73 us
-// where 32 blocks all over the device take 1.0 and 128 blocks 1.3.
+// What orders the accesses to LDS: two barriers per iteration (a group's time step), behind the codes and behind the products.
+// Codes are written in front of the first and read between the two, sums written between the two and read behind the second,
+// states belong to one thread.  Scales are written in front of the first barrier and read behind the second, where other
+// waves are on the next iteration's scales already; so two sets of them take turns (q8_enc_scale).  Rows of X go to LDS at the
+// start of an iteration (two turns), are multiplied behind the second barrier of it (sums in two turns) and count in the next
+// one, their scales in four turns (q8_enc_x_scale).  A host test walks these accesses.
+//
+// Exchange with one group.  The members of a set are block numbers that agree modulo 8, which are dealt to one XCD.  Each says
+// where it runs; if all are on one XCD, words are stored plainly and loaded past the compute unit's own cache (nt), so both
+// ends meet in the XCD's L2: 64 KB per block and step arrive in 0.5 us whenever they are asked for, where agent-scope loads
+// (which everybody uses if the members are spread) take 1.1 to 2.4 us, the longer the earlier they ask (16 MB per step
+// beyond the L2).  A word is the float with the turn of its buffer, two buffers used twice each, in the bit that no state
+// needs (states lie in [-1, 1], whatever X holds: tanh and sigmoid of a NaN are numbers here): whoever polls a word takes none
+// of an earlier turn, whatever a cache may still hold, since a location never goes back to an earlier value.  A buffer is free for step t when
+// this block has read step t - 1: every member had then read step t - 2.  64 sentences, the same kernel with agent-scope
+// loads and stores: 305 us; plain stores and nt loads: 182.
+// With several groups the words' way is hidden, and agent scope is no slower: a word is the float itself, or ENCG_ABSENT (a NaN
+// pattern that is never published) while it is not there, three buffers take turns, and a block that has read the words of step
+// t - 1 puts its own of step t - 2 back to ENCG_ABSENT, for step t + 1 to be published there, and waits for those stores before
+// it publishes step t: whoever polls for step t + 1 has seen step t, and so no word of step t - 2.
 //
 // Nobody has to be resident for the result to be right.  A wait is bounded; a member that gives up says so in the set's
 // flag, at which the others leave as well, and the last member to leave works the whole set off by itself, from the
@@ -39,23 +53,26 @@
 // streams with a batch of 64 sentences each, us per batch: 2110 without turns (an encoder that ends makes room for part of
 // the next two, which wait for each other's room until both give up), 215 with them (a launch per position, before: 358).
 //
-// The chain of a step bounds it (1024 units, 16 slots, in us: words there 1.1, codes 0.35, products 0.45, gates 0.6), with
-// several groups the instructions of the codes and the gates (2.0 us per group).  A launch per position, whose blocks read
-// weights and states again, took 5.6 us at 64 sentences.  q8_encode_batch, sentences of 10 to 60 words, E = 512, us,
-// launches per position -> this kernel: H = 1024, 2 / 16 / 64 / 128 / 200 / 400 sentences 244 / 354 / 411 / 595 / 880 / 1817 ->
-// 127 / 171 / 241 / 393 / 681 / 1309; H = 512, 64 / 200: 390 / 580 -> 197 / 378; H = 256: 380 / 410 -> 184 / 250.
+// The chain of a step bounds it (1024 units, 16 slots, in us behind the second barrier: states published 0.6, words there 1.5,
+// codes 1.9, products 2.5, that is the next barrier), with several groups the instructions of the codes and the gates
+// (2.6 us per group).  q8_encode_batch, sentences of 10 to 60 words, E = 512, H = 1024, us: 4 / 16 / 32 / 64 / 200 sentences
+// 134 / 168 / 192 / 237 / 676 with agent-scope words, four groups' order of waves for all, and the products of X outside;
+// 118 / 141 / 159 / 182 / 614 so.  A launch per position: 411 at 64, 880 at 200.
 // Not kept: waves of one unit tile and a quarter of the k range that multiply all three gates (a third of the LDS reads,
 // more sums to add up: 1 us faster in nothing, 5 slower where a poll comes early); all floats of a step exchanged as
-// (float, tag) pairs (twice the bytes).  The pause before the first poll: too early costs another 64 KB per block and slows
-// the stores that are waited for (64 sentences, 4 / 8 / 12 / 16 times 64 clocks: 263 / 242 / 240 / 242 us; 16: 196 / 173 / 173 / 180).
+// (float, tag) pairs (twice the bytes); two slots per wave on half of the waves with one group (208 us: a slot's codes are a chain).
 #define ENCG_UNITS Q8_ENC_UNITS
 #define ENCG_SLOTS Q8_ENC_SLOTS
 #define ENCG_THREADS 1024
 #define ENCG_PITCH Q8_ENC_PITCH
 #define ENCG_TILE Q8_ENC_TILE
 #define ENCG_ABSENT 0xffffffffu
-#define ENCG_SPINS 4096                // polls of a wait at most (some 5 ms): what follows is slow, not wrong
-#define ENCG_AGENT_LOAD 0x10            // cache policy of a device-coherent load or store (sc1)
+#define ENCG_X_LD 640
+#define ENCG_SPINS 4096                // polls of a wait at most (some 5 ms; four times as many within an XCD): what follows is slow, not wrong
+#define ENCG_AGENT 0x10                 // cache policy of a device-coherent load or store (sc1)
+#define ENCG_XCD 2                      // ... of a load that is not served from the compute unit's own cache but from its XCD's (nt)
+#define ENCG_TURN_BIT 0x40000000u
+#define ENCG_XCC_ID (20 | 3 << 11)      // hardware register XCC_ID, bits 3:0
 
 // The turn on a device (a module's variable, so one per device and process): how many of the last eight blocks (one per XCD;
 // blocks of lower index start earlier) of the encoder whose turn it is have started.  Whoever takes an eight from it has the
@@ -66,9 +83,31 @@
 #define ENCG_TURN 4000000ull
 __device__ unsigned enc_group_turn = 8;
 
-// Clears [words, words + n) and waits for the turn.
-__global__ __launch_bounds__(256) void enc_group_clear_kernel(unsigned *words, int n)
+// Waits for the turn (block 0), clears [words, words + n) (the next `clear` blocks) and quantizes the L rows of X (E floats, at
+// most ENCG_X_LD; the blocks after those, a wave per row), codes at pitch ld.
+__global__ __launch_bounds__(256) void enc_group_front_kernel(unsigned *words, int n, int clear, const float *X, int E, int L, int ld, int8_t *xq, float *xs)
 {
+    if ((int)blockIdx.x > clear) {
+        const int row = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - 1 - clear) * 4 + (int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+        if (row >= L) return;
+        const __amdgpu_buffer_rsrc_t rx = q8_rsrc(X + (size_t)row * E, (size_t)E * sizeof(float));
+        constexpr int C = (ENCG_X_LD + 255) / 256;
+        float4 v[C];
+        float m = 0.0f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rx, (c * 64 + lane) * 16, 0, 0));
+#pragma unroll
+        for (int c = 0; c < C; ++c) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[c].x), fabsf(v[c].y)), fmaxf(fabsf(v[c].z), fabsf(v[c].w))));
+        float scale, inv;
+        q8_scale_of(wave_max_f(m), scale, inv);
+        if (lane == 0) xs[row] = scale;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int k = (c * 64 + lane) * 4;                         // (zeros past E)
+            if (k < ld) *(int *)(xq + (size_t)row * ld + k) = q8_pack4(v[c].x, v[c].y, v[c].z, v[c].w, inv);
+        }
+        return;
+    }
     if (blockIdx.x > 0) {
         const int e = ((int)blockIdx.x - 1) * 256 + (int)threadIdx.x;
         if (e < n) words[e] = ENCG_ABSENT;
@@ -90,20 +129,29 @@ __global__ __launch_bounds__(256) void enc_group_clear_kernel(unsigned *words, i
 
 struct EncGroupArgs {
     const int8_t *Wh[2], *Wht[2];        // [3H x ld], the same tile-packed or NULL
-    const float *bh[2], *gx[2];          // [3H] or NULL; [L x 3H]
+    const float *bh[2], *gx[2];          // [3H] or NULL; XS == 0: [L x 3H]
+    const int8_t *Wx[2], *Wxt[2];        // XS > 0: [3H x ldx], the same tile-packed or NULL
+    const float *bx[2];                  // [3H] or NULL
+    const int8_t *xq;                    // codes [L x ldx] and scales [L] of X
+    const float *xs;
     const int *sent_off;                 // [S + 1]
     float *enc_h;                        // [L x 2H]
-    unsigned *words;                     // [3][2][S][H], the first third ENCG_ABSENT on entry
-    unsigned *ctl;                       // [sets][2]: members that left, a wait that gave up; ENCG_ABSENT on entry
-    int S, H, ld, members, sets_per_dir, spin_limit, pause;
+    unsigned *words;                     // [2 turns, 3 with several groups][2 directions][S][H], the first two ENCG_ABSENT on entry
+    unsigned *ctl;                       // [sets][2]: members that left, a wait that gave up; [sets][32]: the XCD of each member; ENCG_ABSENT on entry
+    int S, H, ld, members, sets_per_dir, spin_limit;
     float wh_scale[2];
+    int ldx;
+    float wx_scale[2];
 };
 
+template <int XS, bool ONE>
 __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 {
-    extern __shared__ __align__(16) int8_t s_codes[];                  // [16][ENCG_PITCH], sums, states, offsets, lengths
-    __shared__ float s_scale[2 * ENCG_SLOTS];
-    __shared__ int s_flag, s_max;
+    static_assert(XS == 0 || ONE, "rows of X are multiplied for one group at a time");
+    extern __shared__ __align__(16) int8_t s_codes[];                  // [16][ENCG_PITCH], sums, states, offsets, lengths; what XS adds
+    __shared__ float s_scale[2 * ENCG_SLOTS], s_xs[4 * ENCG_SLOTS];
+    __shared__ float s_bias[6][ENCG_UNITS];
+    __shared__ int s_flag, s_max, s_far;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, gq = lane >> 4;
     const int H = a.H, S = a.S, ld = a.ld, members = a.members;
@@ -112,11 +160,21 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
     if (set >= 2 * a.sets_per_dir) return;
     // the set's slots, in groups of gs
     const int d = set & 1, c0 = S * (set >> 1) / a.sets_per_dir, ns = S * ((set >> 1) + 1) / a.sets_per_dir - c0;
-    const int ng = (ns + ENCG_SLOTS - 1) / ENCG_SLOTS, gs = (ns + ng - 1) / ng;
+    const int ng = ONE ? 1 : (ns + ENCG_SLOTS - 1) / ENCG_SLOTS, gs = ONE ? ns : (ns + ng - 1) / ng;
     int *s_e = (int *)(s_codes + ENCG_SLOTS * ENCG_PITCH);
     float *s_h = (float *)(s_e + 12 * ENCG_TILE);                      // [ng][16][32] this block's states
     int *s_off = (int *)(s_h + ng * ENCG_SLOTS * ENCG_UNITS), *s_len = s_off + ng * ENCG_SLOTS;      // [ng][16]
-    if (tid == 0) { s_flag = 0; s_max = 0; }
+    constexpr int XP = Q8_ENC_X_PITCH(XS);
+    int8_t *s_xc = (int8_t *)(s_len + ng * ENCG_SLOTS);                // [2][16][XP]
+    int *s_ex = (int *)(s_xc + 2 * ENCG_SLOTS * XP);                   // [2][12 tiles]
+    int8_t *s_wx = (int8_t *)(s_ex + 2 * 12 * ENCG_TILE);              // [12 waves][XS][64 lanes] 16 bytes of the rows of Wx
+    const int *where = (const int *)(a.ctl + 2 * 2 * a.sets_per_dir + 32 * set);              // the XCD of every member, once it has started
+    const int xcd = (int)__builtin_amdgcn_s_getreg(ENCG_XCC_ID);
+    if (tid == 0) {
+        s_flag = 0;
+        s_max = 0;
+        __hip_atomic_store((int *)where + member, xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     for (int e = tid; e < ng * ENCG_SLOTS; e += ENCG_THREADS) {
         const int in = e & (ENCG_SLOTS - 1), slot = (e >> 4) * gs + in;
@@ -130,162 +188,350 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 
     // ---- the parts of a time step ----
     const int rt = wave % 6, kp = wave / 6, gate = rt >> 1, ut = rt & 1;                  // (waves 12 to 15 multiply nothing)
-    v4i av[8];
-    auto weights = [&](int u0) {
-        const int unit0 = u0 + 16 * ut;
-        const bool tiled = a.Wht[d] != nullptr && H % 16 == 0, in = wave < 12;            // (a tile of 16 rows then belongs to one gate)
-        const __amdgpu_buffer_rsrc_t rw = q8_rsrc(tiled ? a.Wht[d] : a.Wh[d], (size_t)(tiled ? (3 * H + 15) / 16 * 16 : 3 * H) * ld);
+    // N k steps of 64 bytes, from step k0 on, of the wave's 16 rows
+    auto rows = [&](const int8_t *W, const int8_t *Wt, int pitch, int unit0, int k0, auto &out) {
+        const bool tiled = Wt != nullptr && H % 16 == 0, in = wave < 12;                  // (a tile of 16 rows then belongs to one gate)
+        const __amdgpu_buffer_rsrc_t rw = q8_rsrc(tiled ? Wt : W, (size_t)(tiled ? (3 * H + 15) / 16 * 16 : 3 * H) * pitch);
         const unsigned row0 = (unsigned)(gate * H + unit0), step = tiled ? 1024u : 64u;
-        const unsigned base = tiled ? ((row0 >> 4) * (unsigned)(ld >> 6) << 10) + 16u * lane : (row0 + i) * (unsigned)ld + 16u * gq;
+        const unsigned base = tiled ? ((row0 >> 4) * (unsigned)(pitch >> 6) << 10) + 16u * lane : (row0 + i) * (unsigned)pitch + 16u * gq;
         const bool ok = in && (tiled ? unit0 : unit0 + i) < H;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int k = kp * 8 + s;
-            const unsigned off = ok && 64 * k + (tiled ? 0 : 16 * gq) < ld ? base + step * k : Q8_OOB;
-            av[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
+        for (int s = 0; s < (int)(sizeof(out) / sizeof(out[0])); ++s) {
+            const int k = k0 + s;
+            const unsigned off = ok && 64 * k + (tiled ? 0 : 16 * gq) < pitch ? base + step * k : Q8_OOB;
+            out[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
         }
     };
-    // one wave, iteration it (groups of time steps, counted): the codes and the scale of its slot's state, floats 4 (lane + 64 c) .. (zero past H)
-    auto codes = [&](const float4 (&v)[4], int it) {
-        float m = 0.0f;
+    v4i av[8];
+    auto weights = [&](int u0) {
+        rows(a.Wh[d], a.Wht[d], ld, u0 + 16 * ut, kp * 8, av);
+        if constexpr (XS > 0) {
+            v4i xv[XS];
+            rows(a.Wx[d], a.Wxt[d], a.ldx, u0 + 16 * ut, kp * XS, xv);
+            if (wave < 12) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v[c].x), "v"(v[c].y));
-            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v[c].z), "v"(v[c].w));
+                for (int s = 0; s < XS; ++s) *(v4i *)(s_wx + ((wave * XS + s) * 64 + lane) * 16) = xv[s];
+            }
         }
-        m = wave_max_f(m);
-        float scale, inv;
-        q8_scale_of(m, scale, inv);
-        if (lane == 0) s_scale[q8_enc_scale(it, wave)] = scale;
+    };
+    // of the 32 units from u0 on, by the block's first 32 threads (in front of a barrier); absent ones are the zero that
+    // changes no sum
+    auto biases = [&](int u0) {
+        if (tid < ENCG_UNITS) {
+            const int unit = u0 + tid;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) *(int *)(s_codes + wave * ENCG_PITCH + 4 * (lane + 64 * c)) = q8_pack4(v[c].x, v[c].y, v[c].z, v[c].w, inv);
+            for (int gt = 0; gt < 3; ++gt) {
+                s_bias[gt][tid] = a.bh[d] && unit < H ? a.bh[d][gt * H + unit] : -0.0f;
+                s_bias[3 + gt][tid] = XS > 0 && a.bx[d] && unit < H ? a.bx[d][gt * H + unit] : -0.0f;
+            }
+        }
+    };
+    // one wave, iteration it (groups of time steps, counted): the codes and the scales of N slots' states, floats 4 (lane + 64 c) ..
+    auto codes = [&](auto &w, int slot, int it) {
+        constexpr int N = sizeof(w) / sizeof(w[0]);
+        float m[N], scale[N], inv[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            m[q] = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m[q]) : "v"(w[q][c].x), "v"(w[q][c].y));
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m[q]) : "v"(w[q][c].z), "v"(w[q][c].w));
+            }
+            m[q] = wave_max_f(m[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            q8_scale_of(m[q], scale[q], inv[q]);
+            if (lane == 0) s_scale[q8_enc_scale(it, slot + q)] = scale[q];
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float4 v = __builtin_bit_cast(float4, w[q][c]);
+                *(int *)(s_codes + (slot + q) * ENCG_PITCH + 4 * (lane + 64 * c)) = q8_pack4(v.x, v.y, v.z, v.w, inv[q]);
+            }
     };
     // (k steps past the rows have zero weights: whatever the codes are there, they add nothing, and no branch makes the wave
     // wait for every operand by itself)
     auto products = [&]() {
         if (wave < 12) {
-            v4i acc[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}};
+            v4i acc[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}}, bv[8];
             const int8_t *bp = s_codes + i * ENCG_PITCH + kp * 512 + 16 * gq;
 #pragma unroll
-            for (int s = 0; s < 8; ++s) acc[s & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[s], *(const v4i *)(bp + 64 * s), acc[s & 1], 0, 0, 0);
+            for (int s = 0; s < 8; ++s) bv[s] = *(const v4i *)(bp + 64 * s);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) acc[s & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[s], bv[s], acc[s & 1], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);         // every operand is requested before the first is waited for
+            __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
             // lane (i, gq) holds units 4 gq + r, r = 0..3, of slot i
             *(v4i *)(s_e + wave * ENCG_TILE + i * 16 + 4 * gq) = acc[0] + acc[1];
         }
     };
+    // the same rows of Wx times the codes of iteration it's rows of X
+    auto xproducts = [&](int it) {
+        if (XS > 0 && wave < 12) {
+            v4i acc[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}};
+            const int8_t *bp = s_xc + ((it & 1) * ENCG_SLOTS + i) * XP + kp * XS * 64 + 16 * gq, *ap = s_wx + (wave * XS * 64 + lane) * 16;
+#pragma unroll
+            for (int s = 0; s < XS; ++s)
+                acc[s & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(*(const v4i *)(ap + 1024 * s), *(const v4i *)(bp + 64 * s), acc[s & 1], 0, 0, 0);
+            *(v4i *)(s_ex + ((it & 1) * 12 + wave) * ENCG_TILE + i * 16 + 4 * gq) = acc[0] + acc[1];
+        }
+    };
+    // a wave's row of X: 16 bytes of codes per lane (lanes past it the last ones again), and the scale
+    v4i xr;
+    float xsr;
+    auto xrequest = [&](int pos) {
+        xr = *(const v4i *)(a.xq + (size_t)pos * a.ldx + min(16 * lane, a.ldx - 16));
+        xsr = a.xs[pos];
+    };
+    auto xleave = [&](int slot, int it) {
+        if (16 * lane < 128 * XS) *(v4i *)(s_xc + ((it & 1) * ENCG_SLOTS + slot) * XP + 16 * lane) = xr;
+        if (lane == 0) s_xs[q8_enc_x_scale(it, slot)] = xsr;
+    };
     const int sl = tid >> 5, u = tid & 31;                             // this thread's (slot, unit) pair, below 16 x 32
-    auto gates = [&](const float (&gx)[3], const float (&bias)[3], float h_prev, int it) {
-        const float ch = a.wh_scale[d] * s_scale[q8_enc_scale(it, sl)];
-        float gh[3];
+    float wh_scale = a.wh_scale[d], wx_scale = a.wx_scale[d];
+    asm volatile("" : "+v"(wh_scale), "+v"(wx_scale));                 // (kept, not read again at every step)
+    // (XS == 0: gx_in the input pre-activations)
+    auto gates = [&](const float (&gx_in)[3], float h_prev, int it) {
+        int eh[6], ex[6];
+        float b[6], gh[3], gx[3];
 #pragma unroll
         for (int gt = 0; gt < 3; ++gt) {
             const int at = (gt * 2 + (u >> 4)) * ENCG_TILE + sl * 16 + (u & 15);
-            float y = (float)(s_e[at] + s_e[at + 6 * ENCG_TILE]) * ch;
-            if (a.bh[d]) y = y + bias[gt];
-            gh[gt] = y;
+            eh[gt] = s_e[at];
+            eh[3 + gt] = s_e[at + 6 * ENCG_TILE];
+            b[gt] = s_bias[gt][u];
+            if (XS > 0) {
+                ex[gt] = s_ex[(it & 1) * 12 * ENCG_TILE + at];
+                ex[3 + gt] = s_ex[((it & 1) * 12 + 6) * ENCG_TILE + at];
+                b[3 + gt] = s_bias[3 + gt][u];
+            }
+        }
+        const float ch = wh_scale * s_scale[q8_enc_scale(it, sl)], cx = XS > 0 ? wx_scale * s_xs[q8_enc_x_scale(it, sl)] : 0.0f;
+#pragma unroll
+        for (int gt = 0; gt < 3; ++gt) {
+            const float y = (float)(eh[gt] + eh[3 + gt]) * ch;
+            gh[gt] = y + b[gt];
+            if (XS > 0) {
+                const float x = (float)(ex[gt] + ex[3 + gt]) * cx;
+                gx[gt] = x + b[3 + gt];
+            } else {
+                gx[gt] = gx_in[gt];
+            }
         }
         return gru_gates(gx, gh, h_prev);
     };
-    auto biases = [&](int unit, float (&bias)[3]) {
+    auto input = [&](int pos, int unit, float (&gx)[3]) {
+        const float *gp = a.gx[d] + (size_t)pos * 3 * H + unit;
 #pragma unroll
-        for (int gt = 0; gt < 3; ++gt) bias[gt] = a.bh[d] && unit < H ? a.bh[d][gt * H + unit] : 0.0f;
+        for (int gt = 0; gt < 3; ++gt) gx[gt] = gp[gt * H];
     };
     // row of enc_h (and of gx) of step t of a slot of length l that begins at o, and the row before it
     auto row = [&](int o, int l, int t) { return d == 0 ? o + t : o + l - 1 - t; };
     const int back = d == 0 ? -1 : 1, col0 = d == 0 ? H : 0;
 
     // ---- all positions ----
-    {
-        const int unit = member * ENCG_UNITS + u;
-        const bool pair = sl < ENCG_SLOTS && unit < H;
-        float bias[3];
+    biases(member * ENCG_UNITS);
+    const int unit = member * ENCG_UNITS + u;
+    const bool pair = unit < H;                                        // (of the first eight waves: a (slot, unit) pair per thread)
+    // words of this direction: byte offset of a buffer; all below 2^31
+    const unsigned size = (unsigned)S * (unsigned)H * 8u, dir = d * (size >> 1);
+    const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.words, (size_t)(ONE ? 2 : 3) * size);
+    const unsigned mine = (unsigned)((c0 + sl) * H + unit) * 4u;
+    // a wait for words that are not there ends: this member leaves, or another has
+    auto give_up = [&](int spins, int limit) {
+        if (spins < limit &&
+            ((spins & 63) != 0 || __hip_atomic_load(a.ctl + 2 * set + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ENCG_ABSENT)) return false;
+        if (lane == 0) {
+            s_flag = 1;
+            __hip_atomic_store(a.ctl + 2 * set + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return true;
+    };
+    if constexpr (ONE) {
+        // ---- one group: a wave per slot, the waves without gates first ----
         weights(member * ENCG_UNITS);
-        biases(unit, bias);
+        if (wave == 15) {
+            // whether every member runs on this XCD
+            int far = 1;
+            for (int spins = 1;; ++spins) {
+                const int x = lane < members ? __hip_atomic_load(where + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcd;
+                if (!__any(x == (int)ENCG_ABSENT)) {
+                    far = __any(x != xcd);
+                    break;
+                }
+                if (give_up(spins, a.spin_limit)) break;
+            }
+            if (lane == 0) s_far = far;
+        }
+        __syncthreads();
+        const bool far = s_far != 0;
+        const int slot = wave ^ 8, max_l = s_max;
+        const int wl = __builtin_amdgcn_readfirstlane(s_len[slot]), wo = __builtin_amdgcn_readfirstlane(s_off[slot]);
+        const int tl = s_len[min(sl, ENCG_SLOTS - 1)], to = s_off[min(sl, ENCG_SLOTS - 1)];
+        auto buffer = [&](int t) { return (unsigned)(t & 1) * size + dir; };
+        auto turn = [&](int t) { return (unsigned)(t & 2) << 29; };    // the bit of a turn's words
+        auto xpos = [&](int t) { return t < wl ? row(wo, wl, t) : 0; };
+        // rows of X: requested behind a step's words, whose wait theirs would prolong, left in LDS at the start of the next
+        // step and multiplied at the end of that, for the one after
+        if (XS > 0) {
+            xrequest(xpos(0));
+            xleave(slot, 0);
+            xrequest(xpos(1));
+            __syncthreads();
+            xproducts(0);
+        }
+        float h_prev = 0.0f, gx[3] = {0.f, 0.f, 0.f};
+        auto ahead = [&](int t) { input(pair && t < tl ? row(to, tl, t) : 0, pair ? unit : 0, gx); };     // the pre-activations of a step to come
+        if (XS == 0) ahead(0);
+        for (int t = 0; t < max_l; ++t) {
+            if (XS > 0) xleave(slot, t + 1);
+            if (t < wl) {                                              // wave-uniform
+                v4u w[1][4];
+                bool there = true;
+                auto poll = [&](auto policy) {                         // (past H: the last ones again, for weights of zero)
+                    const int from = (int)(buffer(t - 1) + (unsigned)((c0 + slot) * H) * 4u);
+                    unsigned first = 16u * lane, m = 0;
+                    asm volatile("" : "+v"(first) :: "memory");        // (every request is made)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        w[0][c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)min(first + 1024u * c, 4u * H - 16u), from, decltype(policy)::value));
+                    // what is there is the state itself once its turn's bit is off
+                    const unsigned bit = turn(t - 1);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        w[0][c] ^= bit;
+                        m |= w[0][c].x | w[0][c].y | w[0][c].z | w[0][c].w;
+                    }
+                    return !__any((m & ENCG_TURN_BIT) != 0);
+                };
+                if (t > 0) {
+                    if (far) {
+                        for (int spins = 1; !(there = poll(std::integral_constant<int, ENCG_AGENT>())) && !give_up(spins, a.spin_limit); ++spins) {}
+                    } else {
+                        for (int spins = 1; !(there = poll(std::integral_constant<int, ENCG_XCD>())) && !give_up(spins, a.spin_limit < ENCG_SPINS ? a.spin_limit : 4 * ENCG_SPINS); ++spins) {}
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) w[0][c] = (v4u){0u, 0u, 0u, 0u};
+                }
+                if (XS > 0) xrequest(xpos(t + 2));
+                if (there) codes(w, slot, t);
+            }
+            __syncthreads();
+            const int flag = s_flag;
+            const float gx_now[3] = {gx[0], gx[1], gx[2]};
+            if (XS == 0) ahead(t + 1);
+            products();
+            __syncthreads();
+            if (flag) break;
+            if (wave < 8) {
+                __builtin_amdgcn_s_setprio(2);                         // everybody waits for them
+                const float hn = gates(gx_now, h_prev, t);
+                if (pair && t < tl) {
+                    const unsigned word = __float_as_uint(hn) ^ turn(t);
+                    const int at = (int)(mine + buffer(t));
+                    if (t + 1 < tl) {
+                        if (far) __builtin_amdgcn_raw_buffer_store_b32(word, rx, at, 0, ENCG_AGENT);
+                        else __builtin_amdgcn_raw_buffer_store_b32(word, rx, at, 0, 0);
+                    }
+                    a.enc_h[(size_t)row(to, tl, t) * 2 * H + col0 + unit] = hn;
+                    h_prev = hn;
+                }
+                __builtin_amdgcn_s_setprio(0);
+            }
+            xproducts(t + 1);
+        }
+    } else {
+        // ---- several groups, one after the other at every step: the gates on the first eight waves, the codes, of two slots
+        // each, on the others ----
+        weights(member * ENCG_UNITS);
         __syncthreads();
         const int max_l = s_max;
-        // words of this direction: byte offsets of the buffers of steps t - 1, t, t + 1, which take turns; all below 2^31
-        const unsigned third = (unsigned)S * (unsigned)H * 8u;
-        const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.words, (size_t)3 * third);
-        unsigned was = 2 * third + d * (third >> 1), now = d * (third >> 1), next = third + d * (third >> 1);
-        // this wave's slot of group g: its words of a step, floats 4 (lane + 64 c) .. (past H: zero, which is there)
-        unsigned at[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) at[c] = 4 * (lane + 64 * c) < H ? (unsigned)((c0 + wave) * H + 4 * (lane + 64 * c)) * 4u : Q8_OOB;
         const unsigned group = (unsigned)(gs * H) * 4u;
-        v4u w4[4];
-        auto request = [&](unsigned buffer) {
-            asm volatile("" ::: "memory");                             // (every request is made)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) w4[c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)at[c], (int)buffer, ENCG_AGENT_LOAD));
-        };
-        const unsigned mine = (unsigned)((c0 + sl) * H + unit) * 4u;
+        auto buffer = [&](int t) { return (unsigned)(t % 3) * size + dir; };
         bool gave_up = false;
         int it = 0;
-        for (int t = 0; t < max_l && !gave_up; ++t) {
-            for (int g = 0; g < ng; ++g, ++it) {
-                const int e0 = g * ENCG_SLOTS, e = min(e0 + sl, ng * ENCG_SLOTS - 1), l = s_len[e], pos = row(s_off[e], l, t);
-                const bool on = pair && t < l;
-                const float *gp = a.gx[d] + (size_t)(on ? pos : 0) * 3 * H + (on ? unit : 0);
-                float gx[3];
-#pragma unroll
-                for (int gt = 0; gt < 3; ++gt) gx[gt] = gp[gt * H];
-                if (t < s_len[e0 + wave]) {                            // wave-uniform
-                    float4 v[4];
-                    bool there = true;
-                    if (t > 0) {
-                        if (ng == 1) {
-                            if (a.spin_limit > 1)
-                                for (int p = 0; p < a.pause; ++p) __builtin_amdgcn_s_sleep(1);
-                            request(was);
-                        }
-                        for (int spins = 1;; ++spins) {
-                            unsigned m = 0;                            // (an absent word is the largest there is)
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) m = max(max(m, max(w4[c].x, w4[c].y)), max(w4[c].z, w4[c].w));
-                            if (!__any(m == ENCG_ABSENT)) break;
-                            if (spins >= a.spin_limit ||
-                                ((spins & 63) == 0 && __hip_atomic_load(a.ctl + 2 * set + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ENCG_ABSENT)) {
-                                if (lane == 0) {
-                                    s_flag = 1;
-                                    __hip_atomic_store(a.ctl + 2 * set + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                }
-                                there = false;
-                                break;
-                            }
-                            request(was + g * group);
-                        }
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = __builtin_bit_cast(float4, w4[c]);
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
-                    if (there) codes(v, it);
-                }
-                __syncthreads();
-                if (s_flag) { gave_up = true; break; }
-                if (on && t + 2 < l) __builtin_amdgcn_raw_buffer_store_b32(ENCG_ABSENT, rx, (int)(mine + g * group), (int)next, ENCG_AGENT_LOAD);
-                if (ng > 1) {                                          // the next group's words, under this one's products and gates
-                    const bool wrap = g + 1 == ng;
-                    if (t + wrap > 0 && t + wrap < s_len[wrap ? wave : e0 + ENCG_SLOTS + wave]) request(wrap ? now : was + (g + 1) * group);
-                }
-                products();
-                __syncthreads();
-                if (tid < ENCG_SLOTS * ENCG_UNITS) {
-                    const float hn = gates(gx, bias, s_h[e0 * ENCG_UNITS + tid], it);
-                    if (on) {
+        if (wave < 8) {
+            float gx[3] = {0.f, 0.f, 0.f};
+            auto ahead = [&](int t, int g) {                           // the pre-activations of an iteration to come
+                const int e = g * ENCG_SLOTS + sl, l = s_len[e];
+                input(pair && t < l ? row(s_off[e], l, t) : 0, pair ? unit : 0, gx);
+            };
+            ahead(0, 0);
+            for (int t = 0; t < max_l && !gave_up; ++t) {
+                for (int g = 0; g < ng; ++g, ++it) {
+                    const int e = g * ENCG_SLOTS + sl, l = s_len[e], pos = row(s_off[e], l, t);
+                    const float h_prev = s_h[g * ENCG_SLOTS * ENCG_UNITS + tid];
+                    const int at = (int)(mine + g * group);
+                    __syncthreads();
+                    const int flag = s_flag;
+                    if (pair && t + 2 < l && !flag) __builtin_amdgcn_raw_buffer_store_b32(ENCG_ABSENT, rx, at, (int)buffer(t + 1), ENCG_AGENT);
+                    products();
+                    __syncthreads();
+                    if (flag) { gave_up = true; break; }
+                    __builtin_amdgcn_s_setprio(2);
+                    const float hn = gates(gx, h_prev, it);
+                    if (pair && t < l) {
                         unsigned word = __float_as_uint(hn);
                         word = word == ENCG_ABSENT ? 0x7fffffffu : word;
                         q8_stores_performed();
-                        if (t + 1 < l) __builtin_amdgcn_raw_buffer_store_b32(word, rx, (int)(mine + g * group), (int)now, ENCG_AGENT_LOAD);
+                        if (t + 1 < l) __builtin_amdgcn_raw_buffer_store_b32(word, rx, at, (int)buffer(t), ENCG_AGENT);
                         a.enc_h[(size_t)pos * 2 * H + col0 + unit] = hn;
-                        s_h[e0 * ENCG_UNITS + tid] = hn;
+                        s_h[g * ENCG_SLOTS * ENCG_UNITS + tid] = hn;
                     }
+                    __builtin_amdgcn_s_setprio(0);
+                    ahead(g + 1 == ng ? t + 1 : t, g + 1 == ng ? 0 : g + 1);
                 }
             }
-            const unsigned first = was;
-            was = now;
-            now = next;
-            next = first;
+        } else {
+            const int pair0 = 2 * (wave - 8);
+            auto len = [&](int g, int q) { return __builtin_amdgcn_readfirstlane(s_len[g * ENCG_SLOTS + pair0 + q]); };
+            // floats 4 (lane + 64 c) .. of the first (past H: zero, which is there)
+            unsigned at[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) at[c] = 4 * (lane + 64 * c) < H ? (unsigned)((c0 + pair0) * H + 4 * (lane + 64 * c)) * 4u : Q8_OOB;
+            v4u w[2][4];
+            // step t's of group g: the words of step t - 1 (none at step 0, and of a sentence that is over: zeros)
+            auto request = [&](int t, int g) {
+                asm volatile("" ::: "memory");                         // (every request is made)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const unsigned from = t > 0 && t < len(g, q) ? buffer(t - 1) + g * group + (unsigned)(q * H) * 4u : Q8_OOB;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        w[q][c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(at[c] == Q8_OOB || from == Q8_OOB ? Q8_OOB : at[c] + from), 0, ENCG_AGENT));
+                }
+            };
+            request(0, 0);
+            for (int t = 0; t < max_l && !gave_up; ++t) {
+                for (int g = 0; g < ng; ++g, ++it) {
+                    bool there = true;
+                    for (int spins = 1;; ++spins) {
+                        unsigned m = 0;                                // (an absent word is the largest there is)
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) m = max(max(m, max(w[q][c].x, w[q][c].y)), max(w[q][c].z, w[q][c].w));
+                        if (!__any(m == ENCG_ABSENT)) break;
+                        if (give_up(spins, a.spin_limit)) {
+                            there = false;
+                            break;
+                        }
+                        request(t, g);
+                    }
+                    if (there) codes(w, pair0, it);
+                    __syncthreads();
+                    const int flag = s_flag;
+                    request(g + 1 == ng ? t + 1 : t, g + 1 == ng ? 0 : g + 1);    // the next group's words, under this one's products and gates
+                    products();
+                    __syncthreads();
+                    if (flag) { gave_up = true; break; }
+                }
+            }
         }
     }
 
@@ -300,29 +546,30 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
     if (!s_flag) return;
     for (int g = 0; g < ng; ++g)
         for (int t = 0; t < s_max; ++t) {
-            const int e0 = g * ENCG_SLOTS, lw = s_len[e0 + wave];
-            if (t < lw) {
-                const float *h = a.enc_h + (size_t)(row(s_off[e0 + wave], lw, t) + back) * 2 * H + col0;
-                float4 v[4];
+            const int e0 = g * ENCG_SLOTS, lw = s_len[e0 + wave], pos0 = t < lw ? row(s_off[e0 + wave], lw, t) : 0;
+            v4u v[1][4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int k = 4 * (lane + 64 * c);
-                    v[c] = t > 0 && k < H ? *(const float4 *)(h + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-                codes(v, 0);
+            for (int c = 0; c < 4; ++c) {
+                const int k = 4 * (lane + 64 * c);
+                v[0][c] = t > 0 && t < lw && k < H ? *(const v4u *)(a.enc_h + (size_t)(pos0 + back) * 2 * H + col0 + k) : (v4u){0u, 0u, 0u, 0u};
+            }
+            codes(v, wave, 0);
+            if (XS > 0) {
+                xrequest(pos0);
+                xleave(wave, 0);
             }
             for (int m = 0; m < members; ++m) {
                 const int unit = m * ENCG_UNITS + u, at = min(e0 + sl, ng * ENCG_SLOTS - 1), l = s_len[at], pos = row(s_off[at], l, t);
                 weights(m * ENCG_UNITS);
-                __syncthreads();
+                __syncthreads();                                       // (behind the gates of the member before)
+                biases(m * ENCG_UNITS);
                 products();
+                xproducts(0);
                 __syncthreads();
                 if (sl < ENCG_SLOTS && unit < H && t < l) {
-                    float bias[3];
-                    biases(unit, bias);
-                    const float *gp = a.gx[d] + (size_t)pos * 3 * H + unit;
-                    const float gx[3] = {gp[0], gp[H], gp[2 * H]};
-                    a.enc_h[(size_t)pos * 2 * H + col0 + unit] = gates(gx, bias, t > 0 ? a.enc_h[(size_t)(pos + back) * 2 * H + col0 + unit] : 0.0f, 0);
+                    float gx[3] = {0.f, 0.f, 0.f};
+                    if (XS == 0) input(pos, unit, gx);
+                    a.enc_h[(size_t)pos * 2 * H + col0 + unit] = gates(gx, t > 0 ? a.enc_h[(size_t)(pos + back) * 2 * H + col0 + unit] : 0.0f, 0);
                 }
             }
             __syncthreads();
@@ -338,25 +585,48 @@ size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd,
     int members, sets, groups, slots;
     if (H % 4 || H > 1024 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || !q8_enc_one_launch(H, S, max_l)) return 0;
     q8_enc_plan(H, S, &members, &sets, &groups, &slots);
-    return (size_t)6 * S * H + 4 * sets;
+    return (size_t)(groups == 1 ? 4 : 6) * S * H + (4 + 2 * 32) * sets;
 }
 
-q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
-                        const float *gxf, const float *gxb, unsigned *words)
+// Whether the kernel multiplies the rows of X itself (its registers hold the rows of Wx of at most ENCG_X_LD bytes).
+bool q8i_enc_group_takes_x(const q8_gru_weights *fwd, int S)
 {
-    const int H = fwd->Wh.cols;
+    int members, sets, groups, slots;
+    q8_enc_plan(fwd->Wh.cols, S, &members, &sets, &groups, &slots);
+    return groups == 1 && fwd->Wx.ld <= ENCG_X_LD;
+}
+
+template <int XS, bool ONE> static q8_status enc_group_launch(q8_ctx *ctx, const EncGroupArgs &a, int blocks, size_t lds)
+{
+    static Q8OncePerDevice asked;
+    const void *kernel = (const void *)enc_group_kernel<XS, ONE>;
+    const q8_status st = q8i_lds(ctx, asked, kernel, Q8_ENC_X_LDS(XS) + Q8_ENC_LDS_MOST, "encoder recurrences");
+    if (st) return st;
+    Q8_LAUNCH(ctx, Q8_KERNEL_GRU, (enc_group_kernel<XS, ONE>), dim3(blocks), dim3(ENCG_THREADS), lds + Q8_ENC_X_LDS(XS), a);
+    return q8i_launch_check(ctx, "encoder recurrences");
+}
+
+// in->X: the kernel multiplies the L rows of X, whose codes and scales go to xq [L x ldx] and xs; NULL: gxf, gxb have the products.
+q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
+                        const q8i_enc_input *in, unsigned *words)
+{
+    const int H = fwd->Wh.cols, L = in->X ? in->L : 0;
     int members, spd, ng, gs;
     const size_t lds = q8_enc_plan(H, S, &members, &spd, &ng, &gs);
-    const int clear = 4 * spd + 2 * S * H;
+    const int clear = (4 + 2 * 32) * spd + 4 * S * H, cb = (clear + 255) / 256;
+    EncGroupArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {in->gxf, in->gxb},
+                      {fwd->Wx.data, bwd->Wx.data}, {fwd->Wx.ld % 64 == 0 ? fwd->Wx.tiles : nullptr, bwd->Wx.ld % 64 == 0 ? bwd->Wx.tiles : nullptr},
+                      {fwd->bx, bwd->bx}, in->xq, in->xs, sent_off, enc_h,
+                      words + (4 + 2 * 32) * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,
+                      {fwd->Wh.scale, bwd->Wh.scale}, fwd->Wx.ld, {fwd->Wx.scale, bwd->Wx.scale}};
+    const int blocks = 8 * members * ((2 * spd + 7) / 8);
     // (the two launches side by side on their queue: a stream that shares it cannot wait for the turn between them)
     static std::mutex pair;
     std::lock_guard<std::mutex> hold(pair);
-    hipLaunchKernelGGL(enc_group_clear_kernel, dim3(1 + (clear + 255) / 256), dim3(256), 0, ctx->stream, words, clear);
+    hipLaunchKernelGGL(enc_group_front_kernel, dim3(1 + cb + (L + 3) / 4), dim3(256), 0, ctx->stream, words, clear, cb, in->X, fwd->Wx.cols, L, fwd->Wx.ld,
+                       in->xq, in->xs);
     const q8_status st = q8i_launch_check(ctx, "clear");
     if (st) return st;
-    EncGroupArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {gxf, gxb}, sent_off, enc_h,
-                      words + 4 * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,
-                      (size_t)gs * H > 8192 ? 11 : 8, {fwd->Wh.scale, bwd->Wh.scale}};
-    Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_group_kernel, dim3(8 * members * ((2 * spd + 7) / 8)), dim3(ENCG_THREADS), lds, a);
-    return q8i_launch_check(ctx, "encoder recurrences");
+    if (!in->X) return ng == 1 ? enc_group_launch<0, true>(ctx, a, blocks, lds) : enc_group_launch<0, false>(ctx, a, blocks, lds);
+    return fwd->Wx.ld <= 512 ? enc_group_launch<4, true>(ctx, a, blocks, lds) : enc_group_launch<5, true>(ctx, a, blocks, lds);
 }

@@ -101,6 +101,12 @@ Q8_INDEX_FN unsigned q8_enc_plan(int H, int S, int *members, int *sets, int *gro
     return Q8_ENC_SLOTS * Q8_ENC_PITCH + 12 * Q8_ENC_TILE * 4 + (unsigned)*groups * (Q8_ENC_SLOTS * Q8_ENC_UNITS * 4 + Q8_ENC_SLOTS * 8);
 }
 
+// What the form that multiplies X itself adds: two turns of the codes of 16 rows of X, 2 xs steps of 64 bytes at a pitch that puts
+// them on different banks, and of the sums, and the block's rows of Wx (none with xs = 0: the products of X are given).
+#define Q8_ENC_X_PITCH(xs) (128 * (xs) + 16)
+#define Q8_ENC_X_LDS(xs) ((xs) ? 2 * (Q8_ENC_SLOTS * Q8_ENC_X_PITCH(xs) + 12 * Q8_ENC_TILE * 4) + 12 * (xs) * 1024 : 0)
+#define Q8_ENC_LDS_MOST 47872
+
 // Whether S sentences of H units and up to max_l words run in that launch (else in one per time step, or three).  It costs 8 us
 // more than the first of those, which a time step gains back 3 us of: q8_encode_batch in us per batch, sentences of equal length,
 // H = 1024, 9 sentences of 1 / 2 / 3 / 4 words 17.5 / 20.3 / 24 / 26.5 against 11.1 / 16.9 / 24 / 29.5.  A group of a set takes 4 us of
@@ -117,3 +123,5 @@ Q8_INDEX_FN int q8_enc_one_launch(int H, int S, int max_l)
 // Where iteration `it` of a block (one group of slots at one time step, counted from the launch's first) keeps the scale of its
 // slot: two sets of 16 in turn, because an iteration's scales are read while other waves write the next one's.
 Q8_INDEX_FN int q8_enc_scale(int it, int slot) { return 16 * (it & 1) + slot; }
+// ... and of its row of X: left there two iterations before it is read, while the scales of two before that are.
+Q8_INDEX_FN int q8_enc_x_scale(int it, int slot) { return 16 * (it & 3) + slot; }

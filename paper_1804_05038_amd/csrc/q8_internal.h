@@ -254,8 +254,16 @@ q8_status q8i_enc_step(q8_ctx *ctx, int phase, const int *sent_off, int S, int t
                        float *hsb);
 // the recurrences of many sentences in one launch: words of scratch it takes (0: not for this shape), and the launch
 size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S, int max_l);
+bool q8i_enc_group_takes_x(const q8_gru_weights *fwd, int S);
+struct q8i_enc_input {
+    const float *gxf, *gxb;              // [L x 3H] products of X with both Wx, biases included, or
+    const float *X;                      // [L x E], if q8i_enc_group_takes_x, with room for its codes [L x ldx] and scales [L]
+    int L;
+    int8_t *xq;
+    float *xs;
+};
 q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
-                        const float *gxf, const float *gxb, unsigned *words);
+                        const q8i_enc_input *in, unsigned *words);
 // one time step of the batched encoder in one launch whose blocks wait for nobody: states [2][S][H] and their blocks' largest
 // magnitudes [2][S][ceil(H / 32)] of the step before (unused at t = 0) in h_in / pm_in, of this one in h_out / pm_out
 bool q8i_enc_cell_ok(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S);

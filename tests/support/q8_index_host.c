@@ -75,3 +75,17 @@ int q8x_panel_route(int rows, int ld, int n, int packed, int pitch)
 }
 
 int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }
+int q8x_enc_x_scale(int it, int slot) { return q8_enc_x_scale(it, slot); }
+
+/* The most LDS of a batched encoder of one group per set that multiplies X itself (rows of 128 xs bytes), and of any plan */
+unsigned q8x_enc_x_lds(int H, int xs)
+{
+    unsigned worst = 0;
+    for (int s = 1; s <= 1024; ++s) {
+        int members, sets, groups, slots;
+        const unsigned lds = q8_enc_plan(H, s, &members, &sets, &groups, &slots);
+        if (groups == 1 && lds + Q8_ENC_X_LDS(xs) > worst) worst = lds + Q8_ENC_X_LDS(xs);
+        if (groups <= 8 && lds > Q8_ENC_LDS_MOST) return 0;
+    }
+    return worst;
+}

@@ -692,6 +692,34 @@ def test_encoder_of_a_batch_whatever_its_blocks_wait_for(q, oracle, E, H, lens, 
     q.q8_encode_check(ctx)
 
 
+@pytest.mark.parametrize("E,H,lens,tiled", [(512, 1024, [1, 9, 4] * 21 + [3], True), (516, 1000, [7, 2, 3], False), (620, 1000, [3] * 17, False),
+                                            (640, 1024, [5, 4] * 30, True), (640, 36, [4] * 40, False), (644, 1024, [2, 6, 3] * 20, False),
+                                            (1000, 100, [3, 4, 8], False), (4, 4, [3], False)])
+def test_encoder_of_a_batch_multiplies_its_rows(q, E, H, lens, tiled):
+    """Rows of X of all widths up to the 640 bytes that the recurrences' launch multiplies itself, and past them: q8_encode's states,
+    bit for bit, with a bound of one poll as well, and with an infinity in a row of X (whose states are numbers all the same)."""
+    rng = np.random.default_rng(E + H)
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=E + (k == "b"), I=E, H=H).items()}
+    big = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=64, max_rows=3 * H, max_ld=1024))
+    G = [q.GruWeights(gpu_mat(q, big, p[k + "Wx"], tiled and E % 64 == 0), gpu_mat(q, big, p[k + "Wh"], tiled), big.f32(p[k + "bx"]),
+                      big.f32(p[k + "bh"]) if k == "f" else None) for k in ("f", "b")]
+    L, off = sum(lens), [0] + list(np.cumsum(lens))
+    X = rng.standard_normal((L, E)).astype(np.float32)
+    ctx = q.Context(workspace_bytes=256 * 1024 + q.q8_encode_batch_bytes(G[0], L, len(lens)))
+    for bad in (None, np.inf):
+        if bad is not None:
+            X[off[1] - 1, E // 2] = bad
+        Xd = big.f32(X)
+        enc = np_(q.q8_encode_batch(ctx, G[0], G[1], Xd, list(lens)))
+        for i in sorted({0, 1 % len(lens), len(lens) // 2, len(lens) - 1}):
+            rows = slice(int(off[i]), int(off[i + 1]))
+            np.testing.assert_array_equal(enc[rows], np_(q.q8_encode(big, G[0], G[1], Xd[rows].contiguous())), "sentence %d" % i)
+    assert np.abs(enc).max() <= 1
+    q.q8_encoder_options(ctx, True, 1)
+    np.testing.assert_array_equal(np_(q.q8_encode_batch(ctx, G[0], G[1], Xd, list(lens))), enc, "a bound of one poll")
+    q.q8_encode_check(ctx)
+
+
 @pytest.mark.parametrize("H,S,group", [(1024, 200, 64), (1000, 90, 60), (516, 512, 64)])
 def test_encoder_groups_of_a_set_keep_their_scales_apart(q, H, S, group):
     """Sets of several groups, whose states lie orders of magnitude apart (so that another sentence's scale would show): every

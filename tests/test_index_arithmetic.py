@@ -137,6 +137,55 @@ def test_no_two_waves_of_the_batched_encoder_meet_in_lds(lib):
                 written.setdefault(key, set()).add(wave)
 
 
+def _enc_x_accesses(lib, last):
+    """The same for one group per set, where the block multiplies rows of X as well: (interval, wave, array, index, write) of a
+    whole run of steps.  Rows go to LDS at the start of a step (the first one's in front), their products are made behind its second barrier."""
+    for w in range(16):
+        yield -2, w, "rows", (0, w ^ 8), True
+        yield -2, w, "row scale", lib.q8x_enc_x_scale(0, w ^ 8), True
+    for t in range(-1, last):
+        at = 2 * t + 2                                       # behind step t's second barrier, in front of the next step's first
+        for w in range(12):
+            for slot in range(16):
+                yield at, w, "rows", ((t + 1) & 1, slot), False
+            yield at, w, "row sums", ((t + 1) & 1, w), True
+        for w in range(16):
+            yield at, w, "rows", ((t + 2) & 1, w ^ 8), True
+            yield at, w, "row scale", lib.q8x_enc_x_scale(t + 2, w ^ 8), True
+            yield at, w, "scale", lib.q8x_enc_scale(t + 1, w ^ 8), True
+            yield at, w, "codes", w ^ 8, True
+        for w in range(8) if t >= 0 else ():
+            for slot in (2 * w, 2 * w + 1):
+                yield at, w, "scale", lib.q8x_enc_scale(t, slot), False
+                yield at, w, "row scale", lib.q8x_enc_x_scale(t, slot), False
+            for tile in range(12):
+                yield at, w, "sums", tile, False
+                yield at, w, "row sums", (t & 1, tile), False
+        for w in range(12):
+            for slot in range(16):
+                yield at + 1, w, "codes", slot, False
+            yield at + 1, w, "sums", w, True
+
+
+def test_no_two_waves_of_the_batched_encoder_meet_in_the_lds_of_x(lib):
+    seen, written = {}, {}
+    for interval, wave, array, at, write in sorted(_enc_x_accesses(lib, 9), key=lambda a: a[0]):
+        key = interval, array, at
+        assert not (write and seen.get(key, {wave}) - {wave}), (key, wave)
+        assert not (written.get(key, {wave}) - {wave}), (key, wave)
+        seen.setdefault(key, set()).add(wave)
+        if write:
+            written.setdefault(key, set()).add(wave)
+    assert all(0 <= lib.q8x_enc_x_scale(it, s) < 64 for it in range(9) for s in range(16))
+
+
+@pytest.mark.parametrize("xs", [4, 5])
+@pytest.mark.parametrize("H", [4, 32, 256, 512, 1000, 1024])
+def test_batched_encoder_with_rows_of_x_fits_the_lds(lib, H, xs):
+    """160 KB of a compute unit, with 2 KB for the kernel's own variables."""
+    assert 0 < lib.q8x_enc_x_lds(H, xs) <= 160 * 1024 - 2048
+
+
 ROUTES = ["staged", "resident", "resident 1024", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "once 128 x 64 trade", "stream"]
 
 
