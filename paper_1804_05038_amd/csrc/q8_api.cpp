@@ -902,13 +902,23 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
     float *gxb = cv.take<float>((size_t)l * 3 * H);
     float *zero = cv.take<float>(H);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_encode: workspace too small");
+    if (l > kMaxNarrow && fwd->Wx.ld != bwd->Wx.ld) return q8_fail(ctx, Q8_ERR_SHAPE, "q8_encode: the two Wx need the same ld");
 
+    // input products and recurrences of all positions in one launch where the shape and the device allow it ...
+    if (ctx->enc_one_launch) {
+        Carver own(ctx);
+        unsigned *words = own.take<unsigned>(q8i_enc_one_words(H));
+        int8_t *xqo = own.take<int8_t>((size_t)l * fwd->Wx.ld);
+        float *xso = own.take<float>(l);
+        int launched = 0;
+        if (own.ok) TRY(q8i_enc_one(ctx, fwd, bwd, X, l, enc_h, words, xqo, xso, (unsigned *)(ctx->ws + Q8_WS_ENC_ERR), &launched));
+        if (launched) return Q8_OK;
+    }
     // input products for every position at once (the same per-vector quantization as l separate products)
     if (l <= kMaxNarrow) {
         q8i_gemv_desc d[2] = {{&fwd->Wx, X, E, fwd->bx, gxf, 3 * H, nullptr}, {&bwd->Wx, X, E, bwd->bx, gxb, 3 * H, nullptr}};
         TRY(q8i_gemv_jobs(ctx, d, 2, l));
     } else {
-        if (fwd->Wx.ld != bwd->Wx.ld) return q8_fail(ctx, Q8_ERR_SHAPE, "q8_encode: the two Wx need the same ld");
         const q8i_quant_job qj = {X, E, E, fwd->Wx.ld, xq, xs, nullptr};            // one quantization serves both
         TRY(q8i_quantize_jobs(ctx, &qj, 1, l));
         const q8i_gemm_job gj[2] = {{&fwd->Wx, xq, xs, fwd->bx, gxf, 3 * H, nullptr, nullptr, nullptr, 0},

@@ -2,6 +2,7 @@
 // recurrent weights in registers for all positions and hand the states to each other through memory.
 #include "q8_internal.h"
 #include "q8_index.h"
+#include <atomic>
 #include <mutex>
 #include <type_traits>
 
@@ -84,14 +85,14 @@
 __device__ unsigned enc_group_turn = 8;
 
 // Waits for the turn (block 0), clears [words, words + n) (the next `clear` blocks) and quantizes the L rows of X (E floats, at
-// most ENCG_X_LD; the blocks after those, a wave per row), codes at pitch ld.
+// most 1024; the blocks after those, a wave per row), codes at pitch ld.
 __global__ __launch_bounds__(256) void enc_group_front_kernel(unsigned *words, int n, int clear, const float *X, int E, int L, int ld, int8_t *xq, float *xs)
 {
     if ((int)blockIdx.x > clear) {
         const int row = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - 1 - clear) * 4 + (int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
         if (row >= L) return;
         const __amdgpu_buffer_rsrc_t rx = q8_rsrc(X + (size_t)row * E, (size_t)E * sizeof(float));
-        constexpr int C = (ENCG_X_LD + 255) / 256;
+        constexpr int C = 4;
         float4 v[C];
         float m = 0.0f;
 #pragma unroll
@@ -144,6 +145,25 @@ struct EncGroupArgs {
     float wx_scale[2];
 };
 
+// The matrix cores' operands of 16 rows of a gate, N k steps of 64 bytes from step k0 on: units unit0 .. of a matrix of H units,
+// pitch bytes per row, tile-packed in Wt if that is there (zeros past H, and past the row).
+template <int N>
+__device__ __forceinline__ void enc_rows(const int8_t *W, const int8_t *Wt, int pitch, int H, int gate, int unit0, int k0, int lane, v4i (&out)[N])
+{
+    const int i = lane & 15, gq = lane >> 4;
+    const bool tiled = Wt != nullptr && H % 16 == 0;                   // (a tile of 16 rows then belongs to one gate)
+    const __amdgpu_buffer_rsrc_t rw = q8_rsrc(tiled ? Wt : W, (size_t)(tiled ? (3 * H + 15) / 16 * 16 : 3 * H) * pitch);
+    const unsigned row0 = (unsigned)(gate * H + unit0), step = tiled ? 1024u : 64u;
+    const unsigned base = tiled ? ((row0 >> 4) * (unsigned)(pitch >> 6) << 10) + 16u * lane : (row0 + i) * (unsigned)pitch + 16u * gq;
+    const bool ok = (tiled ? unit0 : unit0 + i) < H;
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        const int k = k0 + s;
+        const unsigned off = ok && 64 * k + (tiled ? 0 : 16 * gq) < pitch ? base + step * k : Q8_OOB;
+        out[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
+    }
+}
+
 template <int XS, bool ONE>
 __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 {
@@ -188,26 +208,12 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 
     // ---- the parts of a time step ----
     const int rt = wave % 6, kp = wave / 6, gate = rt >> 1, ut = rt & 1;                  // (waves 12 to 15 multiply nothing)
-    // N k steps of 64 bytes, from step k0 on, of the wave's 16 rows
-    auto rows = [&](const int8_t *W, const int8_t *Wt, int pitch, int unit0, int k0, auto &out) {
-        const bool tiled = Wt != nullptr && H % 16 == 0, in = wave < 12;                  // (a tile of 16 rows then belongs to one gate)
-        const __amdgpu_buffer_rsrc_t rw = q8_rsrc(tiled ? Wt : W, (size_t)(tiled ? (3 * H + 15) / 16 * 16 : 3 * H) * pitch);
-        const unsigned row0 = (unsigned)(gate * H + unit0), step = tiled ? 1024u : 64u;
-        const unsigned base = tiled ? ((row0 >> 4) * (unsigned)(pitch >> 6) << 10) + 16u * lane : (row0 + i) * (unsigned)pitch + 16u * gq;
-        const bool ok = in && (tiled ? unit0 : unit0 + i) < H;
-#pragma unroll
-        for (int s = 0; s < (int)(sizeof(out) / sizeof(out[0])); ++s) {
-            const int k = k0 + s;
-            const unsigned off = ok && 64 * k + (tiled ? 0 : 16 * gq) < pitch ? base + step * k : Q8_OOB;
-            out[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, 0));
-        }
-    };
     v4i av[8];
     auto weights = [&](int u0) {
-        rows(a.Wh[d], a.Wht[d], ld, u0 + 16 * ut, kp * 8, av);
+        enc_rows(a.Wh[d], a.Wht[d], ld, wave < 12 ? H : 0, gate, u0 + 16 * ut, kp * 8, lane, av);
         if constexpr (XS > 0) {
             v4i xv[XS];
-            rows(a.Wx[d], a.Wxt[d], a.ldx, u0 + 16 * ut, kp * XS, xv);
+            enc_rows(a.Wx[d], a.Wxt[d], a.ldx, wave < 12 ? H : 0, gate, u0 + 16 * ut, kp * XS, lane, xv);
             if (wave < 12) {
 #pragma unroll
                 for (int s = 0; s < XS; ++s) *(v4i *)(s_wx + ((wave * XS + s) * 64 + lane) * 16) = xv[s];
@@ -393,6 +399,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
                 v4u w[1][4];
                 bool there = true;
                 auto poll = [&](auto policy) {                         // (past H: the last ones again, for weights of zero)
+                    if (decltype(policy)::value == ENCG_AGENT) __builtin_amdgcn_s_sleep(8);    // (too early a poll slows what it waits for)
                     const int from = (int)(buffer(t - 1) + (unsigned)((c0 + slot) * H) * 4u);
                     unsigned first = 16u * lane, m = 0;
                     asm volatile("" : "+v"(first) :: "memory");        // (every request is made)
@@ -576,7 +583,218 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
         }
 }
 
+// ================================================= one sentence, all positions ==
+// Eq. 1 of one sentence, both directions, in one launch whose blocks wait for each other.  A direction's blocks are those
+// block numbers that agree with it modulo 8 (one XCD); a block of twelve waves owns 32 hidden units and keeps their rows of
+// Wh and Wx in registers, wave (rt, kp) as in enc_group_kernel.  A step: four waves (one per SIMD) poll all words of the step
+// before, each takes the maximum by itself and leaves a quarter of the codes in LDS; twelve waves multiply (of the matrix
+// cores' sixteen columns one is used: that takes no sums across lanes); the fifth wave applies the gates, r in its lower
+// half and z in its upper, and publishes.  While the words travel, the next position's products of X are made, from
+// rows that lie in LDS, `chunk` at a time.  Words, turns and what the members do when they are spread over several XCDs: as
+// in enc_group_kernel with one group.  A wait is bounded; a block whose wait gives up sets *err and leaves, the others then
+// leave as well.  Arithmetic of quantize_rows_kernel, the products and encoder_persistent_kernel, value for value.
+// The chain of a step bounds it: 1.48 us per position, E = 512, H = 1024 (encoder_persistent_kernel, 256 blocks all over the
+// device: 1.83, and two launches more in front).  q8_encode of 50 words, us: 99 -> 83; on four streams at once, per sentence 114 -> 52.
+// Not kept: dot products and gates on every wave, two units of sixteen waves or four of eight (129 and 101 us: sums across
+// lanes and sixteen, or eight, waves' gates); a row of X from memory at every step (135: its way is longer than the words').
+// LDS between the two barriers of a step: codes, sums and scales as in enc_group_kernel (states are words' own); sums of X
+// take turns; rows of X are replaced between two barriers of their own.
+struct EncOneArgs {
+    const int8_t *Wh[2], *Wht[2], *Wx[2], *Wxt[2];     // [3H x ld], [3H x ldx], and the same tile-packed or NULL
+    const float *bh[2], *bx[2];          // [3H] or NULL
+    const int8_t *xq;                    // codes [l x ldx] and scales [l] of X
+    const float *xs;
+    float *enc_h;                        // [l x 2H]
+    unsigned *words;                     // [2 turns][2 directions][H], ENCG_ABSENT on entry
+    unsigned *where;                     // [2][32], ENCG_ABSENT on entry
+    unsigned *err;
+    int l, H, ld, ldx, members, first, spin_limit, chunk;
+    float wh_scale[2], wx_scale[2];
+};
+#define ENC1_WAVES 12
+
+template <int XS>
+__global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
+{
+    extern __shared__ __align__(16) int8_t s_x[];                      // [chunk][128 XS] codes of rows of X
+    __shared__ __align__(16) int8_t s_q[1024];
+    __shared__ __align__(16) int s_e[ENC1_WAVES * 16], s_ex[2][ENC1_WAVES * 16];
+    __shared__ float s_scale[2];
+    __shared__ int s_flag, s_far;
+    constexpr int XP = 128 * XS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), gq = lane >> 4;
+    if (blockIdx.x + 8 >= gridDim.x && tid == 0) __hip_atomic_fetch_add(&enc_group_turn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int d = ((int)blockIdx.x - a.first) & 7, member = (int)blockIdx.x >> 3, H = a.H;
+    if (d > 1) return;
+    unsigned *where = a.where + 32 * d;
+    const int xcd = (int)__builtin_amdgcn_s_getreg(ENCG_XCC_ID);
+    if (tid == 0) {
+        s_flag = 0;
+        __hip_atomic_store(where + member, (unsigned)xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const int rt = wave % 6, kp = wave / 6, unit0 = member * ENCG_UNITS;
+    v4i wh[8], wx[XS];
+    enc_rows(a.Wh[d], a.Wht[d], a.ld, H, rt >> 1, unit0 + 16 * (rt & 1), kp * 8, lane, wh);
+    enc_rows(a.Wx[d], a.Wxt[d], a.ldx, H, rt >> 1, unit0 + 16 * (rt & 1), kp * XS, lane, wx);
+    // the gates' wave: unit, and biases of the lane's gate (r or z) and of n
+    const int unit = unit0 + (lane & 31);
+    const bool is = unit < H;
+    float bh[2], bx[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int r = (k == 0 ? lane >> 5 : 2) * H + unit;
+        bh[k] = a.bh[d] && is ? a.bh[d][r] : -0.0f;                    // (absent ones are the zero that changes no sum)
+        bx[k] = a.bx[d] && is ? a.bx[d][r] : -0.0f;
+    }
+    auto give_up = [&](int spins, int limit) {
+        if (spins < limit && ((spins & 63) != 0 || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)) return false;
+        if (lane == 0) {
+            s_flag = 1;
+            __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return true;
+    };
+    __syncthreads();
+    if (wave == ENC1_WAVES - 1) {
+        int far = 1;
+        for (int spins = 1;; ++spins) {
+            const int x = lane < a.members ? (int)__hip_atomic_load(where + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcd;
+            if (!__any(x == (int)ENCG_ABSENT)) {
+                far = __any(x != xcd);
+                break;
+            }
+            if (give_up(spins, a.spin_limit)) break;
+        }
+        if (lane == 0) s_far = far;
+    }
+    auto position = [&](int t) { return d == 0 ? t : a.l - 1 - t; };
+    auto rows_of_x = [&](int t0) {                                     // those of steps t0 .. (in front of a barrier)
+        const int n = min(a.chunk, a.l - t0);
+        for (int r = wave; r < n; r += ENC1_WAVES)
+            if (16 * lane < XP) *(v4i *)(s_x + r * XP + 16 * lane) = *(const v4i *)(a.xq + (size_t)position(t0 + r) * a.ldx + min(16 * lane, a.ldx - 16));
+    };
+    auto xproducts = [&](int t, int r) {                               // (lanes of all columns read the same operand)
+        v4i acc[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}};
+        const int8_t *bp = s_x + r * XP + kp * XS * 64 + 16 * gq;
+#pragma unroll
+        for (int s = 0; s < XS; ++s) acc[s & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wx[s], *(const v4i *)(bp + 64 * s), acc[s & 1], 0, 0, 0);
+        if ((lane & 15) == 0) *(v4i *)(s_ex[t & 1] + wave * 16 + 4 * gq) = acc[0] + acc[1];
+    };
+    rows_of_x(0);
+    __syncthreads();
+    xproducts(0, 0);
+    const bool far = s_far != 0;
+    const __amdgpu_buffer_rsrc_t rx = q8_rsrc(a.words, (size_t)16 * H);
+    auto buffer = [&](int t) { return (unsigned)((t & 1) * 2 + d) * (unsigned)H * 4u; };
+    auto turn = [&](int t) { return (unsigned)(t & 2) << 29; };
+    const int limit = far || a.spin_limit < ENCG_SPINS ? a.spin_limit : 4 * ENCG_SPINS;
+    float wh_scale = a.wh_scale[d], wx_scale = a.wx_scale[d], h_prev = 0.0f, xs_now = a.xs[position(0)];
+    asm volatile("" : "+v"(wh_scale), "+v"(wx_scale));                 // (kept, not read again at every step)
+    for (int t = 0, xrow = 0; t < a.l; ++t) {
+        if (wave < 4) {
+            v4u w[4];                                                  // floats 4 (lane + 64 ((wave + c) % 4)) ..
+            bool there = true;
+            auto poll = [&](auto policy) {
+                if (decltype(policy)::value == ENCG_AGENT) __builtin_amdgcn_s_sleep(8);
+                unsigned first = 16u * lane, m = 0;
+                asm volatile("" : "+v"(first) :: "memory");            // (every request is made)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    w[c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)min(first + 1024u * ((wave + c) & 3), 4u * H - 16u), (int)buffer(t - 1), decltype(policy)::value));
+                const unsigned bit = turn(t - 1);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    w[c] ^= bit;
+                    m |= w[c].x | w[c].y | w[c].z | w[c].w;
+                }
+                return !__any((m & ENCG_TURN_BIT) != 0);
+            };
+            if (t > 0) {
+                if (far) {
+                    for (int spins = 1; !(there = poll(std::integral_constant<int, ENCG_AGENT>())) && !give_up(spins, limit); ++spins) {}
+                } else {
+                    for (int spins = 1; !(there = poll(std::integral_constant<int, ENCG_XCD>())) && !give_up(spins, limit); ++spins) {}
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[c] = (v4u){0u, 0u, 0u, 0u};
+            }
+            if (there) {
+                float m = 0.0f, scale, inv;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(w[c].x), "v"(w[c].y));
+                    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(w[c].z), "v"(w[c].w));
+                }
+                q8_scale_of(wave_max_f(m), scale, inv);
+                const float4 v = __builtin_bit_cast(float4, w[0]);
+                *(int *)(s_q + 4 * (lane + 64 * wave)) = q8_pack4(v.x, v.y, v.z, v.w, inv);
+                if (tid == 0) s_scale[t & 1] = scale;
+            }
+        }
+        __syncthreads();
+        const int flag = s_flag;
+        {
+            v4i acc[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}}, bv[8];
+            const int8_t *bp = s_q + kp * 512 + 16 * gq;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) bv[s] = *(const v4i *)(bp + 64 * s);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) acc[s & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wh[s], bv[s], acc[s & 1], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);         // every operand is requested before the first is waited for
+            __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+            if ((lane & 15) == 0) *(v4i *)(s_e + wave * 16 + 4 * gq) = acc[0] + acc[1];
+        }
+        __syncthreads();
+        if (flag) break;
+        if (wave == 4) {
+            __builtin_amdgcn_s_setprio(2);
+            const int u = lane & 31, at[2] = {32 * (lane >> 5) + u, 64 + u};       // sums of the lane's gate and of n (the other half of k 96 further on)
+            float gh[2], gx[2];
+            int eh[2], ex[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                eh[k] = s_e[at[k]] + s_e[at[k] + 96];
+                ex[k] = s_ex[t & 1][at[k]] + s_ex[t & 1][at[k] + 96];
+            }
+            const float ch = wh_scale * s_scale[t & 1], cx = wx_scale * xs_now;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float y = (float)eh[k] * ch, x = (float)ex[k] * cx;
+                gh[k] = y + bh[k];
+                gx[k] = x + bx[k];
+            }
+            // gru_gates, operation by operation; r and z side by side
+            const float sg = sigmoid_rn(gx[0] + gh[0]);
+            const auto rz = __builtin_amdgcn_permlane32_swap(__float_as_uint(sg), __float_as_uint(sg), false, false);  // [0]: r, [1]: z
+            const float r = __uint_as_float(rz[0]), z = __uint_as_float(rz[1]);
+            const float rn = r * gh[1], pn = gx[1] + rn, nn = tanh_rn(pn), omz = 1.0f - z, t1 = omz * nn, t2 = z * h_prev, hn = t1 + t2;
+            if (lane < 32 && is) {
+                if (t + 1 < a.l) {
+                    const unsigned word = __float_as_uint(hn) ^ turn(t);
+                    if (far) __builtin_amdgcn_raw_buffer_store_b32(word, rx, unit * 4, (int)buffer(t), ENCG_AGENT);
+                    else __builtin_amdgcn_raw_buffer_store_b32(word, rx, unit * 4, (int)buffer(t), 0);
+                }
+                a.enc_h[(size_t)position(t) * 2 * H + (d == 0 ? H : 0) + unit] = hn;
+            }
+            __builtin_amdgcn_s_setprio(0);
+            h_prev = hn;
+            xs_now = a.xs[position(min(t + 1, a.l - 1))];
+        }
+        if (++xrow == a.chunk) {
+            xrow = 0;
+            __syncthreads();                                           // (the last one's row has been multiplied)
+            if (t + 1 < a.l) rows_of_x(t + 1);
+            __syncthreads();
+        }
+        xproducts(t + 1, xrow);
+    }
+}
+
 // =================================================================== host launchers ==
+
+// An encoder's two launches side by side on their queue: a stream that shares it cannot wait for the turn between them.
+static std::mutex enc_pair;
 
 // 4-byte words of scratch (0: not for this shape): the members' words and the sets' counters and flags.
 size_t q8i_enc_group_words(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S, int max_l)
@@ -620,13 +838,51 @@ q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_wei
                       words + (4 + 2 * 32) * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,
                       {fwd->Wh.scale, bwd->Wh.scale}, fwd->Wx.ld, {fwd->Wx.scale, bwd->Wx.scale}};
     const int blocks = 8 * members * ((2 * spd + 7) / 8);
-    // (the two launches side by side on their queue: a stream that shares it cannot wait for the turn between them)
-    static std::mutex pair;
-    std::lock_guard<std::mutex> hold(pair);
+    std::lock_guard<std::mutex> hold(enc_pair);
     hipLaunchKernelGGL(enc_group_front_kernel, dim3(1 + cb + (L + 3) / 4), dim3(256), 0, ctx->stream, words, clear, cb, in->X, fwd->Wx.cols, L, fwd->Wx.ld,
                        in->xq, in->xs);
     const q8_status st = q8i_launch_check(ctx, "clear");
     if (st) return st;
     if (!in->X) return ng == 1 ? enc_group_launch<0, true>(ctx, a, blocks, lds) : enc_group_launch<0, false>(ctx, a, blocks, lds);
     return fwd->Wx.ld <= 512 ? enc_group_launch<4, true>(ctx, a, blocks, lds) : enc_group_launch<5, true>(ctx, a, blocks, lds);
+}
+
+// Eq. 1 of one sentence in one launch.  Q8_OK with *launched = 0 where the shape is not covered, the device cannot hold all blocks
+// at once or the stream is being captured (what it takes then runs elsewhere).  words: 4 H + 64 words of scratch; xq [l x ldx], xs [l]: room
+// for the codes and scales of X; err: set to 1 by the kernel if a wait gave up.
+size_t q8i_enc_one_words(int H) { return (size_t)4 * H + 64; }
+
+q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X, int l, float *enc_h, unsigned *words,
+                      int8_t *xq, float *xs, unsigned *err, int *launched)
+{
+    *launched = 0;
+    const int H = fwd->Wh.cols, ldx = fwd->Wx.ld, members = (H + ENCG_UNITS - 1) / ENCG_UNITS, blocks = 8 * members;
+    if (H > 1024 || H % 4 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || ldx > 1024 || bwd->Wx.ld != ldx) return Q8_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return Q8_OK;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks) {
+        (void)hipGetLastError();
+        return Q8_OK;
+    }
+    // sentences on other streams on other XCDs, two at a time
+    static std::atomic<unsigned> next{0};
+    const int first = 2 * (int)(next.fetch_add(1, std::memory_order_relaxed) & 3), clear = 4 * H + 64, cb = (clear + 255) / 256;
+    const int xs4 = ldx <= 512 ? 4 : ldx <= 640 ? 5 : 8, chunk = l < 49152 / (128 * xs4) ? l : 49152 / (128 * xs4);
+    EncOneArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->Wx.data, bwd->Wx.data},
+                    {ldx % 64 == 0 ? fwd->Wx.tiles : nullptr, ldx % 64 == 0 ? bwd->Wx.tiles : nullptr}, {fwd->bh, bwd->bh}, {fwd->bx, bwd->bx}, xq, xs, enc_h,
+                    words + 64, words, err, l, H, fwd->Wh.ld, ldx, members, first, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS, chunk,
+                    {fwd->Wh.scale, bwd->Wh.scale}, {fwd->Wx.scale, bwd->Wx.scale}};
+    std::lock_guard<std::mutex> hold(enc_pair);
+    hipLaunchKernelGGL(enc_group_front_kernel, dim3(1 + cb + (l + 3) / 4), dim3(256), 0, ctx->stream, words, clear, cb, X, fwd->Wx.cols, l, ldx, xq, xs);
+    q8_status st = q8i_launch_check(ctx, "clear");
+    if (st) return st;
+    const dim3 grid(blocks), block(64 * ENC1_WAVES);
+    const size_t lds = (size_t)chunk * 128 * xs4;
+    if (xs4 == 4) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_one_kernel<4>, grid, block, lds, a);
+    else if (xs4 == 5) Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_one_kernel<5>, grid, block, lds, a);
+    else Q8_LAUNCH(ctx, Q8_KERNEL_GRU, enc_one_kernel<8>, grid, block, lds, a);
+    st = q8i_launch_check(ctx, "encoder recurrence");
+    if (!st) *launched = 1;
+    return st;
 }

@@ -264,6 +264,10 @@ struct q8i_enc_input {
 };
 q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const int *sent_off, int S, float *enc_h,
                         const q8i_enc_input *in, unsigned *words);
+// the encoder of one sentence in one launch (and one that prepares it)
+size_t q8i_enc_one_words(int H);
+q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X, int l, float *enc_h, unsigned *words,
+                      int8_t *xq, float *xs, unsigned *err, int *launched);
 // one time step of the batched encoder in one launch whose blocks wait for nobody: states [2][S][H] and their blocks' largest
 // magnitudes [2][S][ceil(H / 32)] of the step before (unused at t = 0) in h_in / pm_in, of this one in h_out / pm_out
 bool q8i_enc_cell_ok(const q8_gru_weights *fwd, const q8_gru_weights *bwd, int S);

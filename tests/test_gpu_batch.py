@@ -720,6 +720,40 @@ def test_encoder_of_a_batch_multiplies_its_rows(q, E, H, lens, tiled):
     q.q8_encode_check(ctx)
 
 
+@pytest.mark.parametrize("E,H,l,tiled", [(512, 1024, 97, True), (512, 1024, 1, False), (516, 132, 77, False), (640, 36, 2, False), (620, 1000, 30, False),
+                                         (644, 64, 49, False), (1000, 1000, 9, False), (1024, 256, 48, True), (4, 4, 5, False), (1028, 64, 3, False)])
+def test_encoder_of_one_sentence_in_one_launch(q, E, H, l, tiled):
+    """All widths of X that the launch multiplies itself, sentences that fill its rows in LDS and go past them, one width more: the
+    states of a launch per position, bit for bit, from several streams at once as well."""
+    rng = np.random.default_rng(E + l)
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=E + (k == "b"), I=E, H=H).items()}
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=128, max_rows=3 * H, max_ld=1040))
+    G = [q.GruWeights(gpu_mat(q, ctx, p[k + "Wx"], tiled), gpu_mat(q, ctx, p[k + "Wh"], tiled), ctx.f32(p[k + "bx"]) if k == "b" else None,
+                      ctx.f32(p[k + "bh"])) for k in ("f", "b")]
+    X = ctx.f32(rng.standard_normal((l, E)).astype(np.float32))
+    q.q8_encoder_options(ctx, False)
+    want = np_(q.q8_encode(ctx, G[0], G[1], X))
+    q.q8_encoder_options(ctx, True)
+    for _ in range(3):
+        assert_same(q.q8_encode(ctx, G[0], G[1], X), want, "one launch")
+    q.q8_encode_check(ctx)
+    torch.cuda.synchronize()
+    lanes = []
+    for _ in range(4):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            own = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=128, max_rows=3 * H, max_ld=1040), stream=st)
+            lanes.append((st, own, own.empty(l, 2 * H)))
+    for _ in range(5):
+        for st, own, out in lanes:
+            with torch.cuda.stream(st):
+                q.q8_encode(own, G[0], G[1], X, enc_h=out)
+    torch.cuda.synchronize()
+    for _, own, out in lanes:
+        q.q8_encode_check(own)
+        assert_same(out, want, "a stream of its own")
+
+
 @pytest.mark.parametrize("H,S,group", [(1024, 200, 64), (1000, 90, 60), (516, 512, 64)])
 def test_encoder_groups_of_a_set_keep_their_scales_apart(q, H, S, group):
     """Sets of several groups, whose states lie orders of magnitude apart (so that another sentence's scale would show): every
