@@ -79,6 +79,17 @@ bool codes_usable(const q8_codes *c, int ld)
     return c && c->q && c->scale && c->ld == ld && aligned16(c->q);
 }
 
+// ... products and gates in a launch that waits for nobody, the codes of the new states in another.
+q8_status gru_tile(q8_ctx *ctx, const q8_gru_weights *g, const int8_t *xq, const float *xs, const int8_t *hq, const float *hs, const float *h_prev,
+                   float *h_out, int n, const PanelCodesOut *out)
+{
+    const int H = g->Wh.cols;
+    TRY(q8i_gru_tile(ctx, g, xq, xs, hq, hs, h_prev, H, h_out, H, n));
+    if (!out) return Q8_OK;
+    const q8i_quant_job qj[2] = {{h_out, H, H, out->ld1, out->q1, out->s1, nullptr}, {h_out, H, H, out->ld2, out->q2, out->s2, nullptr}};
+    return q8i_quantize_jobs(ctx, qj, out->q2 ? 2 : 1, n);
+}
+
 // xq_pre / xs_pre (with gh_pre only): x arrives quantized.  out: the gates kernel also quantizes h_out.
 // x_keep: x's codes are written to the caller's buffers; with h_given (no gh_pre, no taps) they are there
 // already, like those of h_prev in h_given, and nothing is quantized.
@@ -90,12 +101,14 @@ q8_status gru_panel(q8_ctx *ctx, Carver &cv, const q8_gru_weights *g, const floa
     const int I = g->Wx.cols, H = g->Wh.cols;
     // products, gates and codes in one launch where the shape allows (no pre-activations in memory)
     const bool one_launch = !taps2 && q8i_gru_panel_ok(ctx, g, gh_pre != nullptr, n, H, H, out != nullptr, out ? out->ld1 : 0, out ? out->ld2 : 0, out && out->q2);
+    const bool tile = !taps2 && !gh_pre && !one_launch && q8i_gru_tile_ok(g, n, H, H, out != nullptr);
     auto panel = [&](const int8_t *xq_, const float *xs_, const int8_t *hq_, const float *hs_) {
         return q8i_gru_panel(ctx, g, xq_, xs_, hq_, hs_, gh_pre, h_prev, H, h_out, H, n, out ? out->q1 : nullptr, out ? out->ld1 : 0,
                              out ? out->s1 : nullptr, out ? out->q2 : nullptr, out ? out->ld2 : 0, out ? out->s2 : nullptr, region);
     };
     if (h_given && x_keep && !gh_pre && !taps2) {
         if (one_launch) return panel(x_keep->q, x_keep->scale, h_given->q, h_given->scale);
+        if (tile) return gru_tile(ctx, g, x_keep->q, x_keep->scale, h_given->q, h_given->scale, h_prev, h_out, n, out);
         float *gx = cv.take<float>((size_t)n * 3 * H), *gh = cv.take<float>((size_t)n * 3 * H);
         if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "GRU panel: workspace too small");
         const q8i_gemm_job gj[2] = {{&g->Wx, x_keep->q, x_keep->scale, g->bx, gx, 3 * H, nullptr, nullptr, nullptr, 0},
@@ -117,6 +130,7 @@ q8_status gru_panel(q8_ctx *ctx, Carver &cv, const q8_gru_weights *g, const floa
         TRY(q8i_quantize_jobs(ctx, qj, gh_pre ? 1 : 2, n));
     }
     if (one_launch) return panel(have_x ? xq_pre : xq, have_x ? xs_pre : xs, hq, hs);
+    if (tile) return gru_tile(ctx, g, xq, xs, hq, hs, h_prev, h_out, n, out);
     const q8i_gemm_job gj[2] = {{&g->Wx, have_x ? xq_pre : xq, have_x ? xs_pre : xs, g->bx, gx, 3 * H, taps2 ? taps2[0].acc : nullptr, nullptr, nullptr, 0},
                                 {&g->Wh, hq, hs, g->bh, gh, 3 * H, taps2 ? taps2[1].acc : nullptr, nullptr, nullptr, 0}};
     TRY(q8i_gemm_jobs(ctx, gj, gh_pre ? 1 : 2, n));
@@ -633,20 +647,29 @@ q8_status cgru_decoder_step_batch_loop_q8(q8_ctx *ctx, const q8_cgru_weights *w,
         const q8i_quant_job qj[2] = {{s_mid, H, H, w->att_U.ld, mq_u, ms_u, nullptr}, {s_mid, H, H, w->q.Wh.ld, mq_h, ms_h, nullptr}};
         TRY(q8i_quantize_jobs(ctx, qj, 2, n));
     }
+    const bool s_keep = s_codes && s_codes->q && s_codes->scale && aligned16(s_codes->q) && s_codes->ld >= H &&
+                        q8i_gru_gates_q_ok(H, H, H, s_codes->ld, s_codes->ld);
+    // (GRU q multiplies both where its launch can, and where none takes the products with the recurrent half given)
+    const bool q_tile = !q8i_gru_panel_ok(ctx, &w->q, true, n, H, H, s_keep, s_keep ? s_codes->ld : 0, 0, false) && q8i_gru_tile_ok(&w->q, n, H, H, s_keep);
     const q8i_gemm_job gj[2] = {{&w->att_U, mq_u, ms_u, nullptr, a, A, nullptr, nullptr, nullptr, 0},
                                 {&w->q.Wh, mq_h, ms_h, w->q.bh, ghq, 3 * H, nullptr, nullptr, nullptr, 0}};
-    TRY(q8i_gemm_jobs(ctx, gj, 2, n));
+    TRY(q8i_gemm_jobs(ctx, gj, q_tile ? 1 : 2, n));
     // Eq. 5-6 per hypothesis, against the positions of its own sentence
     int have_codes = 0;
     TRY(q8i_attention(ctx, P, enc_h, max_l, A, C, a, w->att_v, n, e, alpha_out, ctx_out, sent_off, beam, cq, cqs, w->q.Wx.ld, &have_codes));
     if (have_codes && codes_usable(ctx_codes, w->q.Wx.ld)) ctx_codes->valid = 1;
     // Eq. 4: s = q(H_t, s'); the gates kernel can leave s quantized for the caller's next product
     Carver sub = cv;
-    const bool s_keep = s_codes && s_codes->q && s_codes->scale && aligned16(s_codes->q) && s_codes->ld >= H &&
-                        q8i_gru_gates_q_ok(H, H, H, s_codes->ld, s_codes->ld);
     const PanelCodesOut s_out_codes = {s_keep ? s_codes->q : nullptr, s_keep ? s_codes->ld : 0, s_keep ? s_codes->scale : nullptr, nullptr, 0, nullptr};
-    q8_status st = gru_panel(ctx, sub, &w->q, ctx_out, s_mid, n, ghq, s_out, nullptr, have_codes ? cq : nullptr,
-                             have_codes ? cqs : nullptr, s_keep ? &s_out_codes : nullptr, nullptr, nullptr, 1);
+    q8_status st = Q8_OK;
+    if (q_tile) {
+        const q8i_quant_job qj = {ctx_out, C, C, w->q.Wx.ld, cq, cqs, nullptr};
+        if (!have_codes) st = q8i_quantize_jobs(ctx, &qj, 1, n);
+        if (!st) st = gru_tile(ctx, &w->q, cq, cqs, mq_h, ms_h, s_mid, s_out, n, s_keep ? &s_out_codes : nullptr);
+    } else {
+        st = gru_panel(ctx, sub, &w->q, ctx_out, s_mid, n, ghq, s_out, nullptr, have_codes ? cq : nullptr,
+                       have_codes ? cqs : nullptr, s_keep ? &s_out_codes : nullptr, nullptr, nullptr, 1);
+    }
     if (!st && s_keep) s_codes->valid = 1;
     return st;
 }

@@ -80,6 +80,48 @@ Q8_INDEX_FN unsigned q8_panel_weight(int half, int lane, int ks, int ntiles)
 }
 Q8_INDEX_FN unsigned q8_panel_step(int s) { return (unsigned)(s >> 1) * 1024u + (unsigned)(s & 1) * 512u; }
 
+// ---- a GRU transition's products and gates in one launch (gru_tile_kernel) ----
+
+// The 64-byte steps of both products' rows in three parts: the first *nx of Wx, the others of Wh, the longer rows in two.
+// Returns the stages of two steps that the longest part takes.
+Q8_INDEX_FN int q8_gru_parts(int ldx, int ldh, int *nx, int *k0, int *steps)
+{
+    const int sx = (ldx + 63) / 64, sh = (ldh + 63) / 64;
+    *nx = sx >= sh ? 2 : 1;
+    const int two = *nx == 2 ? sx : sh, first = (two + 1) / 2, at = *nx == 2 ? 0 : 1;      // the part that the longer rows begin in
+    k0[at] = 0;
+    steps[at] = first;
+    k0[at + 1] = first;
+    steps[at + 1] = two - first;
+    k0[*nx == 2 ? 2 : 0] = 0;
+    steps[*nx == 2 ? 2 : 0] = *nx == 2 ? sh : sx;
+    int most = first;
+    if (sx + sh - two > most) most = sx + sh - two;
+    return (most + 1) / 2;
+}
+
+// Tiles of 32 vectors per block: the fewest that leave a compute unit one block, four at most.
+Q8_INDEX_FN int q8_gru_tile_columns(int H, int n)
+{
+    const int units = (H + 31) / 32, across = 256 / units > 0 ? 256 / units : 1, ct = ((n + 31) / 32 + across - 1) / across;
+    return ct > 4 ? 4 : ct;
+}
+
+// Whether it is faster than the products and the gates apart.  Transitions alone (q8_gru_step panels, us, apart / in one launch):
+// 64 + 64 bytes per row times 12 / 1024 vectors 10.9 / 7.3 and 12.0 / 8.5, H = 512, 512 + 256 bytes 10.8 / 8.2 and 20.3 / 12.0, H = 1000,
+// 624 + 1008 bytes times 128 / 352 / 1024 12.3 / 11.1, 20.2 / 14.5 and 28.6 / 25.2, H = 1000, 2000 + 1008 bytes times 12 / 1024 14.6 / 12.7 and
+// 37.5 / 32.3; but H = 1024, 1024 + 1024 bytes, row-major, times 12 / 128 11.1 / 13.8 and 13.5 / 14.4 (256: 16.4 / 15.0), H = 512,
+// 1024 + 512 bytes, row-major, times 12 10.8 / 11.2, and more than a block per compute unit, H = 2048 times 700, 43.6 / 47.0.
+// Where the codes of the new states are wanted they cost a launch of 5.9 us, which the gates' kernel apart makes by the way: us per
+// decoder step, both transitions, H = 1000, 4 / 20 / 64 / 80 / 100 / 200 sentences at beam 5, 82 / 92 / 122 / 136 / 164 / 234 apart, 90 / 97 / 124 / 130 / 157 / 226 so,
+// H = 1024, 70 / 100 / 200 sentences 114 / 127 / 200 apart, 108 / 118 / 183 so.
+Q8_INDEX_FN int q8_gru_tile_better(int H, int ldx, int ldh, int n, int codes)
+{
+    const int cols = 32 * q8_gru_tile_columns(H, n);
+    if ((long long)((H + 31) / 32) * ((n + cols - 1) / cols) > 256) return 0;
+    return codes ? (long long)n * H >= 360000 : n > 128 || ldx + ldh < 1024;
+}
+
 // ---- the batched encoder (enc_group_kernel) ----
 
 #define Q8_ENC_UNITS 32

@@ -720,6 +720,21 @@ def test_encoder_of_a_batch_multiplies_its_rows(q, E, H, lens, tiled):
     q.q8_encode_check(ctx)
 
 
+@pytest.mark.parametrize("I,H,n,tiled", [(64, 64, 9, True), (16, 36, 33, False), (100, 4, 700, False), (620, 1000, 129, False), (2000, 1000, 353, False),
+                                         (512, 1024, 1000, True), (2048, 1024, 513, True), (1024, 48, 300, False), (512, 2048, 300, True), (256, 512, 1024, True)])
+def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled):
+    """Products and gates in one launch, at the edges of its blocks (32 units, 32 to 128 vectors, parts of the k range of either
+    product, rows that end inside a step): the states of the narrow kernel on the same vectors, bit for bit."""
+    p = synth.gru_cell(seed=n, I=I, H=H)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=3 * H, max_ld=2048))
+    G = q.GruWeights(gpu_mat(q, ctx, p["Wx"], tiled), gpu_mat(q, ctx, p["Wh"], tiled), ctx.f32(p["bx"]), ctx.f32(p["bh"]) if H != 48 else None)
+    rng = np.random.default_rng(n)
+    x, h = ctx.f32(rng.standard_normal((n, I)).astype(np.float32)), ctx.f32(np.tanh(rng.standard_normal((n, H))).astype(np.float32))
+    got = np_(q.gru_step_q8(ctx, G, x, h))
+    for i in sorted({0, 8, n // 2, n - 8} & set(range(n - 7))):
+        assert_same(got[i:i + 8], np_(q.gru_step_q8(ctx, G, x[i:i + 8].contiguous(), h[i:i + 8].contiguous())), "vectors from %d" % i)
+
+
 @pytest.mark.parametrize("E,H,l,tiled", [(512, 1024, 97, True), (512, 1024, 1, False), (516, 132, 77, False), (640, 36, 2, False), (620, 1000, 30, False),
                                          (644, 64, 49, False), (1000, 1000, 9, False), (1024, 256, 48, True), (4, 4, 5, False), (1028, 64, 3, False)])
 def test_encoder_of_one_sentence_in_one_launch(q, E, H, l, tiled):

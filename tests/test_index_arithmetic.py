@@ -186,6 +186,28 @@ def test_batched_encoder_with_rows_of_x_fits_the_lds(lib, H, xs):
     assert 0 < lib.q8x_enc_x_lds(H, xs) <= 160 * 1024 - 2048
 
 
+@pytest.mark.parametrize("ldx,ldh", [(16, 16), (64, 1024), (512, 1024), (624, 1008), (1024, 1024), (1040, 1024), (2000, 1008), (2048, 1024), (1024, 2048), (4096, 16)])
+def test_gru_parts_cover_both_products_once(lib, ldx, ldh):
+    """Every 64-byte step of either product's rows belongs to one part, and no part has more than the stages' steps."""
+    columns, nx, stages, k0, steps = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), _ints(3), _ints(3)
+    lib.q8x_gru_tile(1024, ldx, ldh, 64, 0, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
+    assert nx.value in (1, 2) and 2 * (stages.value - 1) < max(steps[:]) <= 2 * stages.value
+    for parts, ld in ((range(nx.value), ldx), (range(nx.value, 3), ldh)):
+        assert [s for p in parts for s in range(k0[p], k0[p] + steps[p])] == list(range((ld + 63) // 64))
+
+
+def test_gru_tile_blocks_cover_the_vectors_in_one_round(lib):
+    columns, nx, stages, k0, steps = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), _ints(3), _ints(3)
+    taken = 0
+    for H in (4, 32, 36, 256, 512, 1000, 1024, 2048, 8192):
+        for n in (9, 32, 33, 128, 129, 350, 352, 353, 700, 1000, 1024):
+            for codes in (0, 1):
+                if lib.q8x_gru_tile(H, 512, 512, n, codes, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages)):
+                    taken += 1
+                    assert 1 <= columns.value <= 4 and (H + 31) // 32 * -(-n // (32 * columns.value)) <= 256
+    assert taken
+
+
 ROUTES = ["staged", "resident", "resident 1024", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "once 128 x 64 trade", "stream"]
 
 
