@@ -343,6 +343,13 @@ static q8_status gemm_narrow_any(q8_ctx *ctx, const q8_mat *W, const float *row_
     int8_t *xq = cv.take<int8_t>((size_t)n * W->ld);
     float *xs = cv.take<float>(n);
     if (!cv.ok) return q8_fail(ctx, Q8_ERR_WORKSPACE, "q8_gemm_narrow: workspace too small");
+    // (results over the vectors: quantized first, as a whole)
+    const char *x0 = (const char *)X, *x1 = (const char *)(X + (size_t)(n - 1) * ldx + W->cols), *y0 = (const char *)Y, *y1 = (const char *)(Y + (size_t)(n - 1) * ldy + W->rows);
+    if (!taps && (y1 <= x0 || x1 <= y0)) {
+        int launched = 0;
+        TRY(q8i_gemm_quant(ctx, W, row_scale, X, n, ldx, bias, Y, ldy, &launched));
+        if (launched) return Q8_OK;
+    }
     return q8i_gemm_mfma(ctx, W, X, n, ldx, bias, Y, ldy, taps, xq, xs, row_scale);
 }
 

@@ -214,6 +214,9 @@ struct q8i_gemm_job {           // Y [n x ldy] = dequantize(W . xq) + bias on th
 };
 q8_status q8i_quantize_jobs(q8_ctx *ctx, const q8i_quant_job *d, int njobs, int n);   // njobs <= 3
 q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n);        // njobs <= 3
+// both in one launch where that is faster (*launched says whether it is)
+q8_status q8i_gemm_quant(q8_ctx *ctx, const q8_mat *W, const float *row_scale, const float *X, int n, int ldx, const float *bias, float *Y, int ldy,
+                         int *launched);
 // three products with rows of 1024 / 512 / 2048 bytes (the readout's) over the same vectors in one K-resident launch
 bool q8i_gemm_ksplit3_ok(const q8i_gemm_job *d, int n);
 q8_status q8i_gemm_ksplit3(q8_ctx *ctx, const q8i_gemm_job *d, int n);

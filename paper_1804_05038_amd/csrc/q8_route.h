@@ -79,3 +79,16 @@ static inline int q8_panel_route(const q8_panel_shape *s)
     if (results >= Q8_TILE_FILL && (s->max_ld <= 1024 || s->n > 64 || !s->packed)) return Q8_ROUTE_TILES_128;
     return s->packed ? Q8_ROUTE_TILES_64 : Q8_ROUTE_STAGED;
 }
+
+// Tiles of 16 rows per block of gemm_quant_kernel for n vectors of a product: the fewest that need one round of blocks, four at
+// most; 0 where quantization and product in two launches are faster, which is where too many blocks of four tiles quantize
+// the same vectors again: more than 256 of them with rows of more than 1024 bytes, 550 of more than 512, 850 of fewer.  us per
+// call, two launches / one: 1024 rows of 2048 bytes, packed, times 9 / 30 / 128 / 256 / 400 vectors 8.0 / 4.1, 8.3 / 4.3, 8.7 / 4.9, 9.1 / 5.8, 9.7 / 10.2;
+// 3072 x 2048, row-major, times 64 / 100 11.2 / 7.0, 11.6 / 12.5; 1024 x 1024, row-major, times 400 / 700 9.0 / 7.3, 9.8 / 10.0; 2000 x 620 times 256 / 400
+// 8.0 / 6.2, 8.1 / 9.5; 1024 x 512 times 64 / 700 6.7 / 3.5, 7.6 / 6.6; 8192 x 512, row-major, times 64 / 100 / 200 7.7 / 5.3, 7.6 / 7.6, 9.6 / 12.0.
+static inline int q8_quant_rows(int rows, int ld, int n)
+{
+    const long long tiles = (rows + 15) / 16, groups = (n + 15) / 16;
+    if (n <= 8 || ld > 2048 || (tiles + 3) / 4 * groups > (ld > 1024 ? 256 : ld > 512 ? 550 : 850)) return 0;
+    return tiles * groups <= 256 ? 1 : tiles * groups <= 512 ? 2 : 4;
+}

@@ -77,6 +77,8 @@ int q8x_panel_route(int rows, int ld, int n, int packed, int pitch)
 int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }
 int q8x_enc_x_scale(int it, int slot) { return q8_enc_x_scale(it, slot); }
 
+int q8x_quant_rows(int rows, int ld, int n) { return q8_quant_rows(rows, ld, n); }
+
 /* Columns (tiles of 32 vectors) per block, whether the launch takes the shape, and the parts of the k range, of gru_tile_kernel */
 int q8x_gru_tile(int H, int ldx, int ldh, int n, int codes, int *columns, int *nx, int *k0, int *steps, int *stages)
 {

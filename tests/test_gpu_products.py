@@ -320,3 +320,68 @@ def test_panels_requested_whole(q, oracle, rows, cols, n, tiled, route, by_row):
             acc = (codes @ xq[:cols].astype(np.int64)).astype(np.float32)
             y = acc * ((np_(rs) if by_row else np.float32(M.scale)) * np.float32(xs))
             assert_same(got[j, :rows], y if bias is None else y + bias, "vector %d" % j)
+
+
+# rows, columns, vectors, tile-packed, tiles of 16 rows per block (checked against the library's rule on the host): rows and vectors at the
+# remainders of a block, parts of the k range of no, one and several matrix-core steps
+QUANT_PANELS = [
+    (1, 16, 9, False, 1), (4, 4, 10, False, 1), (257, 320, 16, True, 1), (1024, 516, 30, False, 1), (640, 1024, 17, True, 1), (1000, 2048, 64, True, 1),
+    (1031, 512, 100, True, 2), (3072, 1000, 31, False, 2), (2000, 1100, 40, False, 2),
+    (3072, 512, 200, True, 4), (65, 256, 1024, False, 2), (1000, 620, 333, False, 4), (1030, 2048, 240, True, 4), (8200, 1536, 16, True, 4),
+]
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled,tiles", QUANT_PANELS)
+@pytest.mark.parametrize("by_row", [False, True])
+def test_panels_whose_blocks_quantize(q, oracle, rows, cols, n, tiled, tiles, by_row):
+    """Few vectors are quantized by the blocks that multiply them, with one scale and one per row, results at an odd pitch: the
+    same codes, integer sums and roundings as everywhere, so the same bits; also for vectors of zeros, of next to nothing and with an infinity."""
+    rng = np.random.default_rng(rows + n + cols)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=2112))
+    W, b, X = _w(rng, rows, cols), (rng.standard_normal(rows) * 0.01).astype(np.float32), rng.standard_normal((n, cols)).astype(np.float32)
+    X[1], X[3] = 0.0, np.float32(2.0 ** -101)
+    M, rs = q.q8_quantize_matrix_rows(ctx, W) if by_row else (q.q8_quantize_matrix(ctx, W), None)
+    if tiled:
+        M = q.q8_pack_tiles(ctx, M)
+    codes = np_(M.data)[:, :cols].astype(np.int64)
+    call = lambda Xd, bias, Y: q.q8_gemm_narrow_rows(ctx, M, rs, Xd, bias, Y=Y) if by_row else q.q8_gemm_narrow(ctx, M, Xd, bias, Y=Y)
+    for pitch, bias in ((rows, b), (rows + 3, None)):
+        Y = ctx.empty(n, pitch)
+        Y.fill_(7.0)
+        call(ctx.f32(X), ctx.f32(bias), Y[:, :rows])
+        got = np_(Y)
+        assert (got[:, rows:] == 7.0).all()
+        for j in sorted({0, 1, 3, 15, 16, n // 2, n - 2, n - 1} & set(range(n))):
+            xq, xs = oracle.quantize(X[j])
+            acc = (codes @ xq[:cols].astype(np.int64)).astype(np.float32)
+            y = acc * ((np_(rs) if by_row else np.float32(M.scale)) * np.float32(xs))
+            assert_same(got[j, :rows], y if bias is None else y + bias, "vector %d" % j)
+    X[2, cols // 2] = np.inf
+    one, two = ctx.empty(n, rows), _beside(ctx, X, rows)
+    call(ctx.f32(X), None, one)
+    call(two[1], None, two[0])
+    np.testing.assert_array_equal(np_(one), np_(two[0].contiguous()))
+    assert np.isfinite(np_(one)[np.arange(n) != 2]).all()
+
+
+def _beside(ctx, X, rows):
+    """Results and vectors side by side in one buffer: vectors that lie among their results are quantized in a launch of their own."""
+    at = (rows + 3) // 4 * 4
+    buf = ctx.empty(X.shape[0], at + (X.shape[1] + 3) // 4 * 4)
+    buf[:, at:at + X.shape[1]] = ctx.f32(X)
+    return buf[:, :rows], buf[:, at:at + X.shape[1]]
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled,route", [s for s in LARGE_PANELS + WHOLE_PANELS if s[0] * s[2] <= 1 << 20])
+def test_panels_of_vectors_that_lie_among_their_results(q, rows, cols, n, tiled, route):
+    """Quantization and product in two launches, at the sizes that one launch takes otherwise: the kernels that the products of already
+    quantized vectors use.  The same bits."""
+    rng = np.random.default_rng(rows + n + cols)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=rows, max_ld=4112))
+    M = q.q8_quantize_matrix(ctx, _w(rng, rows, cols))
+    if tiled:
+        M = q.q8_pack_tiles(ctx, M)
+    X, b = rng.standard_normal((n, cols)).astype(np.float32), ctx.f32((rng.standard_normal(rows) * 0.01).astype(np.float32))
+    Y, Xd = _beside(ctx, X, rows)
+    q.q8_gemm_narrow(ctx, M, Xd, b, Y=Y)
+    assert_same(q.q8_gemm_narrow(ctx, M, ctx.f32(X), b), np_(Y.contiguous()), "results")

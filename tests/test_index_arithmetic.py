@@ -186,6 +186,20 @@ def test_batched_encoder_with_rows_of_x_fits_the_lds(lib, H, xs):
     assert 0 < lib.q8x_enc_x_lds(H, xs) <= 160 * 1024 - 2048
 
 
+def test_panel_products_that_quantize_their_vectors(lib):
+    """The device tests' shapes take the kernel, in the form they are listed for, and no shape takes more blocks than the rule says."""
+    from test_gpu_products import QUANT_PANELS
+    seen = set()
+    for rows, cols, n, tiled, tiles in QUANT_PANELS:
+        ld = (cols + 15) // 16 * 16
+        assert lib.q8x_quant_rows(rows, ld, n) == tiles, (rows, cols, n)
+        seen.add((tiles, 1 + (ld > 512) + (ld > 1024)))
+    assert seen == {(t, k) for t in (1, 2, 4) for k in (1, 2, 3)}
+    for n in (1, 8):
+        assert lib.q8x_quant_rows(1024, 512, n) == 0
+    assert lib.q8x_quant_rows(1024, 2064, 9) == 0 and lib.q8x_quant_rows(1024, 2048, 257) == 0 and lib.q8x_quant_rows(1024, 2048, 256) == 4
+
+
 @pytest.mark.parametrize("ldx,ldh", [(16, 16), (64, 1024), (512, 1024), (624, 1008), (1024, 1024), (1040, 1024), (2000, 1008), (2048, 1024), (1024, 2048), (4096, 16)])
 def test_gru_parts_cover_both_products_once(lib, ldx, ldh):
     """Every 64-byte step of either product's rows belongs to one part, and no part has more than the stages' steps."""
