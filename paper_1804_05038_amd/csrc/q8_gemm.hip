@@ -871,6 +871,7 @@ q8_status q8i_gemm_jobs(q8_ctx *ctx, const q8i_gemm_job *d, int njobs, int n)
         if (a.ld % 128) shape.lines = 0;
         if (a.ldy % 4 || ((uintptr_t)a.Y & 15)) shape.whole = 0;
     }
+    if (const int tiles = q8_part_rows(&shape)) return q8i_gemm_part(ctx, jobs, max_rows, shape.max_ld, n, njobs, tiles);
     switch (q8_panel_route(&shape)) {
     case Q8_ROUTE_ONCE_64X64: return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 64, 64, false);
     case Q8_ROUTE_ONCE_128X32: return q8i_gemm_once(ctx, jobs, max_rows, n, njobs, 128, 32, false);

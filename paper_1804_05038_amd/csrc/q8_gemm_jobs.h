@@ -32,5 +32,7 @@ q8_status q8i_gemm_once(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, 
 q8_status q8i_gemm_resident_1024(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs);
 // row_blocks: of all products; each has as many shares of the vectors as give every compute unit a block
 q8_status q8i_gemm_stream(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int n, int njobs, int row_blocks);
+// q8_gemm_quant.hip; tiles of 16 rows per block (q8_part_rows)
+q8_status q8i_gemm_part(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int max_ld, int n, int njobs, int tiles);
 
 #endif

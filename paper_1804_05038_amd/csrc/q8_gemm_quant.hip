@@ -1,5 +1,5 @@
 // q8_gemm_quant.hip -- a panel product of few vectors in one launch: every block quantizes the vectors it multiplies.
-#include "q8_internal.h"
+#include "q8_gemm_jobs.h"
 #include "q8_route.h"
 
 // Block of eight waves: 16 RT rows x 16 vectors.  A wave takes the floats of two vectors, makes their codes by itself (maximum
@@ -100,6 +100,79 @@ __global__ __launch_bounds__(512) void gemm_quant_kernel(GemmQuantArgs a)
         if (a.bias) y = y + bias;
         a.Y[(size_t)(c0 + col) * a.ldy + r0 + row] = y;
     }
+}
+
+// The same from codes that are there already, up to three products in a launch: a wave loads its part of 16 vectors' codes as the
+// matrix cores take them, so nothing waits for anything but its own operands until the parts' sums meet.
+template <int RT, int SW>
+__global__ __launch_bounds__(512) void gemm_part_kernel(GemmJobs jobs)
+{
+    constexpr int SP = 20;
+    __shared__ __align__(16) int s_p[8 * RT * 16 * SP];                // [8 parts][RT][16 vectors][SP]
+    const GemmArgs &a = jobs.j[blockIdx.z];
+    const int r0 = (int)blockIdx.x * 16 * RT, c0 = (int)blockIdx.y * 16, rows = a.rows, ld = a.ld;
+    if (r0 >= rows) return;                                            // the grid is sized for the largest job
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
+    const bool tiled = a.Wt != nullptr;
+    const int S = (ld + 63) >> 6, k0 = S * wave >> 3, k1 = S * (wave + 1) >> 3;
+    const __amdgpu_buffer_rsrc_t rq = q8_rsrc(a.xq, (size_t)a.n * ld), rw = tiled ? q8_rsrc(a.Wt, (size_t)a.ntiles * 16 * ld) : q8_rsrc(a.W, (size_t)rows * ld);
+    v4i xv[SW], av[RT][SW], acc[RT];
+#pragma unroll
+    for (int s = 0; s < SW; ++s) {
+        const int k = 64 * (k0 + s) + 16 * g;
+        xv[s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rq, (int)(c0 + i < a.n && k0 + s < k1 && k < ld ? (unsigned)(c0 + i) * (unsigned)ld + k : Q8_OOB), 0, 0));
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int row0 = r0 + 16 * t;
+        const unsigned base = tiled ? ((unsigned)(row0 >> 4) * (unsigned)(ld >> 6) << 10) + 16u * lane : (unsigned)(row0 + i) * (unsigned)ld + 16u * g;
+        const bool ok = (tiled ? row0 : row0 + i) < rows;
+#pragma unroll
+        for (int s = 0; s < SW; ++s) {
+            const int ks = k0 + s;
+            const bool in = ok && ks < k1 && 64 * ks + (tiled ? 0 : 16 * g) < ld;
+            av[t][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(in ? base + (tiled ? 1024u : 64u) * ks : Q8_OOB), 0, 0));
+        }
+        acc[t] = (v4i){0, 0, 0, 0};
+    }
+    // this thread finishes row `row` of vectors col0, col0 + 32 / RT, ..
+    const int row = tid % (16 * RT), col0 = tid / (16 * RT), at = min(r0 + row, rows - 1);
+    const float bias = a.bias ? a.bias[at] : 0.0f, rs = a.row_scale ? a.row_scale[at] : a.w_scale;
+    float xs[(RT + 1) / 2];
+#pragma unroll
+    for (int j = 0; j < (RT + 1) / 2; ++j) xs[j] = a.xscale[min(c0 + col0 + j * 32 / RT, a.n - 1)];
+#pragma unroll
+    for (int s = 0; s < SW; ++s)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[t][s], xv[s], acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) *(v4i *)(s_p + ((wave * RT + t) * 16 + i) * SP + 4 * g) = acc[t];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < (RT + 1) / 2; ++j) {
+        const int col = col0 + j * 32 / RT;
+        if (col >= 16 || c0 + col >= a.n || r0 + row >= rows) continue;
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) sum += s_p[((w * RT + (row >> 4)) * 16 + col) * SP + (row & 15)];
+        float y = (float)sum * (rs * xs[j]);
+        if (a.bias) y = y + bias;
+        a.Y[(size_t)(c0 + col) * a.ldy + r0 + row] = y;
+    }
+}
+
+template <int RT> static q8_status launch_part(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int max_ld, int n, int njobs)
+{
+    const dim3 grid((max_rows + 16 * RT - 1) / (16 * RT), (n + 15) / 16, njobs);
+    if (max_ld <= 1024) Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_part_kernel<RT, 2>), grid, dim3(512), 0, jobs);
+    else Q8_LAUNCH(ctx, Q8_KERNEL_MFMA, (gemm_part_kernel<RT, 4>), grid, dim3(512), 0, jobs);
+    return q8i_launch_check(ctx, "gemm");
+}
+
+q8_status q8i_gemm_part(q8_ctx *ctx, const GemmJobs &jobs, int max_rows, int max_ld, int n, int njobs, int tiles)
+{
+    return tiles == 1 ? launch_part<1>(ctx, jobs, max_rows, max_ld, n, njobs) : tiles == 2 ? launch_part<2>(ctx, jobs, max_rows, max_ld, n, njobs)
+                                                                                          : launch_part<4>(ctx, jobs, max_rows, max_ld, n, njobs);
 }
 
 template <int RT, int SW> static q8_status launch_quant(q8_ctx *ctx, const GemmQuantArgs &a)

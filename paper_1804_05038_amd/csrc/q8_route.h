@@ -92,3 +92,17 @@ static inline int q8_quant_rows(int rows, int ld, int n)
     if (n <= 8 || ld > 2048 || (tiles + 3) / 4 * groups > (ld > 1024 ? 256 : ld > 512 ? 550 : 850)) return 0;
     return tiles * groups <= 256 ? 1 : tiles * groups <= 512 ? 2 : 4;
 }
+
+// The same for products of codes that are there already (gemm_part_kernel), all of a launch: 0 where the kernel of q8_panel_route is
+// as fast or faster, which is where more than 256 blocks of four tiles read the same operands again, and rows of at most 512
+// bytes (K-resident).  Four decoder steps at beam 5, us, without / with it: rows of 624 / 1008 / 2000 bytes, 4 / 12 sentences 325 / 291, 354 / 331,
+// and with up to 64 blocks per vector group, 30 / 64 sentences 400 / 411, 490 / 545; rows of 512 / 1024 / 2048 bytes, 4 sentences 292 / 285.
+static inline int q8_part_rows(const q8_panel_shape *s)
+{
+    long long tiles = 0, blocks = 0;
+    const int groups = (s->n + 15) / 16;
+    if (!s->plain || s->n <= 8 || s->max_ld > 2048 || s->max_ld <= 512) return 0;
+    for (int t = 0; t < s->njobs; ++t) { tiles += (s->rows[t] + 15) / 16; blocks += (s->rows[t] + 63) / 64; }
+    if (blocks * groups > 256) return 0;
+    return tiles * groups <= 256 ? 1 : tiles * groups <= 512 ? 2 : 4;
+}

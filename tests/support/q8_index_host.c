@@ -78,6 +78,11 @@ int q8x_enc_scale(int it, int slot) { return q8_enc_scale(it, slot); }
 int q8x_enc_x_scale(int it, int slot) { return q8_enc_x_scale(it, slot); }
 
 int q8x_quant_rows(int rows, int ld, int n) { return q8_quant_rows(rows, ld, n); }
+int q8x_part_rows(int rows, int ld, int n, int njobs)
+{
+    q8_panel_shape s = {njobs, {rows, rows, rows}, n, ld, ld, 1, 0, 0, 0, 0};
+    return q8_part_rows(&s);
+}
 
 /* Columns (tiles of 32 vectors) per block, whether the launch takes the shape, and the parts of the k range, of gru_tile_kernel */
 int q8x_gru_tile(int H, int ldx, int ldh, int n, int codes, int *columns, int *nx, int *k0, int *steps, int *stages)

@@ -372,7 +372,12 @@ def _beside(ctx, X, rows):
     return buf[:, :rows], buf[:, at:at + X.shape[1]]
 
 
-@pytest.mark.parametrize("rows,cols,n,tiled,route", [s for s in LARGE_PANELS + WHOLE_PANELS if s[0] * s[2] <= 1 << 20])
+# few results from codes that are there: the k range in eight parts (tiles of 16 rows per block, checked against the rule on the host)
+PART_PANELS = [(1, 516, 9, False, 1), (129, 1024, 31, True, 1), (65, 2048, 33, True, 1), (1000, 1008, 100, False, 2), (1024, 2048, 70, True, 2),
+               (3071, 2000, 61, False, 4), (1030, 1024, 240, True, 4)]
+
+
+@pytest.mark.parametrize("rows,cols,n,tiled,route", [s for s in LARGE_PANELS + WHOLE_PANELS if s[0] * s[2] <= 1 << 20] + PART_PANELS)
 def test_panels_of_vectors_that_lie_among_their_results(q, rows, cols, n, tiled, route):
     """Quantization and product in two launches, at the sizes that one launch takes otherwise: the kernels that the products of already
     quantized vectors use.  The same bits."""

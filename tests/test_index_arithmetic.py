@@ -196,7 +196,11 @@ def test_panel_products_that_quantize_their_vectors(lib):
         seen.add((tiles, 1 + (ld > 512) + (ld > 1024)))
     assert seen == {(t, k) for t in (1, 2, 4) for k in (1, 2, 3)}
     for n in (1, 8):
-        assert lib.q8x_quant_rows(1024, 512, n) == 0
+        assert lib.q8x_quant_rows(1024, 512, n) == 0 and lib.q8x_part_rows(1024, 1024, n, 1) == 0
+    from test_gpu_products import PART_PANELS
+    for rows, cols, n, tiled, tiles in PART_PANELS:
+        assert lib.q8x_part_rows(rows, (cols + 15) // 16 * 16, n, 1) == tiles, (rows, cols, n)
+    assert lib.q8x_part_rows(1024, 1024, 80, 3) == 4 and lib.q8x_part_rows(1024, 1024, 81, 3) == 0 and lib.q8x_part_rows(1024, 512, 9, 1) == 0
     assert lib.q8x_quant_rows(1024, 2064, 9) == 0 and lib.q8x_quant_rows(1024, 2048, 257) == 0 and lib.q8x_quant_rows(1024, 2048, 256) == 4
 
 
