@@ -254,16 +254,17 @@ q8_status output_logits_q8(q8_ctx *ctx, const q8_readout_weights *ro, const q8_m
 /* The encoder of Eq. 1 for n_sent sentences side by side: X [L x E] holds their embedding
  * vectors back to back, sentence s in rows [sent_off[s], sent_off[s + 1]) (sent_off: device
  * int32 [n_sent + 1]; sent_off_host: the same values on the host, sent_off_host[0] = 0);
- * enc_h [L x 2H] as q8_encode.  All input products run as matrix-core panels; the recurrences of all
+ * enc_h [L x 2H] as q8_encode.  The recurrences of all
  * sentences, both directions, are one launch for H <= 1024 (rows of Wh of at most 1024 bytes), up to 512
- * sentences of H = 1024 and, mostly, 3 words and more; else one launch per time step (at H = 1024 for up
+ * sentences of H = 1024 and, mostly, 3 words and more, which multiplies the rows of X as well up to 64 sentences of
+ * H = 1024 and rows of 640 bytes (else they are matrix-core panels in front); else one launch per time step (at H = 1024 for up
  * to 256 sentences) or a quantize / product / gates triple.  Blocks of that launch wait for each other's states, but
  * nothing depends on them running side by side: a wait that takes too long (some milliseconds, or the bound
  * of q8_encoder_options if that is smaller) ends in one block working its sentences off alone, which is
- * slow and gives the same states.  Batched encoders of one process take turns on a device while their blocks
- * start, whatever their streams; beside other kernels whose blocks wait (q8_attention_options names them) and
- * other processes' encoders such a wait is possible, and q8_encoder_options with one_launch = 0 takes it out:
- * a launch per time step or the triple, without any wait.
+ * slow and gives the same states.  Encoders of one process, batched or of one sentence, take turns on a device while their
+ * blocks start, whatever their streams (whoever waits for a turn does so on its stream, 40 ms at most); beside other kernels whose
+ * blocks wait (q8_attention_options names them) and other processes' encoders such a wait is possible, and
+ * q8_encoder_options with one_launch = 0 takes it out: a launch per time step or the triple, without any wait.
  * Values are those of q8_encode sentence by sentence.  Needs q8_encode_batch_bytes(fwd, L, n_sent) bytes of
  * workspace. */
 size_t q8_encode_batch_bytes(const q8_gru_weights *fwd, int total_l, int n_sent);
@@ -286,21 +287,23 @@ q8_status cgru_decoder_step_batch_q8(q8_ctx *ctx, const q8_cgru_weights *w, cons
 
 /* Bidirectional GRU encoder of Eq. 1 over l embedding vectors X [l x E]:
  * enc_h [l x 2H], backward state in columns [0,H), forward state in [H,2H); both
- * recurrences start from zero.  The input products for all positions run as one
- * narrow/MFMA product per direction, the l recurrent steps run in sequence. */
+ * recurrences start from zero.  q8_encoder_options says how it runs. */
 q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd,
                     const float *X, int l, float *enc_h);
 
-/* How q8_encode and q8_encode_batch (see there) run the recurrence.  q8_encode, one_launch != 0 (the default): all positions in one
- * launch where the shape is covered (H % 8 == 0, H <= 2048, rows of Wh of at most 2048 bytes,
- * not under stream capture) and the device can hold 2 H / 8 blocks of 512 threads at once;
- * otherwise, and with one_launch == 0, one launch per position.  Both give the same bits.
- * Inside the one-launch kernel blocks wait for each other's results; every such wait gives up
- * after spin_limit polls (<= 0: the default, 2^20) and the kernel then still ends, leaving enc_h
- * invalid and a flag in the workspace that q8_encode_check reports.  The grid fits the device,
- * so every block runs and the waits end; the bound is a safety net.
- * q8_encode_check waits for the stream and returns Q8_ERR_DEVICE if an encoder launch since the
- * last check gave up (q8_translate and q8_translate_ensemble call it themselves). */
+/* How q8_encode and q8_encode_batch (see there) run.  q8_encode, one_launch != 0 (the default), takes the first of these whose
+ * shape fits, outside of stream capture:
+ *   H <= 1024, rows of Wh and of X (the same pitch for both directions) of at most 1024 bytes, and for H > 512 at least 5 words (8 if
+ *   rows of X are longer than 640 bytes): X is quantized in one launch, all else is another, 2 ceil(H / 32) blocks of 768 threads on two
+ *   of the device's eight XCDs.  Its blocks start in turn with other encoders' (q8_encode_batch above).  A wait for another block's
+ *   states ends after some milliseconds at most, or after spin_limit polls if they are fewer; a block then works
+ *   its direction off alone, which is slow (spin_limit apart, only a block that found no room makes that happen) and gives the same states.
+ *   H % 8 == 0, H <= 2048, rows of Wh of at most 2048 bytes: the products of X, then the recurrence in one launch of 2 H / 8 blocks of 512
+ *   threads, if the device holds them at once.  Its waits end after spin_limit polls, and enc_h is then not valid.
+ * Otherwise, and with one_launch == 0: the products, then a launch per position.  All forms give the same bits.
+ * spin_limit <= 0 is the default, 2^20 polls.
+ * q8_encode_check waits for the stream and returns Q8_ERR_DEVICE if spin_limit ended a wait of q8_encode since the last check: what was
+ * encoded since is not to be relied on (q8_translate and q8_translate_ensemble call it themselves). */
 q8_status q8_encoder_options(q8_ctx *ctx, int one_launch, int spin_limit);
 q8_status q8_encode_check(q8_ctx *ctx);
 
@@ -323,10 +326,11 @@ q8_status q8_encode_check(q8_ctx *ctx);
  * Contexts whose decoder steps may run at the same time on one device (different streams): the
  * blocks of the exchange form wait for each other, so the attention grids that can be in flight
  * together must fit the device together (l n_beam blocks of 1024 threads each, two per compute
- * unit); give the contexts beyond that exchange = 0.  The same holds for q8_encoder_options'
- * one-launch recurrence (2 H / 8 blocks of 512 threads) and for the batched step's one-kernel
- * GRU (H / 32 x ceil(slots / 48) blocks of 768 threads, one per compute unit).  q8_encode_batch's
- * one-launch recurrences fill the device (up to 256 blocks of 1024 threads, one per compute unit): beside
+ * unit); give the contexts beyond that exchange = 0.  The same holds for the recurrence of 2 H / 8 blocks of
+ * 512 threads (q8_encoder_options) and for the batched step's one-kernel
+ * GRU (H / 32 x ceil(slots / 48) blocks of 768 threads, one per compute unit).  The encoders that are one launch
+ * fill the device (q8_encode_batch: up to 256 blocks of 1024 threads, one per compute unit) or two of its XCDs (q8_encode: up to 32
+ * blocks of 768 threads on each, one per compute unit): beside
  * any of these each may wait for the other's room until the encoder's bound (some milliseconds) has
  * passed, which costs time and nothing else; one_launch = 0 there avoids it.  The waits inside the
  * selection kernels (output_logits_beam_q8 and its forms, output_logits_beam_ahead_q8's blocks that

@@ -591,8 +591,10 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 // cores' sixteen columns one is used: that takes no sums across lanes); the fifth wave applies the gates, r in its lower
 // half and z in its upper, and publishes.  While the words travel, the next position's products of X are made, from
 // rows that lie in LDS, `chunk` at a time.  Words, turns and what the members do when they are spread over several XCDs: as
-// in enc_group_kernel with one group.  A wait is bounded; a block whose wait gives up sets *err and leaves, the others then
-// leave as well.  Arithmetic of quantize_rows_kernel, the products and encoder_persistent_kernel, value for value.
+// in enc_group_kernel with one group.  Arithmetic of quantize_rows_kernel, the products and encoder_persistent_kernel, value for value.
+// Nobody has to be resident for the result to be right: a wait is bounded, the first block of a direction whose wait gives up
+// works the direction off by itself (enc_one_alone), and the others leave when they next look at its word.  What they stored
+// before is what it stores, and it reads no states but its own, so it need not be the last.
 // The chain of a step bounds it: 1.48 us per position, E = 512, H = 1024 (encoder_persistent_kernel, 256 blocks all over the
 // device: 1.83, and two launches more in front).  q8_encode of 50 words, us: 99 -> 83; on four streams at once, per sentence 114 -> 52.
 // Not kept: dot products and gates on every wave, two units of sixteen waves or four of eight (129 and 101 us: sums across
@@ -606,12 +608,68 @@ struct EncOneArgs {
     const float *xs;
     float *enc_h;                        // [l x 2H]
     unsigned *words;                     // [2 turns][2 directions][H], ENCG_ABSENT on entry
-    unsigned *where;                     // [2][32], ENCG_ABSENT on entry
-    unsigned *err;
+    unsigned *ctl;                       // [2][4]: a wait gave up, a block works the direction off; [2][32]: the XCD of each member; ENCG_ABSENT on entry
+    unsigned *err;                       // set where the caller's own bound ended a wait
     int l, H, ld, ldx, members, first, spin_limit, chunk;
     float wh_scale[2], wx_scale[2];
 };
 #define ENC1_WAVES 12
+
+// What a block of direction dir does that leaves early (flag 2: the caller's own bound ended its wait): the first one works the
+// direction off, all positions and units, a wave per unit as in encoder_persistent_kernel.  q, xq: 1024 bytes of LDS each.
+// A position of 1024 units takes it 310 us (64: 13).  (Kept out of the loop of enc_one_kernel, down to the claim, and told to be unlikely: with the
+// claim made in the waits, or the loop left through an ordinary branch, a position took 1.55 to 1.70 us in place of 1.50.)
+static __device__ __forceinline__ void enc_one_alone(const EncOneArgs *p, int dir, int flag, int8_t *q, int8_t *xq)
+{
+    const EncOneArgs &a = *p;
+    if (threadIdx.x == 0) {
+        *(unsigned *)q = __hip_atomic_exchange(a.ctl + 4 * dir + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (flag == 2) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    const unsigned before = *(const unsigned *)q;
+    __syncthreads();
+    if (before != ENCG_ABSENT) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), d = __builtin_amdgcn_readfirstlane(dir);
+    const int H = __builtin_amdgcn_readfirstlane(a.H), L = __builtin_amdgcn_readfirstlane(a.l), ld = a.ld, ldx = a.ldx, col0 = d == 0 ? H : 0;
+    const v4i none = {0, 0, 0, 0};
+    for (int t = 0; t < L; ++t) {
+        const int pos = d == 0 ? t : L - 1 - t;
+        float *to = a.enc_h + (size_t)pos * 2 * H + col0;
+        const float *from = to + (d == 0 ? -2 * H : 2 * H);
+        float4 v[4];
+        float m = 0.0f, scale, inv;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int k = 4 * (lane + 64 * c);
+            v[c] = t > 0 && k < H ? *(const float4 *)(from + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            m = fmaxf(m, fmaxf(fmaxf(fabsf(v[c].x), fabsf(v[c].y)), fmaxf(fabsf(v[c].z), fabsf(v[c].w))));
+        }
+        q8_scale_of(wave_max_f(m), scale, inv);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (wave == c) *(int *)(q + 4 * (lane + 64 * c)) = q8_pack4(v[c].x, v[c].y, v[c].z, v[c].w, inv);
+        if (wave == 4 && 16 * lane < ldx) *(v4i *)(xq + 16 * lane) = *(const v4i *)(a.xq + (size_t)pos * ldx + 16 * lane);
+        const float ch = a.wh_scale[d] * scale, cx = a.wx_scale[d] * a.xs[pos];
+        __syncthreads();
+        for (int u = wave; u < H; u += ENC1_WAVES) {
+            float gx[3], gh[3];
+#pragma unroll
+            for (int g = 0; g < 3; ++g) {
+                const int row = g * H + u;
+                const v4i wh = 16 * lane < ld ? *(const v4i *)(a.Wh[d] + (size_t)row * ld + 16 * lane) : none;
+                const v4i wx = 16 * lane < ldx ? *(const v4i *)(a.Wx[d] + (size_t)row * ldx + 16 * lane) : none;
+                const float y = (float)group_sum_i(dot16(wh, *(const v4i *)(q + 16 * lane), 0), 64) * ch;
+                const float x = (float)group_sum_i(dot16(wx, 16 * lane < ldx ? *(const v4i *)(xq + 16 * lane) : none, 0), 64) * cx;
+                gh[g] = a.bh[d] ? y + a.bh[d][row] : y;
+                gx[g] = a.bx[d] ? x + a.bx[d][row] : x;
+            }
+            const float hn = gru_gates(gx, gh, t > 0 ? from[u] : 0.0f);
+            if (lane == 0) to[u] = hn;
+        }
+        __syncthreads();
+    }
+}
 
 template <int XS>
 __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
@@ -626,7 +684,7 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
     if (blockIdx.x + 8 >= gridDim.x && tid == 0) __hip_atomic_fetch_add(&enc_group_turn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int d = ((int)blockIdx.x - a.first) & 7, member = (int)blockIdx.x >> 3, H = a.H;
     if (d > 1) return;
-    unsigned *where = a.where + 32 * d;
+    unsigned *gave_up = a.ctl + 4 * d, *where = a.ctl + 8 + 32 * d;
     const int xcd = (int)__builtin_amdgcn_s_getreg(ENCG_XCC_ID);
     if (tid == 0) {
         s_flag = 0;
@@ -647,10 +705,10 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
         bx[k] = a.bx[d] && is ? a.bx[d][r] : -0.0f;
     }
     auto give_up = [&](int spins, int limit) {
-        if (spins < limit && ((spins & 63) != 0 || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)) return false;
+        if (spins < limit && ((spins & 63) != 0 || __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ENCG_ABSENT)) return false;
         if (lane == 0) {
-            s_flag = 1;
-            __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_flag = spins < a.spin_limit ? 1 : 2;
+            __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return true;
     };
@@ -663,7 +721,7 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
                 far = __any(x != xcd);
                 break;
             }
-            if (give_up(spins, a.spin_limit)) break;
+            if (give_up(spins, min(a.spin_limit, ENCG_SPINS))) break;
         }
         if (lane == 0) s_far = far;
     }
@@ -746,7 +804,7 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
             if ((lane & 15) == 0) *(v4i *)(s_e + wave * 16 + 4 * gq) = acc[0] + acc[1];
         }
         __syncthreads();
-        if (flag) break;
+        if (__builtin_expect(flag, 0)) break;
         if (wave == 4) {
             __builtin_amdgcn_s_setprio(2);
             const int u = lane & 31, at[2] = {32 * (lane >> 5) + u, 64 + u};       // sums of the lane's gate and of n (the other half of k 96 further on)
@@ -789,6 +847,7 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
         }
         xproducts(t + 1, xrow);
     }
+    if (__builtin_expect(s_flag, 0)) enc_one_alone((const EncOneArgs *)__builtin_amdgcn_kernarg_segment_ptr(), d, s_flag, s_q, s_x);
 }
 
 // =================================================================== host launchers ==
@@ -848,9 +907,10 @@ q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_wei
 }
 
 // Eq. 1 of one sentence in one launch.  Q8_OK with *launched = 0 where the shape is not covered, the device cannot hold all blocks
-// at once or the stream is being captured (what it takes then runs elsewhere).  words: 4 H + 64 words of scratch; xq [l x ldx], xs [l]: room
-// for the codes and scales of X; err: set to 1 by the kernel if a wait gave up.
-size_t q8i_enc_one_words(int H) { return (size_t)4 * H + 64; }
+// at once or the stream is being captured (what it takes then runs elsewhere).  words: q8i_enc_one_words of scratch; xq [l x ldx], xs [l]: room
+// for the codes and scales of X; err: set to 1 by the kernel if the context's own bound ended a wait (the states are right all the same).
+#define ENC1_CTL (8 + 2 * 32)
+size_t q8i_enc_one_words(int H) { return (size_t)4 * H + ENC1_CTL; }
 
 q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights *bwd, const float *X, int l, float *enc_h, unsigned *words,
                       int8_t *xq, float *xs, unsigned *err, int *launched)
@@ -871,11 +931,11 @@ q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weigh
     }
     // sentences on other streams on other XCDs, two at a time
     static std::atomic<unsigned> next{0};
-    const int first = 2 * (int)(next.fetch_add(1, std::memory_order_relaxed) & 3), clear = 4 * H + 64, cb = (clear + 255) / 256;
+    const int first = 2 * (int)(next.fetch_add(1, std::memory_order_relaxed) & 3), clear = 4 * H + ENC1_CTL, cb = (clear + 255) / 256;
     const int xs4 = ldx <= 512 ? 4 : ldx <= 640 ? 5 : 8, chunk = l < 49152 / (128 * xs4) ? l : 49152 / (128 * xs4);
     EncOneArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->Wx.data, bwd->Wx.data},
                     {ldx % 64 == 0 ? fwd->Wx.tiles : nullptr, ldx % 64 == 0 ? bwd->Wx.tiles : nullptr}, {fwd->bh, bwd->bh}, {fwd->bx, bwd->bx}, xq, xs, enc_h,
-                    words + 64, words, err, l, H, fwd->Wh.ld, ldx, members, first, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS, chunk,
+                    words + ENC1_CTL, words, err, l, H, fwd->Wh.ld, ldx, members, first, ctx->enc_spin_limit, chunk,
                     {fwd->Wh.scale, bwd->Wh.scale}, {fwd->Wx.scale, bwd->Wx.scale}};
     std::lock_guard<std::mutex> hold(enc_pair);
     hipLaunchKernelGGL(enc_group_front_kernel, dim3(1 + cb + (l + 3) / 4), dim3(256), 0, ctx->stream, words, clear, cb, X, fwd->Wx.cols, l, ldx, xq, xs);

@@ -27,7 +27,7 @@
 #define Q8_GATE_PAUSE_DEFAULT 8      // sleeps of about 0.45 us of the blocks that wait for the search step's decision, before their first poll
                                      // (0 to 14 measured alike; later than that the first poll comes after the decision)
 #define Q8_WS_SCRATCH_SLOT 6144
-#define Q8_WS_ENC_ERR 6208          // set to 1 by the one-launch encoder if a wait gave up (zeroed before each such launch)
+#define Q8_WS_ENC_ERR 6208          // set to 1 by an encoder of one sentence if spin_limit ended a wait (zero until then; q8_encode_check clears it)
 #define Q8_WS_ATT_ERR 6212          // the same for the attention kernel whose blocks wait for each other
 #define Q8_WS_ATT_XCHG 8192
 #define Q8_WS_ATT_XCHG_PER_HYP 2048
@@ -48,7 +48,7 @@ struct q8_ctx {
     // bytes at the top of the workspace held by a composite call (q8_translate) while it
     // issues other calls, which carve from the bottom
     size_t ws_reserved_top;
-    // q8_encode: the recurrence in one cooperative launch where possible (q8_encoder_options), and the
+    // q8_encode, q8_encode_batch: one launch where possible (q8_encoder_options), and the
     // bound of its internal waits in polls
     int enc_one_launch, enc_spin_limit;
     // attention of one sentence: the form whose blocks exchange energies and finish their own slices

@@ -769,6 +769,64 @@ def test_encoder_of_one_sentence_in_one_launch(q, E, H, l, tiled):
         assert_same(out, want, "a stream of its own")
 
 
+@pytest.mark.parametrize("E,H,l,tiled", [(512, 1024, 30, True), (620, 1000, 9, False), (516, 36, 150, False), (1024, 256, 60, True), (4, 4, 5, False)])
+def test_encoder_whose_waits_give_up_gives_the_same_states(q, E, H, l, tiled):
+    """Bounds of a few polls end some wait at the first position or further on, in one direction or both: a block works the
+    direction off, and enc_h is what a launch per position gives, bit for bit.  What the caller's bound ended is reported."""
+    rng = np.random.default_rng(E + l)
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=E + (k == "b"), I=E, H=H).items()}
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=160, max_rows=3 * H, max_ld=1040))
+    G = [q.GruWeights(gpu_mat(q, ctx, p[k + "Wx"], tiled), gpu_mat(q, ctx, p[k + "Wh"], tiled), ctx.f32(p[k + "bx"]) if k == "b" else None,
+                      ctx.f32(p[k + "bh"])) for k in ("f", "b")]
+    X = ctx.f32(rng.standard_normal((l, E)).astype(np.float32))
+    q.q8_encoder_options(ctx, False)
+    want = np_(q.q8_encode(ctx, G[0], G[1], X))
+    out, reported = ctx.empty(l, 2 * H), []
+    for bound in (1, 2, 3, 4, 6, 8, 0):
+        out.fill_(7.0)
+        q.q8_encoder_options(ctx, True, bound)
+        assert_same(q.q8_encode(ctx, G[0], G[1], X, enc_h=out), want, "a bound of %d polls" % bound)
+        try:
+            q.q8_encode_check(ctx)
+        except q.Q8Error:
+            reported.append(bound)
+    assert 0 not in reported and (H <= 32 or 1 in reported)
+
+
+def test_encoders_beside_a_batched_decoder(q):
+    """One sentence's encoder, a batch's and a batched decoder step whose GRUs fill the device, each on a stream of its own and each of
+    blocks that wait for each other: whoever gets the compute units first, all results are what they are alone."""
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=320, max_l=64, max_rows=50000, max_ld=2048) + (64 << 20))
+    m, P, enc_h, off, y, s = _panel_case(q, ctx, 64, 5, 12)
+    p = {k + n: v for k in ("f", "b") for n, v in synth.gru_cell(seed=5 + (k == "b"), I=512, H=1024).items()}
+    G = [q.GruWeights(gpu_mat(q, ctx, p[k + "Wx"], True), gpu_mat(q, ctx, p[k + "Wh"], True), ctx.f32(p[k + "bx"]), ctx.f32(p[k + "bh"])) for k in ("f", "b")]
+    X, lens = ctx.f32(np.random.default_rng(3).standard_normal((260, 512)).astype(np.float32)), [3, 20, 9, 33] * 4
+    step = q.cgru_decoder_step_batch_q8(ctx, m.dec, P, enc_h, off, 5, 12, y, s)
+    one, batch = np_(q.q8_encode(ctx, G[0], G[1], X[:40].contiguous())), np_(q.q8_encode_batch(ctx, G[0], G[1], X, lens))
+    step = {k: np_(v) for k, v in step.items()}
+    torch.cuda.synchronize()
+    lanes = []
+    for _ in range(3):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            lanes.append((st, q.Context(workspace_bytes=ctx.workspace.numel(), stream=st)))
+    X40, got = X[:40].contiguous(), []
+    torch.cuda.synchronize()
+    for _ in range(12):
+        with torch.cuda.stream(lanes[0][0]):
+            got.append((q.q8_encode(lanes[0][1], G[0], G[1], X40), one))
+        with torch.cuda.stream(lanes[1][0]):
+            r = q.cgru_decoder_step_batch_q8(lanes[1][1], m.dec, P, enc_h, off, 5, 12, y, s)
+            got += [(r[k], step[k]) for k in ("s", "ctx")]
+        with torch.cuda.stream(lanes[2][0]):
+            got.append((q.q8_encode_batch(lanes[2][1], G[0], G[1], X, lens), batch))
+    torch.cuda.synchronize()
+    for _, own in lanes:
+        q.q8_encode_check(own)
+    for have, want in got:
+        assert_same(have, want, "a stream of its own")
+
+
 @pytest.mark.parametrize("H,S,group", [(1024, 200, 64), (1000, 90, 60), (516, 512, 64)])
 def test_encoder_groups_of_a_set_keep_their_scales_apart(q, H, S, group):
     """Sets of several groups, whose states lie orders of magnitude apart (so that another sentence's scale would show): every
