@@ -101,7 +101,7 @@ q8_status gru_panel(q8_ctx *ctx, Carver &cv, const q8_gru_weights *g, const floa
     const int I = g->Wx.cols, H = g->Wh.cols;
     // products, gates and codes in one launch where the shape allows (no pre-activations in memory)
     const bool one_launch = !taps2 && q8i_gru_panel_ok(ctx, g, gh_pre != nullptr, n, H, H, out != nullptr, out ? out->ld1 : 0, out ? out->ld2 : 0, out && out->q2);
-    const bool tile = !taps2 && !gh_pre && !one_launch && q8i_gru_tile_ok(g, n, H, H, out != nullptr);
+    const bool tile = !taps2 && !gh_pre && !one_launch && q8i_gru_tile_ok(g, h_prev, H, h_out, H, n, out != nullptr);
     auto panel = [&](const int8_t *xq_, const float *xs_, const int8_t *hq_, const float *hs_) {
         return q8i_gru_panel(ctx, g, xq_, xs_, hq_, hs_, gh_pre, h_prev, H, h_out, H, n, out ? out->q1 : nullptr, out ? out->ld1 : 0,
                              out ? out->s1 : nullptr, out ? out->q2 : nullptr, out ? out->ld2 : 0, out ? out->s2 : nullptr, region);
@@ -657,7 +657,7 @@ q8_status cgru_decoder_step_batch_loop_q8(q8_ctx *ctx, const q8_cgru_weights *w,
     const bool s_keep = s_codes && s_codes->q && s_codes->scale && aligned16(s_codes->q) && s_codes->ld >= H &&
                         q8i_gru_gates_q_ok(H, H, H, s_codes->ld, s_codes->ld);
     // (GRU q multiplies both where its launch can, and where none takes the products with the recurrent half given)
-    const bool q_tile = !q8i_gru_panel_ok(ctx, &w->q, true, n, H, H, s_keep, s_keep ? s_codes->ld : 0, 0, false) && q8i_gru_tile_ok(&w->q, n, H, H, s_keep);
+    const bool q_tile = !q8i_gru_panel_ok(ctx, &w->q, true, n, H, H, s_keep, s_keep ? s_codes->ld : 0, 0, false) && q8i_gru_tile_ok(&w->q, s_mid, H, s_out, H, n, s_keep);
     const q8i_gemm_job gj[2] = {{&w->att_U, mq_u, ms_u, nullptr, a, A, nullptr, nullptr, nullptr, 0},
                                 {&w->q.Wh, mq_h, ms_h, w->q.bh, ghq, 3 * H, nullptr, nullptr, nullptr, 0}};
     TRY(q8i_gemm_jobs(ctx, gj, q_tile ? 1 : 2, n));

@@ -242,7 +242,7 @@ bool q8i_gru_gates_q_ok(int H, int ldh, int ldo, int ld1, int ld2);
 q8_status q8i_gru_gates_q(q8_ctx *ctx, const float *gx, const float *gh, const float *h_prev, int ldh, float *h_out,
                           int ldo, int H, int n, int8_t *q1, int ld1, float *s1, int8_t *q2, int ld2, float *s2);
 // products and gates in one launch (panels; codes of x and h_prev given)
-bool q8i_gru_tile_ok(const q8_gru_weights *g, int n, int ldp, int ldo, bool codes);       // codes: the caller quantizes them itself
+bool q8i_gru_tile_ok(const q8_gru_weights *g, const float *h_prev, int ldp, const float *h_out, int ldo, int n, bool codes);    // codes: the caller quantizes them itself
 q8_status q8i_gru_tile(q8_ctx *ctx, const q8_gru_weights *g, const int8_t *xq, const float *xs, const int8_t *hq, const float *hs,
                        const float *h_prev, int ldp, float *h_out, int ldo, int n);
 // products, gates and the codes of the new states in one launch (panels; shapes: q8i_gru_panel_ok).  gh_pre NULL:

@@ -735,6 +735,29 @@ def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled):
         assert_same(got[i:i + 8], np_(q.gru_step_q8(ctx, G, x[i:i + 8].contiguous(), h[i:i + 8].contiguous())), "vectors from %d" % i)
 
 
+@pytest.mark.parametrize("I,H,n", [(64, 64, 9), (620, 1000, 130), (36, 4, 64)])
+def test_panel_gru_of_results_between_vectors_of_four(q, I, H, n):
+    """Results need the alignment of a float and no more: where they don't begin at 16 bytes, products and gates run apart (the launch of both
+    stores four states at a time).  The same bits, and nothing around them touched."""
+    p = synth.gru_cell(seed=n, I=I, H=H)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=3 * H, max_ld=1024))
+    G = q.GruWeights(gpu_mat(q, ctx, p["Wx"]), gpu_mat(q, ctx, p["Wh"]), ctx.f32(p["bx"]), ctx.f32(p["bh"]))
+    rng = np.random.default_rng(n)
+    x, h = ctx.f32(rng.standard_normal((n, I)).astype(np.float32)), ctx.f32(np.tanh(rng.standard_normal((n, H))).astype(np.float32))
+    out = []
+    for at in (0, 1, 2, 3, 4):
+        buf = ctx.empty(n * H + 8)
+        assert buf.data_ptr() % 16 == 0
+        buf.fill_(7.0)
+        q.q8_profile_begin(ctx, "mfma", 16)
+        q.gru_step_q8(ctx, G, x, h, h_out=buf[at:at + n * H].view(n, H))
+        assert q.q8_profile_end(ctx)[1] == (1 if at % 4 else 0)
+        assert (np_(buf)[:at] == 7.0).all() and (np_(buf)[at + n * H:] == 7.0).all()
+        out.append(np_(buf)[at:at + n * H])
+    for at in (1, 2, 3, 4):
+        assert_same(out[at], out[0], "results %d floats further on" % at)
+
+
 @pytest.mark.parametrize("E,H,l,tiled", [(512, 1024, 97, True), (512, 1024, 1, False), (516, 132, 77, False), (640, 36, 2, False), (620, 1000, 30, False),
                                          (644, 64, 49, False), (1000, 1000, 9, False), (1024, 256, 48, True), (4, 4, 5, False), (1028, 64, 3, False)])
 def test_encoder_of_one_sentence_in_one_launch(q, E, H, l, tiled):
