@@ -720,9 +720,15 @@ def test_encoder_of_a_batch_multiplies_its_rows(q, E, H, lens, tiled):
     q.q8_encode_check(ctx)
 
 
-@pytest.mark.parametrize("I,H,n,tiled", [(64, 64, 9, True), (16, 36, 33, False), (100, 4, 700, False), (620, 1000, 129, False), (2000, 1000, 353, False),
-                                         (512, 1024, 1000, True), (2048, 1024, 513, True), (1024, 48, 300, False), (512, 2048, 300, True), (256, 512, 1024, True)])
-def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled):
+# inputs, units, vectors, tile-packed, tiles of 32 vectors per block of gru_tile_kernel (checked against the library's rule on the host; 0: the
+# kernel whose rows are 512 + 1024 bytes has this one where no codes are wanted)
+TILE_GRUS = [(64, 64, 9, True, 1), (16, 36, 33, False, 1), (100, 4, 700, False, 1), (620, 1000, 129, False, 1), (2000, 1000, 353, False, 2),
+             (512, 1024, 1000, True, 0), (2048, 1024, 513, True, 3), (1024, 48, 300, False, 1), (512, 2048, 300, True, 3), (256, 512, 1024, True, 2),
+             (516, 1000, 801, False, 4), (640, 1024, 1024, True, 4)]
+
+
+@pytest.mark.parametrize("I,H,n,tiled,columns", TILE_GRUS)
+def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled, columns):
     """Products and gates in one launch, at the edges of its blocks (32 units, 32 to 128 vectors, parts of the k range of either
     product, rows that end inside a step): the states of the narrow kernel on the same vectors, bit for bit."""
     p = synth.gru_cell(seed=n, I=I, H=H)
@@ -733,6 +739,42 @@ def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled):
     got = np_(q.gru_step_q8(ctx, G, x, h))
     for i in sorted({0, 8, n // 2, n - 8} & set(range(n - 7))):
         assert_same(got[i:i + 8], np_(q.gru_step_q8(ctx, G, x[i:i + 8].contiguous(), h[i:i + 8].contiguous())), "vectors from %d" % i)
+
+
+# E, H, A, sentences, beam, tile-packed, tiles of 32 vectors per block: batched steps both of whose GRUs run in gru_tile_kernel and leave their
+# states' codes (checked against the library's rule on the host)
+TILE_STEPS = [(512, 1024, 1024, 72, 5, True, 2), (620, 1000, 1000, 80, 5, False, 2), (512, 1024, 64, 129, 7, True, 4), (16, 1024, 64, 358, 1, False, 2),
+              (64, 2048, 64, 44, 4, True, 2)]
+
+
+@pytest.mark.parametrize("E,H,A,S,beam,tiled,columns", TILE_STEPS)
+def test_batched_step_whose_grus_run_in_tiles(q, oracle, E, H, A, S, beam, tiled, columns):
+    """Both transitions in one launch each, and the codes of the new states in another: the states of single sentences' steps, bit for
+    bit (those of GRU r's states enter through u(s') and GRU q), and the codes that the oracle makes of them.  One product launch is left, u(s')."""
+    rng = np.random.default_rng(H + S)
+    p, n, l = synth.cgru_step(seed=2, E=E, H=H, A=A, l=1, n_beam=1), S * beam, 3
+    lens = [1 + i % l for i in range(S)]
+    L, off = sum(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=n, max_l=8, max_rows=3 * H, max_ld=2 * H))
+    w = q.CgruWeights(gpu_gru(q, ctx, p, "dec_r", tiled), gpu_mat(q, ctx, p["att.U"], tiled), ctx.f32(p["att.v"]), gpu_gru(q, ctx, p, "dec_q", tiled))
+    enc_h, P = ctx.f32(np.tanh(rng.standard_normal((L, 2 * H))).astype(np.float32)), ctx.f32(rng.standard_normal((L, A)).astype(np.float32))
+    y, s0 = ctx.f32(rng.standard_normal((n, E)).astype(np.float32)), ctx.f32((rng.standard_normal((n, H)) * rng.uniform(0.05, 3.0, (n, 1))).astype(np.float32))
+    codes = q.Codes(ctx, n, w.r.Wx.ld), q.Codes(ctx, n, w.q.Wx.ld), q.Codes(ctx, n, w.r.Wh.ld)
+    offd = torch.tensor(off, device=ctx.device)
+    for call in range(2):
+        q.q8_profile_begin(ctx, "mfma", 16)
+        r = q.cgru_decoder_step_batch_q8(ctx, w, P, enc_h, offd, beam, l, y, s0, codes=codes)
+        assert q.q8_profile_end(ctx)[1] == 1
+    for si in sorted({0, 1, S // 3, S // 2, S - 2, S - 1}):
+        lo, hi, sl = off[si], off[si + 1], slice(si * beam, (si + 1) * beam)
+        r1 = q.cgru_decoder_step_q8(ctx, w, P[lo:hi].contiguous(), enc_h[lo:hi].contiguous(), y[sl].contiguous(), s0[sl].contiguous())
+        for key in ("s_mid", "ctx", "s"):
+            assert_same(r[key][sl], np_(r1[key]), "sentence %d %s vs single-sentence call" % (si, key))
+    for j in sorted({0, 31, 32, n // 2, n - 1}):
+        for key, c in (("s", codes[2]), ("ctx", codes[1])):
+            want, scale = oracle.quantize(np_(r[key])[j])
+            assert_same(c.q[j, :want.shape[0]], want, "codes of %s, slot %d" % (key, j))
+            assert float(c.scale[j]) == float(scale)
 
 
 @pytest.mark.parametrize("I,H,n", [(64, 64, 9), (620, 1000, 130), (36, 4, 64)])

@@ -226,6 +226,21 @@ def test_gru_tile_blocks_cover_the_vectors_in_one_round(lib):
     assert taken
 
 
+def test_panel_grus_in_tiles(lib):
+    """The device tests' shapes take the kernel, in the form they are listed for: one to four tiles, with codes and without."""
+    from test_gpu_batch import TILE_GRUS, TILE_STEPS
+    columns, nx, stages, k0, steps = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), _ints(3), _ints(3)
+    pitch = lambda cols: (cols + 15) // 16 * 16
+    takes = lambda I, H, n, codes: lib.q8x_gru_tile(H, pitch(I), pitch(H), n, codes, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
+    for I, H, n, tiled, want in TILE_GRUS:
+        assert (I, H, want) == (512, 1024, 0) or (takes(I, H, n, 0) and columns.value == want), (I, H, n)
+    for E, H, A, S, beam, tiled, want in TILE_STEPS:
+        assert S * beam > 336 or (E, H) != (512, 1024)       # (the kernel whose blocks exchange maxima takes up to 336)
+        for I in (E, 2 * H):
+            assert takes(I, H, S * beam, 1) and columns.value == want, (I, H, S, beam)
+    assert {c[-1] for c in TILE_GRUS} == {0, 1, 2, 3, 4} and {c[-1] for c in TILE_STEPS} >= {2, 4}
+
+
 ROUTES = ["staged", "resident", "resident 1024", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "once 128 x 64 trade", "stream"]
 
 
