@@ -293,8 +293,8 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
 
 /* How q8_encode and q8_encode_batch (see there) run.  q8_encode, one_launch != 0 (the default), takes the first of these whose
  * shape fits, outside of stream capture:
- *   H <= 1024, rows of Wh and of X (the same pitch for both directions) of at most 1024 bytes, and for H > 512 at least 5 words (8 if
- *   rows of X are longer than 640 bytes): X is quantized in one launch, all else is another, 2 ceil(H / 32) blocks of 768 threads on two
+ *   H <= 1024, rows of Wh and of X (the same pitch for both directions) of at most 1024 bytes, and, for H > 512 or row-major rows of X of
+ *   640 bytes and more, at least 5 to 8 words: X is quantized in one launch, all else is another, 2 ceil(H / 32) blocks of 768 threads on two
  *   of the device's eight XCDs.  Its blocks start in turn with other encoders' (q8_encode_batch above).  A wait for another block's
  *   states ends after some milliseconds at most, or after spin_limit polls if they are fewer; a block then works
  *   its direction off alone, which is slow (spin_limit apart, only a block that found no room makes that happen) and gives the same states.

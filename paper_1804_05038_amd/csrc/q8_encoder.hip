@@ -918,10 +918,8 @@ q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weigh
     *launched = 0;
     const int H = fwd->Wh.cols, ldx = fwd->Wx.ld, members = (H + ENCG_UNITS - 1) / ENCG_UNITS, blocks = 8 * members;
     if (H > 1024 || H % 4 || fwd->Wh.ld > 1024 || bwd->Wh.ld != fwd->Wh.ld || ldx > 1024 || bwd->Wx.ld != ldx) return Q8_OK;
-    // A few words don't pay for fetching both matrices into 64 blocks' registers (q8_encode, us, encoder_persistent_kernel / this: H = 1024,
-    // E = 512, 2 / 4 / 5 / 8 words 11.0 / 11.6, 14.6 / 14.9, 16.9 / 16.5, 23.0 / 20.8; E = 1024 4 / 7 / 8 words 15.1 / 17.1, 21.1 / 21.6, 23.4 / 23.1;
-    // H = 512, E = 512, 1 / 2 / 4 words 10.3 / 9.3, 10.7 / 10.6, 14.2 / 13.6).
-    if (H > 512 && l < (ldx <= 640 ? 5 : 8)) return Q8_OK;
+    const bool packed = H % 16 == 0 && ldx % 64 == 0 && fwd->Wx.tiles && bwd->Wx.tiles && fwd->Wh.tiles && bwd->Wh.tiles;
+    if (!q8_enc_one_better(H, ldx, packed, l)) return Q8_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return Q8_OK;
     int dev = 0, cus = 0;

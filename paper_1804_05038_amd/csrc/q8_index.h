@@ -122,6 +122,22 @@ Q8_INDEX_FN int q8_gru_tile_better(int H, int ldx, int ldh, int n, int codes)
     return codes ? (long long)n * H >= 360000 : n > 128 || ldx + ldh < 1024;
 }
 
+// ---- the encoder of one sentence (enc_one_kernel) ----
+
+// Whether it is faster than encoder_persistent_kernel for a sentence of l words: a few don't pay for fetching both matrices into the
+// registers of 64 blocks, above all not row-major ones (16 rows per request in place of one KiB).  q8_encode, us, the other / this:
+// H = 1024, packed, rows of X of 512 bytes, 4 / 5 words 14.6 / 14.9, 17.0 / 16.3; 640, 5 / 6 words 17.0 / 17.0, 19.0 / 18.5; 1024, 7 / 8 words 21.1 / 21.6,
+// 23.1 / 23.1.  H = 1024, row-major, 512, 5 / 6 words 16.9 / 17.3, 18.9 / 18.8; 640, 5 / 6 16.9 / 17.8, 18.9 / 19.4 (7: 20.9 / 21.2, 8: 23.1 / 22.7); H = 1000, 640,
+// 5 words 17.0 / 16.9.  H = 512, packed, 1024, 1 / 3 words 9.0 / 8.0, 12.1 / 11.6.  Row-major: H = 256, 512, 1 / 3 words 9.0 / 8.2, 11.7 / 11.6; 704, 1 / 2 / 4 / 5 words
+// 8.9 / 8.6, 10.0 / 10.5, 13.3 / 13.5, 15.2 / 15.2; 1024, 1 / 3 / 5 / 7 / 8 words 9.2 / 9.7, 11.7 / 13.4, 15.1 / 16.4, 18.6 / 19.4, 20.8 / 20.7.
+Q8_INDEX_FN int q8_enc_one_better(int H, int ldx, int packed, int l)
+{
+    const int rows = !packed && H > 1000;
+    if (H > 512) return l >= (ldx > 640 || (rows && ldx == 640) ? 8 : rows && ldx >= 512 ? 6 : 5);
+    if (packed || ldx < 640 || H % 8) return 1;                        // (H % 8: the other is a launch per position)
+    return ldx <= 704 ? l == 1 || l >= 5 : l >= (ldx <= 768 ? 7 : 8);
+}
+
 // ---- the batched encoder (enc_group_kernel) ----
 
 #define Q8_ENC_UNITS 32

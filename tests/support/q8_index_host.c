@@ -50,6 +50,8 @@ void q8x_panel_plans(int rows, int step, int ld, int n, unsigned long long *wors
     }
 }
 
+int q8x_enc_one_better(int H, int ldx, int packed, int l) { return q8_enc_one_better(H, ldx, packed, l); }
+
 int q8x_enc_one_launch(int H, int S, int max_l) { return q8_enc_one_launch(H, S, max_l); }
 
 /* The most LDS of those of [1, S] sentences of H units that are one launch, and 0 if some plan's groups don't cover a set, or its blocks the device */

@@ -241,6 +241,15 @@ def test_panel_grus_in_tiles(lib):
     assert {c[-1] for c in TILE_GRUS} == {0, 1, 2, 3, 4} and {c[-1] for c in TILE_STEPS} >= {2, 4}
 
 
+def test_encoder_of_one_sentence_is_one_launch_from_a_number_of_words_on(lib):
+    """Row-major matrices of few units need more words the longer the rows of X are; beyond 8 words every shape is one launch."""
+    one = lib.q8x_enc_one_better
+    for H, ldx, packed, words in ((1024, 512, 1, 5), (1024, 512, 0, 6), (1024, 448, 0, 5), (1024, 640, 1, 5), (1024, 624, 0, 6), (1024, 640, 0, 8), (1000, 624, 0, 5), (1024, 1024, 1, 8),
+                                  (512, 1024, 1, 1), (256, 512, 0, 1), (256, 768, 0, 7), (64, 1024, 0, 8), (36, 1024, 0, 1)):
+        assert [bool(one(H, ldx, packed, l)) for l in range(1, 12)] == [l >= words for l in range(1, 12)], (H, ldx, packed)
+    assert [l for l in range(1, 8) if one(256, 640, 0, l)] == [1, 5, 6, 7]
+
+
 ROUTES = ["staged", "resident", "resident 1024", "tiles of 64", "tiles of 128", "once 64 x 64", "once 128 x 32", "once 128 x 64", "once 128 x 64 trade", "stream"]
 
 
