@@ -154,12 +154,12 @@ template <int CT> static q8_status gru_tile_launch(q8_ctx *ctx, const GruTileArg
 
 bool q8i_gru_tile_ok(const q8_gru_weights *g, const float *h_prev, int ldp, const float *h_out, int ldo, int n, bool codes)
 {
-    const int H = g->Wh.cols;
+    const int H = g->Wh.cols, packed = H % 16 == 0 && g->Wx.tiles && g->Wx.ld % 64 == 0 && g->Wh.tiles && g->Wh.ld % 64 == 0;
     auto aligned = [](const void *p) { return ((uintptr_t)p & 15) == 0; };       // (states and biases move four at a time)
     return H % 4 == 0 && ldp % 4 == 0 && ldo % 4 == 0 && g->Wx.rows == 3 * H && g->Wh.rows == 3 * H && aligned(g->bx) && aligned(g->bh) &&
            aligned(h_prev) && aligned(h_out) &&
            (size_t)(3 * H + 15) * g->Wx.ld < (1u << 31) && (size_t)(3 * H + 15) * g->Wh.ld < (1u << 31) && (size_t)n * g->Wx.ld < (1u << 31) &&
-           (size_t)n * g->Wh.ld < (1u << 31) && n > 8 && q8_gru_tile_better(H, g->Wx.ld, g->Wh.ld, n, codes);
+           (size_t)n * g->Wh.ld < (1u << 31) && n > 8 && q8_gru_tile_better(H, g->Wx.ld, g->Wh.ld, n, codes, packed);
 }
 
 q8_status q8i_gru_tile(q8_ctx *ctx, const q8_gru_weights *g, const int8_t *xq, const float *xs, const int8_t *hq, const float *hs,

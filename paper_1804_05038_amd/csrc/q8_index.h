@@ -115,11 +115,19 @@ Q8_INDEX_FN int q8_gru_tile_columns(int H, int n)
 // Where the codes of the new states are wanted they cost a launch of 5.9 us, which the gates' kernel apart makes by the way: us per
 // decoder step, both transitions, H = 1000, 4 / 20 / 64 / 80 / 100 / 200 sentences at beam 5, 82 / 92 / 122 / 136 / 164 / 234 apart, 90 / 97 / 124 / 130 / 157 / 226 so,
 // H = 1024, 70 / 100 / 200 sentences 114 / 127 / 200 apart, 108 / 118 / 183 so.
-Q8_INDEX_FN int q8_gru_tile_better(int H, int ldx, int ldh, int n, int codes)
+// Rows of about the same length of both matrices leave one of the three parts half of all steps, and the products apart are at
+// their best with rows of at most 1024 bytes (or whole 128 bytes of 2048): H = 1024, 1024 + 1024 bytes, 129 / 160 / 192 / 224 vectors 13.4 / 13.7 / 14.2 / 14.8 apart,
+// 14.4 / 14.3 / 14.4 / 14.3 in one launch, H = 1000, 1008 + 1008 bytes, 129 / 160 / 176 11.3 / 11.9 / 13.4 and 12.1 / 12.3 / 12.4, H = 2048, 2048 + 2048 bytes, 129 / 176 / 224
+// 21.5 / 24.7 / 26.0 and 23.8 / 25.1 / 25.4 (but H = 1400, 1408 + 1408 bytes, 129 20.8 and 18.0, and packed, H = 1024, 1024 + 1024 bytes, 129 / 144 / 176 10.9 / 11.1 / 12.8 and 11.3 / 11.4 / 11.5).
+Q8_INDEX_FN int q8_gru_tile_better(int H, int ldx, int ldh, int n, int codes, int packed)
 {
-    const int cols = 32 * q8_gru_tile_columns(H, n);
+    const int cols = 32 * q8_gru_tile_columns(H, n), less = ldx < ldh ? ldx : ldh, more = ldx < ldh ? ldh : ldx;
     if ((long long)((H + 31) / 32) * ((n + cols - 1) / cols) > 256) return 0;
-    return codes ? (long long)n * H >= 360000 : n > 128 || ldx + ldh < 1024;
+    if (codes) return (long long)n * H >= 360000;
+    if (ldx + ldh < 1024) return 1;
+    if (8 * less < 7 * more || (more > 1024 && less < 2048)) return n > 128;
+    if (packed) return n > (more >= 1024 ? 144 : 128);
+    return n > (ldx % 128 == 0 && ldh % 128 == 0 ? 192 : 160);
 }
 
 // ---- the encoder of one sentence (enc_one_kernel) ----

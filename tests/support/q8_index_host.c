@@ -87,11 +87,11 @@ int q8x_part_rows(int rows, int ld, int n, int njobs)
 }
 
 /* Columns (tiles of 32 vectors) per block, whether the launch takes the shape, and the parts of the k range, of gru_tile_kernel */
-int q8x_gru_tile(int H, int ldx, int ldh, int n, int codes, int *columns, int *nx, int *k0, int *steps, int *stages)
+int q8x_gru_tile(int H, int ldx, int ldh, int n, int codes, int packed, int *columns, int *nx, int *k0, int *steps, int *stages)
 {
     *columns = q8_gru_tile_columns(H, n);
     *stages = q8_gru_parts(ldx, ldh, nx, k0, steps);
-    return q8_gru_tile_better(H, ldx, ldh, n, codes);
+    return q8_gru_tile_better(H, ldx, ldh, n, codes, packed);
 }
 
 /* The most LDS of a batched encoder of one group per set that multiplies X itself (rows of 128 xs bytes), and of any plan */

@@ -208,7 +208,7 @@ def test_panel_products_that_quantize_their_vectors(lib):
 def test_gru_parts_cover_both_products_once(lib, ldx, ldh):
     """Every 64-byte step of either product's rows belongs to one part, and no part has more than the stages' steps."""
     columns, nx, stages, k0, steps = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), _ints(3), _ints(3)
-    lib.q8x_gru_tile(1024, ldx, ldh, 64, 0, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
+    lib.q8x_gru_tile(1024, ldx, ldh, 64, 0, 0, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
     assert nx.value in (1, 2) and 2 * (stages.value - 1) < max(steps[:]) <= 2 * stages.value
     for parts, ld in ((range(nx.value), ldx), (range(nx.value, 3), ldh)):
         assert [s for p in parts for s in range(k0[p], k0[p] + steps[p])] == list(range((ld + 63) // 64))
@@ -220,7 +220,7 @@ def test_gru_tile_blocks_cover_the_vectors_in_one_round(lib):
     for H in (4, 32, 36, 256, 512, 1000, 1024, 2048, 8192):
         for n in (9, 32, 33, 128, 129, 350, 352, 353, 700, 1000, 1024):
             for codes in (0, 1):
-                if lib.q8x_gru_tile(H, 512, 512, n, codes, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages)):
+                if lib.q8x_gru_tile(H, 512, 512, n, codes, 1, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages)):
                     taken += 1
                     assert 1 <= columns.value <= 4 and (H + 31) // 32 * -(-n // (32 * columns.value)) <= 256
     assert taken
@@ -231,13 +231,16 @@ def test_panel_grus_in_tiles(lib):
     from test_gpu_batch import TILE_GRUS, TILE_STEPS
     columns, nx, stages, k0, steps = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), _ints(3), _ints(3)
     pitch = lambda cols: (cols + 15) // 16 * 16
-    takes = lambda I, H, n, codes: lib.q8x_gru_tile(H, pitch(I), pitch(H), n, codes, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
+    takes = lambda I, H, n, codes, packed: lib.q8x_gru_tile(H, pitch(I), pitch(H), n, codes, packed, ctypes.byref(columns), ctypes.byref(nx), k0, steps, ctypes.byref(stages))
     for I, H, n, tiled, want in TILE_GRUS:
-        assert (I, H, want) == (512, 1024, 0) or (takes(I, H, n, 0) and columns.value == want), (I, H, n)
+        assert (I, H, want) == (512, 1024, 0) or (takes(I, H, n, 0, tiled) and columns.value == want), (I, H, n)
     for E, H, A, S, beam, tiled, want in TILE_STEPS:
         assert S * beam > 336 or (E, H) != (512, 1024)       # (the kernel whose blocks exchange maxima takes up to 336)
         for I in (E, 2 * H):
-            assert takes(I, H, S * beam, 1) and columns.value == want, (I, H, S, beam)
+            assert takes(I, H, S * beam, 1, tiled) and columns.value == want, (I, H, S, beam)
+    for I, H, packed, most in ((1024, 1024, 0, 192), (1024, 1024, 1, 144), (768, 768, 1, 128), (1000, 1000, 0, 160), (2048, 2048, 0, 192), (1400, 1400, 0, 128), (620, 1000, 0, 128), (400, 400, 0, 0)):
+        assert not most or not takes(I, H, most, 0, packed), (I, H)
+        assert takes(I, H, most + 9, 0, packed), (I, H)
     assert {c[-1] for c in TILE_GRUS} == {0, 1, 2, 3, 4} and {c[-1] for c in TILE_STEPS} >= {2, 4}
 
 
