@@ -301,6 +301,8 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
  *   H % 8 == 0, H <= 2048, rows of Wh of at most 2048 bytes: the products of X, then the recurrence in one launch of 2 H / 8 blocks of 512
  *   threads, if the device holds them at once.  Its waits end after spin_limit polls, and enc_h is then not valid.
  * Otherwise, and with one_launch == 0: the products, then a launch per position.  All forms give the same bits.
+ * one_launch == 2: the same forms as 1, but blocks that share an XCD hand their states to each other device-coherently, as blocks that were spread over
+ * several do by themselves.  Slower, the same bits.
  * spin_limit <= 0 is the default, 2^20 polls.
  * q8_encode_check waits for the stream and returns Q8_ERR_DEVICE if spin_limit ended a wait of q8_encode since the last check: what was
  * encoded since is not to be relied on (q8_translate and q8_translate_ensemble call it themselves). */

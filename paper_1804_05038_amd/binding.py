@@ -550,7 +550,7 @@ def output_logits_q8(ctx, ro, W_out, b_out, s=None, y_emb=None, ctx_vec=None, t_
 
 
 def q8_encoder_options(ctx, one_launch=True, spin_limit=0):
-    ctx.check(ctx.lib.q8_encoder_options(ctx.handle, 1 if one_launch else 0, spin_limit))
+    ctx.check(ctx.lib.q8_encoder_options(ctx.handle, int(one_launch or 0), spin_limit))
 
 
 def q8_encode_check(ctx):

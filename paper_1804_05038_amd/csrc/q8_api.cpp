@@ -982,7 +982,7 @@ q8_status q8_encode(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weights
 q8_status q8_encoder_options(q8_ctx *ctx, int one_launch, int spin_limit)
 {
     if (!ctx) return Q8_ERR_NULL;
-    ctx->enc_one_launch = one_launch ? 1 : 0;
+    ctx->enc_one_launch = one_launch == 2 ? 2 : one_launch ? 1 : 0;
     ctx->enc_spin_limit = spin_limit > 0 ? spin_limit : Q8_ENC_SPIN_DEFAULT;
     return Q8_OK;
 }

@@ -139,7 +139,7 @@ struct EncGroupArgs {
     float *enc_h;                        // [L x 2H]
     unsigned *words;                     // [2 turns, 3 with several groups][2 directions][S][H], the first two ENCG_ABSENT on entry
     unsigned *ctl;                       // [sets][2]: members that left, a wait that gave up; [sets][32]: the XCD of each member; ENCG_ABSENT on entry
-    int S, H, ld, members, sets_per_dir, spin_limit;
+    int S, H, ld, members, sets_per_dir, spin_limit, far;               // far: as if the members were not all on one XCD
     float wh_scale[2];
     int ldx;
     float wx_scale[2];
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
             for (int spins = 1;; ++spins) {
                 const int x = lane < members ? __hip_atomic_load(where + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcd;
                 if (!__any(x == (int)ENCG_ABSENT)) {
-                    far = __any(x != xcd);
+                    far = a.far || __any(x != xcd);
                     break;
                 }
                 if (give_up(spins, a.spin_limit)) break;
@@ -610,7 +610,7 @@ struct EncOneArgs {
     unsigned *words;                     // [2 turns][2 directions][H], ENCG_ABSENT on entry
     unsigned *ctl;                       // [2][4]: a wait gave up, a block works the direction off; [2][32]: the XCD of each member; ENCG_ABSENT on entry
     unsigned *err;                       // set where the caller's own bound ended a wait
-    int l, H, ld, ldx, members, first, spin_limit, chunk;
+    int l, H, ld, ldx, members, first, spin_limit, chunk, far;
     float wh_scale[2], wx_scale[2];
 };
 #define ENC1_WAVES 12
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(64 * ENC1_WAVES) void enc_one_kernel(EncOneArgs a)
         for (int spins = 1;; ++spins) {
             const int x = lane < a.members ? (int)__hip_atomic_load(where + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcd;
             if (!__any(x == (int)ENCG_ABSENT)) {
-                far = __any(x != xcd);
+                far = a.far || __any(x != xcd);
                 break;
             }
             if (give_up(spins, min(a.spin_limit, ENCG_SPINS))) break;
@@ -894,7 +894,7 @@ q8_status q8i_enc_group(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_wei
     EncGroupArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->bh, bwd->bh}, {in->gxf, in->gxb},
                       {fwd->Wx.data, bwd->Wx.data}, {fwd->Wx.ld % 64 == 0 ? fwd->Wx.tiles : nullptr, bwd->Wx.ld % 64 == 0 ? bwd->Wx.tiles : nullptr},
                       {fwd->bx, bwd->bx}, in->xq, in->xs, sent_off, enc_h,
-                      words + (4 + 2 * 32) * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS,
+                      words + (4 + 2 * 32) * spd, words, S, H, fwd->Wh.ld, members, spd, ctx->enc_spin_limit < ENCG_SPINS ? ctx->enc_spin_limit : ENCG_SPINS, ctx->enc_one_launch == 2,
                       {fwd->Wh.scale, bwd->Wh.scale}, fwd->Wx.ld, {fwd->Wx.scale, bwd->Wx.scale}};
     const int blocks = 8 * members * ((2 * spd + 7) / 8);
     std::lock_guard<std::mutex> hold(enc_pair);
@@ -933,7 +933,7 @@ q8_status q8i_enc_one(q8_ctx *ctx, const q8_gru_weights *fwd, const q8_gru_weigh
     const int xs4 = ldx <= 512 ? 4 : ldx <= 640 ? 5 : 8, chunk = l < 49152 / (128 * xs4) ? l : 49152 / (128 * xs4);
     EncOneArgs a = {{fwd->Wh.data, bwd->Wh.data}, {fwd->Wh.tiles, bwd->Wh.tiles}, {fwd->Wx.data, bwd->Wx.data},
                     {ldx % 64 == 0 ? fwd->Wx.tiles : nullptr, ldx % 64 == 0 ? bwd->Wx.tiles : nullptr}, {fwd->bh, bwd->bh}, {fwd->bx, bwd->bx}, xq, xs, enc_h,
-                    words + ENC1_CTL, words, err, l, H, fwd->Wh.ld, ldx, members, first, ctx->enc_spin_limit, chunk,
+                    words + ENC1_CTL, words, err, l, H, fwd->Wh.ld, ldx, members, first, ctx->enc_spin_limit, chunk, ctx->enc_one_launch == 2,
                     {fwd->Wh.scale, bwd->Wh.scale}, {fwd->Wx.scale, bwd->Wx.scale}};
     std::lock_guard<std::mutex> hold(enc_pair);
     hipLaunchKernelGGL(enc_group_front_kernel, dim3(1 + cb + (l + 3) / 4), dim3(256), 0, ctx->stream, words, clear, cb, X, fwd->Wx.cols, l, ldx, xq, xs);

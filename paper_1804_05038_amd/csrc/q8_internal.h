@@ -48,7 +48,7 @@ struct q8_ctx {
     // bytes at the top of the workspace held by a composite call (q8_translate) while it
     // issues other calls, which carve from the bottom
     size_t ws_reserved_top;
-    // q8_encode, q8_encode_batch: one launch where possible (q8_encoder_options), and the
+    // q8_encode, q8_encode_batch: one launch where possible (q8_encoder_options; 2: states always handed over device-coherently), and the
     // bound of its internal waits in polls
     int enc_one_launch, enc_spin_limit;
     // attention of one sentence: the form whose blocks exchange energies and finish their own slices

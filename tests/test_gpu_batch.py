@@ -858,6 +858,36 @@ def test_encoder_whose_waits_give_up_gives_the_same_states(q, E, H, l, tiled):
     assert 0 not in reported and (H <= 32 or 1 in reported)
 
 
+@pytest.mark.parametrize("E,H,lens,tiled", [(512, 1024, [30], True), (620, 1000, [9], False), (516, 36, [150], False), (640, 256, [60], True), (4, 4, [5], False),
+                                            (512, 1024, [1, 9, 4] * 21 + [3], True), (516, 1000, [7, 2, 30], False), (644, 1024, [2, 6, 3] * 20, False),
+                                            (640, 36, [4, 17] * 20, False)])
+def test_encoders_whose_blocks_don_t_share_an_xcd(q, E, H, lens, tiled):
+    """States handed over device-coherently, as where a direction's or a set's blocks run on several XCDs: one sentence, and sentences of one group
+    per set with the products of X inside and apart.  What a launch per position gives, bit for bit, again and again, and under a bound of a few polls."""
+    rng = np.random.default_rng(E + len(lens))
+    p = {k + s: v for k in ("f", "b") for s, v in synth.gru_cell(seed=E + (k == "b"), I=E, H=H).items()}
+    L, one = sum(lens), len(lens) == 1
+    ctx = q.Context(workspace_bytes=q.q8_workspace_bytes(max_n=8, max_l=160, max_rows=3 * H, max_ld=1040) + 24 * L * H + (8 << 20))
+    G = [q.GruWeights(gpu_mat(q, ctx, p[k + "Wx"], tiled), gpu_mat(q, ctx, p[k + "Wh"], tiled), ctx.f32(p[k + "bx"]), ctx.f32(p[k + "bh"])) for k in ("f", "b")]
+    X, out = ctx.f32(rng.standard_normal((L, E)).astype(np.float32)), ctx.empty(L, 2 * H)
+    encode = lambda: np_(q.q8_encode(ctx, G[0], G[1], X, enc_h=out) if one else q.q8_encode_batch(ctx, G[0], G[1], X, lens, enc_h=out))
+    q.q8_encoder_options(ctx, False)
+    want = encode()
+    for bound in (0, 0, 0, 1, 3, 0):
+        out.fill_(7.0)
+        q.q8_encoder_options(ctx, 2, bound)
+        q.q8_profile_begin(ctx, "gru", 16)
+        assert_same(encode(), want, "a bound of %d polls" % bound)
+        assert q.q8_profile_end(ctx)[1] == 1
+        if bound == 0:
+            q.q8_encode_check(ctx)
+        elif one:
+            try:
+                q.q8_encode_check(ctx)
+            except q.Q8Error:
+                pass
+
+
 def test_encoders_beside_a_batched_decoder(q):
     """One sentence's encoder, a batch's and a batched decoder step whose GRUs fill the device, each on a stream of its own and each of
     blocks that wait for each other: whoever gets the compute units first, all results are what they are alone."""
