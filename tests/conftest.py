@@ -1,4 +1,3 @@
-import gc
 import os
 import sys
 
@@ -18,12 +17,3 @@ def oracle():
     from oracle import q8_oracle
     q8_oracle.build()
     return q8_oracle
-
-
-@pytest.fixture(autouse=True)
-def _earlier_tests_memory_is_free(request):
-    """Tensors of earlier tests that hang in reference cycles are given back before a test that counts allocated bytes, not in
-    the middle of it."""
-    if "no_alloc" in request.node.nodeid:
-        gc.collect()
-    yield

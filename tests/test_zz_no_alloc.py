@@ -2,6 +2,8 @@
 kernels' scratch in the library's static device array.  Its outputs must equal those of
 cgru_decoder_step_q8 bit for bit, on two calls in a row of which the second is smaller (the array
 keeps the first call's contents), and sizes beyond the array must be refused before any launch."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -9,6 +11,12 @@ import torch
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _earlier_tests_memory_is_free():
+    """Tensors of earlier tests that hang in reference cycles are given back before bytes are counted, not in the middle of it."""
+    gc.collect()
 
 
 def _case(q, ctx, seed, E, H, A, l, n):
