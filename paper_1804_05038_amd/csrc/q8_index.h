@@ -112,9 +112,11 @@ Q8_INDEX_FN int q8_gru_tile_columns(int H, int n)
 // 624 + 1008 bytes times 128 / 352 / 1024 12.3 / 11.1, 20.2 / 14.5 and 28.6 / 25.2, H = 1000, 2000 + 1008 bytes times 12 / 1024 14.6 / 12.7 and
 // 37.5 / 32.3; but H = 1024, 1024 + 1024 bytes, row-major, times 12 / 128 11.1 / 13.8 and 13.5 / 14.4 (256: 16.4 / 15.0), H = 512,
 // 1024 + 512 bytes, row-major, times 12 10.8 / 11.2, and more than a block per compute unit, H = 2048 times 700, 43.6 / 47.0.
-// Where the codes of the new states are wanted they cost a launch of 5.9 us, which the gates' kernel apart makes by the way: us per
-// decoder step, both transitions, H = 1000, 4 / 20 / 64 / 80 / 100 / 200 sentences at beam 5, 82 / 92 / 122 / 136 / 164 / 234 apart, 90 / 97 / 124 / 130 / 157 / 226 so,
-// H = 1024, 70 / 100 / 200 sentences 114 / 127 / 200 apart, 108 / 118 / 183 so.
+// Where the codes of the new states are wanted they cost a launch of 4.8 us, which the gates' kernel apart makes by the way: us per decoder
+// step with codes, apart / in tiles, H = 1000, 310 / 320 / 330 / 340 / 400 / 500 / 1000 vectors 58.1 / 61.2, 57.0 / 60.5, 67.4 / 62.4, 65.8 / 60.8, 67.6 / 62.3, 73.3 / 66.8, 99.1 / 91.9,
+// H = 1024, packed, 337 / 350 / 500 / 1000 69.7 / 64.1, 60.9 / 55.6, 68.0 / 59.1, 99.3 / 89.2, row-major, E = 1024, 320 / 330 / 340 59.0 / 62.0, 67.4 / 68.4, 66.3 / 65.0 (up to 336 of
+// E = 512 gru_panel_kernel's are 57); H = 300, 1000 vectors 55.3 / 57.1.  The line's other side gains too with fewer or more units: H = 512, 600
+// vectors 51.2 / 49.0, H = 2048, 150 71.3 / 61.5.
 // Rows of about the same length of both matrices leave one of the three parts half of all steps, and the products apart are at
 // their best with rows of at most 1024 bytes (or whole 128 bytes of 2048): H = 1024, 1024 + 1024 bytes, 129 / 160 / 192 / 224 vectors 13.4 / 13.7 / 14.2 / 14.8 apart,
 // 14.4 / 14.3 / 14.4 / 14.3 in one launch, H = 1000, 1008 + 1008 bytes, 129 / 160 / 176 11.3 / 11.9 / 13.4 and 12.1 / 12.3 / 12.4, H = 2048, 2048 + 2048 bytes, 129 / 176 / 224
@@ -123,7 +125,7 @@ Q8_INDEX_FN int q8_gru_tile_better(int H, int ldx, int ldh, int n, int codes, in
 {
     const int cols = 32 * q8_gru_tile_columns(H, n), less = ldx < ldh ? ldx : ldh, more = ldx < ldh ? ldh : ldx;
     if ((long long)((H + 31) / 32) * ((n + cols - 1) / cols) > 256) return 0;
-    if (codes) return (long long)n * H >= 360000;
+    if (codes) return (long long)n * H >= 340000;
     if (ldx + ldh < 1024) return 1;
     if (8 * less < 7 * more || (more > 1024 && less < 2048)) return n > 128;
     if (packed) return n > (more >= 1024 ? 144 : 128);

@@ -409,7 +409,7 @@ def test_panel_gru_in_one_launch_equals_products_and_gates_apart(q, ctx, oracle,
     """The transitions of a batched step as one kernel each, whose blocks exchange their partial maxima for the
     codes of the new states (the default where the grid fits the device: up to 336 slots), against the same
     step with that form switched off (matrix-core products, then a gates kernel): the same bits, states and
-    codes.  70 sentences x 5 = 350 slots is past the limit and runs the second form either way."""
+    codes.  From 340000 states on (67 and 70 sentences x 5 slots) the second form is the launch in tiles, past the limit either way."""
     m, P, enc_h, off, y, s = _panel_case(q, ctx, S, beam, l)
     one = _batched_step_with_codes(q, ctx, m, P, enc_h, off, beam, l, y, s)
     again = _batched_step_with_codes(q, ctx, m, P, enc_h, off, beam, l, y, s)
@@ -743,7 +743,7 @@ def test_panel_gru_in_tiles_equals_the_streaming_kernel(q, I, H, n, tiled, colum
 
 # E, H, A, sentences, beam, tile-packed, tiles of 32 vectors per block: batched steps both of whose GRUs run in gru_tile_kernel and leave their
 # states' codes (checked against the library's rule on the host)
-TILE_STEPS = [(512, 1024, 1024, 72, 5, True, 2), (620, 1000, 1000, 80, 5, False, 2), (512, 1024, 64, 129, 7, True, 4), (16, 1024, 64, 358, 1, False, 2),
+TILE_STEPS = [(512, 1024, 1024, 72, 5, True, 2), (512, 1024, 64, 337, 1, True, 2), (620, 1000, 64, 68, 5, False, 2), (620, 1000, 1000, 80, 5, False, 2), (512, 1024, 64, 129, 7, True, 4), (16, 1024, 64, 358, 1, False, 2),
               (64, 2048, 64, 44, 4, True, 2)]
 
 
