@@ -19,7 +19,7 @@
 // with XS > 0 the twelve also multiply the rows of X, whose codes and scales the launch in front made, by the block's rows of
 // Wx, which lie in LDS (XS k steps of 64 bytes per half): a step's products of X are made while the words of the step before
 // travel.  Else (rows of more than 640 bytes) they come from a product launch.  64 sentences of E = 512: 217 us with the
-// products given, 182 so (product launches and their 55 MB of results: 41 us).
+// products given, 182 so (product launches and their 57 MB of results: 41 us).
 // Several groups: eight waves take two slots each, eight apply the gates, and the next group's words are requested before this
 // one's products; bound by instructions and LDS traffic, so the products of X stay outside (200 sentences: 614 us, 717 with
 // them inside).
@@ -39,7 +39,7 @@
 // needs (states lie in [-1, 1], whatever X holds: tanh and sigmoid of a NaN are numbers here): whoever polls a word takes none
 // of an earlier turn, whatever a cache may still hold, since a location never goes back to an earlier value.  A buffer is free for step t when
 // this block has read step t - 1: every member had then read step t - 2.  64 sentences, the same kernel with agent-scope
-// loads and stores: 305 us; plain stores and nt loads: 182.
+// loads and stores (q8_encoder_options, one_launch = 2): 263 us; plain stores and nt loads, timed in turn with it: 161.
 // With several groups the words' way is hidden, and agent scope is no slower: a word is the float itself, or ENCG_ABSENT (a NaN
 // pattern that is never published) while it is not there, three buffers take turns, and a block that has read the words of step
 // t - 1 puts its own of step t - 2 back to ENCG_ABSENT, for step t + 1 to be published there, and waits for those stores before
@@ -595,8 +595,9 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
 // Nobody has to be resident for the result to be right: a wait is bounded, the first block of a direction whose wait gives up
 // works the direction off by itself (enc_one_alone), and the others leave when they next look at its word.  What they stored
 // before is what it stores, and it reads no states but its own, so it need not be the last.
-// The chain of a step bounds it: 1.48 us per position, E = 512, H = 1024 (encoder_persistent_kernel, 256 blocks all over the
-// device: 1.83, and two launches more in front).  q8_encode of 50 words, us: 99 -> 83; on four streams at once, per sentence 114 -> 52.
+// The chain of a step bounds it: 1.50 us per position, E = 512, H = 1024 (encoder_persistent_kernel, 256 blocks all over the
+// device: 1.83, and two launches more in front).  q8_encode of 50 words, us: 99 -> 84, with states handed over device-coherently 124; on 1 / 2 / 3 / 4
+// streams at once, per sentence, 100 / 128 / 120 / 117 -> 84 / 44 / 44 / 48, E = 64 100 / 126 / 118 / 115 -> 83 / 43 / 49 / 53 (more than two wait for their turns to start).
 // Not kept: dot products and gates on every wave, two units of sixteen waves or four of eight (129 and 101 us: sums across
 // lanes and sixteen, or eight, waves' gates); a row of X from memory at every step (135: its way is longer than the words').
 // LDS between the two barriers of a step: codes, sums and scales as in enc_group_kernel (states are words' own); sums of X

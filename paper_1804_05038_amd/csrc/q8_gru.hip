@@ -631,7 +631,7 @@ __global__ __launch_bounds__(EC_THREADS) void enc_cell_kernel(EncCellArgs a)
 }
 
 // ============================================= encoder recurrence in one launch ==
-// (What enc_one_kernel does not take: H above 1024, rows of X of more than 1024 bytes, a few words of H above 512.)
+// (What enc_one_kernel does not take: H above 1024, rows of X of more than 1024 bytes, a few words: q8_enc_one_better.)
 // Eq. 1 for one sentence, both directions, all l positions in ONE launch whose blocks are all
 // resident at once (the launcher checks that the device can hold them; otherwise the caller
 // launches per position).  Block b

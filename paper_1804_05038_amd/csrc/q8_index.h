@@ -175,12 +175,15 @@ Q8_INDEX_FN unsigned q8_enc_plan(int H, int S, int *members, int *sets, int *gro
 #define Q8_ENC_X_LDS(xs) ((xs) ? 2 * (Q8_ENC_SLOTS * Q8_ENC_X_PITCH(xs) + 12 * Q8_ENC_TILE * 4) + 12 * (xs) * 1024 : 0)
 #define Q8_ENC_LDS_MOST 47872
 
-// Whether S sentences of H units and up to max_l words run in that launch (else in one per time step, or three).  It costs 8 us
-// more than the first of those, which a time step gains back 3 us of: q8_encode_batch in us per batch, sentences of equal length,
-// H = 1024, 9 sentences of 1 / 2 / 3 / 4 words 17.5 / 20.3 / 24 / 26.5 against 11.1 / 16.9 / 24 / 29.5.  A group of a set takes 4 us of
-// a time step, so more than eight lose to the three launches (600 / 800 / 1024 sentences of 10 words 1.05 / 1.04 / 1.15 times as
-// long, 400, seven groups, 0.81), and at H <= 512 four, whose launches per time step are of half the blocks, need 7 words
-// (H = 512, 400 sentences of 3 / 4 / 6 / 8 words 1.10 / 1.07 / 1.02 / 0.98; H = 256, 1024 sentences 1.07 / 1.03 / 1.01 / 0.99).
+// Whether S sentences of H units and up to max_l words run in that launch (else in one per time step, or three).  q8_encode_batch
+// in us per batch, sentences of equal length, E = 512, a launch per time step / this: H = 1024, 9 sentences (one group per set) of 1 / 2 / 3 / 4 words
+// 11.7 / 17.7, 17.4 / 20.4, 22.7 / 22.7, 28.3 / 24.8, 65 (two) 15.3 / 20.7, 25.1 / 26.4, 34.8 / 32.5, 43.8 / 37.1, 400 (seven) 35.5 / 41.4, 64.1 / 65.3, 98.1 / 91.5,
+// 127.4 / 109.7.  With fewer units one group pays from 2 words on (H = 512, 9 sentences 16.8 / 15.6; H = 64, 257 sentences 17.7 / 14.9), two or three from 3
+// (H = 512, 129 sentences 24.0 / 25.4, 33.6 / 30.7): 3 words are the line that no shape loses by.  From four groups on, whose launches
+// per time step are of half the blocks, H <= 512 needs 6 to 7 words (H = 512, 400 sentences of 3 / 4 / 6 / 8 words 55.8 / 62.6, 70.0 / 74.6, 105.1 / 101.8, 139.2 / 127.3,
+// 1024 sentences 99.8 / 105.7, 131.7 / 134.6, 197.0 / 188.0, 263.9 / 243.9; H = 256, 1024 sentences 67.6 / 73.2, 86.7 / 89.3, 126.2 / 125.2, 167.5 / 162.0).  A group of a
+// set takes 2.6 us of a time step and more than eight lose to the three launches (measured when it took 4: 600 / 800 / 1024
+// sentences of 1024 units, 10 words, 1.05 / 1.04 / 1.15 times as long, 400, seven groups, 0.81).
 Q8_INDEX_FN int q8_enc_one_launch(int H, int S, int max_l)
 {
     int members, sets, groups, slots;
