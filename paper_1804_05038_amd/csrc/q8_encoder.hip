@@ -340,7 +340,6 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
     const int back = d == 0 ? -1 : 1, col0 = d == 0 ? H : 0;
 
     // ---- all positions ----
-    biases(member * ENCG_UNITS);
     const int unit = member * ENCG_UNITS + u;
     const bool pair = unit < H;                                        // (of the first eight waves: a (slot, unit) pair per thread)
     // words of this direction: byte offset of a buffer; all below 2^31
@@ -359,6 +358,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
     };
     if constexpr (ONE) {
         // ---- one group: a wave per slot, the waves without gates first ----
+        biases(member * ENCG_UNITS);
         weights(member * ENCG_UNITS);
         if (wave == 15) {
             // whether every member runs on this XCD
@@ -456,6 +456,7 @@ __global__ __launch_bounds__(ENCG_THREADS) void enc_group_kernel(EncGroupArgs a)
         // ---- several groups, one after the other at every step: the gates on the first eight waves, the codes, of two slots
         // each, on the others ----
         weights(member * ENCG_UNITS);
+        biases(member * ENCG_UNITS);
         __syncthreads();
         const int max_l = s_max;
         const unsigned group = (unsigned)(gs * H) * 4u;
